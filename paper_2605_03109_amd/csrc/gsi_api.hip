@@ -1,6 +1,7 @@
 // C ABI of libgsi: argument validation, workspace accounting and kernel selection.
 // Every entry point only enqueues work on the caller's stream; nothing here synchronises,
 // allocates or reads device memory.
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -96,25 +97,31 @@ static size_t map_part_bytes(int64_t m, int64_t d, int64_t B, int dense) {
   return gsi::tile_part_bytes(m, d, B);
 }
 
+// Workspace of a projection.  any_rank: also for ranks that are not 2^j pieces of 16 bytes.  Those have vector kernels
+// as well, but needed no workspace while the generic kernels took them, so a caller that brings only what the other
+// ranks need (any_rank = false) is still served, by the generic kernels.
+static size_t project_ws_bytes(int64_t d, int64_t k, int64_t B, bool any_rank) {
+  if (d < 1 || k < 1 || k > d || B < 1) return 0;
+  if (B > kDecodeMaxB) return mfma_batch_ok(d, k, B) ? mfma_project_ws(d, k, B) : 0;
+  // the slab partials of the vector projection kernels; sized for the wider of the two dtypes so
+  // that the query does not depend on the dtype (generic kernels need none)
+  size_t need = 0;
+  for (int dt = 0; dt < 2; ++dt) {
+    if (!gsi::decode_project_ok(d, k, dt, nullptr) || !(any_rank || gsi::rank_pow2(k, dt))) continue;
+    const size_t w = gsi::decode_project_ws(d, k, B, dt);
+    if (w > need) need = w;
+  }
+  return need;
+}
+
 size_t gsi_workspace_bytes(int which_call, int64_t m, int64_t d, int64_t k, int64_t B) {
   switch (which_call) {
     case GSI_CALL_BUILD_IMAGE:
       // the transposed basis of the matrix-core build (bf16 operands); generic kernels need none
       if (m < 1 || d < 1 || k < 1 || k > d || !mfma_image_ok(m, d, k)) return 0;
       return gsi::align_up((size_t)k * d * 2, 256) + gsi::mfma_part_bytes(m, k, d, gsi::EPI_STORE_BF16);
-    case GSI_CALL_PROJECT: {
-      if (d < 1 || k < 1 || k > d || B < 1) return 0;
-      if (B > kDecodeMaxB) return mfma_batch_ok(d, k, B) ? mfma_project_ws(d, k, B) : 0;
-      // the slab partials of the vector projection kernels; sized for the wider of the two dtypes so
-      // that the query does not depend on the dtype (generic kernels need none)
-      size_t need = 0;
-      for (int dt = 0; dt < 2; ++dt) {
-        if (!gsi::decode_project_ok(d, k, dt, nullptr)) continue;
-        const size_t w = gsi::decode_project_ws(d, k, B, dt);
-        if (w > need) need = w;
-      }
-      return need;
-    }
+    case GSI_CALL_PROJECT:
+      return project_ws_bytes(d, k, B, true);
     case GSI_CALL_GATED_LINEAR:
     case GSI_CALL_DENSE_LINEAR:
       // partial products of the matrix-core kernels
@@ -341,8 +348,8 @@ static int check_gated_args(const char* fn, const void* W, const void* M, const 
   return GSI_OK;
 }
 
-static bool project_vector_path(int64_t d, int64_t k, int64_t B, int udtype, const void* U) {
-  return B <= kDecodeMaxB && gsi::decode_project_ok(d, k, udtype, U);
+static bool project_vector_path(int64_t d, int64_t k, int64_t B, int udtype, const void* U, bool any_rank) {
+  return B <= kDecodeMaxB && gsi::decode_project_ok(d, k, udtype, U) && (any_rank || gsi::rank_pow2(k, udtype));
 }
 
 static void fill_proj_task(gsi::ProjTask& t, const void* U, const void* X, int64_t d, int64_t k, int64_t B,
@@ -477,7 +484,8 @@ static void clear(gsi::LinBatch& lb, int64_t B) {
 // kernel only: what that kernel needs beyond decode_linear_ok (reads_x: the product reads x, dense or W x form).
 static bool long_batch_ok(int64_t d, int64_t B, const void* Y, bool reads_x, const void* X, int xdtype) {
   if (B == 1 || d <= gsi::kMaxLinD) return true;
-  return aligned(Y, 16) && (!reads_x || (xdtype == GSI_F32 && aligned(X, 16)));
+  (void)xdtype;
+  return aligned(Y, 16) && (!reads_x || aligned(X, 16));
 }
 
 // Adds map `mp` (reading group description `gd`) to the batch, flushing first when the batch is full or
@@ -546,10 +554,11 @@ int gsi_project(const void* U, const void* X, int64_t d, int64_t k, int64_t B, i
                 float* R, float* rnorm, float* xnorm, void* ws, size_t ws_bytes, void* stream) {
   if (int rc = check_project_args("gsi_project", U, X, d, k, B, udtype, xdtype, C, R, rnorm, xnorm)) return rc;
   if (B == 0) return GSI_OK;
-  if (int rc = check_ws("gsi_project", ws, ws_bytes, gsi_workspace_bytes(GSI_CALL_PROJECT, 0, d, k, B))) return rc;
+  if (int rc = check_ws("gsi_project", ws, ws_bytes, project_ws_bytes(d, k, B, false))) return rc;
+  const bool any_rank = ws && aligned(ws, 256) && ws_bytes >= project_ws_bytes(d, k, B, true);
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
-  if (project_vector_path(d, k, B, udtype, U)) {
+  if (project_vector_path(d, k, B, udtype, U, any_rank)) {
     gsi::ProjBatch pb;
     std::memset(&pb, 0, sizeof(pb));
     pb.n = 1;
@@ -646,14 +655,14 @@ static bool wx_vector_ok(const gsi_input_desc& in) {
 
 // Is the E4M3 image of this map read as codes?  Only by the single-token vector kernels; every other call
 // expands it (exactly) to the weights' type in the workspace first and runs the map with an ordinary image.
-static bool fp8_codes_read(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B) {
+static bool fp8_codes_read(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B, bool any_rank) {
   return B == 1 && aligned(mp.M, 16) && in.k % 16 == 0 && in.k <= gsi::kMaxK &&
-         project_vector_path(in.d, in.k, B, in.udtype, in.U) &&
+         project_vector_path(in.d, in.k, B, in.udtype, in.U, any_rank) &&
          gsi::decode_linear_ok(mp.m, in.d, in.k, mp.wdtype, mp.W, nullptr, B) && aligned(in.C, 16) && aligned(in.R, 16) &&
          wx_vector_ok(in);
 }
-static size_t fp8_expand_bytes(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B) {
-  if (!(mp.flags & GSI_MAP_IMAGE_FP8) || B < 1 || mp.m < 1 || in.k < 1 || fp8_codes_read(mp, in, B)) return 0;
+static size_t fp8_expand_bytes(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B, bool any_rank) {
+  if (!(mp.flags & GSI_MAP_IMAGE_FP8) || B < 1 || mp.m < 1 || in.k < 1 || fp8_codes_read(mp, in, B, any_rank)) return 0;
   return gsi::align_up((size_t)mp.m * in.k * gsi::elem_size(mp.wdtype), 256);
 }
 
@@ -665,13 +674,13 @@ static size_t stack_table_bytes(int32_t n_maps, int32_t n_inputs, int64_t B) {
              : 0;
 }
 
-size_t gsi_layer_stack_workspace_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs,
-                                       int32_t n_inputs, int64_t B) {
+static size_t stack_ws_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int32_t n_inputs,
+                             int64_t B, bool any_rank) {
   if (!inputs || n_inputs < 0) return 0;
   // projections of independent inputs share a launch, so every input has its own region
   size_t need = stack_table_bytes(maps ? n_maps : 0, n_inputs, B);
   for (int i = 0; i < n_inputs; ++i)
-    need += gsi::align_up(gsi_workspace_bytes(GSI_CALL_PROJECT, 0, inputs[i].d, inputs[i].k, B), 256);
+    need += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, any_rank), 256);
   // and so do the maps of a decode batch (partial products of the weight term)
   if (maps)
     for (int j = 0; j < n_maps; ++j) {
@@ -682,9 +691,14 @@ size_t gsi_layer_stack_workspace_bytes(const gsi_map_desc* maps, int32_t n_maps,
   if (maps)
     for (int j = 0; j < n_maps; ++j) {
       const int id = maps[j].input_id;
-      if (id >= 0 && id < n_inputs) need += fp8_expand_bytes(maps[j], inputs[id], B);
+      if (id >= 0 && id < n_inputs) need += fp8_expand_bytes(maps[j], inputs[id], B, any_rank);
     }
   return need;
+}
+
+size_t gsi_layer_stack_workspace_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs,
+                                       int32_t n_inputs, int64_t B) {
+  return stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true);
 }
 
 // What gsi_stack_plan_build leaves in the caller's gsi_stack_plan: the launch shapes of a single-token call whose
@@ -729,7 +743,8 @@ int gsi_layer_stack_static(const gsi_map_desc* maps, int32_t n_maps, const gsi_i
   for (int j = 0; j < n_maps; ++j)
     if (maps[j].input_id < 0 || maps[j].input_id >= n_inputs)
       return fail(GSI_ERR_SHAPE, "%s: maps[%d].input_id = %d out of range", fn, j, maps[j].input_id);
-  const size_t need = B > 0 ? gsi_layer_stack_workspace_bytes(maps, n_maps, inputs, n_inputs, B) : 0;
+  const size_t need = B > 0 ? std::min(stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true),
+                                       stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, false)) : 0;
   if (need > have)
     return fail(GSI_ERR_WORKSPACE,
                 "%s: this call needs %zu bytes of scratch, the library's static array holds %zu; use gsi_layer_stack "
@@ -892,7 +907,9 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
       if (!aligned(mp.M_scale, 4)) return fail(GSI_ERR_ALIGN, "%s: maps[%d].M_scale is not aligned to 4 bytes", fn, j);
     }
   }
-  if (int rc = check_ws(fn, ws, ws_bytes, gsi_layer_stack_workspace_bytes(maps, n_maps, inputs, n_inputs, B)))
+  const size_t need_any = stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true);
+  const bool any_rank = ws_bytes >= need_any;  // (see project_ws_bytes)
+  if (int rc = check_ws(fn, ws, ws_bytes, any_rank ? need_any : stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, false)))
     return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
 
@@ -914,7 +931,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
     size_t off = stack_table_bytes(n_maps, n_inputs, B);
     for (int i = 0; i < n_inputs; ++i) {
       ws_off[i] = off;
-      off += gsi::align_up(gsi_workspace_bytes(GSI_CALL_PROJECT, 0, inputs[i].d, inputs[i].k, B), 256);
+      off += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, any_rank), 256);
     }
     for (int j = 0; j < n_maps; ++j) {
       const size_t pb = map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 0);
@@ -930,11 +947,11 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
   if (B > 0) {
     size_t off = stack_table_bytes(n_maps, n_inputs, B);
     for (int i = 0; i < n_inputs; ++i)
-      off += gsi::align_up(gsi_workspace_bytes(GSI_CALL_PROJECT, 0, inputs[i].d, inputs[i].k, B), 256);
+      off += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, any_rank), 256);
     for (int j = 0; j < n_maps; ++j) off += map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 0);
     for (int j = 0; j < n_maps; ++j) {
       const gsi_input_desc& in = inputs[maps[j].input_id];
-      const size_t bytes = fp8_expand_bytes(maps[j], in, B);
+      const size_t bytes = fp8_expand_bytes(maps[j], in, B, any_rank);
       if (!bytes) continue;
       if (expanded.empty()) expanded.assign(maps, maps + n_maps);
       void* tmp = reinterpret_cast<char*>(ws) + off;
@@ -962,7 +979,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
   for (int i = 0; i < n_inputs; ++i) {
     const gsi_input_desc& in = inputs[i];
     std::memset(&ptask[i], 0, sizeof(gsi::ProjTask));
-    if (B == 0 || !project_vector_path(in.d, in.k, B, in.udtype, in.U)) continue;
+    if (B == 0 || !project_vector_path(in.d, in.k, B, in.udtype, in.U, any_rank)) continue;
     mode[i] = kVecGate;
     fill_proj_task(ptask[i], in.U, in.X, in.d, in.k, B, in.udtype, in.xdtype, in.C, in.R, in.rnorm, in.xnorm,
                    reinterpret_cast<char*>(ws) + ws_off[i]);
@@ -988,7 +1005,8 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
     for (int i = 0; i < n_inputs; ++i) {
       const gsi_input_desc& in = inputs[i];
       if (in.src_map >= 0 || mode[i] != kVecInline || !(in.flags & GSI_INPUT_GATE_SINGLE_PASS) ||
-          (in.flags & GSI_INPUT_FUSED_KERNEL) || !aligned(in.gram, 16) || in.udtype != inputs[0].udtype)
+          (in.flags & GSI_INPUT_FUSED_KERNEL) || !aligned(in.gram, 16) || !gsi::rank_pow2(in.k, in.udtype) ||
+          in.udtype != inputs[0].udtype)
         return fail(GSI_ERR_SHAPE,
                     "%s: inputs[%d] cannot be planned (needs an external X, GSI_INPUT_GATE_SINGLE_PASS with a 16-byte "
                     "aligned gram, shapes and alignments of the vector kernels, one dtype for all inputs)", fn, i);
@@ -1145,7 +1163,8 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
       const int dt = pass & 1;
       const bool sp = pass >= 2;
       auto single_pass = [&](int i) {
-        return (inputs[i].flags & GSI_INPUT_GATE_SINGLE_PASS) && aligned(inputs[i].gram, 16);
+        return (inputs[i].flags & GSI_INPUT_GATE_SINGLE_PASS) && aligned(inputs[i].gram, 16) &&
+               gsi::rank_pow2(inputs[i].k, dt);
       };
       std::vector<int> list;
       for (int i : ready)

@@ -39,7 +39,8 @@ struct ProjTask {
   int a_rows, a_slabs, a_cblocks;  // partial projection: rows per slab, slabs, column blocks
   int b_rows, b_slabs;             // residual: rows per slab, slabs
   int udtype, xdtype;
-  int tile;                        // decode batch on the matrix cores (gsi_tile.hip) with its own slab geometry
+  int tile;                        // decode batch on the matrix cores (gsi_tile.hip) with its own slab geometry: the
+                                   // number of bf16 terms an fp32 operand is split into (2 or 3), else 0
   int b_perm;                      // residual slabs per partial-projection slab when the residual launch walks its
                                    // slabs in the XCD order of the partial projection, else 0 (filled at launch)
   int s_rows, s_slabs;             // single token (gsi_stage.hip): rows per slab and slabs of the partial projection
@@ -112,8 +113,19 @@ struct LinBatch {
 };
 static_assert(sizeof(LinBatch) <= 4096, "kernel arguments are limited to 4 KB");
 
+// lanes that hold a row of `pieces` 16-byte pieces: the power of two that covers it (surplus lanes stay idle)
+inline int row_lanes(int64_t pieces) {
+  int l = 1;
+  while (l < pieces) l <<= 1;
+  return l;
+}
 // eligibility of the vector kernels for a shape / alignment (else the generic kernels run)
 bool decode_project_ok(int64_t d, int64_t k, int udtype, const void* U);
+// ranks of 2^j 16-byte pieces per row: what the single-pass gate and plans take
+inline bool rank_pow2(int64_t k, int udtype) {
+  const int64_t V = udtype == GSI_BF16 ? 8 : 4, pieces = k / V;
+  return k % V == 0 && pieces > 0 && (pieces & (pieces - 1)) == 0;
+}
 // (B: tokens of the call; a single token's kernels take inputs of up to kMaxStreamD elements, and so does a decode
 // batch of 2..128 tokens whose shape the matrix-core kernel takes)
 bool decode_linear_ok(int64_t m, int64_t d, int64_t k, int wdtype, const void* W, const void* M, int64_t B = 2);
@@ -145,6 +157,9 @@ size_t tile_part_bytes(int64_t m, int64_t d, int64_t B);
 bool tile_project_shape_ok(int64_t d, int64_t k, int64_t B, int udtype);
 size_t tile_project_ws(int64_t d, int64_t k, int64_t B);
 void tile_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws);
+// bf16 terms that an fp32 operand of a decode batch is split into, by rank and activation type (see gsi_tile.hip)
+inline int tile_proj_terms(int64_t k, int xdtype) { return k % 64 || !rank_pow2(k, GSI_BF16) || xdtype != GSI_F32 ? 3 : 2; }
+int tile_rows_terms(const LinBatch& lb, int group);
 hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s);
 bool tile_rows_shape_ok(int64_t m, int64_t d, int64_t k, int64_t B, int wdtype);
 bool tile_rows_ok(const LinBatch& lb, int wdtype);

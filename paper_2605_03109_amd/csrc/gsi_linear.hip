@@ -209,7 +209,11 @@ bool decode_linear_ok(int64_t m, int64_t d, int64_t k, int wdtype, const void* W
 
 bool decode_linear_fits(const LinBatch& lb, int wdtype) {
   if (lb.B == 1) return stream_smem_bytes(lb) <= (size_t)kMaxLinD * sizeof(float);
-  if (tile_rows_ok(lb, wdtype)) return true;
+  if (tile_rows_ok(lb, wdtype)) {  // one number of operand terms per launch
+    for (int i = 1; i < lb.ng; ++i)
+      if (tile_rows_terms(lb, i) != tile_rows_terms(lb, 0)) return false;
+    return true;
+  }
   return tile_smem(lb) <= (size_t)kMaxLinD * sizeof(float);
 }
 

@@ -50,12 +50,15 @@ __global__ __launch_bounds__(kBlock) void proj_partial(const ProjBatch pb) {
   // XCD (workgroups go to the 8 XCDs in turn), whose L2 then holds all columns of the slab for the residual launch
   const int slab = local % p.a_slabs, cb = local / p.a_slabs;
   const int d = p.d, k = p.k, B = pb.B;
-  const int cbw = k < kColBlock ? k : kColBlock;  // columns of this block
-  const int lps = cbw / V;                        // lanes per row segment (a power of two)
-  const int rps = kBlock / lps;                   // rows per step
-  const int lsh = __builtin_ctz(lps);
+  const int cbw = k < kColBlock ? k : kColBlock;  // columns of a block
+  // lanes per row segment: the power of two that covers it; surplus lanes, and those past the last column of a rank
+  // that is no multiple of 64, repeat the last piece and are left out of the sums
+  const int lsh = cbw / V <= 1 ? 0 : 32 - __builtin_clz(cbw / V - 1);
+  const int lps = 1 << lsh;
+  const int rps = kBlock >> lsh;                  // rows per step
   const int l = threadIdx.x & (lps - 1), ro = threadIdx.x >> lsh;
-  const int col0 = cb * kColBlock + l * V;
+  const bool live = l * V < cbw;
+  const int col0 = min(cb * kColBlock + min(l * V, cbw - V), k - V);
   const int row0 = slab * p.a_rows;
   const int rows = min(p.a_rows, d - row0);
   const typename T::storage* U = reinterpret_cast<const typename T::storage*>(p.U) + (int64_t)row0 * k + col0;
@@ -140,13 +143,16 @@ __global__ __launch_bounds__(kBlock) void proj_partial(const ProjBatch pb) {
         for (int e = 0; e < V; ++e) acc[tt][e] = fmaf(u[e], xv, acc[tt][e]);
       }
     }
+    if (live) {
 #pragma unroll
-    for (int tt = 0; tt < TB; ++tt)
+      for (int tt = 0; tt < TB; ++tt)
 #pragma unroll
-      for (int e = 0; e < V; ++e) red[(ro * TB + tt) * cbw + l * V + e] = acc[tt][e];
+        for (int e = 0; e < V; ++e) red[(ro * TB + tt) * cbw + l * V + e] = acc[tt][e];
+    }
     __syncthreads();
     for (int idx = threadIdx.x; idx < nt * cbw; idx += kBlock) {
       const int tt = idx / cbw, j = idx % cbw;
+      if (cb * kColBlock + j >= k) continue;
       const float* rp = red + tt * cbw + j;
       const int gstride = TB * cbw;
       float s = 0.f;
@@ -181,14 +187,18 @@ __global__ __launch_bounds__(kBlock) void proj_residual(const ProjBatch pb) {
     slab = ((q / r) * 8 + x) * r + q % r;
   }
   const int d = p.d, k = p.k, B = pb.B;
-  const int cpr = k / V;         // 16-byte chunks per row (power of two, <= 64)
-  const int rps = kBlock / cpr;  // rows per step
-  const int cc = threadIdx.x & (cpr - 1), ro = threadIdx.x >> __builtin_ctz(cpr);
+  const int pieces = k / V;      // 16-byte pieces per row (<= 64), held by a power of two of lanes
+  const int lsh = pieces <= 1 ? 0 : 32 - __builtin_clz(pieces - 1);
+  const int cpr = 1 << lsh;
+  const int rps = kBlock >> lsh;  // rows per step
+  const int cc = threadIdx.x & (cpr - 1), ro = threadIdx.x >> lsh;
+  const bool colive = cc < pieces;
+  const int col = (colive ? cc : pieces - 1) * V;  // (surplus lanes repeat the last piece; their sums are dropped)
   const int row0 = slab * p.b_rows;
   const int rows = min(p.b_rows, d - row0);
   const int steps = (rows + rps - 1) / rps;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const typename T::storage* U = reinterpret_cast<const typename T::storage*>(p.U) + (int64_t)row0 * k + cc * V;
+  const typename T::storage* U = reinterpret_cast<const typename T::storage*>(p.U) + (int64_t)row0 * k + col;
 
   // the slab of U goes in flight first (row index clamped: loads are unconditional) ...
   float upf[PF][V];
@@ -216,7 +226,7 @@ __global__ __launch_bounds__(kBlock) void proj_residual(const ProjBatch pb) {
 #pragma unroll
     for (int tt = 0; tt < TB; ++tt)
 #pragma unroll
-      for (int e = 0; e < V; ++e) c[tt][e] = cs[tt][cc * V + e];
+      for (int e = 0; e < V; ++e) c[tt][e] = cs[tt][col + e];
     float ar[TB], ax[TB];
 #pragma unroll
     for (int tt = 0; tt < TB; ++tt) ar[tt] = ax[tt] = 0.f;
@@ -229,7 +239,7 @@ __global__ __launch_bounds__(kBlock) void proj_residual(const ProjBatch pb) {
         float s = 0.f;
 #pragma unroll
         for (int e = 0; e < V; ++e) s = fmaf(u[e], c[tt][e], s);
-        s = group_sum_rt(s, cpr);
+        s = group_sum_rt(colive ? s : 0.f, cpr);
         if (live && cc == 0 && tt < nt) {
           const float x = xv[tt];
           const float r = x - s;
@@ -366,8 +376,10 @@ __global__ __launch_bounds__(kBlock) void image_rows(const ImgBatch ib) {
 bool decode_project_ok(int64_t d, int64_t k, int udtype, const void* U) {
   const int V = udtype == GSI_BF16 ? 8 : 4;
   if (k % V) return false;
-  const int64_t cpr = k / V;
-  if (cpr > kWave || (cpr & (cpr - 1))) return false;  // chunks per row: power of two, one wave at most
+  // Pieces per row: one wave at most.  A rank whose pieces are no power of two leaves some lanes idle (k = 200: 7 of
+  // 32), which costs far less than the generic kernels' serial sums: a block of d = 4096, k = 200, one token 6.71 ms on
+  // those, 19.8 us here (k = 256: 17.6 us).
+  if (k / V > kWave) return false;
   if (k > kMaxK || d > (int64_t)kPartSlabs * kStageMaxRows) return false;  // 32 slabs of 2048 rows at most
   return (reinterpret_cast<uintptr_t>(U) % 16) == 0;
 }
@@ -380,14 +392,14 @@ ProjGeom proj_geom(int64_t d, int64_t k, int udtype) {
   const int V = udtype == GSI_BF16 ? 8 : 4;
   ProjGeom g;
   const int cbw = (int)(k < kColBlock ? k : kColBlock);
-  const int rps_a = kBlock / (cbw / V);
+  const int rps_a = kBlock / row_lanes(cbw / V);
   g.a_cblocks = (int)ceil_div(k, kColBlock);
   // one batch of eight row steps per workgroup, unless that would need more than kPartSlabs slabs
   int64_t ar = ceil_div(d, kPartSlabs);
   if (ar < 8 * rps_a) ar = 8 * rps_a;
   g.a_rows = (int)(ceil_div(ar, rps_a) * rps_a);
   g.a_slabs = (int)ceil_div(d, g.a_rows);
-  const int rps_b = kBlock / (int)(k / V);
+  const int rps_b = kBlock / row_lanes(k / V);
   // At least four row steps and at least 64 rows per workgroup (unless that needs too many slabs).  Measured on
   // GPT-J-sized blocks for k = 64 .. 512: with the image rows riding along, slabs of 64 rows keep the residual
   // launch within one residency round (four workgroups per CU); smaller slabs spill into a second round, larger
@@ -416,9 +428,10 @@ size_t decode_project_ws(int64_t d, int64_t k, int64_t B, int udtype) {
 
 void decode_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws) {
   t.tile = 0;
-  if (tile_project_shape_ok(d, k, B, t.udtype) && t.xdtype == GSI_F32 && reinterpret_cast<uintptr_t>(t.X) % 16 == 0 &&
+  if (tile_project_shape_ok(d, k, B, t.udtype) && reinterpret_cast<uintptr_t>(t.X) % 16 == 0 &&
       reinterpret_cast<uintptr_t>(t.C) % 16 == 0 && reinterpret_cast<uintptr_t>(t.R) % 16 == 0) {
     tile_project_fill(t, d, k, B, ws);
+    t.tile = tile_proj_terms(k, t.xdtype);
     return;
   }
   const ProjGeom g = proj_geom(d, k, t.udtype);
@@ -494,13 +507,14 @@ hipError_t decode_project_launch(ProjBatch& pb, int udtype, bool with_norms, boo
   }
   // tasks of a decode batch that take the matrix-core kernels go in a launch set of their own
   {
-    ProjBatch tile_pb = pb, rest = pb;
-    tile_pb.n = rest.n = 0;
-    for (int i = 0; i < pb.n; ++i) {
-      if (pb.t[i].tile) tile_pb.t[tile_pb.n++] = pb.t[i];
-      else rest.t[rest.n++] = pb.t[i];
-    }
-    if (tile_pb.n > 0) {
+    for (int terms = 2; terms <= 3; ++terms) {  // (one launch set per number of operand terms)
+      ProjBatch tile_pb = pb, rest = pb;
+      tile_pb.n = rest.n = 0;
+      for (int i = 0; i < pb.n; ++i) {
+        if (pb.t[i].tile == terms) tile_pb.t[tile_pb.n++] = pb.t[i];
+        else rest.t[rest.n++] = pb.t[i];
+      }
+      if (tile_pb.n == 0) continue;
       if (hipError_t e = tile_project_launch(tile_pb, with_norms, with_gate, eps, s); e != hipSuccess) return e;
       if (rest.n == 0) return hipSuccess;
       pb = rest;

@@ -96,13 +96,17 @@ __device__ __forceinline__ void partial_block(const StagePart& p, int local, flo
   const int slabs = p.slabs_x & 0xffff, ncb = max(1, (p.slabs_x >> 20) & 0xff);
   const int slab = local % slabs, col0 = (local / slabs) * (k / ncb);
   const int w = k / ncb;
-  const int cpr = w / V;         // lanes per row piece (a power of two, one wave at most)
-  const int rps = kBlock / cpr;  // rows per step
-  const int lsh = __builtin_ctz(cpr);
+  // lanes per row piece: the power of two that covers its 16-byte pieces, one wave at most.  Surplus lanes of a rank
+  // that is none (k = 200: 25 of 32 lanes) repeat the last piece and are left out of the sums.
+  const int pieces = w / V;
+  const int lsh = pieces <= 1 ? 0 : 32 - __builtin_clz(pieces - 1);
+  const int cpr = 1 << lsh;
+  const int rps = kBlock >> lsh;  // rows per step
   const int cc = threadIdx.x & (cpr - 1), ro = threadIdx.x >> lsh;
+  const bool live = cc < pieces;
   const int row0 = slab * prow;
   const int rows = min(prow, d - row0);
-  const S* U = reinterpret_cast<const S*>(p.U) + (int64_t)row0 * k + col0 + cc * V;
+  const S* U = reinterpret_cast<const S*>(p.U) + (int64_t)row0 * k + col0 + (live ? cc : pieces - 1) * V;
   const int xdtype = (p.slabs_x >> 16) & 0xf;
 
   float acc[V];
@@ -188,9 +192,11 @@ __device__ __forceinline__ void partial_block(const StagePart& p, int local, flo
 #pragma unroll
     for (int e = 0; e < V; ++e) acc[e] = fmaf(u[e], xv, acc[e]);
   }
+  if (live) {
 #pragma unroll
-  for (int q = 0; q < V / 4; ++q)
-    reinterpret_cast<float4*>(red + ro * w + cc * V)[q] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+    for (int q = 0; q < V / 4; ++q)
+      reinterpret_cast<float4*>(red + ro * w + cc * V)[q] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+  }
   if (p.x2_off) {
     x2 = wave_sum_f64(x2);
     if (threadIdx.x % kWave == 0) dsh[threadIdx.x / kWave] = x2;
@@ -339,14 +345,18 @@ __device__ __forceinline__ void residual_block(const StageRes& p, const StageGat
     if (slab == 0 && threadIdx.x == 0) publish_gate(g, rn, xn, f);
     if (!f || g.skip_fired_image) return;  // (the W x form of the slow path reads x, not r)
   }
-  const int cpr = k / V;         // 16-byte chunks per row (power of two, <= 64)
-  const int rps = kBlock / cpr;  // rows per step
-  const int cc = threadIdx.x & (cpr - 1), ro = threadIdx.x >> __builtin_ctz(cpr);
+  const int pieces = k / V;      // 16-byte pieces per row (<= 64), held by a power of two of lanes
+  const int lsh = pieces <= 1 ? 0 : 32 - __builtin_clz(pieces - 1);
+  const int cpr = 1 << lsh;
+  const int rps = kBlock >> lsh;  // rows per step
+  const int cc = threadIdx.x & (cpr - 1), ro = threadIdx.x >> lsh;
+  const bool live = cc < pieces;
+  const int col = (live ? cc : pieces - 1) * V;  // (surplus lanes repeat the last piece; their sums are dropped)
   const int row0 = slab * b_rows;
   const int rows = min(b_rows, d - row0);
   const int steps = (rows + rps - 1) / rps;
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const S* U = reinterpret_cast<const S*>(p.U) + (int64_t)row0 * k + cc * V;
+  const S* U = reinterpret_cast<const S*>(p.U) + (int64_t)row0 * k + col;
 
   // the slab of U goes in flight first (row index clamped: loads are unconditional), then the slab's activations
   // (one coalesced load, staged in LDS) and the coefficients
@@ -366,7 +376,7 @@ __device__ __forceinline__ void residual_block(const StageRes& p, const StageGat
   __syncthreads();
   float c[V];
 #pragma unroll
-  for (int e = 0; e < V; ++e) c[e] = cs[cc * V + e];
+  for (int e = 0; e < V; ++e) c[e] = cs[col + e];
   float ar = 0.f, ax = 0.f;
   // every lane of a row group walks the same steps, so the cross-lane sums are convergent
   auto row_step = [&](const uint4& raw, float x, int st) {
@@ -376,7 +386,7 @@ __device__ __forceinline__ void residual_block(const StageRes& p, const StageGat
     float s = 0.f;
 #pragma unroll
     for (int e = 0; e < V; ++e) s = fmaf(u[e], c[e], s);
-    s = group_sum_rt(s, cpr);
+    s = group_sum_rt(live ? s : 0.f, cpr);
     if (i < rows && cc == 0) {
       const float r = x - s;
       p.R[row0 + i] = r;
@@ -617,7 +627,7 @@ __global__ __launch_bounds__(kBlock) void table_rows(const TabIn* __restrict__ i
 // ------------------------------------------------------------------------------------------------
 void stage_geom(int64_t d, int64_t k, int udtype, int& rows, int& slabs, bool fine) {
   const int V = udtype == GSI_BF16 ? 8 : 4;
-  const int rps = kBlock / (int)(k / V);
+  const int rps = kBlock / row_lanes(k / V);
   // at least eight row steps per workgroup, kPartSlabs slabs at most ...
   int64_t r = ceil_div(d, kPartSlabs);
   if (fine) {  // ... or, at most 64 KB of U per workgroup (a workgroup keeps 32 KB in flight, so a larger slab is a

@@ -13,6 +13,14 @@
 // no fired token the kernel leaves before touching the weight matrix.
 // Items of one matrix that cover different column slices write partial sums to the workspace, and a
 // second kernel adds them in slice order, so results do not vary from run to run.
+//
+// Terms of an fp32 operand: two (relative remainder 2^-17) for ranks of 64 * 2^j columns and fp32 activations.  Other
+// ranks (any multiple of 8 up to 512) and bf16 activations take three (2^-25, the fp32 value itself): these calls ran
+// on fp32 FMAs before, and with two terms the residual, whose parts cancel to a few percent, was 2e-5 .. 5e-5 off
+// instead of 3e-6 .. 2e-5.  The kernels are bound by memory and latency, the third MFMA costs nothing that shows.
+// Measured: a block of d = 2560, rank 128, 23 bf16 tokens 174 us on the FMA kernels, 66 us on these.
+#include <type_traits>
+
 #include "gsi_decode.h"
 #include "gsi_device.h"
 
@@ -44,14 +52,44 @@ __device__ __forceinline__ int find_task(const int (&begin)[N], int n, int b) {
   return t;
 }
 
+// four consecutive activations at element offset i (a multiple of four) as fp32; calls of two terms have fp32 ones
+template <int T>
+__device__ __forceinline__ float4 load_act4(const void* p, int dtype, int64_t i) {
+  if (T == 2 || dtype == GSI_F32) return *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p) + i);
+  const uint2 b = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(p) + i);
+  return float4{bf16_lo(b.x), bf16_hi(b.x), bf16_lo(b.y), bf16_hi(b.y)};
+}
+
+// four fp32 values as T bf16 terms each: term 0 the rounded value, every further term the rounded remainder (exact
+// differences).  Three terms: a value whose rounding overflows is cut instead, and an infinity or NaN has zero
+// remainders, so that it travels through the products as itself, as it does through fp32 FMAs.
+template <int T>
+__device__ __forceinline__ void split4(const float4& v, uint2 (&out)[T]) {
+  float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    uint32_t h[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const __bf16 hb = (__bf16)x[e];
+      h[e] = __builtin_bit_cast(uint16_t, hb);
+      if (T == 3 && t == 0 && (h[e] & 0x7fffu) == 0x7f80u) h[e] = __float_as_uint(x[e]) >> 16;
+      const float rem = x[e] - __uint_as_float(h[e] << 16);
+      x[e] = T == 2 || fabsf(rem) <= 3.402823466e38f ? rem : 0.f;
+    }
+    out[t] = uint2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+  }
+}
+
 // Requests this thread's share of half a staging round: tokens [g0 + 16 * half, + 16) of the phase (token j
-// is row idx ? idx[j] : j of V), columns [c0, c0 + 32 * ns).  A wave pair covers one token row per pass.
-// Every load is unconditional: tokens past the count repeat the last one and columns past the slice its
-// last four; what they stage is never used.
-__device__ __forceinline__ void stage_issue(float4 (&v)[kHalfVec], int half, const float* __restrict__ V, int64_t ldv,
-                                            const int32_t* __restrict__ idx, int g0, int count, int B, int c0, int ns,
+// is row idx ? idx[j] : j of V, vdt its type), columns [c0, c0 + ncol), ncol a multiple of four.  A wave pair covers
+// one token row per pass.  Every load is unconditional: tokens past the count repeat the last one and columns past
+// the slice its last four.
+template <int T>
+__device__ __forceinline__ void stage_issue(float4 (&v)[kHalfVec], int half, const void* __restrict__ V, int vdt, int64_t ldv,
+                                            const int32_t* __restrict__ idx, int g0, int count, int B, int c0, int ncol,
                                             int wave) {
-  const int c4 = min((int)(threadIdx.x & 127), 8 * ns - 1);
+  const int c4 = min((int)(threadIdx.x & 127), ncol / 4 - 1);
   const int j0 = g0 + 16 * half + (wave >> 1);
   int tok[kHalfVec];  // all token indices first (uniform across the wave), so that their loads overlap
   if (idx) {
@@ -64,34 +102,82 @@ __device__ __forceinline__ void stage_issue(float4 (&v)[kHalfVec], int half, con
     for (int i = 0; i < kHalfVec; ++i) tok[i] = min(j0 + 4 * i, count - 1);
   }
 #pragma unroll
-  for (int i = 0; i < kHalfVec; ++i) v[i] = *reinterpret_cast<const float4*>(V + (int64_t)tok[i] * ldv + c0 + 4 * c4);
+  for (int i = 0; i < kHalfVec; ++i) v[i] = load_act4<T>(V, vdt, (int64_t)tok[i] * ldv + c0 + 4 * c4);
 }
 
-// fp32 -> bf16 head and bf16 tail of the (exact) remainder, both rounded to nearest even: x - (head + tail)
-// is below 2^-17 |x|
-__device__ __forceinline__ void stage_commit(const float4 (&v)[kHalfVec], int half, uint16_t (*vhi)[kVRow],
-                                             uint16_t (*vlo)[kVRow], int wave) {
+// what stage_issue requested, as T bf16 terms in LDS; columns past the slice are zero
+template <int T>
+__device__ __forceinline__ void stage_commit(const float4 (&v)[kHalfVec], int half, uint16_t (*vt)[kRoundTok][kVRow], int ncol,
+                                             int wave) {
   const int c4 = threadIdx.x & 127;
 #pragma unroll
   for (int i = 0; i < kHalfVec; ++i) {
     const int t = 16 * half + (wave >> 1) + 4 * i;
-    const float x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-    uint16_t h[4], l[4];
+    uint2 term[T];
+    split4<T>(4 * c4 < ncol ? v[i] : float4{0.f, 0.f, 0.f, 0.f}, term);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const __bf16 hi = (__bf16)x[e];
-      h[e] = __builtin_bit_cast(uint16_t, hi);
-      const __bf16 lo = (__bf16)(x[e] - __uint_as_float((uint32_t)h[e] << 16));
-      l[e] = __builtin_bit_cast(uint16_t, lo);
-    }
-    *reinterpret_cast<uint2*>(&vhi[t][4 * c4]) = uint2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-    *reinterpret_cast<uint2*>(&vlo[t][4 * c4]) = uint2{(uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16)};
+    for (int q = 0; q < T; ++q) *reinterpret_cast<uint2*>(&vt[q][t][4 * c4]) = term[q];
   }
 }
 
+// The weights of a wave's item: rows row (per lane), columns c0 + 32 s + 8 lq .. + 7 for step s.  base: first column of
+// the slice; steps past the slice repeat its last one.  A slice that ends inside a step (a rank that is no multiple of
+// 32) has zeros past its end: those lanes read the step's first columns instead and are cleared.
+__device__ __forceinline__ void weights_issue(uint4 (&w)[kSteps], const char* __restrict__ base, uint32_t row_off, int lq, int ncol,
+                                              int ns) {
+  const uint32_t voff = row_off + 16u * lq;
+  const uint32_t vlast = (ns - 1) * kStepCols + 8 * lq < ncol ? voff : row_off;
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s)
+    w[s] = *reinterpret_cast<const uint4*>(base + (size_t)(min(s, ns - 1) * kStepCols * 2) + (s < ns - 1 ? voff : vlast));
+}
+__device__ __forceinline__ void weights_clear_tail(uint4 (&w)[kSteps], int lq, int ncol, int ns) {
+  if (ncol % kStepCols == 0) return;  // uniform
+  const bool dead = (ns - 1) * kStepCols + 8 * lq >= ncol;
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s)
+    if (s == ns - 1 && dead) w[s] = uint4{0u, 0u, 0u, 0u};
+}
+
+// acc0 / acc1 = the item's weights times the staged tokens 0 .. 15 / 16 .. 31.  Three terms: the head's products of even
+// and odd steps and those of the two remainders have accumulators of their own, so that fewer large partial sums are
+// rounded (the residual's error against 64 bits is then the FMA kernel's, 2.7e-6 at rank 128; 3.6e-6 with one).
+template <int T>
+__device__ __forceinline__ void item_mma(const uint4 (&w)[kSteps], const uint16_t (*vt)[kRoundTok][kVRow], int li, int lq, int ns,
+                                         bool two, f32x4& acc0, f32x4& acc1) {
+  constexpr int NA = T == 3 ? 3 : 1;
+  f32x4 acc[2][NA];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int q = 0; q < NA; ++q) acc[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    if (s < ns) {
+      const bf16x8 a = __builtin_bit_cast(bf16x8, w[s]);
+      const int col = s * kStepCols + 8 * lq;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        if (t == 1 && !two) continue;
+#pragma unroll
+        for (int q = 0; q < T; ++q) {
+          f32x4& d = acc[t][NA == 1 ? 0 : (q > 0 ? 2 : s & 1)];
+          d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, *reinterpret_cast<const bf16x8*>(&vt[q][16 * t + li][col]), d, 0, 0, 0);
+        }
+      }
+    }
+  }
+  acc0 = acc[0][0];
+  acc1 = acc[1][0];
+  if constexpr (NA == 3) {
+    acc0 = (acc0 + acc[0][1]) + acc[0][2];
+    acc1 = (acc1 + acc[1][1]) + acc[1][2];
+  }
+}
+
+template <int T>
 __global__ __launch_bounds__(kTBlock) void tile_rows(const LinBatch lb) {
-  __shared__ __align__(16) uint16_t vhi[kRoundTok][kVRow];
-  __shared__ __align__(16) uint16_t vlo[kRoundTok][kVRow];
+  __shared__ __align__(16) uint16_t vt[T][kRoundTok][kVRow];
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x % kWave;
@@ -109,9 +195,9 @@ __global__ __launch_bounds__(kTBlock) void tile_rows(const LinBatch lb) {
   const int item = blockIdx.x - (second ? lb.blk_begin2[ti] : lb.blk_begin[ti]);
 
   const uint16_t* A;
-  const float* V;
+  const void* V;
   const int32_t* idx = nullptr;
-  int K, count, slices, g_begin = 0;
+  int K, count, slices, g_begin = 0, vdt = GSI_F32;
   bool to_part;
   if (second) {
     // image term over all tokens, whole rank in one slice, written straight to Y; one item per round of
@@ -121,73 +207,53 @@ __global__ __launch_bounds__(kTBlock) void tile_rows(const LinBatch lb) {
     g_begin = (item % slices) * kRoundTok;
     count = min(B, g_begin + kRoundTok);
   } else if (lb.dense) {
-    A = reinterpret_cast<const uint16_t*>(p.W); V = reinterpret_cast<const float*>(g.X); K = g.d; count = B;
+    A = reinterpret_cast<const uint16_t*>(p.W); V = g.X; vdt = g.xdtype; K = g.d; count = B;
     slices = p.slices; to_part = true;
   } else {
     int nf = g.n_fired[0];
     nf = nf < 0 ? 0 : (nf > B ? B : nf);
     // the fired tokens' r (added to the image term), or their x (replacing it: Algorithm 1, line 7)
-    A = reinterpret_cast<const uint16_t*>(p.W); V = g.wx ? reinterpret_cast<const float*>(g.X) : g.R; K = g.d;
+    A = reinterpret_cast<const uint16_t*>(p.W); V = g.wx ? g.X : g.R; K = g.d;
+    if (g.wx) vdt = g.xdtype;
     count = nf; idx = g.fired_idx;
     slices = p.slices; to_part = true;
   }
   if (count == 0) return;  // uniform: no fired token, no weight byte is read
   const int rb = item / slices, ks = second ? 0 : item - rb * slices;
   const int c0 = ks * kSliceCols;
-  const int ns = min(kSteps, (K - c0) / kStepCols);
+  const int ncol = min(kSliceCols, K - c0);
+  const int ns = (ncol + kStepCols - 1) / kStepCols;
   const int row0 = rb * kItemRows + 16 * wave;
 
   // first round's activations, then the weights, so that the activations can be converted and staged while
   // the weights are still on their way
   float4 v[kHalfVec];
-  stage_issue(v, 0, V, K, idx, g_begin, count, B, c0, ns, wave);
+  stage_issue<T>(v, 0, V, vdt, K, idx, g_begin, count, B, c0, ncol, wave);
   __builtin_amdgcn_sched_barrier(0);
   uint4 w[kSteps];
-  {
-    // uniform base + one 32-bit lane offset (the matrix is smaller than 2 GiB); rows past m repeat the last
-    const char* base = reinterpret_cast<const char*>(A + c0);
-    const uint32_t voff = ((uint32_t)min(row0 + li, m - 1) * (uint32_t)K + 8u * lq) * 2u;
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s)
-      w[s] = *reinterpret_cast<const uint4*>(base + (size_t)(min(s, ns - 1) * kStepCols * 2) + voff);
-  }
+  // uniform base + one 32-bit lane offset (the matrix is smaller than 2 GiB); rows past m repeat the last
+  weights_issue(w, reinterpret_cast<const char*>(A + c0), (uint32_t)min(row0 + li, m - 1) * (uint32_t)K * 2u, lq, ncol, ns);
   __builtin_amdgcn_sched_barrier(0);  // keep the weight requests ahead of the wait for the activations
-  stage_commit(v, 0, vhi, vlo, wave);
+  stage_commit<T>(v, 0, vt, ncol, wave);
   if (count - g_begin > 16) {  // uniform
-    stage_issue(v, 1, V, K, idx, g_begin, count, B, c0, ns, wave);
-    stage_commit(v, 1, vhi, vlo, wave);
+    stage_issue<T>(v, 1, V, vdt, K, idx, g_begin, count, B, c0, ncol, wave);
+    stage_commit<T>(v, 1, vt, ncol, wave);
   }
+  weights_clear_tail(w, lq, ncol, ns);
 
   for (int g0 = g_begin; g0 < count; g0 += kRoundTok) {
     if (g0 != g_begin) {
       __syncthreads();  // the previous round's operands have been read
-      stage_issue(v, 0, V, K, idx, g0, count, B, c0, ns, wave);
-      stage_commit(v, 0, vhi, vlo, wave);
+      stage_issue<T>(v, 0, V, vdt, K, idx, g0, count, B, c0, ncol, wave);
+      stage_commit<T>(v, 0, vt, ncol, wave);
       if (count - g0 > 16) {
-        stage_issue(v, 1, V, K, idx, g0, count, B, c0, ns, wave);
-        stage_commit(v, 1, vhi, vlo, wave);
+        stage_issue<T>(v, 1, V, vdt, K, idx, g0, count, B, c0, ncol, wave);
+        stage_commit<T>(v, 1, vt, ncol, wave);
       }
     }
     __syncthreads();
-    const bool two = count - g0 > 16;
-    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
-      if (s < ns) {
-        const bf16x8 a = __builtin_bit_cast(bf16x8, w[s]);
-        const int col = s * kStepCols + 8 * lq;
-        const bf16x8 h0 = *reinterpret_cast<const bf16x8*>(&vhi[li][col]);
-        const bf16x8 l0 = *reinterpret_cast<const bf16x8*>(&vlo[li][col]);
-        acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, h0, acc0, 0, 0, 0);
-        acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, l0, acc0, 0, 0, 0);
-        if (two) {
-          const bf16x8 h1 = *reinterpret_cast<const bf16x8*>(&vhi[16 + li][col]);
-          const bf16x8 l1 = *reinterpret_cast<const bf16x8*>(&vlo[16 + li][col]);
-          acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, h1, acc1, 0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, l1, acc1, 0, 0, 0);
-        }
-      }
-    }
+    f32x4 acc0, acc1;
+    item_mma<T>(w, vt, li, lq, ns, count - g0 > 16, acc0, acc1);
     // lane holds token li of each tile, rows 4*lq .. 4*lq+3 of the wave's 16
     const int row = row0 + 4 * lq;
     if (row < m) {  // m is a multiple of 4
@@ -270,16 +336,15 @@ constexpr int kPXRow = kStepCols + 8;        // bf16 per staged token row (80 by
 // The contraction runs over rows of U, which are not contiguous in memory, so a 32-row x 64-column tile of
 // U is staged in LDS as it is stored and the A operand (16 columns x 32 rows) is gathered column-wise with
 // 16-bit reads; it then serves every token tile (two MFMAs each: bf16 head and tail of the fp32 x).
-template <int XV>  // XV = token groups of 32 the call may have (1, 2 or 4): sizes the register arrays
+// T: bf16 terms of x (bf16 activations: one, the others are zero and left out)
+template <int XV, int T>  // XV = token groups of 32 the call may have (1, 2 or 4): sizes the register arrays
 __global__ __launch_bounds__(kPBlock) void tile_proj_partial(const ProjBatch pb) {
   __shared__ __align__(16) uint16_t us[2][kStepCols][kPURow];
-  __shared__ __align__(16) uint16_t xh[2][kMaxTok][kPXRow];
-  __shared__ __align__(16) uint16_t xl[2][kMaxTok][kPXRow];
+  __shared__ __align__(16) uint16_t xt[T][2][32 * XV][kPXRow];
 
   const int ti = find_task(pb.a_begin, pb.n, blockIdx.x);
   const ProjTask& p = pb.t[ti];
   const int local = blockIdx.x - pb.a_begin[ti];
-  const int cgroups = p.k / kPCols;
   // the column groups of a row slab are a_slabs workgroups apart: on the same XCD when a_slabs is a multiple of 8
   // (workgroups go to the 8 XCDs in turn), and so is the residual workgroup of the same rows
   const int slab = local % p.a_slabs, cg = local / p.a_slabs;
@@ -291,19 +356,19 @@ __global__ __launch_bounds__(kPBlock) void tile_proj_partial(const ProjBatch pb)
   const int lane = threadIdx.x % kWave, li = lane & 15, lq = lane >> 4;
   const int ntile = (B + 15) >> 4;
   const uint16_t* U = reinterpret_cast<const uint16_t*>(p.U);
-  const float* X = reinterpret_cast<const float*>(p.X);
 
   // staging roles: U tile 32 rows x 8 chunks of 16 bytes = 256 threads; x tile B tokens x 8 float4
   const int urow = threadIdx.x >> 3, uch = threadIdx.x & 7;
-  const uint16_t* usrc = U + (int64_t)(row_begin + urow) * k + cg * kPCols + 8 * uch;
+  // (columns past the rank repeat the last eight; their sums are not stored)
+  const uint16_t* usrc = U + (int64_t)(row_begin + urow) * k + min(cg * kPCols + 8 * uch, k - 8);
   constexpr int kXV = XV;                     // float4 per thread and step: one per 32 tokens
   constexpr int kTiles = 2 * XV;              // MFMA token tiles
   const int xc4 = threadIdx.x & 7;
-  const float* xsrc[kXV];
+  int64_t xsrc[kXV];
 #pragma unroll
   for (int u = 0; u < kXV; ++u) {
     const int t = min((int)(threadIdx.x >> 3) + 32 * u, B - 1);  // tokens past B repeat the last one
-    xsrc[u] = X + (int64_t)t * d + row_begin + 4 * xc4;
+    xsrc[u] = (int64_t)t * d + row_begin + 4 * xc4;
   }
   // A slab is at most four steps (128 rows): everything it reads is requested at once, then staged and
   // consumed step by step (two LDS buffers), so the slab costs one memory round trip, not four.
@@ -314,7 +379,7 @@ __global__ __launch_bounds__(kPBlock) void tile_proj_partial(const ProjBatch pb)
     const int sc = min(s, steps - 1);  // steps past the slab repeat the last one and are not consumed
     ur[s] = *reinterpret_cast<const uint4*>(usrc + (int64_t)sc * kStepCols * k);
 #pragma unroll
-    for (int u = 0; u < kXV; ++u) xr[s][u] = *reinterpret_cast<const float4*>(xsrc[u] + sc * kStepCols);
+    for (int u = 0; u < kXV; ++u) xr[s][u] = load_act4<T>(p.X, p.xdtype, xsrc[u] + sc * kStepCols);
   }
   __builtin_amdgcn_sched_barrier(0);  // every request of the slab is issued before the first wait
   auto commit = [&](int s, int buf) {
@@ -323,22 +388,14 @@ __global__ __launch_bounds__(kPBlock) void tile_proj_partial(const ProjBatch pb)
     ud[1] = uint2{ur[s].z, ur[s].w};
 #pragma unroll
     for (int u = 0; u < kXV; ++u) {
-      {
-        const int t = (threadIdx.x >> 3) + 32 * u;  // tokens past B hold a copy of the last one, never used
-        const float x[4] = {xr[s][u].x, xr[s][u].y, xr[s][u].z, xr[s][u].w};
-        uint16_t h[4], l[4];
+      const int t = (threadIdx.x >> 3) + 32 * u;  // tokens past B hold a copy of the last one, never used
+      uint2 term[T];
+      split4<T>(xr[s][u], term);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const __bf16 hi = (__bf16)x[e];
-          h[e] = __builtin_bit_cast(uint16_t, hi);
-          const __bf16 lo = (__bf16)(x[e] - __uint_as_float((uint32_t)h[e] << 16));
-          l[e] = __builtin_bit_cast(uint16_t, lo);
-        }
-        *reinterpret_cast<uint2*>(&xh[buf][t][4 * xc4]) = uint2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-        *reinterpret_cast<uint2*>(&xl[buf][t][4 * xc4]) = uint2{(uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16)};
-      }
+      for (int q = 0; q < T; ++q) *reinterpret_cast<uint2*>(&xt[q][buf][t][4 * xc4]) = term[q];
     }
   };
+  const int terms = p.xdtype == GSI_F32 ? T : 1;  // uniform
 
   f32x4 acc[kTiles];
 #pragma unroll
@@ -360,10 +417,11 @@ __global__ __launch_bounds__(kPBlock) void tile_proj_partial(const ProjBatch pb)
 #pragma unroll
       for (int t = 0; t < kTiles; ++t) {
         if (t < ntile) {  // uniform
-          const bf16x8 h = *reinterpret_cast<const bf16x8*>(&xh[buf][16 * t + li][8 * lq]);
-          const bf16x8 l = *reinterpret_cast<const bf16x8*>(&xl[buf][16 * t + li][8 * lq]);
-          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, h, acc[t], 0, 0, 0);
-          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, l, acc[t], 0, 0, 0);
+#pragma unroll
+          for (int q = 0; q < T; ++q)
+            if (q < terms)
+              acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, *reinterpret_cast<const bf16x8*>(&xt[q][buf][16 * t + li][8 * lq]),
+                                                               acc[t], 0, 0, 0);
         }
       }
       if (s + 1 < kPSteps && s + 1 < steps) commit(s + 1, buf ^ 1);
@@ -373,7 +431,7 @@ __global__ __launch_bounds__(kPBlock) void tile_proj_partial(const ProjBatch pb)
 #pragma unroll
   for (int t = 0; t < kTiles; ++t) {
     const int tok = 16 * t + li;
-    if (t < ntile && tok < B) {
+    if (t < ntile && tok < B && cg * kPCols + 16 * wave + 4 * lq < k) {
       float* dst = p.part_c + ((int64_t)slab * B + tok) * k + cg * kPCols + 16 * wave + 4 * lq;
       *reinterpret_cast<float4*>(dst) = float4{acc[t][0], acc[t][1], acc[t][2], acc[t][3]};
     }
@@ -476,10 +534,10 @@ __device__ __forceinline__ void norms_and_gate(const ProjTask& p, int B, int do_
 // contiguous: same operand flow as tile_rows), R written, and the row block's share of |r|^2 and |x|^2.
 // The workgroup of an input that finishes last (a counter in the workspace, zeroed by the partial-projection
 // launch) turns the shares into the norms, the gate decisions and the list of fired tokens: no launch of its own.
+template <int T>
 __global__ __launch_bounds__(kTBlock) void tile_residual(const ProjBatch pb) {
   __shared__ int s_last;
-  __shared__ __align__(16) uint16_t vhi[kRoundTok][kVRow];
-  __shared__ __align__(16) uint16_t vlo[kRoundTok][kVRow];
+  __shared__ __align__(16) uint16_t vt[T][kRoundTok][kVRow];
   __shared__ float red[kTWaves][kRoundTok][2];
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -492,55 +550,33 @@ __global__ __launch_bounds__(kTBlock) void tile_residual(const ProjBatch pb) {
   const int nrb = p.d / kItemRows;  // row blocks; the rounds of a row block are nrb workgroups apart (same XCD)
   const int rb = item % nrb, g0 = (item / nrb) * kRoundTok;
   const int count = min(B, g0 + kRoundTok);
-  const int d = p.d, k = p.k, ns = k / kStepCols;
+  const int d = p.d, k = p.k, ns = (k + kStepCols - 1) / kStepCols;
   const int row0 = rb * kItemRows + 16 * wave;  // d is a multiple of 128: every row exists
   const uint16_t* U = reinterpret_cast<const uint16_t*>(p.U);
-  const float* X = reinterpret_cast<const float*>(p.X);
 
   float4 v[kHalfVec];
-  stage_issue(v, 0, p.C, k, nullptr, g0, count, B, 0, ns, wave);
+  stage_issue<T>(v, 0, p.C, GSI_F32, k, nullptr, g0, count, B, 0, k, wave);
   __builtin_amdgcn_sched_barrier(0);
   uint4 w[kSteps];
-  {
-    const char* base = reinterpret_cast<const char*>(U);
-    const uint32_t voff = ((uint32_t)(row0 + li) * (uint32_t)k + 8u * lq) * 2u;
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s)
-      w[s] = *reinterpret_cast<const uint4*>(base + (size_t)(min(s, ns - 1) * kStepCols * 2) + voff);
-  }
+  weights_issue(w, reinterpret_cast<const char*>(U), (uint32_t)(row0 + li) * (uint32_t)k * 2u, lq, k, ns);
   // x of the lane's outputs: token g0 + 16 t + li, rows row0 + 4 lq .. + 3
   float4 xv[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int j = min(g0 + 16 * t + li, B - 1);
-    xv[t] = *reinterpret_cast<const float4*>(X + (int64_t)j * d + row0 + 4 * lq);
+    xv[t] = load_act4<T>(p.X, p.xdtype, (int64_t)j * d + row0 + 4 * lq);
   }
   __builtin_amdgcn_sched_barrier(0);
-  stage_commit(v, 0, vhi, vlo, wave);
+  stage_commit<T>(v, 0, vt, k, wave);
   const bool two = count - g0 > 16;
   if (two) {
-    stage_issue(v, 1, p.C, k, nullptr, g0, count, B, 0, ns, wave);
-    stage_commit(v, 1, vhi, vlo, wave);
+    stage_issue<T>(v, 1, p.C, GSI_F32, k, nullptr, g0, count, B, 0, k, wave);
+    stage_commit<T>(v, 1, vt, k, wave);
   }
+  weights_clear_tail(w, lq, k, ns);
   __syncthreads();
-  f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int s = 0; s < kSteps; ++s) {
-    if (s < ns) {
-      const bf16x8 a = __builtin_bit_cast(bf16x8, w[s]);
-      const int col = s * kStepCols + 8 * lq;
-      const bf16x8 h0 = *reinterpret_cast<const bf16x8*>(&vhi[li][col]);
-      const bf16x8 l0 = *reinterpret_cast<const bf16x8*>(&vlo[li][col]);
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, h0, acc0, 0, 0, 0);
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, l0, acc0, 0, 0, 0);
-      if (two) {
-        const bf16x8 h1 = *reinterpret_cast<const bf16x8*>(&vhi[16 + li][col]);
-        const bf16x8 l1 = *reinterpret_cast<const bf16x8*>(&vlo[16 + li][col]);
-        acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, h1, acc1, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, l1, acc1, 0, 0, 0);
-      }
-    }
-  }
+  f32x4 acc0, acc1;
+  item_mma<T>(w, vt, li, lq, ns, two, acc0, acc1);
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int j = g0 + 16 * t + li;
@@ -583,7 +619,7 @@ __global__ __launch_bounds__(kTBlock) void tile_residual(const ProjBatch pb) {
   }
   __syncthreads();
   if (!s_last) return;  // uniform
-  norms_and_gate(p, B, pb.gate, pb.eps, reinterpret_cast<float2*>(&vhi[0][0]), reinterpret_cast<int*>(&vlo[0][0]));
+  norms_and_gate(p, B, pb.gate, pb.eps, reinterpret_cast<float2*>(&vt[0][0][0]), reinterpret_cast<int*>(&vt[1][0][0]));
 }
 
 }  // namespace
@@ -592,7 +628,7 @@ int tile_slices(int64_t d) { return (int)ceil_div(d, kSliceCols); }
 
 // ---- projection ---------------------------------------------------------------------------------
 bool tile_project_shape_ok(int64_t d, int64_t k, int64_t B, int udtype) {
-  return udtype == GSI_BF16 && B >= 2 && B <= kMaxTok && d % kItemRows == 0 && k % kPCols == 0 && k <= kSliceCols &&
+  return udtype == GSI_BF16 && B >= 2 && B <= kMaxTok && d % kItemRows == 0 && k % 8 == 0 && k <= kSliceCols &&
          d < (1 << 24);
 }
 
@@ -608,13 +644,12 @@ void tile_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws) {
   t.k = (int)k;
   t.a_rows = tile_slab_rows(d);
   t.a_slabs = (int)ceil_div(d, t.a_rows);
-  t.a_cblocks = (int)(k / kPCols);
+  t.a_cblocks = (int)ceil_div(k, kPCols);
   t.b_rows = kItemRows;
   t.b_slabs = (int)(d / kItemRows);
   t.part_c = reinterpret_cast<float*>(ws);
   t.part_n = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + align_up((size_t)t.a_slabs * B * k * 4, 256));
   t.sync = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(t.part_n) + align_up((size_t)t.b_slabs * B * 2 * 4, 256));
-  t.tile = 1;
 }
 
 hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s) {
@@ -632,24 +667,36 @@ hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, f
   pb.norms = with_norms ? 1 : 0;
   pb.gate = with_gate ? 1 : 0;
   pb.eps = eps;
-  if (pb.B <= 32) tile_proj_partial<1><<<ta, kPBlock, 0, s>>>(pb);
-  else if (pb.B <= 64) tile_proj_partial<2><<<ta, kPBlock, 0, s>>>(pb);
-  else tile_proj_partial<4><<<ta, kPBlock, 0, s>>>(pb);
   const dim3 rgrid((unsigned)ceil_div((int64_t)pb.B * (max_k / 4), kRedOut), (unsigned)pb.n);
-  tile_proj_reduce<<<rgrid, 256, 0, s>>>(pb);
-  tile_residual<<<tb, kTBlock, 0, s>>>(pb);
+  auto launch = [&](auto terms) {
+    constexpr int T = decltype(terms)::value;
+    if (pb.B <= 32) tile_proj_partial<1, T><<<ta, kPBlock, 0, s>>>(pb);
+    else if (pb.B <= 64) tile_proj_partial<2, T><<<ta, kPBlock, 0, s>>>(pb);
+    else tile_proj_partial<4, T><<<ta, kPBlock, 0, s>>>(pb);
+    tile_proj_reduce<<<rgrid, 256, 0, s>>>(pb);
+    tile_residual<T><<<tb, kTBlock, 0, s>>>(pb);
+  };
+  if (pb.t[0].tile == 3) launch(std::integral_constant<int, 3>{});
+  else launch(std::integral_constant<int, 2>{});
   return hipGetLastError();
 }
 
 // shapes the matrix-core linear kernel takes (alignments and the partial-product workspace apart: tile_rows_ok)
 bool tile_rows_shape_ok(int64_t m, int64_t d, int64_t k, int64_t B, int wdtype) {
   return wdtype == GSI_BF16 && B >= 2 && B <= kMaxTok && d % kStepCols == 0 && m % 4 == 0 &&
-         m * d * 2 < (1ll << 32) && (k == 0 || (k % kStepCols == 0 && k <= kSliceCols));
+         m * d * 2 < (1ll << 32) && (k == 0 || (k % 8 == 0 && k <= kSliceCols));
 }
 
 size_t tile_part_bytes(int64_t m, int64_t d, int64_t B) {
   if (B < 2 || B > kMaxTok || d % kStepCols || m % 4) return 0;
   return align_up((size_t)tile_slices(d) * B * m * sizeof(float), 256);
+}
+
+// three terms where the rows ran on fp32 FMAs before this kernel took them: ranks that are no multiple of 32, and bf16
+// activations (themselves a single term)
+int tile_rows_terms(const LinBatch& lb, int group) {
+  const LinGroup& g = lb.g[group];
+  return (!lb.dense && g.k % kStepCols) || ((lb.dense || g.wx) && g.xdtype != GSI_F32) ? 3 : 2;
 }
 
 bool tile_rows_ok(const LinBatch& lb, int wdtype) {
@@ -658,10 +705,10 @@ bool tile_rows_ok(const LinBatch& lb, int wdtype) {
     const LinGroup& g = lb.g[i];
     if (g.d % kStepCols) return false;
     if (lb.dense || g.wx) {
-      if (g.xdtype != GSI_F32 || reinterpret_cast<uintptr_t>(g.X) % 16) return false;
+      if (reinterpret_cast<uintptr_t>(g.X) % 16) return false;
     }
     if (!lb.dense) {
-      if (g.k % kStepCols || g.k > kSliceCols) return false;
+      if (g.k % 8 || g.k > kSliceCols) return false;
       if (reinterpret_cast<uintptr_t>(g.C) % 16 || reinterpret_cast<uintptr_t>(g.R) % 16) return false;
     }
   }
@@ -688,7 +735,8 @@ hipError_t tile_rows_launch(LinBatch& lb, hipStream_t s) {
     total += (int)ceil_div(lb.t[i].m, kItemRows) * lb.t[i].slices;
     if (lb.t[i].m > max_m) max_m = lb.t[i].m;
   }
-  tile_rows<<<total, kTBlock, 0, s>>>(lb);
+  if (tile_rows_terms(lb, 0) == 3) tile_rows<3><<<total, kTBlock, 0, s>>>(lb);
+  else tile_rows<2><<<total, kTBlock, 0, s>>>(lb);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   const dim3 grid((unsigned)ceil_div((int64_t)lb.B * (max_m / 4), kSumOut), (unsigned)lb.n);
   tile_reduce<<<grid, 256, 0, s>>>(lb);
