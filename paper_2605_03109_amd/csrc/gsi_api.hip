@@ -176,7 +176,7 @@ int gsi_build_gram(const void* U, int64_t d, int64_t k, int udtype, float* E, vo
   GSI_REQUIRE_ALIGNED(U, gsi::elem_size(udtype));
   GSI_REQUIRE_ALIGNED(E, 4);
   if (k > 65535 * 16) return fail(GSI_ERR_SHAPE, "gsi_build_gram: k = %lld is too large", (long long)k);
-  hipError_t e = gsi::generic_build_gram(U, d, k, udtype, E, static_cast<hipStream_t>(stream));
+  hipError_t e = gsi::build_gram(U, d, k, udtype, E, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "gsi_build_gram");
   return GSI_OK;
 }

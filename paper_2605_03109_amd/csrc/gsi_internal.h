@@ -15,7 +15,6 @@ inline size_t align_up(size_t a, size_t b) { return (a + b - 1) / b * b; }
 // ---- generic kernels: any shape, element-wise access ---------------------------------------------
 hipError_t generic_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d, int64_t k, int wdtype,
                                hipStream_t s);
-hipError_t generic_build_gram(const void* U, int64_t d, int64_t k, int udtype, float* E, hipStream_t s);
 hipError_t generic_project(const void* U, const void* X, int64_t d, int64_t k, int64_t B, int udtype, int xdtype,
                            float* C, float* R, float* rnorm, float* xnorm, hipStream_t s);
 hipError_t generic_gated_linear(const void* W, const void* M, const float* C, const float* R,
@@ -24,6 +23,9 @@ hipError_t generic_gated_linear(const void* W, const void* M, const float* C, co
                                 int xdtype = 0);  // X: fired tokens get y = W x
 hipError_t generic_dense_linear(const void* W, const void* X, int64_t m, int64_t d, int64_t B, int wdtype,
                                 int xdtype, float* Y, hipStream_t s);
+
+// ---- E = U^T U - I (gsi_gram.hip): any shape -----------------------------------------------------------
+hipError_t build_gram(const void* U, int64_t d, int64_t k, int udtype, float* E, hipStream_t s);
 
 // ---- the image in 8-bit floating point (gsi_fp8.hip) ---------------------------------------------------
 hipError_t quantize_image_fp8(const void* M, int mdtype, int64_t m, int64_t k, uint8_t* M8, float* scale,
