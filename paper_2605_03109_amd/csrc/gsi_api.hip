@@ -85,51 +85,75 @@ static bool mfma_image_ok(int64_t m, int64_t d, int64_t k) {
 static bool mfma_batch_ok(int64_t d, int64_t k, int64_t B) {
   return B > kDecodeMaxB && d % 64 == 0 && k % 64 == 0 && B < (1ll << 30) && B * d < (1ll << 31);
 }
-static size_t mfma_project_ws(int64_t d, int64_t k, int64_t B) {
-  return gsi::align_up((size_t)k * d * 2, 256) + gsi::align_up((size_t)gsi::mfma_res_tiles(d) * B * 2 * 4, 256) +
-         gsi::mfma_part_bytes(B, k, d, gsi::EPI_STORE_F32);
+static size_t mfma_project_ws(int64_t d, int64_t k, int64_t B, bool full) {
+  return gsi::align_up((size_t)k * d * 2, 256) + gsi::align_up((size_t)gsi::mfma_res_tiles(d, full) * B * 2 * 4, 256) +
+         gsi::mfma_part_bytes(B, k, d, gsi::EPI_STORE_F32, full);
 }
 // workspace of one linear map of a call with B tokens: partial products of the decode-batch kernel, or of
 // the split contraction of the prefill-sized W term (dense = 1: of the dense product)
-static size_t map_part_bytes(int64_t m, int64_t d, int64_t B, int dense) {
+static size_t map_part_bytes(int64_t m, int64_t d, int64_t B, int dense, bool full) {
   if (B > kDecodeMaxB)
-    return d % 64 == 0 ? gsi::mfma_part_bytes(B, m, d, dense ? gsi::EPI_STORE_F32 : gsi::EPI_SCATTER_ADD) : 0;
+    return d % 64 == 0 ? gsi::mfma_part_bytes(B, m, d, dense ? gsi::EPI_STORE_F32 : gsi::EPI_SCATTER_ADD, full) : 0;
   return gsi::tile_part_bytes(m, d, B);
 }
 
-// Workspace of a projection.  any_rank: also for ranks that are not 2^j pieces of 16 bytes.  Those have vector kernels
-// as well, but needed no workspace while the generic kernels took them, so a caller that brings only what the other
-// ranks need (any_rank = false) is still served, by the generic kernels.
-static size_t project_ws_bytes(int64_t d, int64_t k, int64_t B, bool any_rank) {
+// Workspaces come in two sizes.  full: what the queries name.  Less: what they named before ranks other than 2^j pieces
+// of 16 bytes had vector kernels (none for those) and prefill-sized products were split as finely as now; a call that
+// brings only that much (a fixed scratch memory it used to fit) is still served, those ranks by the generic kernels.
+static size_t project_ws_bytes(int64_t d, int64_t k, int64_t B, bool full) {
   if (d < 1 || k < 1 || k > d || B < 1) return 0;
-  if (B > kDecodeMaxB) return mfma_batch_ok(d, k, B) ? mfma_project_ws(d, k, B) : 0;
+  if (B > kDecodeMaxB) return mfma_batch_ok(d, k, B) ? mfma_project_ws(d, k, B, full) : 0;
   // the slab partials of the vector projection kernels; sized for the wider of the two dtypes so
   // that the query does not depend on the dtype (generic kernels need none)
   size_t need = 0;
   for (int dt = 0; dt < 2; ++dt) {
-    if (!gsi::decode_project_ok(d, k, dt, nullptr) || !(any_rank || gsi::rank_pow2(k, dt))) continue;
+    if (!gsi::decode_project_ok(d, k, dt, nullptr) || !(full || gsi::rank_pow2(k, dt))) continue;
     const size_t w = gsi::decode_project_ws(d, k, B, dt);
     if (w > need) need = w;
   }
   return need;
 }
 
-size_t gsi_workspace_bytes(int which_call, int64_t m, int64_t d, int64_t k, int64_t B) {
+static size_t call_ws_bytes(int which_call, int64_t m, int64_t d, int64_t k, int64_t B, bool full) {
   switch (which_call) {
     case GSI_CALL_BUILD_IMAGE:
       // the transposed basis of the matrix-core build (bf16 operands); generic kernels need none
       if (m < 1 || d < 1 || k < 1 || k > d || !mfma_image_ok(m, d, k)) return 0;
-      return gsi::align_up((size_t)k * d * 2, 256) + gsi::mfma_part_bytes(m, k, d, gsi::EPI_STORE_BF16);
+      return gsi::align_up((size_t)k * d * 2, 256) + gsi::mfma_part_bytes(m, k, d, gsi::EPI_STORE_BF16, full);
     case GSI_CALL_PROJECT:
-      return project_ws_bytes(d, k, B, true);
+      return project_ws_bytes(d, k, B, full);
     case GSI_CALL_GATED_LINEAR:
     case GSI_CALL_DENSE_LINEAR:
       // partial products of the matrix-core kernels
       if (m < 1 || d < 1 || B < 1) return 0;
-      return map_part_bytes(m, d, B, which_call == GSI_CALL_DENSE_LINEAR);
+      return map_part_bytes(m, d, B, which_call == GSI_CALL_DENSE_LINEAR, full);
     default:
       return 0;
   }
+}
+
+size_t gsi_workspace_bytes(int which_call, int64_t m, int64_t d, int64_t k, int64_t B) {
+  return call_ws_bytes(which_call, m, d, k, B, true);
+}
+
+// does the workspace of a stand-alone call have the full size?  (GSI_OK: at least the smaller one)
+static int check_call_ws(const char* fn, int which_call, int64_t m, int64_t d, int64_t k, int64_t B, const void* ws,
+                         size_t ws_bytes, bool& full) {
+  full = ws_bytes >= call_ws_bytes(which_call, m, d, k, B, true) && aligned(ws, 256);
+  return full ? check_ws(fn, ws, ws_bytes, call_ws_bytes(which_call, m, d, k, B, true))
+              : check_ws(fn, ws, ws_bytes, call_ws_bytes(which_call, m, d, k, B, false));
+}
+
+// D[M,N] = A[M,K] B[N,K]^T (unsplit unless the caller adds a workspace)
+static gsi::GemmProb gemm_prob(const void* A, int64_t lda, const void* B, int64_t ldb, void* D, int64_t ldd, int64_t M,
+                               int64_t N, int64_t K, int epi) {
+  gsi::GemmProb g;
+  std::memset(&g, 0, sizeof(g));
+  g.A = A; g.B = B; g.D = D;
+  g.lda = (int)lda; g.ldb = (int)ldb; g.ldd = (int)ldd;
+  g.M = (int)M; g.N = (int)N; g.K = (int)K;
+  g.epi = epi; g.max_splits = 1;
+  return g;
 }
 
 int gsi_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d, int64_t k, int wdtype, void* ws,
@@ -143,23 +167,20 @@ int gsi_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d,
   GSI_REQUIRE_ALIGNED(W, es);
   GSI_REQUIRE_ALIGNED(U, es);
   GSI_REQUIRE_ALIGNED(M, es);
-  if (int rc = check_ws("gsi_build_image", ws, ws_bytes, gsi_workspace_bytes(GSI_CALL_BUILD_IMAGE, m, d, k, 0)))
-    return rc;
+  bool full;
+  if (int rc = check_call_ws("gsi_build_image", GSI_CALL_BUILD_IMAGE, m, d, k, 0, ws, ws_bytes, full)) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (wdtype == GSI_BF16 && mfma_image_ok(m, d, k) && aligned(W, 16) && aligned(U, 2) && aligned(M, 8)) {
     // matrix cores: M = W (U^T)^T with the basis transposed once into the workspace
-    e = gsi::mfma_transpose_bf16(U, ws, (int)d, (int)k, s);
+    gsi::TransposeTask tr{U, ws, (int)d, (int)k, 0};
+    e = gsi::mfma_transpose_bf16(&tr, 1, s);
     if (e == hipSuccess) {
-      gsi::GemmArgs g;
-      std::memset(&g, 0, sizeof(g));
-      g.A = W; g.lda = d; g.a_f32 = 0;
-      g.B = ws; g.ldb = d;
-      g.D = M; g.ldd = k;
-      g.M = (int)m; g.N = (int)k; g.K = (int)d;
-      if (gsi::mfma_part_bytes(m, k, d, gsi::EPI_STORE_BF16))
+      gsi::GemmProb g = gemm_prob(W, d, ws, d, M, k, m, k, d, gsi::EPI_STORE_BF16);
+      g.max_splits = gsi::mfma_splits(m, k, d, gsi::EPI_STORE_BF16, full);
+      if (g.max_splits > 1)
         g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + gsi::align_up((size_t)k * d * 2, 256));
-      e = gsi::mfma_gemm_nt(g, gsi::EPI_STORE_BF16, s);
+      e = gsi::mfma_gemm_nt(&g, 1, 0, gsi::EPI_STORE_BF16, s);
     }
   } else {
     e = gsi::generic_build_image(W, U, M, m, d, k, wdtype, s);
@@ -348,8 +369,8 @@ static int check_gated_args(const char* fn, const void* W, const void* M, const 
   return GSI_OK;
 }
 
-static bool project_vector_path(int64_t d, int64_t k, int64_t B, int udtype, const void* U, bool any_rank) {
-  return B <= kDecodeMaxB && gsi::decode_project_ok(d, k, udtype, U) && (any_rank || gsi::rank_pow2(k, udtype));
+static bool project_vector_path(int64_t d, int64_t k, int64_t B, int udtype, const void* U, bool full) {
+  return B <= kDecodeMaxB && gsi::decode_project_ok(d, k, udtype, U) && (full || gsi::rank_pow2(k, udtype));
 }
 
 static void fill_proj_task(gsi::ProjTask& t, const void* U, const void* X, int64_t d, int64_t k, int64_t B,
@@ -359,57 +380,77 @@ static void fill_proj_task(gsi::ProjTask& t, const void* U, const void* X, int64
   gsi::decode_project_fill(t, d, k, B, ws);
 }
 
-// Prefill-sized projection on the matrix cores: C = X U, R = X - C U^T with per-tile partial norms, then
-// the norm (+ gate) kernel.  `gate` may be null (norms only).
-// `img` (optional): image terms Y = C M^T of maps that read this input; they need c only, so they ride in the
-// residual's launch as further right-hand factors of the same left operand.
+// Prefill-sized projections of independent inputs on the matrix cores: C = X U, then R = X - C U^T with per-tile partial
+// norms and, beside it, the image terms Y = C M^T of maps that read the inputs (they need c only), then norms and gate.
+// Every step is one launch over all inputs: a block's four used to take 36 launches that each filled the chip a few times
+// at most, with a ramp, a tail and a partial last round of their own.
+struct MfmaInput {
+  const void* U;
+  const void* X;
+  int64_t d, k;
+  int xdtype;
+  float *C, *R, *rnorm, *xnorm;
+  uint8_t* mask;
+  int32_t* fired_idx;
+  int32_t* n_fired;
+  char* ws;
+};
 struct ImageRider {
+  int in;           // index of the input
   const void* M;
   float* Y;
   int64_t m;
 };
-static hipError_t mfma_project(const void* U, const void* X, int64_t d, int64_t k, int64_t B, int xdtype, float* C,
-                               float* R, float* rnorm, float* xnorm, uint8_t* mask, int32_t* fired_idx,
-                               int32_t* n_fired, bool with_gate, float eps, void* ws, hipStream_t s,
-                               const ImageRider* img = nullptr, int n_img = 0) {
-  void* Ut = ws;
-  float* part_n = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + gsi::align_up((size_t)k * d * 2, 256));
-  hipError_t e = gsi::mfma_transpose_bf16(U, Ut, (int)d, (int)k, s);
-  if (e != hipSuccess) return e;
-  gsi::GemmArgs g;
-  std::memset(&g, 0, sizeof(g));
-  g.A = X; g.lda = d; g.a_f32 = xdtype == GSI_F32;
-  g.B = Ut; g.ldb = d;
-  g.D = C; g.ldd = k;
-  g.M = (int)B; g.N = (int)k; g.K = (int)d;
-  if (gsi::mfma_part_bytes(B, k, d, gsi::EPI_STORE_F32))
-    g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + gsi::align_up((size_t)k * d * 2, 256) +
-                                      gsi::align_up((size_t)gsi::mfma_res_tiles(d) * B * 2 * 4, 256));
-  e = gsi::mfma_gemm_nt(g, gsi::EPI_STORE_F32, s);
-  if (e != hipSuccess) return e;
-  std::memset(&g, 0, sizeof(g));
-  g.A = C; g.lda = k; g.a_f32 = 1;
-  g.B = U; g.ldb = k;
-  g.D = R; g.ldd = d;
-  g.M = (int)B; g.N = (int)d; g.K = (int)k;
-  g.X = X; g.xdtype = xdtype; g.ldx = d; g.part_n = part_n; g.part_tokens = (int)B;
-  if (n_img > 0) {
-    g.nseg = 1 + n_img;
-    g.seg[0] = gsi::GemmSeg{U, k, R, d, (int)d, 0, gsi::EPI_RESIDUAL};
-    for (int q = 0; q < n_img; ++q) g.seg[1 + q] = gsi::GemmSeg{img[q].M, k, img[q].Y, img[q].m, (int)img[q].m, 0, gsi::EPI_STORE_F32};
-    e = gsi::mfma_gemm_nt(g, gsi::EPI_MULTI, s);
-  } else {
-    e = gsi::mfma_gemm_nt(g, gsi::EPI_RESIDUAL, s);
+static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img, int n_img, int64_t B, bool with_gate,
+                               float eps, bool full, hipStream_t s) {
+  static thread_local std::vector<gsi::TransposeTask> tr;
+  static thread_local std::vector<gsi::GemmProb> pr;
+  tr.clear();
+  for (int i = 0; i < n; ++i) tr.push_back(gsi::TransposeTask{in[i].U, in[i].ws, (int)in[i].d, (int)in[i].k, 0});
+  if (hipError_t e = gsi::mfma_transpose_bf16(tr.data(), n, s); e != hipSuccess) return e;
+  auto part_n = [&](int i) { return reinterpret_cast<float*>(in[i].ws + gsi::align_up((size_t)in[i].k * in[i].d * 2, 256)); };
+  for (int xdt = 0; xdt < 2; ++xdt) {
+    pr.clear();
+    for (int i = 0; i < n; ++i) {
+      const int64_t d = in[i].d, k = in[i].k;
+      if (in[i].xdtype != xdt) continue;
+      gsi::GemmProb g = gemm_prob(in[i].X, d, in[i].ws, d, in[i].C, k, B, k, d, gsi::EPI_STORE_F32);
+      g.max_splits = gsi::mfma_splits(B, k, d, gsi::EPI_STORE_F32, full);
+      if (g.max_splits > 1)
+        g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(part_n(i)) +
+                                          gsi::align_up((size_t)gsi::mfma_res_tiles(d, full) * B * 2 * 4, 256));
+      pr.push_back(g);
+    }
+    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s); e != hipSuccess)
+      return e;
   }
-  if (e != hipSuccess) return e;
-  gsi::ProjBatch pb;
-  std::memset(&pb, 0, sizeof(pb));
-  pb.n = 1;
-  pb.B = (int)B;
-  pb.t[0].part_n = part_n; pb.t[0].b_slabs = gsi::mfma_res_tiles(d);
-  pb.t[0].rnorm = rnorm; pb.t[0].xnorm = xnorm;
-  pb.t[0].mask = mask; pb.t[0].fired_idx = fired_idx; pb.t[0].n_fired = n_fired;
-  return gsi::decode_norms_launch(pb, with_gate, eps, s);
+  pr.clear();
+  for (int i = 0; i < n; ++i) {
+    gsi::GemmProb g = gemm_prob(in[i].C, in[i].k, in[i].U, in[i].k, in[i].R, in[i].d, B, in[i].d, in[i].k, gsi::EPI_RESIDUAL);
+    g.X = in[i].X; g.xdtype = in[i].xdtype;
+    g.part_n = part_n(i);
+    g.sync = reinterpret_cast<unsigned*>(in[i].ws);  // (the transposed basis is not read any more)
+    pr.push_back(g);
+    for (int q = 0; q < n_img; ++q)
+      if (img[q].in == i)
+        pr.push_back(gemm_prob(in[i].C, in[i].k, img[q].M, in[i].k, img[q].Y, img[q].m, B, img[q].m, in[i].k, gsi::EPI_STORE_F32));
+  }
+  for (gsi::GemmProb& g : pr) g.res_cols = full ? 64 : 128;
+  if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), 1, gsi::EPI_PROJECTED, s); e != hipSuccess) return e;
+  for (int i = 0; i < n;) {
+    gsi::ProjBatch pb;
+    std::memset(&pb, 0, sizeof(pb));
+    pb.B = (int)B;
+    for (; i < n && pb.n < gsi::kMaxTasks; ++i) {
+      gsi::ProjTask& t = pb.t[pb.n++];
+      t.part_n = part_n(i); t.b_slabs = gsi::mfma_res_tiles(in[i].d, full);
+      t.sync = reinterpret_cast<unsigned*>(in[i].ws);
+      t.rnorm = in[i].rnorm; t.xnorm = in[i].xnorm;
+      t.mask = in[i].mask; t.fired_idx = in[i].fired_idx; t.n_fired = in[i].n_fired;
+    }
+    if (hipError_t e = gsi::decode_norms_launch(pb, with_gate, eps, s); e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 static bool mfma_project_path(const void* U, const void* X, int64_t d, int64_t k, int64_t B, int udtype, int xdtype,
@@ -418,37 +459,47 @@ static bool mfma_project_path(const void* U, const void* X, int64_t d, int64_t k
          aligned(R, 16) && (xdtype == GSI_F32 || xdtype == GSI_BF16);
 }
 
-// Prefill-sized gated map on the matrix cores: Y = C M^T for every token, then Y[fired] += R[fired] W^T
-// over the compacted list (row tiles beyond the device-side count exit at once).
-static hipError_t mfma_gated(const void* W, const void* M, const float* C, const float* R, const int32_t* fired_idx,
-                             const int32_t* n_fired, int64_t m, int64_t d, int64_t k, int64_t B, float* Y,
-                             float* part, hipStream_t s, const void* Xwx = nullptr, int xdtype = 0,
-                             bool image_done = false) {
-  gsi::GemmArgs g;
-  hipError_t e = hipSuccess;
-  if (!image_done) {
-    std::memset(&g, 0, sizeof(g));
-    g.A = C; g.lda = k; g.a_f32 = 1;
-    g.B = M; g.ldb = k;
-    g.D = Y; g.ldd = m;
-    g.M = (int)B; g.N = (int)m; g.K = (int)k;
-    e = gsi::mfma_gemm_nt(g, gsi::EPI_STORE_F32, s);
-    if (e != hipSuccess) return e;
-  }
-  std::memset(&g, 0, sizeof(g));
-  // r enters rounded once to bf16: its term is scaled by the residual ratio, so the rounding (2^-9 relative)
+// Prefill-sized gated maps on the matrix cores: Y = C M^T for every token (unless an earlier launch wrote it), then
+// Y[fired] += R[fired] W^T over the compacted list (row tiles beyond the device-side count exit at once); one launch of
+// each over all maps.
+struct MfmaMap {
+  const void* W;
+  const void* M;
+  const float* C;
+  const float* R;
+  const void* Xwx;   // fired tokens get y = W x, fed exactly as the dense product feeds x; else null
+  int xdtype;
+  const int32_t* fired_idx;
+  const int32_t* n_fired;
+  int64_t m, d, k;
+  float* Y;
+  float* part;
+  bool image_done;
+};
+static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, bool full, hipStream_t s) {
+  static thread_local std::vector<gsi::GemmProb> pr;
+  pr.clear();
+  for (int j = 0; j < n; ++j)
+    if (!mp[j].image_done)
+      pr.push_back(gemm_prob(mp[j].C, mp[j].k, mp[j].M, mp[j].k, mp[j].Y, mp[j].m, B, mp[j].m, mp[j].k, gsi::EPI_STORE_F32));
+  if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), 1, gsi::EPI_STORE_F32, s); e != hipSuccess) return e;
+  // r enters rounded once to bf16 (mode 2): its term is scaled by the residual ratio, so the rounding (2^-9 relative)
   // adds a few 1e-4 of |y| at most, beside the 1.7e-3 that the bf16 image already costs
-  g.A = R; g.lda = d; g.a_f32 = 2;
-  if (Xwx) {  // fired tokens get y = W x, fed exactly as the dense product feeds x
-    g.A = Xwx;
-    g.a_f32 = xdtype == GSI_F32 ? 1 : 0;
+  for (int mode = 0; mode < 3; ++mode) {
+    pr.clear();
+    for (int j = 0; j < n; ++j) {
+      const MfmaMap& q = mp[j];
+      if (mode != (!q.Xwx ? 2 : q.xdtype == GSI_F32 ? 1 : 0)) continue;
+      const int epi = q.Xwx ? gsi::EPI_SCATTER_STORE : gsi::EPI_SCATTER_ADD;
+      gsi::GemmProb g = gemm_prob(q.Xwx ? q.Xwx : q.R, q.d, q.W, q.d, q.Y, q.m, B, q.m, q.d, epi);
+      g.row_idx = q.fired_idx; g.n_rows_dev = q.n_fired;
+      g.max_splits = gsi::mfma_splits(B, q.m, q.d, epi, full);
+      g.part = g.max_splits > 1 ? q.part : nullptr;
+      pr.push_back(g);
+    }
+    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), mode, gsi::EPI_SCATTER, s); e != hipSuccess) return e;
   }
-  g.B = W; g.ldb = d;
-  g.D = Y; g.ldd = m;
-  g.M = (int)B; g.N = (int)m; g.K = (int)d;
-  g.row_idx = fired_idx; g.n_rows_dev = n_fired;
-  g.part = gsi::mfma_part_bytes(B, m, d, gsi::EPI_SCATTER_ADD) ? part : nullptr;
-  return gsi::mfma_gemm_nt(g, Xwx ? gsi::EPI_SCATTER_STORE : gsi::EPI_SCATTER_ADD, s);
+  return hipSuccess;
 }
 
 static bool mfma_gated_path(const void* W, const void* M, const float* C, const float* R, int64_t d, int64_t k,
@@ -463,16 +514,12 @@ static bool mfma_dense_path(const void* W, const void* X, int64_t m, int64_t d, 
   return wdtype == GSI_BF16 && B > kDecodeMaxB && d % 64 == 0 && m % 4 == 0 && B * m < (1ll << 31) &&
          aligned(W, 16) && aligned(X, 16) && aligned(Y, 16);
 }
-static hipError_t mfma_dense(const void* W, const void* X, int64_t m, int64_t d, int64_t B, int xdtype, float* Y,
-                             float* part, hipStream_t s) {
-  gsi::GemmArgs g;
-  std::memset(&g, 0, sizeof(g));
-  g.A = X; g.lda = d; g.a_f32 = xdtype == GSI_F32;
-  g.B = W; g.ldb = d;
-  g.D = Y; g.ldd = m;
-  g.M = (int)B; g.N = (int)m; g.K = (int)d;
-  g.part = gsi::mfma_part_bytes(B, m, d, gsi::EPI_STORE_F32) ? part : nullptr;
-  return gsi::mfma_gemm_nt(g, gsi::EPI_STORE_F32, s);
+static gsi::GemmProb mfma_dense_prob(const void* W, const void* X, int64_t m, int64_t d, int64_t B, float* Y, float* part,
+                                     bool full) {
+  gsi::GemmProb g = gemm_prob(X, d, W, d, Y, m, B, m, d, gsi::EPI_STORE_F32);
+  g.max_splits = gsi::mfma_splits(B, m, d, gsi::EPI_STORE_F32, full);
+  g.part = g.max_splits > 1 ? part : nullptr;
+  return g;
 }
 
 static void clear(gsi::LinBatch& lb, int64_t B) {
@@ -554,11 +601,11 @@ int gsi_project(const void* U, const void* X, int64_t d, int64_t k, int64_t B, i
                 float* R, float* rnorm, float* xnorm, void* ws, size_t ws_bytes, void* stream) {
   if (int rc = check_project_args("gsi_project", U, X, d, k, B, udtype, xdtype, C, R, rnorm, xnorm)) return rc;
   if (B == 0) return GSI_OK;
-  if (int rc = check_ws("gsi_project", ws, ws_bytes, project_ws_bytes(d, k, B, false))) return rc;
-  const bool any_rank = ws && aligned(ws, 256) && ws_bytes >= project_ws_bytes(d, k, B, true);
+  bool full;
+  if (int rc = check_call_ws("gsi_project", GSI_CALL_PROJECT, 0, d, k, B, ws, ws_bytes, full)) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
-  if (project_vector_path(d, k, B, udtype, U, any_rank)) {
+  if (project_vector_path(d, k, B, udtype, U, full)) {
     gsi::ProjBatch pb;
     std::memset(&pb, 0, sizeof(pb));
     pb.n = 1;
@@ -566,7 +613,8 @@ int gsi_project(const void* U, const void* X, int64_t d, int64_t k, int64_t B, i
     fill_proj_task(pb.t[0], U, X, d, k, B, udtype, xdtype, C, R, rnorm, xnorm, ws);
     e = gsi::decode_project_launch(pb, udtype, true, false, 0.f, s);
   } else if (mfma_project_path(U, X, d, k, B, udtype, xdtype, C, R)) {
-    e = mfma_project(U, X, d, k, B, xdtype, C, R, rnorm, xnorm, nullptr, nullptr, nullptr, false, 0.f, ws, s);
+    const MfmaInput in{U, X, d, k, xdtype, C, R, rnorm, xnorm, nullptr, nullptr, nullptr, static_cast<char*>(ws)};
+    e = mfma_project(&in, 1, nullptr, 0, B, false, 0.f, full, s);
   } else {
     e = gsi::generic_project(U, X, d, k, B, udtype, xdtype, C, R, rnorm, xnorm, s);
   }
@@ -589,8 +637,8 @@ int gsi_gated_linear(const void* W, const void* M, const float* C, const float* 
   if (int rc = check_gated_args("gsi_gated_linear", W, M, C, R, fired_idx, n_fired, m, d, k, B, wdtype, Y, ydtype))
     return rc;
   if (B == 0) return GSI_OK;
-  if (int rc = check_ws("gsi_gated_linear", ws, ws_bytes, gsi_workspace_bytes(GSI_CALL_GATED_LINEAR, m, d, k, B)))
-    return rc;
+  bool full;
+  if (int rc = check_call_ws("gsi_gated_linear", GSI_CALL_GATED_LINEAR, m, d, k, B, ws, ws_bytes, full)) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (!mfma_gated_path(W, M, C, R, d, k, B, wdtype, m, Y) && gsi::decode_linear_ok(m, d, k, wdtype, W, M, B) &&
@@ -605,7 +653,8 @@ int gsi_gated_linear(const void* W, const void* M, const float* C, const float* 
     e = bt.add(0, gd, W, M, (float*)Y, m, B == 1, gsi::tile_part_bytes(m, d, B) ? (float*)ws : nullptr);
     if (e == hipSuccess) e = bt.flush();
   } else if (mfma_gated_path(W, M, C, R, d, k, B, wdtype, m, Y)) {
-    e = mfma_gated(W, M, C, R, fired_idx, n_fired, m, d, k, B, (float*)Y, (float*)ws, s);
+    const MfmaMap mp{W, M, C, R, nullptr, 0, fired_idx, n_fired, m, d, k, (float*)Y, (float*)ws, false};
+    e = mfma_gated(&mp, 1, B, full, s);
   } else {
     e = gsi::generic_gated_linear(W, M, C, R, fired_idx, n_fired, m, d, k, B, wdtype, (float*)Y, s);
   }
@@ -625,12 +674,13 @@ int gsi_dense_linear(const void* W, const void* X, int64_t m, int64_t d, int64_t
   GSI_REQUIRE_ALIGNED(W, gsi::elem_size(wdtype));
   GSI_REQUIRE_ALIGNED(X, gsi::elem_size(xdtype));
   GSI_REQUIRE_ALIGNED(Y, 4);
-  if (int rc = check_ws("gsi_dense_linear", ws, ws_bytes, gsi_workspace_bytes(GSI_CALL_DENSE_LINEAR, m, d, 0, B)))
-    return rc;
+  bool full;
+  if (int rc = check_call_ws("gsi_dense_linear", GSI_CALL_DENSE_LINEAR, m, d, 0, B, ws, ws_bytes, full)) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (mfma_dense_path(W, X, m, d, B, wdtype, Y)) {
-    e = mfma_dense(W, X, m, d, B, xdtype, Y, (float*)ws, s);
+    const gsi::GemmProb g = mfma_dense_prob(W, X, m, d, B, Y, (float*)ws, full);
+    e = gsi::mfma_gemm_nt(&g, 1, xdtype == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s);
   } else if (gsi::decode_linear_ok(m, d, 0, wdtype, W, nullptr, B) && aligned(X, 16) &&
              long_batch_ok(d, B, Y, true, X, xdtype)) {
     gsi::LinBatch lb;
@@ -655,14 +705,14 @@ static bool wx_vector_ok(const gsi_input_desc& in) {
 
 // Is the E4M3 image of this map read as codes?  Only by the single-token vector kernels; every other call
 // expands it (exactly) to the weights' type in the workspace first and runs the map with an ordinary image.
-static bool fp8_codes_read(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B, bool any_rank) {
+static bool fp8_codes_read(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B, bool full) {
   return B == 1 && aligned(mp.M, 16) && in.k % 16 == 0 && in.k <= gsi::kMaxK &&
-         project_vector_path(in.d, in.k, B, in.udtype, in.U, any_rank) &&
+         project_vector_path(in.d, in.k, B, in.udtype, in.U, full) &&
          gsi::decode_linear_ok(mp.m, in.d, in.k, mp.wdtype, mp.W, nullptr, B) && aligned(in.C, 16) && aligned(in.R, 16) &&
          wx_vector_ok(in);
 }
-static size_t fp8_expand_bytes(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B, bool any_rank) {
-  if (!(mp.flags & GSI_MAP_IMAGE_FP8) || B < 1 || mp.m < 1 || in.k < 1 || fp8_codes_read(mp, in, B, any_rank)) return 0;
+static size_t fp8_expand_bytes(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B, bool full) {
+  if (!(mp.flags & GSI_MAP_IMAGE_FP8) || B < 1 || mp.m < 1 || in.k < 1 || fp8_codes_read(mp, in, B, full)) return 0;
   return gsi::align_up((size_t)mp.m * in.k * gsi::elem_size(mp.wdtype), 256);
 }
 
@@ -675,23 +725,23 @@ static size_t stack_table_bytes(int32_t n_maps, int32_t n_inputs, int64_t B) {
 }
 
 static size_t stack_ws_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int32_t n_inputs,
-                             int64_t B, bool any_rank) {
+                             int64_t B, bool full) {
   if (!inputs || n_inputs < 0) return 0;
   // projections of independent inputs share a launch, so every input has its own region
   size_t need = stack_table_bytes(maps ? n_maps : 0, n_inputs, B);
   for (int i = 0; i < n_inputs; ++i)
-    need += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, any_rank), 256);
+    need += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, full), 256);
   // and so do the maps of a decode batch (partial products of the weight term)
   if (maps)
     for (int j = 0; j < n_maps; ++j) {
       const int id = maps[j].input_id;
-      if (id >= 0 && id < n_inputs) need += map_part_bytes(maps[j].m, inputs[id].d, B, 0);
+      if (id >= 0 && id < n_inputs) need += map_part_bytes(maps[j].m, inputs[id].d, B, 0, full);
     }
   // E4M3 images that are not read as codes are expanded to the weights' type
   if (maps)
     for (int j = 0; j < n_maps; ++j) {
       const int id = maps[j].input_id;
-      if (id >= 0 && id < n_inputs) need += fp8_expand_bytes(maps[j], inputs[id], B, any_rank);
+      if (id >= 0 && id < n_inputs) need += fp8_expand_bytes(maps[j], inputs[id], B, full);
     }
   return need;
 }
@@ -771,15 +821,20 @@ int gsi_layer_stack_timed(const gsi_map_desc* maps, int32_t n_maps, const gsi_in
   return GSI_OK;
 }
 
-size_t gsi_dense_stack_workspace_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs,
-                                       int32_t n_inputs, int64_t B) {
+static size_t dense_stack_ws_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int32_t n_inputs,
+                                   int64_t B, bool full) {
   if (!maps || !inputs || n_maps < 0 || n_inputs < 0) return 0;
   size_t need = 0;  // partial products of the several-token matrix-core kernel, one region per map
   for (int j = 0; j < n_maps; ++j) {
     const int id = maps[j].input_id;
-    if (id >= 0 && id < n_inputs) need += map_part_bytes(maps[j].m, inputs[id].d, B, 1);
+    if (id >= 0 && id < n_inputs) need += map_part_bytes(maps[j].m, inputs[id].d, B, 1, full);
   }
   return need;
+}
+
+size_t gsi_dense_stack_workspace_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs,
+                                       int32_t n_inputs, int64_t B) {
+  return dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true);
 }
 
 int gsi_dense_stack(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int32_t n_inputs,
@@ -804,26 +859,30 @@ int gsi_dense_stack(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_de
     }
   }
   if (B == 0) return GSI_OK;
-  if (int rc = check_ws(fn, ws, ws_bytes, gsi_dense_stack_workspace_bytes(maps, n_maps, inputs, n_inputs, B)))
-    return rc;
+  const bool full = ws_bytes >= dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true);
+  if (int rc = check_ws(fn, ws, ws_bytes, dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, full))) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   std::vector<float*> part(n_maps, nullptr);
   {
     size_t off = 0;
     for (int j = 0; j < n_maps; ++j) {
-      const size_t pb = map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 1);
+      const size_t pb = map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 1, full);
       if (pb) part[j] = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + off);
       off += pb;
     }
   }
   std::vector<char> done(n_maps, 0);
-  for (int j = 0; j < n_maps; ++j) {  // prefill-sized batches: one matrix-core product per map
-    const gsi_map_desc& mp = maps[j];
-    const gsi_input_desc& in = inputs[mp.input_id];
-    if (!mfma_dense_path(mp.W, in.X, mp.m, in.d, B, mp.wdtype, mp.Y)) continue;
-    if (hipError_t e = mfma_dense(mp.W, in.X, mp.m, in.d, B, in.xdtype, mp.Y, part[j], s); e != hipSuccess)
+  for (int xdt = 0; xdt < 2; ++xdt) {  // prefill-sized batches: the matrix-core products of all maps in one launch
+    std::vector<gsi::GemmProb> pr;
+    for (int j = 0; j < n_maps; ++j) {
+      const gsi_map_desc& mp = maps[j];
+      const gsi_input_desc& in = inputs[mp.input_id];
+      if (in.xdtype != xdt || !mfma_dense_path(mp.W, in.X, mp.m, in.d, B, mp.wdtype, mp.Y)) continue;
+      pr.push_back(mfma_dense_prob(mp.W, in.X, mp.m, in.d, B, mp.Y, part[j], full));
+      done[j] = 1;
+    }
+    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s); e != hipSuccess)
       return hip_fail(e, fn);
-    done[j] = 1;
   }
   for (int dt = 0; dt < 2; ++dt) {
     LinBatcher bt;
@@ -908,8 +967,8 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
     }
   }
   const size_t need_any = stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true);
-  const bool any_rank = ws_bytes >= need_any;  // (see project_ws_bytes)
-  if (int rc = check_ws(fn, ws, ws_bytes, any_rank ? need_any : stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, false)))
+  const bool full = ws_bytes >= need_any;  // (else the smaller workspace: see project_ws_bytes)
+  if (int rc = check_ws(fn, ws, ws_bytes, full ? need_any : stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, false)))
     return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
 
@@ -931,10 +990,10 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
     size_t off = stack_table_bytes(n_maps, n_inputs, B);
     for (int i = 0; i < n_inputs; ++i) {
       ws_off[i] = off;
-      off += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, any_rank), 256);
+      off += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, full), 256);
     }
     for (int j = 0; j < n_maps; ++j) {
-      const size_t pb = map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 0);
+      const size_t pb = map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 0, full);
       if (pb) part[j] = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + off);
       off += pb;
     }
@@ -947,11 +1006,11 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
   if (B > 0) {
     size_t off = stack_table_bytes(n_maps, n_inputs, B);
     for (int i = 0; i < n_inputs; ++i)
-      off += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, any_rank), 256);
-    for (int j = 0; j < n_maps; ++j) off += map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 0);
+      off += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, full), 256);
+    for (int j = 0; j < n_maps; ++j) off += map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 0, full);
     for (int j = 0; j < n_maps; ++j) {
       const gsi_input_desc& in = inputs[maps[j].input_id];
-      const size_t bytes = fp8_expand_bytes(maps[j], in, B, any_rank);
+      const size_t bytes = fp8_expand_bytes(maps[j], in, B, full);
       if (!bytes) continue;
       if (expanded.empty()) expanded.assign(maps, maps + n_maps);
       void* tmp = reinterpret_cast<char*>(ws) + off;
@@ -979,7 +1038,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
   for (int i = 0; i < n_inputs; ++i) {
     const gsi_input_desc& in = inputs[i];
     std::memset(&ptask[i], 0, sizeof(gsi::ProjTask));
-    if (B == 0 || !project_vector_path(in.d, in.k, B, in.udtype, in.U, any_rank)) continue;
+    if (B == 0 || !project_vector_path(in.d, in.k, B, in.udtype, in.U, full)) continue;
     mode[i] = kVecGate;
     fill_proj_task(ptask[i], in.U, in.X, in.d, in.k, B, in.udtype, in.xdtype, in.C, in.R, in.rnorm, in.xnorm,
                    reinterpret_cast<char*>(ws) + ws_off[i]);
@@ -1303,26 +1362,33 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
           return hip_fail(e, fn);
       }
     }
+    if (B > kDecodeMaxB) {  // prefill-sized: every ready input that takes the matrix cores, and its maps' image terms
+      static thread_local std::vector<MfmaInput> min;
+      static thread_local std::vector<ImageRider> riders;
+      min.clear();
+      riders.clear();
+      for (int i : ready) {
+        const gsi_input_desc& in = inputs[i];
+        if (mode[i] != kGeneric || !mfma_project_path(in.U, in.X, in.d, in.k, B, in.udtype, in.xdtype, in.C, in.R)) continue;
+        for (int j = 0; j < n_maps; ++j) {
+          const gsi_map_desc& mp = maps[j];
+          if (mp.input_id != i || img_done[j]) continue;
+          if (!mfma_gated_path(mp.W, mp.M, in.C, in.R, in.d, in.k, B, mp.wdtype, mp.m, mp.Y) || !wx_vector_ok(in)) continue;
+          riders.push_back(ImageRider{(int)min.size(), mp.M, mp.Y, mp.m});
+          img_done[j] = 1;
+        }
+        min.push_back(MfmaInput{in.U, in.X, in.d, in.k, in.xdtype, in.C, in.R, in.rnorm, in.xnorm, in.mask, in.fired_idx,
+                                in.n_fired, reinterpret_cast<char*>(ws) + ws_off[i]});
+      }
+      if (!min.empty())
+        if (hipError_t e = mfma_project(min.data(), (int)min.size(), riders.data(), (int)riders.size(), B, true, eps, full, s);
+            e != hipSuccess)
+          return hip_fail(e, fn);
+    }
     for (int i : ready) {
       const gsi_input_desc& in = inputs[i];
       if (mode[i] == kGeneric) {
-        if (B > 0 && mfma_project_path(in.U, in.X, in.d, in.k, B, in.udtype, in.xdtype, in.C, in.R)) {
-          // image terms of this input's maps that take the matrix-core path ride in the residual's launch
-          ImageRider riders[gsi::kMaxGemmSegs - 1];
-          int n_riders = 0;
-          for (int j = 0; j < n_maps && n_riders < gsi::kMaxGemmSegs - 1; ++j) {
-            const gsi_map_desc& mp = maps[j];
-            if (mp.input_id != i || img_done[j]) continue;
-            if (!mfma_gated_path(mp.W, mp.M, in.C, in.R, in.d, in.k, B, mp.wdtype, mp.m, mp.Y) || !wx_vector_ok(in))
-              continue;
-            riders[n_riders++] = ImageRider{mp.M, mp.Y, mp.m};
-            img_done[j] = 1;
-          }
-          hipError_t e = mfma_project(in.U, in.X, in.d, in.k, B, in.xdtype, in.C, in.R, in.rnorm, in.xnorm, in.mask,
-                                      in.fired_idx, in.n_fired, true, eps, reinterpret_cast<char*>(ws) + ws_off[i], s,
-                                      riders, n_riders);
-          if (e != hipSuccess) return hip_fail(e, fn);
-        } else {
+        if (!(B > 0 && mfma_project_path(in.U, in.X, in.d, in.k, B, in.udtype, in.xdtype, in.C, in.R))) {
           if (B > 0) {
             hipError_t e = gsi::generic_project(in.U, in.X, in.d, in.k, B, in.udtype, in.xdtype, in.C, in.R,
                                                 in.rnorm, in.xnorm, s);
@@ -1457,17 +1523,28 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
       }
       if (hipError_t e = bt.flush(); e != hipSuccess) return hip_fail(e, fn);
     }
+    if (B > kDecodeMaxB) {  // prefill-sized maps
+      static thread_local std::vector<MfmaMap> mm;
+      mm.clear();
+      for (int j : mready) {
+        const gsi_map_desc& mp = maps[j];
+        const gsi_input_desc& in = inputs[mp.input_id];
+        if (map_done[j] == 2 || map_fused[j] || !mfma_gated_path(mp.W, mp.M, in.C, in.R, in.d, in.k, B, mp.wdtype, mp.m, mp.Y) ||
+            !wx_vector_ok(in))
+          continue;
+        mm.push_back(MfmaMap{mp.W, mp.M, in.C, in.R, (in.flags & GSI_INPUT_SLOW_PATH_WX) ? in.X : nullptr, in.xdtype, in.fired_idx,
+                             in.n_fired, mp.m, in.d, in.k, mp.Y, part[j], img_done[j] != 0});
+        map_done[j] = 2;
+      }
+      if (!mm.empty())
+        if (hipError_t e = mfma_gated(mm.data(), (int)mm.size(), B, full, s); e != hipSuccess) return hip_fail(e, fn);
+    }
     for (int j : mready) {
       const gsi_map_desc& mp = maps[j];
       const gsi_input_desc& in = inputs[mp.input_id];
       if (map_done[j] != 2 && !map_fused[j] && B > 0) {
-        hipError_t e;
         const bool wx = (in.flags & GSI_INPUT_SLOW_PATH_WX) != 0;
-        if (mfma_gated_path(mp.W, mp.M, in.C, in.R, in.d, in.k, B, mp.wdtype, mp.m, mp.Y) && wx_vector_ok(in))
-          e = mfma_gated(mp.W, mp.M, in.C, in.R, in.fired_idx, in.n_fired, mp.m, in.d, in.k, B, mp.Y, part[j], s,
-                         wx ? in.X : nullptr, in.xdtype, img_done[j] != 0);
-        else
-          e = gsi::generic_gated_linear(mp.W, mp.M, in.C, in.R, in.fired_idx, in.n_fired, mp.m, in.d, in.k, B,
+        hipError_t e = gsi::generic_gated_linear(mp.W, mp.M, in.C, in.R, in.fired_idx, in.n_fired, mp.m, in.d, in.k, B,
                                         mp.wdtype, mp.Y, s, wx ? in.X : nullptr, in.xdtype);
         if (e != hipSuccess) return hip_fail(e, fn);
       }

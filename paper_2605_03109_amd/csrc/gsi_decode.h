@@ -141,7 +141,8 @@ hipError_t decode_project_launch(ProjBatch& pb, int udtype, bool with_norms, boo
                                  hipStream_t s, ImgBatch* img = nullptr);
 // stand-alone image launch for one token: y = M c with c read from C (tasks' C set, part_c null)
 hipError_t decode_image_launch(ImgBatch& ib, int wdtype, hipStream_t s);
-// norms (and gate) of tasks whose part_n / b_slabs / rnorm / xnorm (mask, fired_idx, n_fired) are set
+// norms (and gate) of prefill-sized tasks whose part_n / b_slabs / rnorm / xnorm (mask, fired_idx, n_fired, and a
+// cleared counter sync) are set
 hipError_t decode_norms_launch(const ProjBatch& pb, bool with_gate, float eps, hipStream_t s);
 // can a set of tasks share one single-token launch (LDS budget)?
 // (wdtype: a decode batch whose maps all take the matrix-core kernel needs no LDS vector and always fits)

@@ -4,54 +4,57 @@
 
 namespace gsi {
 
-enum { EPI_STORE_BF16 = 0, EPI_STORE_F32 = 1, EPI_RESIDUAL = 2, EPI_SCATTER_ADD = 3, EPI_SCATTER_STORE = 4, EPI_MULTI = 5 };
+// What becomes of A B^T.  EPI_RESIDUAL and EPI_STORE_F32 problems share launches (EPI_PROJECTED: a residual and the image
+// rows beside it), and so do EPI_SCATTER_ADD and EPI_SCATTER_STORE (EPI_SCATTER).
+enum { EPI_STORE_BF16 = 0, EPI_STORE_F32 = 1, EPI_RESIDUAL = 2, EPI_SCATTER_ADD = 3, EPI_SCATTER_STORE = 4,
+       EPI_PROJECTED = 5, EPI_SCATTER = 6 };
 
-// One right-hand factor of a product with several (EPI_MULTI): the same A against B_0, B_1, ... side by side in
-// one launch, each with its own output and epilogue (EPI_RESIDUAL or EPI_STORE_F32).
-struct GemmSeg {
-  const void* B;
-  int64_t ldb;
-  void* D;
-  int64_t ldd;
-  int N;
-  int tile_begin;  // first column tile of this factor in the launch (filled by mfma_gemm_nt)
-  int epi;
-};
-constexpr int kMaxGemmSegs = 4;
-
-// D = A B^T, A[M,K] (bf16, or fp32 split into two bf16 terms), B[N,K] bf16, both row-major.
-struct GemmArgs {
+// One product D = A B^T of a launch: A[M,K] (bf16, or fp32 fed as bf16), B[N,K] bf16, both row-major.
+struct GemmProb {
   const void* A;
-  int64_t lda;
-  int a_f32;                  // A is 0: bf16; 1: fp32, fed as bf16 head + tail (two passes); 2: fp32, rounded once to bf16
   const void* B;
-  int64_t ldb;
   void* D;                    // bf16 or fp32 [.., ldd]
-  int64_t ldd;
-  int M, N, K;                // K a multiple of 64; M * N below 2^31
-  const int32_t* row_idx;     // optional: row i of A is A[row_idx[i]], and (scatter-add) row i of D is D[row_idx[i]]
+  const void* X;              // residual: D = X - A B^T, X[M, ldd]
+  float* part_n;              // ... and per-row partial sums of squares [column tiles][M][2]
+  unsigned* sync;             // ... and a counter that the launch clears for the norm kernel behind it (may be null)
+  const int32_t* row_idx;     // optional: row i of A is A[row_idx[i]], and (scatter) row i of D is D[row_idx[i]]
   const int32_t* n_rows_dev;  // optional: device count of valid rows (<= M)
-  // residual epilogue: D = X - A B^T and per-row partial sums of squares
-  const void* X;
+  float* part;                // split contraction: workspace [splits][M][N] of partial sums, or null (then no split)
+  int lda, ldb, ldd;
+  int M, N, K;                // K a multiple of 64; M * N below 2^31
+  int epi;
   int xdtype;
-  int64_t ldx;
-  float* part_n;              // [tiles of N][part_tokens][2]
-  int part_tokens;
-  // split contraction: workspace [splits][M][N] of partial sums, or null (then no split); `splits` is set
-  // by mfma_gemm_nt from mfma_splits()
-  float* part;
-  int splits;
-  // EPI_MULTI: the right-hand factors (B, ldb, D, ldd, N above are then unused)
-  GemmSeg seg[kMaxGemmSegs];
-  int nseg;
+  int max_splits;             // in: splits of the contraction that `part` has room for (mfma_splits), 1 without it
+  int res_cols;               // EPI_PROJECTED: columns per partial norm, 64 or 128 (the same in every problem)
+  int splits, col_tiles, blk_begin;  // filled at launch
 };
+constexpr int kMaxProbs = 24;
+struct GemmArgs {
+  GemmProb p[kMaxProbs];
+  int n;
+};
+static_assert(sizeof(GemmArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
-// how many ways mfma_gemm_nt splits the contraction of an M x N x K problem, and the workspace that takes
-int mfma_splits(int64_t M, int64_t N, int64_t K, int epi);
-size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi);
+// How many ways the contraction of an M x N x K problem is split, and the workspace that takes.  full: the
+// caller's workspace has the size that the queries name; else only what they named while tiles had one size (a fixed
+// scratch memory that a call used to fit), and the product is split less.
+int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool full);
+size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, bool full);
 
-hipError_t mfma_gemm_nt(const GemmArgs& g, int epi, hipStream_t s);
-hipError_t mfma_transpose_bf16(const void* U, void* Ut, int rows, int cols, hipStream_t s);
-int mfma_res_tiles(int64_t d);  // column tiles of the residual GEMM = partial norms per token
+// Products of one launch (n of any number; more than kMaxProbs take several launches).  a_f32: A is 0: bf16; 1: fp32, fed as
+// bf16 head + tail (two passes); 2: fp32, rounded once to bf16.  epi: EPI_STORE_BF16, EPI_STORE_F32, EPI_PROJECTED or
+// EPI_SCATTER; every problem's own epi belongs to it.
+hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s);
+
+// Ut[j][i] = U[i][j] for n bf16 matrices U[rows, cols]
+struct TransposeTask {
+  const void* U;
+  void* Ut;
+  int rows, cols;
+  int blk_begin;  // filled at launch
+};
+hipError_t mfma_transpose_bf16(TransposeTask* tasks, int n, hipStream_t s);
+// column tiles of the residual GEMM = partial norms per token (full: see mfma_splits)
+int mfma_res_tiles(int64_t d, bool full);
 
 }  // namespace gsi

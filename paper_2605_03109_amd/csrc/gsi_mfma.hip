@@ -8,8 +8,8 @@
 // or fp32 split on the fly into a bf16 head and a bf16 tail (two MFMA passes) so that an fp32 operand
 // on the main term is not rounded to 8 bits (the bf16 image already uses most of the 2e-3 budget).
 //
-// Workgroup tile 256 x 256 x 64, eight waves 4 x 2 (two per SIMD, so that one wave's MFMAs cover the
-// other's LDS reads and staging), each wave 64 x 128 as 2 x 4 v_mfma_f32_32x32x16_bf16 fragments.
+// Workgroup tile 256 x 256 x 64 (or 128 x 256 x 64), eight waves 4 x 2 (2 x 4; two per SIMD, so that one wave's MFMAs
+// cover the other's LDS reads and staging), each wave 64 x 128 (64 x 64) as v_mfma_f32_32x32x16_bf16 fragments.
 // Both operand tiles are staged in LDS as bf16 (row stride padded to 144 bytes: conflict-free 128-bit
 // reads); an fp32 A operand is converted on the way in.  Global loads are whole 128-byte row segments per
 // eight lanes.  LDS holds two k-tiles: tile t is multiplied while tile t + 1 is written, a unit per MFMA step,
@@ -19,8 +19,17 @@
 // of the contraction index is as good as another as long as both operands agree.
 // What bounds the loop is LDS, not the matrix cores: a k-tile is 2048 MFMA cycles per SIMD, and its LDS
 // traffic (192 KB of operand reads at 128 bytes a cycle, 64 KB of staging writes at about 75) is 2400.
-// Problems with few output tiles split the contraction over blockIdx.z; the partial sums go to the workspace
+// (Built and measured beside it: 256 x 256 tiles by four waves of 128 x 128, accumulators in AGPRs, memory to LDS without
+// registers: 1012 TFLOP/s against 1004 on 2048 x 16384 x 4096, 899 against 998 at 16384 columns, and no second workgroup
+// to cover an epilogue; 128 x 256 x 32 tiles by four waves, two workgroups per unit: 795.)
+// A launch takes the products of all inputs, or of all maps, of a call (GemmProb): one product of a block is 64 to 512
+// tiles, one or two rounds of the 256 compute units with a ramp and a tail of its own.  The row tile is chosen
+// for the whole launch (plan_rows).  A block's prefill, 2048 tokens at rank 512: 36 launches 1007 us, 7 launches
+// 747 us; the pair 4096 / 16384, 333 tokens at rank 256: 14 launches 438 us, 7 launches 173 us.
+// Problems with few output tiles split the contraction; the partial sums go to the workspace
 // and a second kernel adds them in split order and applies the epilogue.
+// The residual and image products are short (the rank) with long epilogues (every output row of a block: 0.5 GB), so they
+// run on tiles of 128 rows, two workgroups per unit: one's epilogue beside the other's products.
 // Operands that are N-contiguous in memory (U as the right factor of W U and X U) are transposed
 // once into the workspace.
 #include <algorithm>
@@ -34,10 +43,10 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
-constexpr int BM = 256, BN = 256, BK = 64;      // BK: the host's unit of the contraction (K is a multiple of it)
-constexpr int WTM = 64, WTN = 128;              // wave tile: the eight waves sit 4 x 2 on the workgroup tile
+constexpr int BN = 256, BK = 64;                // BK: the host's unit of the contraction (K is a multiple of it)
+constexpr int WTM = 64;                         // rows of a wave tile
 constexpr int kThreads = 512;
-constexpr int kAF = WTM / 32, kBF = WTN / 32;   // A, B fragments per wave
+constexpr int kAF = WTM / 32;                   // A fragments per wave
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // a native vector: loads and stores of it are
                                                               // instructions, not aggregate copies
@@ -47,7 +56,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // a native vector:
 // Geometry of a staged k-tile by mode.  The head + tail form keeps two tiles of A per stage, so its k-tile is 32
 // columns deep (two MFMA steps of two passes each: as many MFMAs between barriers as the 64-deep tile of the
 // other modes) and two stages still fit in LDS.
-template <int AM>
+// TM: rows of the workgroup tile, 256 or 128 (eight waves 4 x 2 or 2 x 4, each 64 x 128 or 64 x 64).
+template <int AM, int TM>
 struct Geo {
   static constexpr int BKT = AM == 1 ? 32 : 64;          // columns of a k-tile
   static constexpr int LD = BKT + 8;                     // padded LDS row stride, bf16 elements (80 or 144 bytes:
@@ -55,18 +65,21 @@ struct Geo {
   static constexpr int KS = BKT / 16;                    // MFMA steps per k-tile
   static constexpr int CPR = BKT / 8;                    // staging units (8 elements) per tile row
   static constexpr int RPP = kThreads / CPR;             // tile rows covered by one unit index of all threads
-  static constexpr int NU = BM / RPP;                    // units of A (and of B) per thread and k-tile
+  static constexpr int NU = BN / RPP;                    // units of B per thread and k-tile
+  static constexpr int NA = TM / RPP;                    // ... and of A
   static constexpr int NP = AM == 1 ? 2 : 1;             // LDS tiles of A per stage
-  static constexpr int kATile = BM * LD;                 // elements of one LDS tile of A
-  static constexpr int kStage = (NP * BM + BN) * LD;     // elements of one stage
-  static_assert(NU == KS, "one staging unit per MFMA step");
-  static_assert(BM == BN, "A and B tiles are staged alike");
+  static constexpr int kATile = TM * LD;                 // elements of one LDS tile of A
+  static constexpr int kStage = (NP * TM + BN) * LD;     // elements of one stage
+  static constexpr int WN = TM == 256 ? 2 : 4;           // waves side by side
+  static constexpr int WTN = BN / WN;                    // columns of a wave tile
+  static constexpr int kBF = WTN / 32;                   // B fragments per wave
+  static_assert(NU == KS, "one staging unit of B per MFMA step");
 };
 
-template <int AM>
+template <int AM, int TM>
 struct Stage {
-  u32x4 a[Geo<AM>::NU][AM ? 2 : 1];
-  u32x4 b[Geo<AM>::NU];
+  u32x4 a[Geo<AM, TM>::NA][AM ? 2 : 1];
+  u32x4 b[Geo<AM, TM>::NU];
 };
 
 // 8 fp32 -> 8 bf16 (RNE), and the bf16 of what is left
@@ -90,61 +103,66 @@ __device__ __forceinline__ u32x4 round8(const u32x4& x0, const u32x4& x1, u32x4*
 
 // requests unit u of k-tile kt of both operands (unit u of a thread: tile row tid / CPR + RPP u, columns
 // 8 (tid % CPR) .. + 8; the pointers already point at that row and column of k-tile 0)
-template <int AM>
-__device__ __forceinline__ void issue_unit(Stage<AM>& st, int u, const char* const (&ap)[Geo<AM>::NU],
-                                           const char* const (&bp)[Geo<AM>::NU], int kt) {
+template <int AM, int TM>
+__device__ __forceinline__ void issue_unit(Stage<AM, TM>& st, int u, const char* const (&ap)[Geo<AM, TM>::NA],
+                                           const char* const (&bp)[Geo<AM, TM>::NU], int kt) {
+  using G = Geo<AM, TM>;
   constexpr int ES = AM ? 4 : 2;
-  const char* p = ap[u] + (int64_t)kt * Geo<AM>::BKT * ES;
-  st.a[u][0] = *reinterpret_cast<const u32x4*>(p);
-  if constexpr (AM != 0) st.a[u][1] = *reinterpret_cast<const u32x4*>(p + 16);
-  st.b[u] = *reinterpret_cast<const u32x4*>(bp[u] + (int64_t)kt * Geo<AM>::BKT * 2);
+  if (u < G::NA) {
+    const char* p = ap[u] + (int64_t)kt * G::BKT * ES;
+    st.a[u][0] = *reinterpret_cast<const u32x4*>(p);
+    if constexpr (AM != 0) st.a[u][1] = *reinterpret_cast<const u32x4*>(p + 16);
+  }
+  st.b[u] = *reinterpret_cast<const u32x4*>(bp[u] + (int64_t)kt * G::BKT * 2);
 }
-template <int AM>
-__device__ __forceinline__ void issue(Stage<AM>& st, const char* const (&ap)[Geo<AM>::NU], const char* const (&bp)[Geo<AM>::NU],
-                                      int kt) {
+template <int AM, int TM>
+__device__ __forceinline__ void issue(Stage<AM, TM>& st, const char* const (&ap)[Geo<AM, TM>::NA],
+                                      const char* const (&bp)[Geo<AM, TM>::NU], int kt) {
 #pragma unroll
-  for (int u = 0; u < Geo<AM>::NU; ++u) issue_unit<AM>(st, u, ap, bp, kt);
+  for (int u = 0; u < Geo<AM, TM>::NU; ++u) issue_unit<AM, TM>(st, u, ap, bp, kt);
 }
 
 // writes unit u of the staged k-tile to the LDS stage at `stage` as bf16 (fp32 A: rounded, or head and tail tiles)
-template <int AM>
-__device__ __forceinline__ void commit_unit(const Stage<AM>& st, int u, uint16_t* stage, int tid) {
-  using G = Geo<AM>;
+template <int AM, int TM>
+__device__ __forceinline__ void commit_unit(const Stage<AM, TM>& st, int u, uint16_t* stage, int tid) {
+  using G = Geo<AM, TM>;
   const int off = ((tid / G::CPR) + G::RPP * u) * G::LD + 8 * (tid % G::CPR);
-  u32x4* d0 = reinterpret_cast<u32x4*>(stage + off);
-  if constexpr (AM == 0) {
-    *d0 = st.a[u][0];
-  } else if constexpr (AM == 2) {
-    *d0 = round8(st.a[u][0], st.a[u][1], nullptr);
-  } else {
-    u32x4 tail;
-    *d0 = round8(st.a[u][0], st.a[u][1], &tail);
-    *reinterpret_cast<u32x4*>(stage + G::kATile + off) = tail;
+  if (u < G::NA) {
+    u32x4* d0 = reinterpret_cast<u32x4*>(stage + off);
+    if constexpr (AM == 0) {
+      *d0 = st.a[u][0];
+    } else if constexpr (AM == 2) {
+      *d0 = round8(st.a[u][0], st.a[u][1], nullptr);
+    } else {
+      u32x4 tail;
+      *d0 = round8(st.a[u][0], st.a[u][1], &tail);
+      *reinterpret_cast<u32x4*>(stage + G::kATile + off) = tail;
+    }
   }
   *reinterpret_cast<u32x4*>(stage + G::NP * G::kATile + off) = st.b[u];
 }
-template <int AM>
-__device__ __forceinline__ void commit(const Stage<AM>& st, uint16_t* stage, int tid) {
+template <int AM, int TM>
+__device__ __forceinline__ void commit(const Stage<AM, TM>& st, uint16_t* stage, int tid) {
 #pragma unroll
-  for (int u = 0; u < Geo<AM>::NU; ++u) commit_unit<AM>(st, u, stage, tid);
+  for (int u = 0; u < Geo<AM, TM>::NU; ++u) commit_unit<AM, TM>(st, u, stage, tid);
 }
 
 // The MFMA operands of one step (16 columns of the k-tile) of a wave: lane half lh takes one half of the tile's
 // columns, eight per step (both operands in the same order, so the order of the contraction index does not
 // matter)
-template <int AM>
+template <int AM, int TM>
 struct Ops {
   bf16x8 a[kAF];
   bf16x8 al[AM == 1 ? kAF : 1];
-  bf16x8 b[kBF];
+  bf16x8 b[Geo<AM, TM>::kBF];
 };
-template <int AM>
-__device__ __forceinline__ void read_ops(Ops<AM>& o, const uint16_t* stage, int wm, int wn, int lc, int lh, int j) {
-  using G = Geo<AM>;
+template <int AM, int TM>
+__device__ __forceinline__ void read_ops(Ops<AM, TM>& o, const uint16_t* stage, int wm, int wn, int lc, int lh, int j) {
+  using G = Geo<AM, TM>;
   const int col = (G::BKT / 2) * lh + 8 * j;
   const uint16_t* Bq = stage + G::NP * G::kATile;
 #pragma unroll
-  for (int n = 0; n < kBF; ++n) o.b[n] = *reinterpret_cast<const bf16x8*>(Bq + (WTN * wn + 32 * n + lc) * G::LD + col);
+  for (int n = 0; n < G::kBF; ++n) o.b[n] = *reinterpret_cast<const bf16x8*>(Bq + (G::WTN * wn + 32 * n + lc) * G::LD + col);
 #pragma unroll
   for (int i = 0; i < kAF; ++i) {
     const int off = (WTM * wm + 32 * i + lc) * G::LD + col;
@@ -152,8 +170,9 @@ __device__ __forceinline__ void read_ops(Ops<AM>& o, const uint16_t* stage, int 
     if constexpr (AM == 1) o.al[i] = *reinterpret_cast<const bf16x8*>(stage + G::kATile + off);
   }
 }
-template <int AM>
-__device__ __forceinline__ void mma(const Ops<AM>& o, f32x16 (&acc)[kAF][kBF]) {
+template <int AM, int TM>
+__device__ __forceinline__ void mma(const Ops<AM, TM>& o, f32x16 (&acc)[kAF][Geo<AM, TM>::kBF]) {
+  constexpr int kBF = Geo<AM, TM>::kBF;
 #pragma unroll
   for (int i = 0; i < kAF; ++i) {
 #pragma unroll
@@ -165,60 +184,60 @@ __device__ __forceinline__ void mma(const Ops<AM>& o, f32x16 (&acc)[kAF][kBF]) {
   }
 }
 
-template <int AM, int EPI>
-__global__ __launch_bounds__(kThreads) void gemm_nt(const GemmArgs g) {
-  using G = Geo<AM>;
+template <int AM, int EPI, int TM>
+__global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm_nt(const GemmArgs args) {
+  using G = Geo<AM, TM>;
+  constexpr int WTN = G::WTN, kBF = G::kBF;
   // two stages, each the tile(s) of A followed by the tile of B
   __shared__ __align__(16) uint16_t lds[2 * G::kStage];
 
+  // the problem of this workgroup, and its tile: column tiles of a row tile side by side, row tiles of a split, splits
+  int pi = 0;
+  for (int q = 1; q < args.n; ++q)
+    if ((int)blockIdx.x >= args.p[q].blk_begin) pi = q;
+  const GemmProb& g = args.p[pi];
+  const int local = blockIdx.x - g.blk_begin;
+  const int row_tiles = (g.M + TM - 1) / TM;
+  const int tile_n = local % g.col_tiles, tile_m = (local / g.col_tiles) % row_tiles, split = local / (g.col_tiles * row_tiles);
+  if constexpr (EPI == EPI_PROJECTED) {
+    if (local == 0 && threadIdx.x == 0 && g.sync) *g.sync = 0u;
+  }
   int Mrows = g.M;
   if (g.n_rows_dev) {
     const int nd = g.n_rows_dev[0];
     Mrows = nd < Mrows ? nd : Mrows;
   }
-  const int tile_m = blockIdx.y;
-  if (tile_m * BM >= Mrows) return;  // uniform
-  // the right-hand factor of this workgroup: the only one, or the segment its column tile falls in
-  int tile_n = blockIdx.x, N = g.N, epi = EPI;
-  const void* Bmat = g.B;
-  void* Dmat = g.D;
-  int64_t ldb = g.ldb, ldd = g.ldd;
-  if constexpr (EPI == EPI_MULTI) {
-    int si = 0;
-#pragma unroll
-    for (int q = 1; q < kMaxGemmSegs; ++q)
-      if (q < g.nseg && (int)blockIdx.x >= g.seg[q].tile_begin) si = q;
-    const GemmSeg& sg = g.seg[si];
-    tile_n = blockIdx.x - sg.tile_begin;
-    N = sg.N; epi = sg.epi; Bmat = sg.B; Dmat = sg.D; ldb = sg.ldb; ldd = sg.ldd;
-  }
+  if (tile_m * TM >= Mrows) return;  // uniform
+  const int N = g.N;
+  void* const Dmat = g.D;
+  const int64_t lda = g.lda, ldb = g.ldb, ldd = g.ldd;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lc = lane & 31, lh = lane >> 5;
-  const int wm = wave >> 1, wn = wave & 1;
+  const int wm = wave / G::WN, wn = wave % G::WN;
   constexpr int ES = AM ? 4 : 2;  // bytes per element of A
 
   // k-tiles of this split
   const int nk = g.K / G::BKT;  // K is a multiple of 64
-  const int splits = g.splits > 1 ? g.splits : 1;
-  const int kt0 = (int)(((int64_t)nk * blockIdx.z) / splits), kt1 = (int)(((int64_t)nk * (blockIdx.z + 1)) / splits);
+  const int splits = g.splits;
+  const int kt0 = (int)(((int64_t)nk * split) / splits), kt1 = (int)(((int64_t)nk * (split + 1)) / splits);
 
   // staging pointers: a thread's unit u is tile row tid / CPR + RPP u, 8 columns at 8 (tid % CPR); rows past the
   // end repeat the last one (their results are not stored)
-  const char* ap[G::NU];
+  const char* ap[G::NA];
   const char* bp[G::NU];
 #pragma unroll
-  for (int u = 0; u < G::NU; ++u) {
-    int grow = tile_m * BM + (tid / G::CPR) + G::RPP * u;
+  for (int u = 0; u < G::NA; ++u) {
+    int grow = tile_m * TM + (tid / G::CPR) + G::RPP * u;
     grow = grow < Mrows ? grow : Mrows - 1;
     if (g.row_idx) grow = g.row_idx[grow];
-    ap[u] = reinterpret_cast<const char*>(g.A) + ((int64_t)grow * g.lda + 8 * (tid % G::CPR)) * ES;
+    ap[u] = reinterpret_cast<const char*>(g.A) + ((int64_t)grow * lda + 8 * (tid % G::CPR)) * ES;
   }
 #pragma unroll
   for (int u = 0; u < G::NU; ++u) {
     int grow = tile_n * BN + (tid / G::CPR) + G::RPP * u;
     grow = grow < N ? grow : N - 1;
-    bp[u] = reinterpret_cast<const char*>(Bmat) + ((int64_t)grow * ldb + 8 * (tid % G::CPR)) * 2;
+    bp[u] = reinterpret_cast<const char*>(g.B) + ((int64_t)grow * ldb + 8 * (tid % G::CPR)) * 2;
   }
 
   f32x16 acc[kAF][kBF];
@@ -235,36 +254,67 @@ __global__ __launch_bounds__(kThreads) void gemm_nt(const GemmArgs g) {
     // One barrier per tile, before the last step: by then every wave has written its share of the next stage
     // and has the last step's operands in registers, so the first operands of the next tile are read behind
     // the last step's MFMAs.  Past the range the last tile is requested (and staged) again and never used.
-    Stage<AM> st;
-    issue<AM>(st, ap, bp, kt0);
-    commit<AM>(st, lds, tid);
-    issue<AM>(st, ap, bp, kt0 + 1 < kt1 ? kt0 + 1 : kt0);
+    Stage<AM, TM> st;
+    issue<AM, TM>(st, ap, bp, kt0);
+    commit<AM, TM>(st, lds, tid);
+    issue<AM, TM>(st, ap, bp, kt0 + 1 < kt1 ? kt0 + 1 : kt0);
     __syncthreads();
-    Ops<AM> o[2];
-    read_ops<AM>(o[0], lds, wm, wn, lc, lh, 0);
-    for (int kt = kt0; kt < kt1; ++kt) {
-      uint16_t* cur = lds + ((kt - kt0) & 1) * G::kStage;
-      uint16_t* nxt = lds + (((kt - kt0) & 1) ^ 1) * G::kStage;
-      const int kt2 = kt + 2 < kt1 ? kt + 2 : kt1 - 1;
+    if constexpr (AM == 1 && TM == 128) {
+      // two workgroups per compute unit (one's epilogue beside the other's products): operands are read step by step, the
+      // other waves of the SIMD cover the reads
+      const char* pa = ap[0] + (int64_t)(kt0 + 1 < kt1 ? kt0 + 1 : kt0) * G::BKT * ES;  // the k-tile requested last
+      const char* pb[G::NU];
 #pragma unroll
-      for (int j = 0; j < G::KS; ++j) {
-        if (j + 1 < G::KS) {
-          read_ops<AM>(o[(j + 1) & 1], cur, wm, wn, lc, lh, j + 1);
-        } else {
-          __syncthreads();
-          read_ops<AM>(o[(j + 1) & 1], nxt, wm, wn, lc, lh, 0);
-        }
-        mma<AM>(o[j & 1], acc);
-        if (j + 1 < G::KS) {
-          // a unit behind every step but the last two, which share the step before the barrier
-          commit_unit<AM>(st, j, nxt, tid);
-          issue_unit<AM>(st, j, ap, bp, kt2);
-          if (j + 2 == G::KS) {
-            commit_unit<AM>(st, j + 1, nxt, tid);
-            issue_unit<AM>(st, j + 1, ap, bp, kt2);
+      for (int u = 0; u < G::NU; ++u) pb[u] = bp[u] + (int64_t)(kt0 + 1 < kt1 ? kt0 + 1 : kt0) * G::BKT * 2;
+      static_assert(G::NA == 1, "one staging unit of A per thread");
+      int cur = 0;
+      for (int kt = kt0; kt < kt1; ++kt) {
+        const int step = kt + 2 < kt1 ? G::BKT : 0;
+#pragma unroll
+        for (int j = 0; j < G::KS; ++j) {
+          Ops<AM, TM> o;
+          read_ops<AM, TM>(o, lds + cur, wm, wn, lc, lh, j);
+          mma<AM, TM>(o, acc);
+          commit_unit<AM, TM>(st, j, lds + (G::kStage - cur), tid);
+          if (j == 0) {
+            pa += step * ES;
+            st.a[0][0] = *reinterpret_cast<const u32x4*>(pa);
+            st.a[0][1] = *reinterpret_cast<const u32x4*>(pa + 16);
           }
+          pb[j] += step * 2;
+          st.b[j] = *reinterpret_cast<const u32x4*>(pb[j]);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
+        cur = G::kStage - cur;
+        __syncthreads();
+      }
+    } else {
+      Ops<AM, TM> o[2];
+      read_ops<AM, TM>(o[0], lds, wm, wn, lc, lh, 0);
+      for (int kt = kt0; kt < kt1; ++kt) {
+        uint16_t* cur = lds + ((kt - kt0) & 1) * G::kStage;
+        uint16_t* nxt = lds + (((kt - kt0) & 1) ^ 1) * G::kStage;
+        const int kt2 = kt + 2 < kt1 ? kt + 2 : kt1 - 1;
+#pragma unroll
+        for (int j = 0; j < G::KS; ++j) {
+          if (j + 1 < G::KS) {
+            read_ops<AM, TM>(o[(j + 1) & 1], cur, wm, wn, lc, lh, j + 1);
+          } else {
+            __syncthreads();
+            read_ops<AM, TM>(o[(j + 1) & 1], nxt, wm, wn, lc, lh, 0);
+          }
+          mma<AM, TM>(o[j & 1], acc);
+          if (j + 1 < G::KS) {
+            // a unit behind every step but the last two, which share the step before the barrier
+            commit_unit<AM, TM>(st, j, nxt, tid);
+            issue_unit<AM, TM>(st, j, ap, bp, kt2);
+            if (j + 2 == G::KS) {
+              commit_unit<AM, TM>(st, j + 1, nxt, tid);
+              issue_unit<AM, TM>(st, j + 1, ap, bp, kt2);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     }
   }
@@ -276,9 +326,11 @@ __global__ __launch_bounds__(kThreads) void gemm_nt(const GemmArgs g) {
   __syncthreads();  // the operand tiles are no longer read
   constexpr int kSR = 8, kSLD = WTN + 4;  // strip rows, padded strip stride (floats)
   float* strip = reinterpret_cast<float*>(lds) + wave * (kSR * kSLD);
-  const bool partial = g.splits > 1;
-  float* const pdst = partial ? g.part + (int64_t)blockIdx.z * g.M * N : nullptr;
-  const int er = lane >> 5, ec = 4 * (lane & 31);  // row parity and first column of the lane's reads
+  const bool partial = splits > 1;
+  float* const pdst = partial ? g.part + (int64_t)split * g.M * N : nullptr;
+  // a lane reads four columns of one row, the wave kRL rows at a time
+  constexpr int kLR = WTN / 4, kRL = kWave / kLR, kReads = kSR / kRL;  // lanes per strip row, rows per read, reads per strip
+  const int er = lane / kLR, ec = 4 * (lane % kLR);
 #pragma unroll
   for (int c = 0; c < WTM / kSR; ++c) {
     // strip c: rows 8 c .. 8 c + 7 of the wave tile = fragment c / 4, accumulator elements 4 (c % 4) .. + 3
@@ -295,35 +347,35 @@ __global__ __launch_bounds__(kThreads) void gemm_nt(const GemmArgs g) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const int col = tile_n * BN + WTN * wn + ec;
-    float4 val[kSR / 2];
-    int row[kSR / 2];
+    float4 val[kReads];
+    int row[kReads];
 #pragma unroll
-    for (int q = 0; q < kSR / 2; ++q) {
-      row[q] = tile_m * BM + WTM * wm + kSR * c + 2 * q + er;
-      val[q] = *reinterpret_cast<const float4*>(&strip[(2 * q + er) * kSLD + ec]);
+    for (int q = 0; q < kReads; ++q) {
+      row[q] = tile_m * TM + WTM * wm + kSR * c + kRL * q + er;
+      val[q] = *reinterpret_cast<const float4*>(&strip[(kRL * q + er) * kSLD + ec]);
     }
     if (partial) {
 #pragma unroll
-      for (int q = 0; q < kSR / 2; ++q)
+      for (int q = 0; q < kReads; ++q)
         if (row[q] < Mrows && col < N)  // N is a multiple of 4 here (checked on the host)
           *reinterpret_cast<float4*>(pdst + (int64_t)row[q] * N + col) = val[q];
-    } else if (EPI == EPI_RESIDUAL || (EPI == EPI_MULTI && epi == EPI_RESIDUAL)) {
+    } else if (EPI == EPI_PROJECTED && g.epi == EPI_RESIDUAL) {
       // r = x - acc; R written; per row the sums of r^2 and x^2 over this wave's 128 columns
-      float4 x[kSR / 2];
+      float4 x[kReads];
 #pragma unroll
-      for (int q = 0; q < kSR / 2; ++q) {
+      for (int q = 0; q < kReads; ++q) {
         x[q] = float4{0.f, 0.f, 0.f, 0.f};
         if (row[q] < Mrows && col < N) {
           if (g.xdtype == GSI_F32) {
-            x[q] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(g.X) + (int64_t)row[q] * g.ldx + col);
+            x[q] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(g.X) + (int64_t)row[q] * ldd + col);
           } else {
-            const uint2 xb = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(g.X) + (int64_t)row[q] * g.ldx + col);
+            const uint2 xb = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(g.X) + (int64_t)row[q] * ldd + col);
             x[q] = float4{bf16_lo(xb.x), bf16_hi(xb.x), bf16_lo(xb.y), bf16_hi(xb.y)};
           }
         }
       }
 #pragma unroll
-      for (int q = 0; q < kSR / 2; ++q) {
+      for (int q = 0; q < kReads; ++q) {
         const bool live = row[q] < Mrows && col < N;
         const float4 r = float4{x[q].x - val[q].x, x[q].y - val[q].y, x[q].z - val[q].z, x[q].w - val[q].w};
         float sr = 0.f, sx = 0.f;
@@ -332,29 +384,29 @@ __global__ __launch_bounds__(kThreads) void gemm_nt(const GemmArgs g) {
           sr = fmaf(r.x, r.x, fmaf(r.y, r.y, fmaf(r.z, r.z, r.w * r.w)));
           sx = fmaf(x[q].x, x[q].x, fmaf(x[q].y, x[q].y, fmaf(x[q].z, x[q].z, x[q].w * x[q].w)));
         }
-        sr = group_sum_rt(sr, 32);
-        sx = group_sum_rt(sx, 32);
-        if ((lane & 31) == 0 && row[q] < Mrows && tile_n * BN + WTN * wn < N) {
-          float* pn = g.part_n + ((int64_t)(tile_n * (BN / WTN) + wn) * g.part_tokens + row[q]) * 2;
+        sr = group_sum_rt(sr, kLR);
+        sx = group_sum_rt(sx, kLR);
+        if (lane % kLR == 0 && row[q] < Mrows && tile_n * BN + WTN * wn < N) {
+          float* pn = g.part_n + ((int64_t)(tile_n * G::WN + wn) * g.M + row[q]) * 2;
           pn[0] = sr;
           pn[1] = sx;
         }
       }
     } else {
 #pragma unroll
-      for (int q = 0; q < kSR / 2; ++q) {
+      for (int q = 0; q < kReads; ++q) {
         if (row[q] < Mrows && col < N) {
           if constexpr (EPI == EPI_STORE_BF16) {
             uint2 o;
             o.x = (uint32_t)f32_to_bf16_bits(val[q].x) | ((uint32_t)f32_to_bf16_bits(val[q].y) << 16);
             o.y = (uint32_t)f32_to_bf16_bits(val[q].z) | ((uint32_t)f32_to_bf16_bits(val[q].w) << 16);
             *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(Dmat) + (int64_t)row[q] * ldd + col) = o;
-          } else if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_MULTI) {
+          } else if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_PROJECTED) {
             *reinterpret_cast<float4*>(reinterpret_cast<float*>(Dmat) + (int64_t)row[q] * ldd + col) = val[q];
           } else {  // scatter: one workgroup owns an output element, so the update is ordered
             const int drow = g.row_idx ? g.row_idx[row[q]] : row[q];
             float4* dp = reinterpret_cast<float4*>(reinterpret_cast<float*>(Dmat) + (int64_t)drow * ldd + col);
-            if constexpr (EPI == EPI_SCATTER_STORE) {
+            if (g.epi == EPI_SCATTER_STORE) {
               *dp = val[q];
             } else {
               const float4 o = *dp;
@@ -373,7 +425,9 @@ __global__ __launch_bounds__(kThreads) void gemm_nt(const GemmArgs g) {
 // A thread owns four consecutive columns; the blocks stride over the live rows (a device-side count for the
 // scatter-add product), so the launch does not grow with rows that did not fire.
 template <int EPI>
-__global__ __launch_bounds__(256) void splitk_finish(const GemmArgs g) {
+__global__ __launch_bounds__(256) void splitk_finish(const GemmArgs args) {
+  const GemmProb& g = args.p[blockIdx.y];
+  if (g.splits <= 1) return;
   int Mrows = g.M;
   if (g.n_rows_dev) {
     const int nd = g.n_rows_dev[0];
@@ -403,7 +457,7 @@ __global__ __launch_bounds__(256) void splitk_finish(const GemmArgs g) {
     } else {
       const int drow = g.row_idx ? g.row_idx[row] : row;
       float4* dp = reinterpret_cast<float4*>(reinterpret_cast<float*>(g.D) + (int64_t)drow * g.ldd + col);
-      if constexpr (EPI == EPI_SCATTER_STORE) {
+      if (g.epi == EPI_SCATTER_STORE) {
         *dp = s;
       } else {
         const float4 o = *dp;
@@ -413,97 +467,174 @@ __global__ __launch_bounds__(256) void splitk_finish(const GemmArgs g) {
   }
 }
 
-// Ut[j][i] = U[i][j] for a bf16 matrix U[rows, cols]; 32 x 32 tiles through LDS
-__global__ __launch_bounds__(256) void transpose_bf16(const uint16_t* __restrict__ U, uint16_t* __restrict__ Ut,
-                                                      int rows, int cols) {
-  __shared__ uint16_t tile[32][33];
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-  for (int y = ty; y < 32; y += 8) {
-    const int r = r0 + y, c = c0 + tx;
-    tile[y][tx] = (r < rows && c < cols) ? U[(int64_t)r * cols + c] : (uint16_t)0;
+// Ut[j][i] = U[i][j] for bf16 matrices U[rows, cols]: 64 x 64 tiles through LDS, whole 128-byte rows on both sides
+// (32 x 32 tiles: 64-byte rows, 8.4 us for 4096 x 512; the block's four bases at rank 512, 15 us in one launch)
+constexpr int kMaxTransposes = 64;
+struct TransposeArgs {
+  TransposeTask t[kMaxTransposes];
+  int n;
+};
+static_assert(sizeof(TransposeArgs) <= 4096, "kernel arguments are limited to 4 KB");
+__global__ __launch_bounds__(256) void transpose_bf16(const TransposeArgs a) {
+  constexpr int T = 64;
+  __shared__ uint16_t tile[T][T + 2];
+  int ti = 0;
+  for (int q = 1; q < a.n; ++q)
+    if ((int)blockIdx.x >= a.t[q].blk_begin) ti = q;
+  const TransposeTask& t = a.t[ti];
+  const uint16_t* __restrict__ U = reinterpret_cast<const uint16_t*>(t.U);
+  uint16_t* __restrict__ Ut = reinterpret_cast<uint16_t*>(t.Ut);
+  const int rows = t.rows, cols = t.cols, ct = (cols + T - 1) / T;
+  const int local = blockIdx.x - t.blk_begin;
+  const int r0 = (local / ct) * T, c0 = (local % ct) * T;
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  uint16_t v[T / 4];
+#pragma unroll
+  for (int q = 0; q < T / 4; ++q) {
+    const int r = r0 + ty + 4 * q, c = c0 + tx;
+    v[q] = (r < rows && c < cols) ? U[(int64_t)r * cols + c] : (uint16_t)0;
   }
+#pragma unroll
+  for (int q = 0; q < T / 4; ++q) tile[ty + 4 * q][tx] = v[q];
   __syncthreads();
-  for (int y = ty; y < 32; y += 8) {
-    const int c = c0 + y, r = r0 + tx;
-    if (r < rows && c < cols) Ut[(int64_t)c * rows + r] = tile[tx][y];
+#pragma unroll
+  for (int q = 0; q < T / 4; ++q) {
+    const int c = c0 + ty + 4 * q, r = r0 + tx;
+    if (r < rows && c < cols) Ut[(int64_t)c * rows + r] = tile[tx][ty + 4 * q];
   }
 }
 
-template <int AM>
-hipError_t launch_epi(const GemmArgs& g, int epi, hipStream_t s) {
-  const int splits = g.splits > 1 ? g.splits : 1;
-  dim3 grid((unsigned)ceil_div(g.N, BN), (unsigned)ceil_div(g.M, BM), (unsigned)splits);
-  if (epi == EPI_MULTI) {
-    grid.x = (unsigned)(g.seg[g.nseg - 1].tile_begin + ceil_div(g.seg[g.nseg - 1].N, BN));
-    gemm_nt<AM, EPI_MULTI><<<grid, kThreads, 0, s>>>(g);
-    return hipGetLastError();
-  }
-  switch (epi) {
-    case EPI_STORE_BF16: gemm_nt<AM, EPI_STORE_BF16><<<grid, kThreads, 0, s>>>(g); break;
-    case EPI_STORE_F32: gemm_nt<AM, EPI_STORE_F32><<<grid, kThreads, 0, s>>>(g); break;
-    case EPI_RESIDUAL: gemm_nt<AM, EPI_RESIDUAL><<<grid, kThreads, 0, s>>>(g); break;
-    case EPI_SCATTER_STORE: gemm_nt<AM, EPI_SCATTER_STORE><<<grid, kThreads, 0, s>>>(g); break;
-    default: gemm_nt<AM, EPI_SCATTER_ADD><<<grid, kThreads, 0, s>>>(g); break;
-  }
-  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  if (splits > 1) {
-    const unsigned fb = (unsigned)std::min<int64_t>(ceil_div((int64_t)g.M * (g.N / 4), 256), 4096);
-    switch (epi) {
-      case EPI_STORE_BF16: splitk_finish<EPI_STORE_BF16><<<fb, 256, 0, s>>>(g); break;
-      case EPI_STORE_F32: splitk_finish<EPI_STORE_F32><<<fb, 256, 0, s>>>(g); break;
-      case EPI_SCATTER_STORE: splitk_finish<EPI_SCATTER_STORE><<<fb, 256, 0, s>>>(g); break;
-      default: splitk_finish<EPI_SCATTER_ADD><<<fb, 256, 0, s>>>(g); break;
+template <int AM, int EPI>
+hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
+  int64_t blocks = 0;
+  bool split = false;
+  int64_t most = 0;
+  for (int i = 0; i < g.n; ++i) {
+    GemmProb& p = g.p[i];
+    p.col_tiles = (int)ceil_div(p.N, BN);
+    p.blk_begin = (int)blocks;
+    blocks += (int64_t)p.col_tiles * ceil_div(p.M, tm) * p.splits;
+    if (p.splits > 1) {
+      split = true;
+      most = std::max(most, (int64_t)p.M * (p.N / 4));
     }
   }
+  if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
+  if (tm == 128) gemm_nt<AM, EPI, 128><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+  else gemm_nt<AM, EPI, 256><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  if constexpr (EPI != EPI_PROJECTED)
+    if (split) splitk_finish<EPI><<<dim3((unsigned)std::min<int64_t>(ceil_div(most, 256), 4096), (unsigned)g.n), 256, 0, s>>>(g);
   return hipGetLastError();
+}
+
+template <int AM>
+hipError_t launch_epi(GemmArgs& g, int epi, int tm, hipStream_t s) {
+  switch (epi) {
+    case EPI_STORE_BF16: return launch_group<AM, EPI_STORE_BF16>(g, tm, s);
+    case EPI_STORE_F32: return launch_group<AM, EPI_STORE_F32>(g, tm, s);
+    case EPI_PROJECTED: return launch_group<AM, EPI_PROJECTED>(g, tm, s);
+    default: return launch_group<AM, EPI_SCATTER>(g, tm, s);
+  }
+}
+
+// rows that a product is sized for: the scatter products run over the fired rows only (a device-side count): a quarter
+int64_t rows_expected(int64_t M, int epi) {
+  return (epi == EPI_SCATTER_ADD || epi == EPI_SCATTER_STORE) ? std::max<int64_t>(std::min<int64_t>(M, 128), M / 4) : M;
+}
+constexpr int kUnits = 256;      // compute units: one workgroup each
+constexpr int kMaxDepth = 64;    // k-tiles of 64 columns per workgroup, where a product has fewer tiles than the chip units
+constexpr int kMinDepth = 8;     // k-tiles that a split keeps at least
+constexpr int kMaxSplits = 32;
+
+}  // namespace
+
+// The split is a property of the product alone, so that a product gives the same bits in whatever launch it runs (the
+// row tile, which plan_rows chooses for a launch, does not change the order of a sum).  Products of fewer tiles (of 128
+// rows) than there are units are cut into parts of 4096 columns, which makes the products of a block alike; those of so few
+// tiles (less than an eighth of the units) that even their parts are less than a quarter of the chip, and image builds,
+// which are alone in their launch, are cut further, down to 512 columns.  Measured, GEMM + sums of the partials: projections of a block, 2048 tokens:
+// parts of 4096 columns 85 + 7 us, 2048: 91 + 15, 1024: 108 + 25; its W r products 326 + 16, 326 + 54, 381 + 93; the
+// projections of the pair at 333 tokens 105 + 5, 59 + 5, 34 + 5; an image of 4096 x 4096 x 256: 57, 33 + 6, 22 + 7.
+int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool full) {
+  if (epi == EPI_RESIDUAL) return 1;
+  const int64_t m = rows_expected(M, epi), nk = ceil_div(K, BK);
+  int s = 1;
+  if (!full) {
+    const int64_t tiles = ceil_div(std::max<int64_t>(m, 256), 256) * ceil_div(N, BN);
+    while (s < 8 && tiles * s < kUnits && nk / (s * 2) >= 4) s *= 2;
+    return s;
+  }
+  const int64_t tiles = ceil_div(m, 128) * ceil_div(N, BN);
+  if (tiles < kUnits) s = (int)std::min<int64_t>(ceil_div(nk, kMaxDepth), kMaxSplits);
+  const int64_t want = epi == EPI_STORE_BF16 ? kUnits : tiles < kUnits / 8 ? kUnits / 4 : 0;
+  while (s * 2 <= kMaxSplits && tiles * s < want && nk / (s * 2) >= kMinDepth) s *= 2;
+  return s;
+}
+
+size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, bool full) {
+  const int s = mfma_splits(M, N, K, epi, full);
+  return s > 1 ? align_up((size_t)s * M * N * sizeof(float), 256) : 0;
+}
+
+namespace {
+
+// Row tile of a launch: the one with the least estimated time.  A workgroup takes its k-tiles and the time of about six
+// more for its first loads and its epilogue; a tile of 128 rows takes 0.6 of the time of one of 256 (the same right-hand
+// tile, half the products); the launch lasts as long as the work spread over the units, or its longest workgroup, and about
+// half of that workgroup again for the tail.
+int plan_rows(const GemmArgs& g, int epi) {
+  // (the norm shares of a residual are per 64 columns with tiles of 128 rows, per 128 with 256)
+  if (epi == EPI_PROJECTED) return g.p[0].res_cols == 64 ? 128 : 256;
+  double cost[2];
+  for (int t = 0; t < 2; ++t) {
+    const int tm = t ? 128 : 256;
+    const double per = t ? 0.6 : 1.0;
+    double total = 0.0, longest = 0.0;
+    for (int i = 0; i < g.n; ++i) {
+      const GemmProb& p = g.p[i];
+      const double one = per * (double)(ceil_div(ceil_div(p.K, BK), p.splits) + 6);
+      total += one * (double)(p.splits * ceil_div(rows_expected(p.M, p.epi), tm) * ceil_div(p.N, BN));
+      longest = std::max(longest, one);
+    }
+    cost[t] = std::max(total / kUnits, longest) + 0.5 * longest;
+  }
+  return cost[1] <= cost[0] ? 128 : 256;
 }
 
 }  // namespace
 
-int mfma_splits(int64_t M, int64_t N, int64_t K, int epi) {
-  if (epi == EPI_RESIDUAL) return 1;
-  // the scatter-add product runs over the fired rows only (a device-side count): size it for a quarter of them
-  const int64_t m_eff = (epi == EPI_SCATTER_ADD || epi == EPI_SCATTER_STORE) ? std::max<int64_t>(BM, M / 4) : M;
-  const int64_t tiles = ceil_div(m_eff, BM) * ceil_div(N, BN);
-  const int64_t nk = ceil_div(K, BK);
-  int s = 1;
-  while (s < 8 && tiles * s < 256 && nk / (s * 2) >= 4) s *= 2;  // fill the chip, keep >= 4 k-tiles per split
-  return s;
-}
-
-size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi) {
-  const int s = mfma_splits(M, N, K, epi);
-  return s > 1 ? align_up((size_t)s * M * N * sizeof(float), 256) : 0;
-}
-
-hipError_t mfma_gemm_nt(const GemmArgs& g0, int epi, hipStream_t s) {
-  if (g0.M <= 0 || (epi != EPI_MULTI && g0.N <= 0)) return hipSuccess;
-  GemmArgs g = g0;
-  if (epi == EPI_MULTI) {  // several right-hand factors side by side, never split
-    if (g.nseg < 1 || g.nseg > kMaxGemmSegs) return hipErrorInvalidValue;
-    int t = 0;
-    for (int i = 0; i < g.nseg; ++i) {
-      g.seg[i].tile_begin = t;
-      t += (int)ceil_div(g.seg[i].N, BN);
-    }
-    g.N = g.seg[0].N;
-    g.splits = 1;
-    g.part = nullptr;
-    if (g.a_f32 == 2) return launch_epi<2>(g, epi, s);
-    return g.a_f32 ? launch_epi<1>(g, epi, s) : launch_epi<0>(g, epi, s);
+hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s) {
+  GemmArgs g;
+  int i = 0;
+  while (i < n) {
+    g.n = 0;
+    for (; i < n && g.n < kMaxProbs; ++i)
+      if (probs[i].M > 0 && probs[i].N > 0) g.p[g.n++] = probs[i];
+    if (g.n == 0) break;
+    for (int q = 0; q < g.n; ++q) g.p[q].splits = g.p[q].part ? g.p[q].max_splits : 1;
+    const int tm = plan_rows(g, epi);
+    const hipError_t e = a_f32 == 2 ? launch_epi<2>(g, epi, tm, s) : a_f32 ? launch_epi<1>(g, epi, tm, s) : launch_epi<0>(g, epi, tm, s);
+    if (e != hipSuccess) return e;
   }
-  g.splits = g.part ? mfma_splits(g.M, g.N, g.K, epi) : 1;
-  if (g.a_f32 == 2) return launch_epi<2>(g, epi, s);
-  return g.a_f32 ? launch_epi<1>(g, epi, s) : launch_epi<0>(g, epi, s);
+  return hipSuccess;
 }
 
-hipError_t mfma_transpose_bf16(const void* U, void* Ut, int rows, int cols, hipStream_t s) {
-  dim3 grid((unsigned)ceil_div(cols, 32), (unsigned)ceil_div(rows, 32));
-  transpose_bf16<<<grid, 256, 0, s>>>(reinterpret_cast<const uint16_t*>(U), reinterpret_cast<uint16_t*>(Ut), rows, cols);
-  return hipGetLastError();
+hipError_t mfma_transpose_bf16(TransposeTask* tasks, int n, hipStream_t s) {
+  for (int i = 0; i < n;) {
+    TransposeArgs a;
+    int blocks = 0;
+    for (a.n = 0; i < n && a.n < kMaxTransposes; ++i, ++a.n) {
+      a.t[a.n] = tasks[i];
+      a.t[a.n].blk_begin = blocks;
+      blocks += (int)(ceil_div(tasks[i].rows, 64) * ceil_div(tasks[i].cols, 64));
+    }
+    transpose_bf16<<<(unsigned)blocks, 256, 0, s>>>(a);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
-int mfma_res_tiles(int64_t d) { return (int)ceil_div(d, WTN); }
+int mfma_res_tiles(int64_t d, bool full) { return (int)ceil_div(d, full ? 64 : 128); }
 
 }  // namespace gsi
