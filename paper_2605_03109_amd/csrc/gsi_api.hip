@@ -108,7 +108,7 @@ static size_t project_ws_bytes(int64_t d, int64_t k, int64_t B, bool full) {
   size_t need = 0;
   for (int dt = 0; dt < 2; ++dt) {
     if (!gsi::decode_project_ok(d, k, dt, nullptr) || !(full || gsi::rank_pow2(k, dt))) continue;
-    const size_t w = gsi::decode_project_ws(d, k, B, dt);
+    const size_t w = gsi::decode_project_ws(d, k, B, dt, full);
     if (w > need) need = w;
   }
   return need;
@@ -374,10 +374,10 @@ static bool project_vector_path(int64_t d, int64_t k, int64_t B, int udtype, con
 }
 
 static void fill_proj_task(gsi::ProjTask& t, const void* U, const void* X, int64_t d, int64_t k, int64_t B,
-                           int udtype, int xdtype, float* C, float* R, float* rnorm, float* xnorm, void* ws) {
+                           int udtype, int xdtype, float* C, float* R, float* rnorm, float* xnorm, void* ws, bool full) {
   t.U = U; t.X = X; t.C = C; t.R = R; t.rnorm = rnorm; t.xnorm = xnorm;
   t.udtype = udtype; t.xdtype = xdtype;
-  gsi::decode_project_fill(t, d, k, B, ws);
+  gsi::decode_project_fill(t, d, k, B, ws, full);
 }
 
 // Prefill-sized projections of independent inputs on the matrix cores: C = X U, then R = X - C U^T with per-tile partial
@@ -610,7 +610,7 @@ int gsi_project(const void* U, const void* X, int64_t d, int64_t k, int64_t B, i
     std::memset(&pb, 0, sizeof(pb));
     pb.n = 1;
     pb.B = (int)B;
-    fill_proj_task(pb.t[0], U, X, d, k, B, udtype, xdtype, C, R, rnorm, xnorm, ws);
+    fill_proj_task(pb.t[0], U, X, d, k, B, udtype, xdtype, C, R, rnorm, xnorm, ws, full);
     e = gsi::decode_project_launch(pb, udtype, true, false, 0.f, s);
   } else if (mfma_project_path(U, X, d, k, B, udtype, xdtype, C, R)) {
     const MfmaInput in{U, X, d, k, xdtype, C, R, rnorm, xnorm, nullptr, nullptr, nullptr, static_cast<char*>(ws)};
@@ -1041,7 +1041,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
     if (B == 0 || !project_vector_path(in.d, in.k, B, in.udtype, in.U, full)) continue;
     mode[i] = kVecGate;
     fill_proj_task(ptask[i], in.U, in.X, in.d, in.k, B, in.udtype, in.xdtype, in.C, in.R, in.rnorm, in.xnorm,
-                   reinterpret_cast<char*>(ws) + ws_off[i]);
+                   reinterpret_cast<char*>(ws) + ws_off[i], full);
     ptask[i].mask = in.mask; ptask[i].fired_idx = in.fired_idx; ptask[i].n_fired = in.n_fired;
     if (B != 1) continue;
     int readers = 0;

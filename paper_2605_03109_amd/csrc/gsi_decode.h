@@ -40,7 +40,8 @@ struct ProjTask {
   int b_rows, b_slabs;             // residual: rows per slab, slabs
   int udtype, xdtype;
   int tile;                        // decode batch on the matrix cores (gsi_tile.hip) with its own slab geometry: the
-                                   // number of bf16 terms an fp32 operand is split into (2 or 3), else 0
+                                   // number of bf16 terms an fp32 operand is split into (2 or 3), kTileF32 for fp32
+                                   // storage (gsi_tile_f32.hip), else 0
   int b_perm;                      // residual slabs per partial-projection slab when the residual launch walks its
                                    // slabs in the XCD order of the partial projection, else 0 (filled at launch)
   int s_rows, s_slabs;             // single token (gsi_stage.hip): rows per slab and slabs of the partial projection
@@ -130,9 +131,10 @@ inline bool rank_pow2(int64_t k, int udtype) {
 // batch of 2..128 tokens whose shape the matrix-core kernel takes)
 bool decode_linear_ok(int64_t m, int64_t d, int64_t k, int wdtype, const void* W, const void* M, int64_t B = 2);
 
-size_t decode_project_ws(int64_t d, int64_t k, int64_t B, int udtype);
+// full: with what the decode batches of fp32 storage take on the matrix cores (else the FMA kernels run them)
+size_t decode_project_ws(int64_t d, int64_t k, int64_t B, int udtype, bool full);
 // fills d, k, slab geometry and the two workspace pointers of a task whose other fields are set
-void decode_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws);
+void decode_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws, bool full);
 
 // partial projection + residual (+ norms, + gate): with_norms = false leaves the norms to the
 // single-token linear kernel (which reads part_n itself)
@@ -161,6 +163,15 @@ void tile_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws);
 // bf16 terms that an fp32 operand of a decode batch is split into, by rank and activation type (see gsi_tile.hip)
 inline int tile_proj_terms(int64_t k, int xdtype) { return k % 64 || !rank_pow2(k, GSI_BF16) || xdtype != GSI_F32 ? 3 : 2; }
 int tile_rows_terms(const LinBatch& lb, int group);
+hipError_t tile_proj_reduce_launch(const ProjBatch& pb, hipStream_t s);  // C = the slab partials added
+// ... and with fp32 storage (gsi_tile_f32.hip): any shape that the vector kernels take
+constexpr int kTileF32 = 4;
+constexpr int kMaxTileTok = 128;  // tokens of a decode batch on the matrix cores
+bool f32_project_shape_ok(int64_t d, int64_t k, int64_t B, int udtype);
+size_t f32_project_ws(int64_t d, int64_t k, int64_t B);
+void f32_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws);
+hipError_t f32_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s);
+hipError_t f32_rows_launch(LinBatch& lb, hipStream_t s);
 hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s);
 bool tile_rows_shape_ok(int64_t m, int64_t d, int64_t k, int64_t B, int wdtype);
 bool tile_rows_ok(const LinBatch& lb, int wdtype);

@@ -207,7 +207,16 @@ bool decode_linear_ok(int64_t m, int64_t d, int64_t k, int wdtype, const void* W
   return m < (1ll << 30);
 }
 
+// fp32 storage: X is read in 16-byte pieces (what reads C and R was checked by the callers)
+static bool f32_rows_ok(const LinBatch& lb, int wdtype) {
+  if (wdtype != GSI_F32 || lb.B < 2 || lb.B > kMaxTileTok) return false;
+  for (int i = 0; i < lb.ng; ++i)
+    if ((lb.dense || lb.g[i].wx) && reinterpret_cast<uintptr_t>(lb.g[i].X) % 16) return false;
+  return true;
+}
+
 bool decode_linear_fits(const LinBatch& lb, int wdtype) {
+  if (f32_rows_ok(lb, wdtype)) return true;
   if (lb.B == 1) return stream_smem_bytes(lb) <= (size_t)kMaxLinD * sizeof(float);
   if (tile_rows_ok(lb, wdtype)) {  // one number of operand terms per launch
     for (int i = 1; i < lb.ng; ++i)
@@ -221,6 +230,7 @@ hipError_t decode_linear_launch(LinBatch& lb, int wdtype, hipStream_t s, hipEven
   if (lb.n == 0 || lb.B == 0) return hipSuccess;
   if (lb.B == 1) return stream_rows_launch(lb, wdtype, s, e0, e1);
   if (tile_rows_ok(lb, wdtype)) return tile_rows_launch(lb, s);
+  if (f32_rows_ok(lb, wdtype)) return f32_rows_launch(lb, s);
   if (tile_smem(lb) > (size_t)kMaxLinD * sizeof(float)) return hipErrorInvalidValue;  // (callers rule this out)
   int total = 0;
   for (int i = 0; i < lb.n; ++i) {

@@ -466,7 +466,7 @@ ProjGeom proj_geom(int64_t d, int64_t k, int udtype) {
 }
 }  // namespace
 
-size_t decode_project_ws(int64_t d, int64_t k, int64_t B, int udtype) {
+size_t decode_project_ws(int64_t d, int64_t k, int64_t B, int udtype, bool full) {
   const ProjGeom g = proj_geom(d, k, udtype);
   int s_rows = 0, s_slabs = 0;
   if (B == 1) stage_geom(d, k, udtype, s_rows, s_slabs, true);  // the finer of the two geometries
@@ -476,11 +476,18 @@ size_t decode_project_ws(int64_t d, int64_t k, int64_t B, int udtype) {
   size_t need = align_up(part_slabs * B * k * 4 * (B == 1 ? 2 : 1), 256) +
                 align_up(std::max((size_t)g.b_slabs * B * 2 * 4, sizeof(double) * kGateDoubles), 256);
   if (tile_project_shape_ok(d, k, B, udtype)) need = std::max(need, tile_project_ws(d, k, B));
+  if (full && f32_project_shape_ok(d, k, B, udtype)) need = std::max(need, f32_project_ws(d, k, B));
   return need;
 }
 
-void decode_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws) {
+void decode_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws, bool full) {
   t.tile = 0;
+  if (full && f32_project_shape_ok(d, k, B, t.udtype) && reinterpret_cast<uintptr_t>(t.X) % 16 == 0 &&
+      reinterpret_cast<uintptr_t>(t.C) % 16 == 0 && reinterpret_cast<uintptr_t>(t.R) % 16 == 0) {
+    f32_project_fill(t, d, k, B, ws);
+    t.tile = kTileF32;
+    return;
+  }
   if (tile_project_shape_ok(d, k, B, t.udtype) && reinterpret_cast<uintptr_t>(t.X) % 16 == 0 &&
       reinterpret_cast<uintptr_t>(t.C) % 16 == 0 && reinterpret_cast<uintptr_t>(t.R) % 16 == 0) {
     tile_project_fill(t, d, k, B, ws);
@@ -549,7 +556,7 @@ hipError_t decode_project_launch(ProjBatch& pb, int udtype, bool with_norms, boo
   }
   // tasks of a decode batch that take the matrix-core kernels go in a launch set of their own
   {
-    for (int terms = 2; terms <= 3; ++terms) {  // (one launch set per number of operand terms)
+    for (int terms = 2; terms <= kTileF32; ++terms) {  // (one launch set per number of operand terms, one for fp32)
       ProjBatch tile_pb = pb, rest = pb;
       tile_pb.n = rest.n = 0;
       for (int i = 0; i < pb.n; ++i) {
@@ -557,7 +564,9 @@ hipError_t decode_project_launch(ProjBatch& pb, int udtype, bool with_norms, boo
         else rest.t[rest.n++] = pb.t[i];
       }
       if (tile_pb.n == 0) continue;
-      if (hipError_t e = tile_project_launch(tile_pb, with_norms, with_gate, eps, s); e != hipSuccess) return e;
+      const hipError_t e = terms == kTileF32 ? f32_project_launch(tile_pb, with_norms, with_gate, eps, s)
+                                             : tile_project_launch(tile_pb, with_norms, with_gate, eps, s);
+      if (e != hipSuccess) return e;
       if (rest.n == 0) return hipSuccess;
       pb = rest;
     }

@@ -23,6 +23,7 @@
 
 #include "gsi_decode.h"
 #include "gsi_device.h"
+#include "gsi_tile_common.h"
 
 namespace gsi {
 namespace {
@@ -37,7 +38,6 @@ constexpr int kSteps = 16;                         // MFMA steps per item
 constexpr int kStepCols = 32;                      // contraction columns per MFMA
 constexpr int kSliceCols = kSteps * kStepCols;     // 512 columns per item
 constexpr int kRoundTok = 32;                      // tokens staged per round (two MFMA token tiles)
-constexpr int kMaxTok = 128;                       // tokens per call
 constexpr int kMaxTokTiles = kMaxTok / 16;
 constexpr int kVRow = kSliceCols + 8;              // bf16 per staged token row: 16 bytes of padding keep
                                                    // the 16 lanes of a 128-bit LDS read on distinct banks
@@ -50,14 +50,6 @@ __device__ __forceinline__ int find_task(const int (&begin)[N], int n, int b) {
   for (int i = 1; i < N; ++i)
     if (i < n && b >= begin[i]) t = i;
   return t;
-}
-
-// four consecutive activations at element offset i (a multiple of four) as fp32; calls of two terms have fp32 ones
-template <int T>
-__device__ __forceinline__ float4 load_act4(const void* p, int dtype, int64_t i) {
-  if (T == 2 || dtype == GSI_F32) return *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p) + i);
-  const uint2 b = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(p) + i);
-  return float4{bf16_lo(b.x), bf16_hi(b.x), bf16_lo(b.y), bf16_hi(b.y)};
 }
 
 // four fp32 values as T bf16 terms each: term 0 the rounded value, every further term the rounded remainder (exact
@@ -102,7 +94,7 @@ __device__ __forceinline__ void stage_issue(float4 (&v)[kHalfVec], int half, con
     for (int i = 0; i < kHalfVec; ++i) tok[i] = min(j0 + 4 * i, count - 1);
   }
 #pragma unroll
-  for (int i = 0; i < kHalfVec; ++i) v[i] = load_act4<T>(V, vdt, (int64_t)tok[i] * ldv + c0 + 4 * c4);
+  for (int i = 0; i < kHalfVec; ++i) v[i] = load_act4<T == 2>(V, vdt, (int64_t)tok[i] * ldv + c0 + 4 * c4);
 }
 
 // what stage_issue requested, as T bf16 terms in LDS; columns past the slice are zero
@@ -379,7 +371,7 @@ __global__ __launch_bounds__(kPBlock) void tile_proj_partial(const ProjBatch pb)
     const int sc = min(s, steps - 1);  // steps past the slab repeat the last one and are not consumed
     ur[s] = *reinterpret_cast<const uint4*>(usrc + (int64_t)sc * kStepCols * k);
 #pragma unroll
-    for (int u = 0; u < kXV; ++u) xr[s][u] = load_act4<T>(p.X, p.xdtype, xsrc[u] + sc * kStepCols);
+    for (int u = 0; u < kXV; ++u) xr[s][u] = load_act4<T == 2>(p.X, p.xdtype, xsrc[u] + sc * kStepCols);
   }
   __builtin_amdgcn_sched_barrier(0);  // every request of the slab is issued before the first wait
   auto commit = [&](int s, int buf) {
@@ -474,62 +466,6 @@ __global__ __launch_bounds__(256) void tile_proj_reduce(const ProjBatch pb) {
   }
 }
 
-// |r|, |x| per token from the row blocks' shares, then the gate and the ordered list of fired tokens
-// (Eq. (gate); Algorithm 1, line 4), by the 512 threads of one workgroup.  16 threads share a token (4 beyond
-// 32 tokens): each adds its part of the shares in order, the part sums are then added in order.
-// red: 512 float2 and two ints of LDS.
-__device__ __forceinline__ void norms_and_gate(const ProjTask& p, int B, int do_gate, float eps, float2* red,
-                                               int* wave_count) {
-  const int slots = B <= 32 ? 32 : kMaxTok, parts = kTBlock / slots;
-  const int t = threadIdx.x % slots, part = threadIdx.x / slots;
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int per = (p.b_slabs + parts - 1) / parts;
-  const int s_begin = part * per, s_end = min(p.b_slabs, s_begin + per);
-  float sr = 0.f, sx = 0.f;
-  const float2* src = reinterpret_cast<const float2*>(p.part_n) + min(t, B - 1);
-  for (int s0 = s_begin; s0 < s_end; s0 += 8) {
-    unsigned long long q[8];  // (|r|^2, |x|^2) shares, read past the caches: other workgroups of this launch wrote them
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      q[u] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(src + (int64_t)min(s0 + u, p.b_slabs - 1) * B),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (s0 + u < s_end) { sr += __uint_as_float((unsigned)q[u]); sx += __uint_as_float((unsigned)(q[u] >> 32)); }
-  }
-  red[part * slots + t] = float2{sr, sx};
-  __syncthreads();
-  // the threads of part 0 (thread index = token) finish the job; the others only keep the barriers
-  const bool head = part == 0;
-  sr = red[t].x;
-  sx = red[t].y;
-  for (int w = 1; w < parts; ++w) {
-    sr += red[w * slots + t].x;
-    sx += red[w * slots + t].y;
-  }
-  const float rn = sqrtf(sr), xn = sqrtf(sx);
-  if (head && t < B) {
-    p.rnorm[t] = rn;
-    p.xnorm[t] = xn;
-  }
-  if (!do_gate) return;  // uniform
-  const bool fired = head && t < B && gate_fires(rn, xn, eps);
-  if (head && t < B) p.mask[t] = fired ? 1 : 0;
-  const unsigned long long ballot = __ballot(fired);
-  const int rank_in_wave = __popcll(ballot & ((1ull << lane) - 1ull));
-  if (wave < kMaxTok / kWave && lane == 0) wave_count[wave] = __popcll(ballot);
-  __syncthreads();
-  int before = 0, total = 0;
-#pragma unroll
-  for (int wv = 0; wv < kMaxTok / kWave; ++wv) {
-    const int c = wave_count[wv];
-    if (wv < wave) before += c;
-    total += c;
-  }
-  if (fired) p.fired_idx[before + rank_in_wave] = t;
-  if (threadIdx.x == 0) p.n_fired[0] = total;
-}
-
 // r = x - U c for 128 rows x 32 tokens per workgroup (the weights of this product are the rows of U, which are
 // contiguous: same operand flow as tile_rows), R written, and the row block's share of |r|^2 and |x|^2.
 // The workgroup of an input that finishes last (a counter in the workspace, zeroed by the partial-projection
@@ -564,7 +500,7 @@ __global__ __launch_bounds__(kTBlock) void tile_residual(const ProjBatch pb) {
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int j = min(g0 + 16 * t + li, B - 1);
-    xv[t] = load_act4<T>(p.X, p.xdtype, (int64_t)j * d + row0 + 4 * lq);
+    xv[t] = load_act4<T == 2>(p.X, p.xdtype, (int64_t)j * d + row0 + 4 * lq);
   }
   __builtin_amdgcn_sched_barrier(0);
   stage_commit<T>(v, 0, vt, k, wave);
@@ -619,7 +555,7 @@ __global__ __launch_bounds__(kTBlock) void tile_residual(const ProjBatch pb) {
   }
   __syncthreads();
   if (!s_last) return;  // uniform
-  norms_and_gate(p, B, pb.gate, pb.eps, reinterpret_cast<float2*>(&vt[0][0][0]), reinterpret_cast<int*>(&vt[1][0][0]));
+  norms_and_gate<kTBlock>(p, B, pb.gate, pb.eps, reinterpret_cast<float2*>(&vt[0][0][0]), reinterpret_cast<int*>(&vt[1][0][0]));
 }
 
 }  // namespace
@@ -652,32 +588,40 @@ void tile_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws) {
   t.sync = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(t.part_n) + align_up((size_t)t.b_slabs * B * 2 * 4, 256));
 }
 
+hipError_t tile_proj_reduce_launch(const ProjBatch& pb, hipStream_t s) {
+  int max_k = 0;
+  for (int i = 0; i < pb.n; ++i) max_k = max_k > pb.t[i].k ? max_k : pb.t[i].k;
+  const dim3 grid((unsigned)ceil_div((int64_t)pb.B * (max_k / 4), kRedOut), (unsigned)pb.n);
+  tile_proj_reduce<<<grid, 256, 0, s>>>(pb);
+  return hipGetLastError();
+}
+
 hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s) {
   if (pb.n == 0 || pb.B == 0) return hipSuccess;
   const int rounds = (int)ceil_div(pb.B, kRoundTok);
-  int ta = 0, tb = 0, max_k = 0;
+  int ta = 0, tb = 0;
   for (int i = 0; i < pb.n; ++i) {
     pb.a_begin[i] = ta;
     pb.b_begin[i] = tb;
     ta += pb.t[i].a_slabs * pb.t[i].a_cblocks;
     tb += pb.t[i].b_slabs * rounds;
-    if (pb.t[i].k > max_k) max_k = pb.t[i].k;
   }
   pb.b_total = tb;
   pb.norms = with_norms ? 1 : 0;
   pb.gate = with_gate ? 1 : 0;
   pb.eps = eps;
-  const dim3 rgrid((unsigned)ceil_div((int64_t)pb.B * (max_k / 4), kRedOut), (unsigned)pb.n);
+  hipError_t err = hipSuccess;
   auto launch = [&](auto terms) {
     constexpr int T = decltype(terms)::value;
     if (pb.B <= 32) tile_proj_partial<1, T><<<ta, kPBlock, 0, s>>>(pb);
     else if (pb.B <= 64) tile_proj_partial<2, T><<<ta, kPBlock, 0, s>>>(pb);
     else tile_proj_partial<4, T><<<ta, kPBlock, 0, s>>>(pb);
-    tile_proj_reduce<<<rgrid, 256, 0, s>>>(pb);
+    err = tile_proj_reduce_launch(pb, s);
     tile_residual<T><<<tb, kTBlock, 0, s>>>(pb);
   };
   if (pb.t[0].tile == 3) launch(std::integral_constant<int, 3>{});
   else launch(std::integral_constant<int, 2>{});
+  if (err != hipSuccess) return err;
   return hipGetLastError();
 }
 
