@@ -150,8 +150,8 @@ size_t gsi_extend_basis_workspace_bytes(int64_t d, int64_t K);
 
 /* The same step for n bases in ONE set of launches (Section 5.4 "Time-dimension tracking": every basis of a model
  * sees every token).  Each basis is extended exactly as gsi_extend_basis would extend it, bit for bit, on its own
- * verdict; a token after which no basis grows costs seven nearly empty launches for the whole call instead of seven
- * per basis.  descs: HOST array, one entry per basis with the arguments of gsi_extend_basis (maps: HOST array of
+ * verdict; a token after which no basis grows costs a few nearly empty launches for the whole call instead of as
+ * many per basis.  descs: HOST array, one entry per basis with the arguments of gsi_extend_basis (maps: HOST array of
  * n_maps entries, may be NULL when n_maps is 0; gram and extended may be NULL); all bases of a call share one
  * udtype; n <= 65535 and at most 65535 maps in all.  tau as in gsi_extend_basis, one value for the call.
  * ws: gsi_extend_many_workspace_bytes(descs, n) bytes, 256-byte aligned (the call copies its descriptor table there).

@@ -15,13 +15,17 @@
 // first one, forming) the verdict and leaves at once when there is nothing to do, so a token that does not extend
 // the basis costs a handful of empty launches and no pass over U or W.  All sums have a fixed order.
 //
-// Launches: s partials (+ the candidate verdict) | s | r2 and shares of |r2|^2 | final verdict + the stored column
-// | image columns of all maps | U^T u partials | E's row and column.  An extension moves U three times and every
-// W once; operands whose rows are 16-byte aligned are read with 16-byte loads, several in flight per lane.
+// Launches: s partials (+ the candidate verdict) | s, r2 and shares of |r2|^2 | final verdict, the stored column, the image
+// columns of all maps and the partials of U^T u | E's row and column.  The three jobs of the third launch need the stored
+// column u = r2 / |r2| rounded, and each workgroup forms the part it reads from r2 and the shares itself (the same
+// arithmetic everywhere), so none waits for another; the workgroup that reads the new column of U takes u for it.  An
+// extension moves U three times and every W once; operands whose rows are 16-byte aligned are read with 16-byte loads,
+// several in flight per lane.  (s in a launch of its own, the column and U^T u likewise: seven launches of 4 to 5 us around
+// one of 24 us; three maps 4096 x 4096 on a basis of 4096 x 512: 51.7 us, 43.4 us with these four.)
 //
 // Every launch covers ALL bases of a call (one grid dimension is the basis, or the map): a token's pass over the
-// bases of a whole model is these seven launches, not seven per basis, and what it costs when no basis grows is
-// seven nearly empty launches.  The records of a call with several bases sit in a table in the workspace (copied
+// bases of a whole model is these four launches, not four per basis, and what it costs when no basis grows is
+// four nearly empty launches.  The records of a call with several bases sit in a table in the workspace (copied
 // there by the call); a call with one basis carries its record in the kernel arguments.
 #include <hip/hip_runtime.h>
 
@@ -40,7 +44,9 @@ constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / kWave;
 constexpr int kCols = 64;       // columns of U per workgroup in the projections
 constexpr int kRowsPerWg = 32;  // rows of U per workgroup in the residual
-constexpr int kImgRows = kWaves;  // rows of W per workgroup and turn in the image launch: one per wave
+constexpr int kImgPerWave = 4;    // rows of W per wave and turn in the image launch
+constexpr int kImgRows = kWaves * kImgPerWave;
+constexpr int kLdsK = 2048;       // ranks whose s the residual workgroups add up themselves (in LDS)
 constexpr int kFewMaps = 8;     // maps whose records fit the kernel arguments
 constexpr int kSumBlock = 64;   // a wave per workgroup in the slab sums
 
@@ -55,7 +61,7 @@ struct ExtMapArg {  // the maps of an image launch: a device table, or up to kFe
 
 struct ExtWs {
   ExtState* st;
-  float *part, *sv, *r2, *ust, *pn;
+  float *part, *sv, *r2, *pn;
 };
 __host__ __device__ __forceinline__ size_t a256(size_t b) { return (b + 255) / 256 * 256; }
 __host__ __device__ __forceinline__ ExtWs ext_ws(const ExtIn& in) {
@@ -69,117 +75,145 @@ __host__ __device__ __forceinline__ ExtWs ext_ws(const ExtIn& in) {
   p += a256((size_t)in.K * 4);
   w.r2 = reinterpret_cast<float*>(p);
   p += a256((size_t)in.d * 4);
-  w.ust = reinterpret_cast<float*>(p);
-  p += a256((size_t)in.d * 4);
   w.pn = reinterpret_cast<float*>(p);
   return w;
 }
 
-// part[slab][j] = sum over the slab's rows of U[i, j] v[i]   (grid: column blocks x slabs x bases).
-// first: this is the projection s = U^T r of the step: every workgroup forms the candidate verdict from the token's
-// norms and the column counter (the first one of a basis records it); else the projection U^T u for E, run iff the
-// basis grew and the caller keeps E.
+// the candidate's norm: every workgroup of a basis adds the shares of |r2|^2 in the same fixed order; 1 / |r2|, or 0 when
+// the basis does not grow
+__device__ __forceinline__ float ext_inverse(const ExtIn& in, const ExtWs& w, float* sh) {
+  const int cand = w.st->cand;  // (requested with the shares, which are not used if it is zero)
+  float t = 0.f;
+  for (int q = threadIdx.x; q < in.wgs; q += kBlock) t += w.pn[q];
+  t = group_sum<kWave>(t);
+  if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = t;
+  __syncthreads();
+  float tot = 0.f;
+#pragma unroll
+  for (int q = 0; q < kWaves; ++q) tot += sh[q];
+  const float n2 = sqrtf(tot);
+  return cand && n2 > 0.f ? 1.f / n2 : 0.f;
+}
+// element of the stored column, widened
 template <class T>
-__global__ __launch_bounds__(kBlock) void ext_proj(const ExtArg a, float tau, int first) {
+__device__ __forceinline__ float stored(float v) {
+  typename T::storage t;
+  T::store(&t, 0, v);
+  return T::load(&t, 0);
+}
+
+// part[slab][j] = sum over the rows of slabs slab0, slab0 + step, ... of U[i, j] v[i] for the 64 columns of block cb.
+// v: the residual r (inv == 0), or the stored column u = r2 inv, which stands in for column kc of U as well (another
+// workgroup of the launch is writing it).
+template <class T>
+__device__ __forceinline__ void proj_block(const ExtIn& in, const ExtWs& w, const float* __restrict__ v, float inv, int kc, int cb,
+                                           int slab0, int step) {
   using S = typename T::storage;
-  const ExtIn in = a.tab ? a.tab[blockIdx.z] : a.one;
-  const ExtWs w = ext_ws(in);
   const int64_t d = in.d, K = in.K;
-  if ((int64_t)blockIdx.x * kCols >= K || (int)blockIdx.y >= in.slabs) return;  // (the grid is sized for the largest basis)
-  const float* v;
-  if (first) {
-    const int k = in.k_cur[0];
-    const bool cand = k >= 0 && k < K && gate_fires(in.rnorm[0], in.xnorm[0], tau);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
-      w.st->kc = k;
-      w.st->cand = cand ? 1 : 0;
-      w.st->ext = 0;
-      w.st->inv = 0.f;
-    }
-    if (!cand) return;
-    v = in.R;
-  } else {
-    if (!in.gram || !w.st->ext) return;
-    v = w.ust;
-  }
   const S* U = static_cast<const S*>(in.U);
   float* part = w.part;
   constexpr int V = T::kVec;
   constexpr int TPR = kCols / V;        // threads per row segment of 64 columns
   constexpr int RG = kBlock / TPR;      // rows in flight per pass of the workgroup
   __shared__ float sh[RG][kCols + 1];
+  const bool use_u = inv != 0.f;
+  auto value = [&](int64_t i) { return use_u ? stored<T>(v[i] * inv) : v[i]; };
   // (a call with many bases launches fewer workgroups per basis than it has slabs: the workgroup takes several)
-  for (int slab = blockIdx.y; slab < in.slabs; slab += gridDim.y) {
-  const int64_t r0 = (int64_t)slab * in.rows_per_slab;
-  const int64_t r1 = r0 + in.rows_per_slab < d ? r0 + in.rows_per_slab : d;
-  if (in.uvec) {
-    const int rg = threadIdx.x / TPR, cv = threadIdx.x % TPR;
-    const int64_t col0 = (int64_t)blockIdx.x * kCols + cv * V;
-    float acc[V];
+  for (int slab = slab0; slab < in.slabs; slab += step) {
+    const int64_t r0 = (int64_t)slab * in.rows_per_slab;
+    const int64_t r1 = r0 + in.rows_per_slab < d ? r0 + in.rows_per_slab : d;
+    if (in.uvec) {
+      const int rg = threadIdx.x / TPR, cv = threadIdx.x % TPR;
+      const int64_t col0 = (int64_t)cb * kCols + cv * V;
+      const int own = use_u ? (int)(kc - col0) : -1;  // the element that is column kc
+      float acc[V];
 #pragma unroll
-    for (int e = 0; e < V; ++e) acc[e] = 0.f;
-    if (col0 < K) {  // K is a multiple of V here: whole vectors
-      for (int64_t i = r0 + rg; i < r1; i += 4 * RG) {
-        float f[4][V], wt[4];
+      for (int e = 0; e < V; ++e) acc[e] = 0.f;
+      if (col0 < K) {  // K is a multiple of V here: whole vectors
+        for (int64_t i = r0 + rg; i < r1; i += 4 * RG) {
+          float f[4][V], wt[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {  // four rows requested before the first is used; rows past the slab repeat
-          const int64_t ii = i + q * RG;  // the last one with weight zero
-          const int64_t ic = ii < r1 ? ii : r1 - 1;
-          T::load_vec(U + ic * K + col0, f[q]);
-          wt[q] = ii < r1 ? v[ic] : 0.f;
+          for (int q = 0; q < 4; ++q) {  // four rows requested before the first is used; rows past the slab repeat
+            const int64_t ii = i + q * RG;  // the last one with weight zero
+            const int64_t ic = ii < r1 ? ii : r1 - 1;
+            T::load_vec(U + ic * K + col0, f[q]);
+            wt[q] = ii < r1 ? value(ic) : 0.f;
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < V; ++e) acc[e] = fmaf(e == own ? wt[q] : f[q][e], wt[q], acc[e]);
         }
+      }
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int e = 0; e < V; ++e) acc[e] = fmaf(f[q][e], wt[q], acc[e]);
+      for (int e = 0; e < V; ++e) sh[rg][cv * V + e] = acc[e];
+      __syncthreads();
+      const int64_t col = (int64_t)cb * kCols + threadIdx.x;
+      if (threadIdx.x < kCols && col < K) {
+        float s = 0.f;
+        for (int q = 0; q < RG; ++q) s += sh[q][threadIdx.x];
+        part[(int64_t)slab * K + col] = s;
+      }
+    } else {
+      constexpr int RL = kBlock / kCols;
+      const int64_t col = (int64_t)cb * kCols + threadIdx.x % kCols;
+      const int rl = threadIdx.x / kCols;
+      float acc = 0.f;
+      if (col < K)
+        for (int64_t i = r0 + rl; i < r1; i += RL) {
+          const float x = value(i);
+          acc = fmaf(use_u && col == kc ? x : T::load(U, i * K + col), x, acc);
+        }
+      sh[rl][threadIdx.x % kCols] = acc;
+      __syncthreads();
+      if (rl == 0 && col < K) {
+        float s = 0.f;
+        for (int q = 0; q < RL; ++q) s += sh[q][threadIdx.x];
+        part[(int64_t)slab * K + col] = s;
       }
     }
-#pragma unroll
-    for (int e = 0; e < V; ++e) sh[rg][cv * V + e] = acc[e];
-    __syncthreads();
-    const int64_t col = (int64_t)blockIdx.x * kCols + threadIdx.x;
-    if (threadIdx.x < kCols && col < K) {
-      float s = 0.f;
-      for (int q = 0; q < RG; ++q) s += sh[q][threadIdx.x];
-      part[(int64_t)slab * K + col] = s;
-    }
-  } else {
-    constexpr int RL = kBlock / kCols;
-    const int64_t col = (int64_t)blockIdx.x * kCols + threadIdx.x % kCols;
-    const int rl = threadIdx.x / kCols;
-    float acc = 0.f;
-    if (col < K)
-      for (int64_t i = r0 + rl; i < r1; i += RL) acc = fmaf(T::load(U, i * K + col), v[i], acc);
-    sh[rl][threadIdx.x % kCols] = acc;
-    __syncthreads();
-    if (rl == 0 && col < K) {
-      float s = 0.f;
-      for (int q = 0; q < RL; ++q) s += sh[q][threadIdx.x];
-      part[(int64_t)slab * K + col] = s;
-    }
-  }
-  __syncthreads();  // the sums have been read before the next slab's are written
+    __syncthreads();  // the sums have been read before the next slab's are written
   }
 }
 
-// sum over the slabs, in slab order, of part[slab][j]; eight requests in flight
+// Partials of s = U^T r (grid: column blocks x slabs x bases); every workgroup forms the candidate verdict from the
+// token's norms and the column counter, the first one of a basis records it.
+template <class T>
+__global__ __launch_bounds__(kBlock) void ext_proj(const ExtArg a, float tau) {
+  const ExtIn in = a.tab ? a.tab[blockIdx.z] : a.one;
+  const ExtWs w = ext_ws(in);
+  if ((int64_t)blockIdx.x * kCols >= in.K || (int)blockIdx.y >= in.slabs) return;  // (the grid is sized for the largest basis)
+  const int k = in.k_cur[0];
+  const bool cand = k >= 0 && k < in.K && gate_fires(in.rnorm[0], in.xnorm[0], tau);
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    w.st->kc = k;
+    w.st->cand = cand ? 1 : 0;
+    w.st->ext = 0;
+    w.st->inv = 0.f;
+  }
+  if (!cand) return;
+  proj_block<T>(in, w, in.R, 0.f, k, blockIdx.x, blockIdx.y, gridDim.y);
+}
+
+// sum over the slabs, in slab order, of part[slab][j]; sixteen requests in flight
 __device__ __forceinline__ float slab_sum(const float* __restrict__ part, int slabs, int64_t K, int64_t j) {
   float t = 0.f;
-  for (int q0 = 0; q0 < slabs; q0 += 8) {
-    float v[8];
+  for (int q0 = 0; q0 < slabs; q0 += 16) {
+    float v[16];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)min(q0 + u, slabs - 1) * K + j];
+    for (int u = 0; u < 16; ++u) v[u] = part[(int64_t)min(q0 + u, slabs - 1) * K + j];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < 16; ++u)
       if (q0 + u < slabs) t += v[u];
   }
   return t;
 }
 
+// s of bases of more than kLdsK columns (the residual workgroups add up the others themselves)
 __global__ __launch_bounds__(kSumBlock) void ext_sum(const ExtArg a) {
   const ExtIn in = a.tab ? a.tab[blockIdx.y] : a.one;
   const ExtWs w = ext_ws(in);
-  if (!w.st->cand) return;
+  if (in.K <= kLdsK || !w.st->cand) return;
   const int64_t j = (int64_t)blockIdx.x * kSumBlock + threadIdx.x;
   if (j >= in.K) return;
   w.sv[j] = slab_sum(w.part, in.slabs, in.K, j);
@@ -196,44 +230,65 @@ __global__ __launch_bounds__(kBlock) void ext_resid(const ExtArg a) {
   const int64_t d = in.d, K = in.K;
   const S* U = static_cast<const S*>(in.U);
   const float* v = in.R;
-  const float* s = w.sv;
   float* r2 = w.r2;
   constexpr int V = T::kVec;
   __shared__ float shn[kWaves];
+  __shared__ __align__(16) float ss[kLdsK];
+  const float* s = w.sv;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  // rows r0 + wave, + 4, ... of a workgroup's 32: a wave's eight are requested together (rows past the end repeat the last)
+  constexpr int NR = kRowsPerWg / kWaves;
+  uint4 raw[NR];
+  const int64_t chunks = K / V;
+  auto request = [&](int64_t r0, int64_t c) {
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const int64_t i = r0 + wave + q * kWaves;
+      raw[q] = *reinterpret_cast<const uint4*>(U + (i < d ? i : d - 1) * K + (c < chunks ? c : chunks - 1) * V);
+    }
+  };
+  if (in.uvec) request((int64_t)blockIdx.x * kRowsPerWg, lane);  // ahead of the sums below
+  if (K <= kLdsK) {  // uniform
+    for (int64_t j = threadIdx.x; j < K; j += kBlock) ss[j] = slab_sum(w.part, in.slabs, K, j);
+    __syncthreads();
+    s = ss;
+  }
   for (int blk = blockIdx.x; blk < in.wgs; blk += gridDim.x) {
   const int64_t r0 = (int64_t)blk * kRowsPerWg;
   const int64_t r1 = r0 + kRowsPerWg < d ? r0 + kRowsPerWg : d;
   float nn = 0.f;
   if (in.uvec) {
-    const int64_t chunks = K / V;
-    for (int64_t i = r0 + wave; i < r1; i += 2 * kWaves) {
-      const int64_t i2 = i + kWaves < r1 ? i + kWaves : i;  // the second row of the pair, or the first again
-      float a0 = 0.f, a1 = 0.f;
-      for (int64_t c = lane; c < chunks; c += kWave) {
-        float f0[V], f1[V], sv[V];
-        T::load_vec(U + i * K + c * V, f0);
-        T::load_vec(U + i2 * K + c * V, f1);
+    float acc[NR];
 #pragma unroll
-        for (int q = 0; q < V / 4; ++q) {
-          const float4 x = *reinterpret_cast<const float4*>(s + c * V + 4 * q);
-          sv[4 * q] = x.x; sv[4 * q + 1] = x.y; sv[4 * q + 2] = x.z; sv[4 * q + 3] = x.w;
-        }
+    for (int q = 0; q < NR; ++q) acc[q] = 0.f;
+    for (int64_t c = lane; c - lane < chunks; c += kWave) {  // (whole waves)
+      if (c != lane || blk != (int)blockIdx.x) request(r0, c);
+      const bool live = c < chunks;
+      const float* sp = s + (live ? c : chunks - 1) * V;
+      float sv[V];
 #pragma unroll
-        for (int e = 0; e < V; ++e) {
-          a0 = fmaf(f0[e], sv[e], a0);
-          a1 = fmaf(f1[e], sv[e], a1);
-        }
+      for (int q = 0; q < V / 4; ++q) {
+        const float4 x = *reinterpret_cast<const float4*>(sp + 4 * q);
+        sv[4 * q] = x.x; sv[4 * q + 1] = x.y; sv[4 * q + 2] = x.z; sv[4 * q + 3] = x.w;
       }
-      a0 = group_sum<kWave>(a0);
-      a1 = group_sum<kWave>(a1);
-      const float ra = v[i] - a0;
-      if (lane == 0) r2[i] = ra;
-      nn = fmaf(ra, ra, nn);  // (every lane holds the same value)
-      if (i2 != i) {
-        const float rb = v[i2] - a1;
-        if (lane == 0) r2[i2] = rb;
-        nn = fmaf(rb, rb, nn);
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        float f[V];
+        T::widen(raw[q], f);
+        float t = acc[q];
+#pragma unroll
+        for (int e = 0; e < V; ++e) t = fmaf(f[e], sv[e], t);
+        acc[q] = live ? t : acc[q];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const float t = group_sum<kWave>(acc[q]);
+      const int64_t i = r0 + wave + q * kWaves;
+      if (i < r1) {  // uniform
+        const float ra = v[i] - t;
+        if (lane == 0) r2[i] = ra;
+        nn = fmaf(ra, ra, nn);  // (every lane holds the same value)
       }
     }
   } else {
@@ -257,103 +312,140 @@ __global__ __launch_bounds__(kBlock) void ext_resid(const ExtArg a) {
   }
 }
 
-// The final verdict (every workgroup of a basis adds the shares of |r2|^2 in the same fixed order; the first one
-// records the verdict, the column counter and the caller's flag), then column kc of U <- r2 / |r2| rounded to
-// storage; ust = the stored values widened.
+// Column kc of U <- r2 / |r2| rounded to storage; the first workgroup of a basis records the verdict, the column counter
+// and the caller's flag.
 template <class T>
-__global__ __launch_bounds__(kBlock) void ext_column(const ExtArg a) {
+__device__ __forceinline__ void column_block(const ExtIn& in, const ExtWs& w, float inv, int blk, int blocks) {
   using S = typename T::storage;
-  const ExtIn in = a.tab ? a.tab[blockIdx.y] : a.one;
-  const ExtWs w = ext_ws(in);
-  const int64_t d = in.d, K = in.K;
-  if ((int64_t)blockIdx.x * kBlock >= d) return;  // (block 0 of a basis always stays)
-  __shared__ float sh[kBlock];
-  __shared__ float s_inv;
-  const int cand = w.st->cand, kc = w.st->kc;
-  float t = 0.f;
-  if (cand)
-    for (int q = threadIdx.x; q < in.wgs; q += kBlock) t += w.pn[q];
-  sh[threadIdx.x] = t;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float tot = 0.f;
-    for (int q = 0; q < kBlock; ++q) tot += sh[q];
-    const float n2 = sqrtf(tot);
-    const int ext = (cand && n2 > 0.f) ? 1 : 0;
-    s_inv = ext ? 1.f / n2 : 0.f;
-    if (blockIdx.x == 0) {
-      w.st->ext = ext;
-      w.st->inv = s_inv;
-      if (ext) in.k_cur[0] = kc + 1;
-      if (in.extended) in.extended[0] = ext;
-    }
+  const int kc = w.st->kc;
+  if (blk == 0 && threadIdx.x == 0) {
+    const int ext = inv != 0.f ? 1 : 0;
+    w.st->ext = ext;
+    w.st->inv = inv;
+    if (ext) in.k_cur[0] = kc + 1;
+    if (in.extended) in.extended[0] = ext;
   }
-  __syncthreads();
-  const float inv = s_inv;
   if (inv == 0.f) return;  // uniform
   S* U = static_cast<S*>(in.U);
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < d; i += (int64_t)gridDim.x * kBlock) {
-    const int64_t at = i * K + kc;
-    T::store(U, at, w.r2[i] * inv);
-    w.ust[i] = T::load(U, at);
-  }
+  for (int64_t i = (int64_t)blk * kBlock + threadIdx.x; i < in.d; i += (int64_t)blocks * kBlock)
+    T::store(U, i * in.K + kc, w.r2[i] * inv);
 }
 
-// M[row, kc] = sum_i W[row, i] ust[i] (grid: row blocks x maps).  A workgroup takes kImgRows rows of one map, a
-// wave one row at a time (16-byte loads, eight in flight per lane, when the rows allow them).
+// M[row, kc] = sum_i W[row, i] u[i]: a workgroup takes kImgRows rows of a map a turn, a wave kImgPerWave of them.  A wave
+// keeps its lanes' share of u in registers for a block of columns (2048 in bf16) and streams its rows past it, four
+// 16-byte loads per lane and row, three rows under way (u read again for every row: three bytes of cache traffic for a byte
+// of W, 4.2 TB/s).
+// (Requesting the first rows ahead of the verdict costs more in registers than it hides: 26 us against 24.)
 template <class T>
-__global__ __launch_bounds__(kBlock) void ext_image(const ExtArg a, const ExtMapArg ma) {
+__device__ __forceinline__ void image_rows_block(const ExtIn& in, const ExtWs& w, const ExtMapRec& p, float inv, int blk, int blocks) {
   using S = typename T::storage;
-  const ExtMapRec p = ma.tab ? ma.tab[blockIdx.y] : ma.few[blockIdx.y];
-  if ((int64_t)blockIdx.x * kImgRows >= p.m) return;
-  const ExtIn in = a.tab ? a.tab[p.in] : a.one;
-  const ExtWs w = ext_ws(in);
-  if (!w.st->ext) return;
   constexpr int V = T::kVec;
-  constexpr int NL = 8;
+  constexpr int NL = 4, NB = 3;  // loads per lane and row, rows under way
   const int64_t d = in.d, K = in.K;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const float* uv = w.ust;
   const int kc = w.st->kc;
-  for (int64_t row_begin = (int64_t)blockIdx.x * kImgRows; row_begin < p.m; row_begin += (int64_t)gridDim.x * kImgRows)
-  for (int r = wave; r < kImgRows; r += kWaves) {
-    const int64_t row = row_begin + r;
-    if (row >= p.m) break;  // (whole waves leave together)
-    const S* wr = static_cast<const S*>(p.W) + row * d;
-    float acc = 0.f;
-    if (p.vec) {
-      const int64_t chunks = d / V;
-      for (int64_t c0 = 0; c0 < chunks; c0 += (int64_t)kWave * NL) {
-        uint4 raw[NL];
+  const S* W = static_cast<const S*>(p.W);
+  const int64_t chunks = d / V;
+  for (int64_t row_begin = (int64_t)blk * kImgRows; row_begin < p.m; row_begin += (int64_t)blocks * kImgRows) {
+    const int64_t row0 = row_begin + wave * kImgPerWave;
+    if (row0 >= p.m) continue;  // (whole waves)
+    float acc[kImgPerWave];
 #pragma unroll
-        for (int q = 0; q < NL; ++q) {  // chunks past the row repeat its last one and are not used
-          int64_t c = c0 + lane + (int64_t)q * kWave;
-          c = c < chunks ? c : chunks - 1;
-          raw[q] = load_stream16(wr + c * V);
-        }
+    for (int r = 0; r < kImgPerWave; ++r) acc[r] = 0.f;
+    if (p.vec) {
+      for (int64_t c0 = 0; c0 < chunks; c0 += (int64_t)kWave * NL) {
+        uint4 raw[NB][NL];
+        auto request = [&](uint4 (&buf)[NL], int r) {  // rows past the matrix and chunks past the row repeat the last one
+          const S* wr = W + (row0 + r < p.m ? row0 + r : p.m - 1) * d;
+#pragma unroll
+          for (int q = 0; q < NL; ++q) {
+            const int64_t c = c0 + lane + (int64_t)q * kWave;
+            buf[q] = load_stream16(wr + (c < chunks ? c : chunks - 1) * V);
+          }
+        };
+#pragma unroll
+        for (int r = 0; r < NB - 1; ++r) request(raw[r], r);
+        float u[NL][V];
 #pragma unroll
         for (int q = 0; q < NL; ++q) {
           const int64_t c = c0 + lane + (int64_t)q * kWave;
-          if (c < chunks) {
-            float f[V];
-            T::widen(raw[q], f);
+          const float* src = w.r2 + (c < chunks ? c : chunks - 1) * V;
 #pragma unroll
-            for (int e4 = 0; e4 < V / 4; ++e4) {
-              const float4 x = *reinterpret_cast<const float4*>(uv + c * V + 4 * e4);
-              acc = fmaf(f[4 * e4], x.x, acc);
-              acc = fmaf(f[4 * e4 + 1], x.y, acc);
-              acc = fmaf(f[4 * e4 + 2], x.z, acc);
-              acc = fmaf(f[4 * e4 + 3], x.w, acc);
-            }
+          for (int e = 0; e < V; e += 4) {
+            const float4 x = *reinterpret_cast<const float4*>(src + e);
+            u[q][e] = stored<T>(x.x * inv); u[q][e + 1] = stored<T>(x.y * inv);
+            u[q][e + 2] = stored<T>(x.z * inv); u[q][e + 3] = stored<T>(x.w * inv);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < kImgPerWave; ++r) {
+          if (r + NB - 1 < kImgPerWave) request(raw[(r + NB - 1) % NB], r + NB - 1);
+          __builtin_amdgcn_sched_barrier(0);  // later rows' requests stay ahead of this row's arithmetic
+#pragma unroll
+          for (int q = 0; q < NL; ++q) {
+            float f[V];
+            T::widen(raw[r % NB][q], f);
+            float t = 0.f;
+#pragma unroll
+            for (int e = 0; e < V; ++e) t = fmaf(f[e], u[q][e], t);
+            acc[r] += c0 + lane + (int64_t)q * kWave < chunks ? t : 0.f;
           }
         }
       }
     } else {
-      for (int64_t i = lane; i < d; i += kWave) acc = fmaf(T::load(wr, i), uv[i], acc);
+      for (int64_t i = lane; i < d; i += kWave) {
+        const float x = stored<T>(w.r2[i] * inv);
+#pragma unroll
+        for (int r = 0; r < kImgPerWave; ++r)
+          acc[r] = fmaf(T::load(W, (row0 + r < p.m ? row0 + r : p.m - 1) * d + i), x, acc[r]);
+      }
     }
-    acc = group_sum<kWave>(acc);
-    if (lane == 0) T::store(static_cast<S*>(p.M), row * K + kc, acc);
+#pragma unroll
+    for (int r = 0; r < kImgPerWave; ++r) {
+      const float t = group_sum<kWave>(acc[r]);
+      if (lane == 0 && row0 + r < p.m) T::store(static_cast<S*>(p.M), (row0 + r) * K + kc, t);
+    }
   }
+}
+
+// What needs the stored column: workgroups of three kinds, told apart by their index: n bases x col_wgs columns, n bases x
+// (pcols x pslabs) partials of U^T u, maps x img_wgs image rows.
+struct ExtStore {
+  int col_wgs, pcols, pslabs, img_wgs, n, n_maps;
+};
+template <class T>
+__global__ __launch_bounds__(kBlock) void ext_store(const ExtArg a, const ExtMapArg ma, const ExtStore g) {
+  __shared__ float sh[kWaves];
+  int b = blockIdx.x;
+  if (b < g.n * g.col_wgs) {
+    const int blk = b % g.col_wgs;
+    const ExtIn in = a.tab ? a.tab[b / g.col_wgs] : a.one;
+    if (blk > 0 && (int64_t)blk * kBlock >= in.d) return;
+    const ExtWs w = ext_ws(in);
+    column_block<T>(in, w, ext_inverse(in, w, sh), blk, g.col_wgs);
+    return;
+  }
+  b -= g.n * g.col_wgs;
+  const int per = g.pcols * g.pslabs;
+  if (b < g.n * per) {
+    const ExtIn in = a.tab ? a.tab[b / per] : a.one;
+    const int cb = b % per % g.pcols, slab = b % per / g.pcols;
+    if (!in.gram || (int64_t)cb * kCols >= in.K || slab >= in.slabs) return;
+    const ExtWs w = ext_ws(in);
+    if (!w.st->cand) return;
+    const float inv = ext_inverse(in, w, sh);
+    if (inv != 0.f) proj_block<T>(in, w, w.r2, inv, w.st->kc, cb, slab, g.pslabs);
+    return;
+  }
+  b -= g.n * per;
+  const ExtMapRec p = ma.tab ? ma.tab[b / g.img_wgs] : ma.few[b / g.img_wgs];
+  const int blk = b % g.img_wgs;
+  if ((int64_t)blk * kImgRows >= p.m) return;
+  const ExtIn in = a.tab ? a.tab[p.in] : a.one;
+  const ExtWs w = ext_ws(in);
+  if (!w.st->cand) return;
+  const float inv = ext_inverse(in, w, sh);
+  if (inv != 0.f) image_rows_block<T>(in, w, p, inv, blk, g.img_wgs);
 }
 
 // E[j, kc] = E[kc, j] = (U^T u)[j] - (j == kc), the projection over the extended basis added over its slabs
@@ -417,33 +509,34 @@ hipError_t launch_all(const ExtIn* in, int n, const ExtMapRec* maps, int n_maps,
   const dim3 pgrid((unsigned)pc, (unsigned)std::min<int64_t>(slabs_max, std::max<int64_t>(1, kGridCap / (pc * n))), (unsigned)n);
   const dim3 kgrid((unsigned)ceil_div(K_max, kSumBlock), (unsigned)n);
   const int64_t per_basis = std::max<int64_t>(8, kGridCap / n);
-  ext_proj<T><<<pgrid, kBlock, 0, s>>>(a, tau, 1);
-  ext_sum<<<kgrid, kSumBlock, 0, s>>>(a);
+  ext_proj<T><<<pgrid, kBlock, 0, s>>>(a, tau);
+  if (K_max > kLdsK) ext_sum<<<kgrid, kSumBlock, 0, s>>>(a);
   ext_resid<T><<<dim3((unsigned)std::min<int64_t>(wgs_max, per_basis), (unsigned)n), kBlock, 0, s>>>(a);
-  ext_column<T><<<dim3((unsigned)std::min<int64_t>(ceil_div(d_max, kBlock), per_basis), (unsigned)n), kBlock, 0, s>>>(a);
-  if (n_maps > 0) {
+  ExtStore g;
+  g.n = n;
+  g.col_wgs = (int)std::min<int64_t>(ceil_div(d_max, kBlock), std::max<int64_t>(1, per_basis / 8));
+  g.pcols = any_gram ? (int)pgrid.x : 0;
+  g.pslabs = any_gram ? (int)pgrid.y : 0;
+  // the maps of one basis travel in the kernel arguments, kFewMaps at a time: the first launch does the other jobs as well
+  for (int j0 = 0; j0 == 0 || (!mtab && j0 < n_maps); j0 += kFewMaps) {
     ExtMapArg ma;
     std::memset(&ma, 0, sizeof(ma));
-    if (mtab) {
-      ma.tab = mtab;
-      const int64_t per_map = std::max<int64_t>(8, 2 * kGridCap / n_maps);
-      ext_image<T><<<dim3((unsigned)std::min<int64_t>(ceil_div(m_max, kImgRows), per_map), (unsigned)n_maps), kBlock, 0, s>>>(a, ma);
-    } else {
-      for (int j0 = 0; j0 < n_maps; j0 += kFewMaps) {
-        const int nm = std::min(kFewMaps, n_maps - j0);
-        int64_t mm = 0;
-        for (int q = 0; q < nm; ++q) {
-          ma.few[q] = maps[j0 + q];
-          mm = std::max<int64_t>(mm, maps[j0 + q].m);
-        }
-        ext_image<T><<<dim3((unsigned)ceil_div(mm, kImgRows), (unsigned)nm), kBlock, 0, s>>>(a, ma);
+    ma.tab = mtab;
+    g.n_maps = mtab ? n_maps : std::min(kFewMaps, n_maps - j0);
+    int64_t mm = m_max;
+    if (!mtab) {
+      mm = 0;
+      for (int q = 0; q < g.n_maps; ++q) {
+        ma.few[q] = maps[j0 + q];
+        mm = std::max<int64_t>(mm, maps[j0 + q].m);
       }
     }
+    g.img_wgs = g.n_maps > 0 ? (int)std::min<int64_t>(ceil_div(mm, kImgRows), std::max<int64_t>(8, 2 * kGridCap / g.n_maps)) : 0;
+    if (j0 > 0) g.n = 0;
+    const int64_t blocks = (int64_t)g.n * (g.col_wgs + (int64_t)g.pcols * g.pslabs) + (int64_t)g.n_maps * g.img_wgs;
+    if (blocks > 0) ext_store<T><<<(unsigned)blocks, kBlock, 0, s>>>(a, ma, g);
   }
-  if (any_gram) {
-    ext_proj<T><<<pgrid, kBlock, 0, s>>>(a, tau, 0);
-    ext_gram<<<kgrid, kSumBlock, 0, s>>>(a);
-  }
+  if (any_gram) ext_gram<<<kgrid, kSumBlock, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -452,7 +545,7 @@ hipError_t launch_all(const ExtIn* in, int n, const ExtMapRec* maps, int n_maps,
 size_t extend_ws_bytes(int64_t d, int64_t K) {
   const Geom g = geom(d);
   return align_up(sizeof(ExtState), 256) + align_up((size_t)g.slabs * K * 4, 256) + align_up((size_t)K * 4, 256) +
-         2 * align_up((size_t)d * 4, 256) + align_up((size_t)g.wgs * 4, 256);
+         align_up((size_t)d * 4, 256) + align_up((size_t)g.wgs * 4, 256);
 }
 
 size_t extend_table_bytes(int n, int n_maps) {
