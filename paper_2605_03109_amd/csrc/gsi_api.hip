@@ -566,7 +566,7 @@ struct LinBatcher {
     return e;
   }
   hipError_t add(int gkey, const gsi::LinGroup& gd, const void* W, const void* M, float* Y, int64_t m,
-                 bool need_image = false, float* part = nullptr, const float* mscale = nullptr) {
+                 bool need_image = false, float* part = nullptr, const float* mscale = nullptr, bool img_done = false) {
     for (int attempt = 0; attempt < 2; ++attempt) {
       int gi = -1;
       for (int i = 0; i < lb.ng; ++i)
@@ -579,6 +579,7 @@ struct LinBatcher {
       if (gi >= 0 && trial.n < gsi::kMaxLinTasks) {
         gsi::LinTask& t = trial.t[trial.n++];
         t.W = W; t.M = M; t.Y = Y; t.m = (int)m; t.group = gi; t.part = part; t.slices = 0;
+        t.img_done = img_done ? 1 : 0;
         if (gsi::decode_linear_fits(trial, wdtype)) {
           if (gi == lb.ng) gkeys[gi] = gkey;
           lb = trial;
@@ -1116,6 +1117,16 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
   gate_inline.assign(n_inputs, 0);
   part_ncb.assign(n_inputs, 1);
   int remaining = n_inputs + n_maps;
+  // An image term that rides in a launch of its inputs' residuals is written while the x of the inputs of that wave are
+  // still read: a Y that lies over one of them waits for the launch of the weight term.
+  auto clear_of_inputs = [&](const gsi_map_desc& mp, const std::vector<int>& wave) {
+    const uintptr_t y0 = reinterpret_cast<uintptr_t>(mp.Y), y1 = y0 + (uintptr_t)B * mp.m * sizeof(float);
+    for (int i : wave) {
+      const uintptr_t x0 = reinterpret_cast<uintptr_t>(inputs[i].X);
+      if (y0 < x0 + (uintptr_t)B * inputs[i].d * gsi::elem_size(inputs[i].xdtype) && x0 < y1) return false;
+    }
+    return true;
+  };
   while (remaining > 0) {
     int progressed = 0;
     std::vector<int>& ready = sc.ready;
@@ -1196,9 +1207,12 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
       gsi::ProjBatch pb;
       std::memset(&pb, 0, sizeof(pb));
       pb.B = (int)B;
+      gsi::TileImgBatch ib;  // image terms of a bf16 decode batch: with the residuals, not in front of the weight term
+      ib.n = 0;
       auto flush = [&]() -> hipError_t {
         if (pb.n == 0) return hipSuccess;
-        hipError_t e = gsi::decode_project_launch(pb, dt, true, true, eps, s);
+        hipError_t e = gsi::decode_project_launch(pb, dt, true, true, eps, s, &ib);
+        ib.n = 0;
         std::memset(&pb, 0, sizeof(pb));
         pb.B = (int)B;
         return e;
@@ -1206,6 +1220,17 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
       for (int i : ready) {
         if (mode[i] != kVecGate || inputs[i].udtype != dt) continue;
         pb.t[pb.n++] = ptask[i];
+        const gsi_input_desc& in = inputs[i];
+        for (int j = 0; (ptask[i].tile == 2 || ptask[i].tile == 3) && j < n_maps && ib.n < gsi::kMaxLinTasks; ++j) {
+          const gsi_map_desc& mp = maps[j];
+          const bool wx = (in.flags & GSI_INPUT_SLOW_PATH_WX) != 0;
+          if (mp.input_id != i || mp.wdtype != dt || !part[j] || !wx_vector_ok(in) ||
+              !gsi::decode_linear_ok(mp.m, in.d, in.k, mp.wdtype, mp.W, mp.M, B) ||
+              !gsi::tile_image_ok(mp.m, in.k, mp.M, in.C, mp.Y) || !clear_of_inputs(mp, ready))
+            continue;
+          ib.t[ib.n++] = gsi::TileImg{mp.M, in.C, mp.Y, (int)mp.m, (int)in.k, gsi::tile_image_terms(in.k, wx, in.xdtype), 0};
+          img_done[j] = 1;
+        }
         if (pb.n == gsi::kMaxTasks)
           if (hipError_t e = flush(); e != hipSuccess) return hip_fail(e, fn);
       }
@@ -1373,7 +1398,9 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
         for (int j = 0; j < n_maps; ++j) {
           const gsi_map_desc& mp = maps[j];
           if (mp.input_id != i || img_done[j]) continue;
-          if (!mfma_gated_path(mp.W, mp.M, in.C, in.R, in.d, in.k, B, mp.wdtype, mp.m, mp.Y) || !wx_vector_ok(in)) continue;
+          if (!mfma_gated_path(mp.W, mp.M, in.C, in.R, in.d, in.k, B, mp.wdtype, mp.m, mp.Y) || !wx_vector_ok(in) ||
+              !clear_of_inputs(mp, ready))
+            continue;
           riders.push_back(ImageRider{(int)min.size(), mp.M, mp.Y, mp.m});
           img_done[j] = 1;
         }
@@ -1516,7 +1543,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
           gd.fired_idx_out = in.fired_idx; gd.n_fired_out = in.n_fired;
         }
         if (hipError_t e = bt.add(mp.input_id, gd, mp.W, mp.M, mp.Y, mp.m, B == 1 && !img_done[j], part[j],
-                                  (mp.flags & GSI_MAP_IMAGE_FP8) ? mp.M_scale : nullptr);
+                                  (mp.flags & GSI_MAP_IMAGE_FP8) ? mp.M_scale : nullptr, img_done[j] != 0);
             e != hipSuccess)
           return hip_fail(e, fn);
         map_done[j] = 2;

@@ -73,6 +73,19 @@ struct ImgBatch {
   int n, total;         // tasks, workgroups
 };
 
+// Image terms of a decode batch that ride in the residual launch (gsi_tile.hip)
+struct TileImg {
+  const void* M;
+  const float* C;  // the input's coefficients [B][k]
+  float* Y;
+  int m, k, terms, blk_begin;
+};
+struct TileImgBatch {
+  TileImg t[kMaxLinTasks];
+  int n;
+};
+static_assert(sizeof(ProjBatch) + sizeof(TileImgBatch) + 16 <= 4096, "kernel arguments are limited to 4 KB");
+
 // One input group as seen by the linear kernels: its projection outputs and its gate.
 struct LinGroup {
   const float* C;
@@ -100,6 +113,7 @@ struct LinTask {
   float* part;   // several-token matrix-core kernel: partial products [slices][B][m] of the weight term
   int m, group;
   int slices;    // ... column slices of the weight term (filled at launch)
+  int img_done;  // ... the image term was written by the launch of the residuals
 };
 
 struct LinBatch {
@@ -138,9 +152,9 @@ void decode_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws,
 
 // partial projection + residual (+ norms, + gate): with_norms = false leaves the norms to the
 // single-token linear kernel (which reads part_n itself)
-// `img` (single token only): image maps whose workgroups ride in the residual launch
+// `img`: image terms that ride in the residual launch (tasks with tile 2 or 3 only)
 hipError_t decode_project_launch(ProjBatch& pb, int udtype, bool with_norms, bool with_gate, float eps,
-                                 hipStream_t s, ImgBatch* img = nullptr);
+                                 hipStream_t s, const TileImgBatch* img = nullptr);
 // stand-alone image launch for one token: y = M c with c read from C (tasks' C set, part_c null)
 hipError_t decode_image_launch(ImgBatch& ib, int wdtype, hipStream_t s);
 // norms (and gate) of prefill-sized tasks whose part_n / b_slabs / rnorm / xnorm (mask, fired_idx, n_fired, and a
@@ -163,6 +177,8 @@ void tile_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws);
 // bf16 terms that an fp32 operand of a decode batch is split into, by rank and activation type (see gsi_tile.hip)
 inline int tile_proj_terms(int64_t k, int xdtype) { return k % 64 || !rank_pow2(k, GSI_BF16) || xdtype != GSI_F32 ? 3 : 2; }
 int tile_rows_terms(const LinBatch& lb, int group);
+int tile_image_terms(int64_t k, bool reads_x, int xdtype);  // (reads_x: the weight term reads x)
+bool tile_image_ok(int64_t m, int64_t k, const void* M, const void* C, const void* Y);
 hipError_t tile_proj_reduce_launch(const ProjBatch& pb, hipStream_t s);  // C = the slab partials added
 // ... and with fp32 storage (gsi_tile_f32.hip): any shape that the vector kernels take
 constexpr int kTileF32 = 4;
@@ -172,7 +188,8 @@ size_t f32_project_ws(int64_t d, int64_t k, int64_t B);
 void f32_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws);
 hipError_t f32_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s);
 hipError_t f32_rows_launch(LinBatch& lb, hipStream_t s);
-hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s);
+// (ib: image terms of its inputs' maps that ride in the residual launch; the geometry fields are filled here)
+hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s, TileImgBatch& ib);
 bool tile_rows_shape_ok(int64_t m, int64_t d, int64_t k, int64_t B, int wdtype);
 bool tile_rows_ok(const LinBatch& lb, int wdtype);
 hipError_t tile_rows_launch(LinBatch& lb, hipStream_t s);

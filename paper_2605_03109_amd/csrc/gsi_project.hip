@@ -531,25 +531,16 @@ hipError_t decode_image_launch(ImgBatch& ib, int wdtype, hipStream_t s) {
 }
 
 hipError_t decode_project_launch(ProjBatch& pb, int udtype, bool with_norms, bool with_gate, float eps,
-                                 hipStream_t s, ImgBatch* img) {
+                                 hipStream_t s, const TileImgBatch* img) {
   if (pb.n == 0 || pb.B == 0) return hipSuccess;
   if (pb.B == 1) {
-    // one token: the staged kernel, first the partial projections, then residuals (+ the image rows that ride along)
+    // one token: the staged kernel, first the partial projections, then residuals
     StageArgs a;
     stage_clear(a, eps);
     for (int i = 0; i < pb.n; ++i) stage_add_part(a, pb.t[i]);
     if (hipError_t e = stage_launch(a, udtype, s); e != hipSuccess) return e;
     stage_clear(a, eps);
     for (int i = 0; i < pb.n; ++i) stage_add_res(a, pb.t[i], false);
-    if (img)
-      for (int j = 0; j < img->n; ++j) {
-        const ImgTask& it = img->t[j];
-        int res = -1;
-        for (int i = 0; i < pb.n; ++i)
-          if (pb.t[i].part_c == it.part_c) res = i;
-        if (res < 0) return hipErrorInvalidValue;
-        stage_add_img(a, res, it.M, it.Y, it.scale, it.m);
-      }
     if (hipError_t e = stage_launch(a, udtype, s); e != hipSuccess) return e;
     if (with_norms) proj_norms<<<pb.n, kBlock, 0, s>>>(pb, with_gate ? 1 : 0, eps);
     return hipGetLastError();
@@ -564,8 +555,16 @@ hipError_t decode_project_launch(ProjBatch& pb, int udtype, bool with_norms, boo
         else rest.t[rest.n++] = pb.t[i];
       }
       if (tile_pb.n == 0) continue;
+      TileImgBatch ib;
+      ib.n = 0;
+      for (int j = 0; img && j < img->n; ++j)
+        for (int i = 0; i < tile_pb.n; ++i)
+          if (tile_pb.t[i].C == img->t[j].C) {
+            ib.t[ib.n++] = img->t[j];
+            break;
+          }
       const hipError_t e = terms == kTileF32 ? f32_project_launch(tile_pb, with_norms, with_gate, eps, s)
-                                             : tile_project_launch(tile_pb, with_norms, with_gate, eps, s);
+                                             : tile_project_launch(tile_pb, with_norms, with_gate, eps, s, ib);
       if (e != hipSuccess) return e;
       if (rest.n == 0) return hipSuccess;
       pb = rest;

@@ -19,6 +19,7 @@
 // on fp32 FMAs before, and with two terms the residual, whose parts cancel to a few percent, was 2e-5 .. 5e-5 off
 // instead of 3e-6 .. 2e-5.  The kernels are bound by memory and latency, the third MFMA costs nothing that shows.
 // Measured: a block of d = 2560, rank 128, 23 bf16 tokens 174 us on the FMA kernels, 66 us on these.
+#include <algorithm>
 #include <type_traits>
 
 #include "gsi_decode.h"
@@ -73,58 +74,81 @@ __device__ __forceinline__ void split4(const float4& v, uint2 (&out)[T]) {
   }
 }
 
-// Requests this thread's share of half a staging round: tokens [g0 + 16 * half, + 16) of the phase (token j
-// is row idx ? idx[j] : j of V, vdt its type), columns [c0, c0 + ncol), ncol a multiple of four.  A wave pair covers
-// one token row per pass.  Every load is unconditional: tokens past the count repeat the last one and columns past
-// the slice its last four.
+// Requests this thread's share of a staging round: tokens [g0, g0 + 32) of the phase (token j is row idx ? idx[j] : j of
+// V, vdt its type), columns [c0, c0 + ncol), ncol a multiple of four; the second sixteen tokens only where two is set.  A
+// wave pair covers one token row per pass.  Every load is unconditional: tokens past the count repeat the last one and
+// columns past the slice its last four.  The second half goes out first: loads return in order, so a wait for the first
+// half is the same number on both paths and never one for the weights that are requested next.  (Requested behind the
+// weights, the second half waited for them too: 18.9 us instead of 17.8 for the residuals of 64 tokens.)
 template <int T>
-__device__ __forceinline__ void stage_issue(float4 (&v)[kHalfVec], int half, const void* __restrict__ V, int vdt, int64_t ldv,
+__device__ __forceinline__ void stage_issue(float4 (&v)[2][kHalfVec], bool two, const void* __restrict__ V, int vdt, int64_t ldv,
                                             const int32_t* __restrict__ idx, int g0, int count, int B, int c0, int ncol,
                                             int wave) {
   const int c4 = min((int)(threadIdx.x & 127), ncol / 4 - 1);
-  const int j0 = g0 + 16 * half + (wave >> 1);
-  int tok[kHalfVec];  // all token indices first (uniform across the wave), so that their loads overlap
+  const int j0 = g0 + (wave >> 1);
+  int tok[2][kHalfVec];  // all token indices first (uniform across the wave), so that their loads overlap
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < kHalfVec; ++i) tok[h][i] = min(j0 + 16 * h + 4 * i, count - 1);
   if (idx) {
 #pragma unroll
-    for (int i = 0; i < kHalfVec; ++i) tok[i] = idx[min(j0 + 4 * i, count - 1)];
+    for (int h = 0; h < 2; ++h) {
+      if (h == 1 && !two) continue;
 #pragma unroll
-    for (int i = 0; i < kHalfVec; ++i) tok[i] = min(max(tok[i], 0), B - 1);
-  } else {
+      for (int i = 0; i < kHalfVec; ++i) tok[h][i] = idx[tok[h][i]];
 #pragma unroll
-    for (int i = 0; i < kHalfVec; ++i) tok[i] = min(j0 + 4 * i, count - 1);
+      for (int i = 0; i < kHalfVec; ++i) tok[h][i] = min(max(tok[h][i], 0), B - 1);
+    }
   }
 #pragma unroll
-  for (int i = 0; i < kHalfVec; ++i) v[i] = load_act4<T == 2>(V, vdt, (int64_t)tok[i] * ldv + c0 + 4 * c4);
+  for (int h = 1; h >= 0; --h) {
+    if (h == 1 && !two) continue;  // uniform
+#pragma unroll
+    for (int i = 0; i < kHalfVec; ++i) v[h][i] = load_act4<T == 2>(V, vdt, (int64_t)tok[h][i] * ldv + c0 + 4 * c4);
+  }
 }
 
-// what stage_issue requested, as T bf16 terms in LDS; columns past the slice are zero
+// what stage_issue requested, as T bf16 terms in LDS; columns past the slice are zero (three terms;
+// with two, slices end with a step)
 template <int T>
-__device__ __forceinline__ void stage_commit(const float4 (&v)[kHalfVec], int half, uint16_t (*vt)[kRoundTok][kVRow], int ncol,
+__device__ __forceinline__ void stage_commit(const float4 (&v)[2][kHalfVec], bool two, uint16_t* vt, int vrow, int ncol,
                                              int wave) {
   const int c4 = threadIdx.x & 127;
 #pragma unroll
-  for (int i = 0; i < kHalfVec; ++i) {
-    const int t = 16 * half + (wave >> 1) + 4 * i;
-    uint2 term[T];
-    split4<T>(4 * c4 < ncol ? v[i] : float4{0.f, 0.f, 0.f, 0.f}, term);
+  for (int h = 0; h < 2; ++h) {
+    if ((h == 1 && !two) || 4 * c4 >= vrow - 8) continue;
 #pragma unroll
-    for (int q = 0; q < T; ++q) *reinterpret_cast<uint2*>(&vt[q][t][4 * c4]) = term[q];
+    for (int i = 0; i < kHalfVec; ++i) {
+      const int t = 16 * h + (wave >> 1) + 4 * i;
+      uint2 term[T];
+      split4<T>(T == 2 || 4 * c4 < ncol ? v[h][i] : float4{0.f, 0.f, 0.f, 0.f}, term);
+#pragma unroll
+      for (int q = 0; q < T; ++q) *reinterpret_cast<uint2*>(vt + (q * kRoundTok + t) * vrow + 4 * c4) = term[q];
+    }
   }
 }
 
 // The weights of a wave's item: rows row (per lane), columns c0 + 32 s + 8 lq .. + 7 for step s.  base: first column of
 // the slice; steps past the slice repeat its last one.  A slice that ends inside a step (a rank that is no multiple of
-// 32) has zeros past its end: those lanes read the step's first columns instead and are cleared.
+// 32, three terms only) has zeros past its end: those lanes read the step's first columns instead and are cleared.
+template <int T>
 __device__ __forceinline__ void weights_issue(uint4 (&w)[kSteps], const char* __restrict__ base, uint32_t row_off, int lq, int ncol,
                                               int ns) {
   const uint32_t voff = row_off + 16u * lq;
-  const uint32_t vlast = (ns - 1) * kStepCols + 8 * lq < ncol ? voff : row_off;
+  if (T == 2 && ns == kSteps) {  // uniform: a whole slice, at constant offsets
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) w[s] = *reinterpret_cast<const uint4*>(base + s * kStepCols * 2 + voff);
+    return;
+  }
+  const uint32_t vlast = T == 2 || (ns - 1) * kStepCols + 8 * lq < ncol ? voff : row_off;
 #pragma unroll
   for (int s = 0; s < kSteps; ++s)
     w[s] = *reinterpret_cast<const uint4*>(base + (size_t)(min(s, ns - 1) * kStepCols * 2) + (s < ns - 1 ? voff : vlast));
 }
+template <int T>
 __device__ __forceinline__ void weights_clear_tail(uint4 (&w)[kSteps], int lq, int ncol, int ns) {
-  if (ncol % kStepCols == 0) return;  // uniform
+  if (T == 2 || ncol % kStepCols == 0) return;  // uniform
   const bool dead = (ns - 1) * kStepCols + 8 * lq >= ncol;
 #pragma unroll
   for (int s = 0; s < kSteps; ++s)
@@ -135,27 +159,43 @@ __device__ __forceinline__ void weights_clear_tail(uint4 (&w)[kSteps], int lq, i
 // and odd steps and those of the two remainders have accumulators of their own, so that fewer large partial sums are
 // rounded (the residual's error against 64 bits is then the FMA kernel's, 2.7e-6 at rank 128; 3.6e-6 with one).
 template <int T>
-__device__ __forceinline__ void item_mma(const uint4 (&w)[kSteps], const uint16_t (*vt)[kRoundTok][kVRow], int li, int lq, int ns,
-                                         bool two, f32x4& acc0, f32x4& acc1) {
+__device__ __forceinline__ void item_mma(const uint4 (&w)[kSteps], const uint16_t* vt, int vrow, int li, int lq,
+                                         int ns, bool two, f32x4& acc0, f32x4& acc1) {
   constexpr int NA = T == 3 ? 3 : 1;
   f32x4 acc[2][NA];
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int q = 0; q < NA; ++q) acc[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto step = [&](int s, int t) {  // column step s of token tile t
+    const bf16x8 a = __builtin_bit_cast(bf16x8, w[s]);
+    const int col = s * kStepCols + 8 * lq;
 #pragma unroll
-  for (int s = 0; s < kSteps; ++s) {
-    if (s < ns) {
-      const bf16x8 a = __builtin_bit_cast(bf16x8, w[s]);
-      const int col = s * kStepCols + 8 * lq;
+    for (int q = 0; q < T; ++q) {
+      f32x4& d = acc[t][NA == 1 ? 0 : (q > 0 ? 2 : s & 1)];
+      d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          a, *reinterpret_cast<const bf16x8*>(vt + (q * kRoundTok + 16 * t + li) * vrow + col), d, 0, 0, 0);
+    }
+  };
+  if (T == 2 && ns == kSteps) {
+    // a whole slice: no branch per step, so the LDS reads run ahead of the products (the pair, 16 tokens: 72.5 -> 70.5 us
+    // with the constant offsets of weights_issue, 32 tokens 77.2 -> 75.0)
+    if (two) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        if (t == 1 && !two) continue;
+      for (int s = 0; s < kSteps; ++s) {
+        step(s, 0);
+        step(s, 1);
+      }
+    } else {
 #pragma unroll
-        for (int q = 0; q < T; ++q) {
-          f32x4& d = acc[t][NA == 1 ? 0 : (q > 0 ? 2 : s & 1)];
-          d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, *reinterpret_cast<const bf16x8*>(&vt[q][16 * t + li][col]), d, 0, 0, 0);
-        }
+      for (int s = 0; s < kSteps; ++s) step(s, 0);
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+      if (s < ns) {
+        step(s, 0);
+        if (two) step(s, 1);
       }
     }
   }
@@ -169,7 +209,7 @@ __device__ __forceinline__ void item_mma(const uint4 (&w)[kSteps], const uint16_
 
 template <int T>
 __global__ __launch_bounds__(kTBlock) void tile_rows(const LinBatch lb) {
-  __shared__ __align__(16) uint16_t vt[T][kRoundTok][kVRow];
+  __shared__ __align__(16) uint16_t vt[T * kRoundTok * kVRow];
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x % kWave;
@@ -219,33 +259,26 @@ __global__ __launch_bounds__(kTBlock) void tile_rows(const LinBatch lb) {
 
   // first round's activations, then the weights, so that the activations can be converted and staged while
   // the weights are still on their way
-  float4 v[kHalfVec];
-  stage_issue<T>(v, 0, V, vdt, K, idx, g_begin, count, B, c0, ncol, wave);
+  float4 v[2][kHalfVec];
+  const bool two0 = count - g_begin > 16;  // uniform
+  stage_issue<T>(v, two0, V, vdt, K, idx, g_begin, count, B, c0, ncol, wave);
   __builtin_amdgcn_sched_barrier(0);
   uint4 w[kSteps];
   // uniform base + one 32-bit lane offset (the matrix is smaller than 2 GiB); rows past m repeat the last
-  weights_issue(w, reinterpret_cast<const char*>(A + c0), (uint32_t)min(row0 + li, m - 1) * (uint32_t)K * 2u, lq, ncol, ns);
+  weights_issue<T>(w, reinterpret_cast<const char*>(A + c0), (uint32_t)min(row0 + li, m - 1) * (uint32_t)K * 2u, lq, ncol, ns);
   __builtin_amdgcn_sched_barrier(0);  // keep the weight requests ahead of the wait for the activations
-  stage_commit<T>(v, 0, vt, ncol, wave);
-  if (count - g_begin > 16) {  // uniform
-    stage_issue<T>(v, 1, V, vdt, K, idx, g_begin, count, B, c0, ncol, wave);
-    stage_commit<T>(v, 1, vt, ncol, wave);
-  }
-  weights_clear_tail(w, lq, ncol, ns);
+  stage_commit<T>(v, two0, vt, kVRow, ncol, wave);
+  weights_clear_tail<T>(w, lq, ncol, ns);
 
   for (int g0 = g_begin; g0 < count; g0 += kRoundTok) {
     if (g0 != g_begin) {
       __syncthreads();  // the previous round's operands have been read
-      stage_issue<T>(v, 0, V, vdt, K, idx, g0, count, B, c0, ncol, wave);
-      stage_commit<T>(v, 0, vt, ncol, wave);
-      if (count - g0 > 16) {
-        stage_issue<T>(v, 1, V, vdt, K, idx, g0, count, B, c0, ncol, wave);
-        stage_commit<T>(v, 1, vt, ncol, wave);
-      }
+      stage_issue<T>(v, count - g0 > 16, V, vdt, K, idx, g0, count, B, c0, ncol, wave);
+      stage_commit<T>(v, count - g0 > 16, vt, kVRow, ncol, wave);
     }
     __syncthreads();
     f32x4 acc0, acc1;
-    item_mma<T>(w, vt, li, lq, ns, count - g0 > 16, acc0, acc1);
+    item_mma<T>(w, vt, kVRow, li, lq, ns, count - g0 > 16, acc0, acc1);
     // lane holds token li of each tile, rows 4*lq .. 4*lq+3 of the wave's 16
     const int row = row0 + 4 * lq;
     if (row < m) {  // m is a multiple of 4
@@ -470,15 +503,63 @@ __global__ __launch_bounds__(256) void tile_proj_reduce(const ProjBatch pb) {
 // contiguous: same operand flow as tile_rows), R written, and the row block's share of |r|^2 and |x|^2.
 // The workgroup of an input that finishes last (a counter in the workspace, zeroed by the partial-projection
 // launch) turns the shares into the norms, the gate decisions and the list of fired tokens: no launch of its own.
+//
+// Image terms y = M c of a call's maps ride behind the residual workgroups (ib): both need c alone.  By itself the
+// residual is short of work and bound by latency (160 workgroups of 128 rows for an MLP pair), and in front of the W
+// items, where gated_linear alone still has them, the image items take the places of workgroups that stream weights.
+// The pair of 4096 and 16384 columns, rank 256, 64 tokens: this launch 17.8 -> 20.6 us, the W items 62.6 -> 50 us; the call
+// 97.5 -> 93.6 us (20 tokens: 75.5 -> 73.7, 128: 125.3 -> 116.8; a block at rank 200, 24 tokens: 54.1 -> 47.2).
+// LDS holds the operand of the launch's largest rank only (vrow), so that the short items of small ranks share a unit.
+template <int TI>
+__device__ __forceinline__ void image_item(const TileImg& p, int item, int B, uint16_t* vt, int vrow, int wave,
+                                           int li, int lq) {
+  const int nrb = (p.m + kItemRows - 1) / kItemRows;
+  const int rb = item % nrb, g0 = (item / nrb) * kRoundTok;
+  const int count = min(B, g0 + kRoundTok);
+  const int m = p.m, k = p.k, ns = (k + kStepCols - 1) / kStepCols;
+  const int row0 = rb * kItemRows + 16 * wave;
+  const bool two = count - g0 > 16;  // uniform
+  float4 v[2][kHalfVec];
+  stage_issue<TI>(v, two, p.C, GSI_F32, k, nullptr, g0, count, B, 0, k, wave);
+  __builtin_amdgcn_sched_barrier(0);
+  uint4 w[kSteps];
+  weights_issue<TI>(w, reinterpret_cast<const char*>(p.M), (uint32_t)min(row0 + li, m - 1) * (uint32_t)k * 2u, lq, k, ns);
+  __builtin_amdgcn_sched_barrier(0);
+  stage_commit<TI>(v, two, vt, vrow, k, wave);
+  weights_clear_tail<TI>(w, lq, k, ns);
+  __syncthreads();
+  f32x4 acc0, acc1;
+  item_mma<TI>(w, vt, vrow, li, lq, ns, two, acc0, acc1);
+  const int row = row0 + 4 * lq;
+  if (row >= m) return;  // m is a multiple of 4
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int j = g0 + 16 * t + li;
+    const f32x4 a = t ? acc1 : acc0;
+    if (j < count) *reinterpret_cast<float4*>(p.Y + (int64_t)j * m + row) = float4{a[0], a[1], a[2], a[3]};
+  }
+}
+
 template <int T>
-__global__ __launch_bounds__(kTBlock) void tile_residual(const ProjBatch pb) {
+__global__ __launch_bounds__(kTBlock, 4) void tile_residual(const ProjBatch pb, const TileImgBatch ib, int vrow) {
+  extern __shared__ __align__(16) uint16_t vt[];  // [T][kRoundTok][vrow]
   __shared__ int s_last;
-  __shared__ __align__(16) uint16_t vt[T][kRoundTok][kVRow];
   __shared__ float red[kTWaves][kRoundTok][2];
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x % kWave, li = lane & 15, lq = lane >> 4;
   const int B = pb.B;
+  if ((int)blockIdx.x >= pb.b_total) {
+    const int item = blockIdx.x - pb.b_total;
+    int ii = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxLinTasks; ++i)
+      if (i < ib.n && item >= ib.t[i].blk_begin) ii = i;
+    const TileImg& p = ib.t[ii];
+    if (T == 2 || p.terms == 2) image_item<2>(p, item - p.blk_begin, B, vt, vrow, wave, li, lq);
+    else image_item<T>(p, item - p.blk_begin, B, vt, vrow, wave, li, lq);
+    return;
+  }
   const int ti = find_task(pb.b_begin, pb.n, blockIdx.x);
   const ProjTask& p = pb.t[ti];
   const int rounds = (B + kRoundTok - 1) / kRoundTok;
@@ -490,11 +571,12 @@ __global__ __launch_bounds__(kTBlock) void tile_residual(const ProjBatch pb) {
   const int row0 = rb * kItemRows + 16 * wave;  // d is a multiple of 128: every row exists
   const uint16_t* U = reinterpret_cast<const uint16_t*>(p.U);
 
-  float4 v[kHalfVec];
-  stage_issue<T>(v, 0, p.C, GSI_F32, k, nullptr, g0, count, B, 0, k, wave);
+  float4 v[2][kHalfVec];
+  const bool two = count - g0 > 16;  // uniform
+  stage_issue<T>(v, two, p.C, GSI_F32, k, nullptr, g0, count, B, 0, k, wave);
   __builtin_amdgcn_sched_barrier(0);
   uint4 w[kSteps];
-  weights_issue(w, reinterpret_cast<const char*>(U), (uint32_t)(row0 + li) * (uint32_t)k * 2u, lq, k, ns);
+  weights_issue<T>(w, reinterpret_cast<const char*>(U), (uint32_t)(row0 + li) * (uint32_t)k * 2u, lq, k, ns);
   // x of the lane's outputs: token g0 + 16 t + li, rows row0 + 4 lq .. + 3
   float4 xv[2];
 #pragma unroll
@@ -503,16 +585,11 @@ __global__ __launch_bounds__(kTBlock) void tile_residual(const ProjBatch pb) {
     xv[t] = load_act4<T == 2>(p.X, p.xdtype, (int64_t)j * d + row0 + 4 * lq);
   }
   __builtin_amdgcn_sched_barrier(0);
-  stage_commit<T>(v, 0, vt, k, wave);
-  const bool two = count - g0 > 16;
-  if (two) {
-    stage_issue<T>(v, 1, p.C, GSI_F32, k, nullptr, g0, count, B, 0, k, wave);
-    stage_commit<T>(v, 1, vt, k, wave);
-  }
-  weights_clear_tail(w, lq, k, ns);
+  stage_commit<T>(v, two, vt, vrow, k, wave);
+  weights_clear_tail<T>(w, lq, k, ns);
   __syncthreads();
   f32x4 acc0, acc1;
-  item_mma<T>(w, vt, li, lq, ns, two, acc0, acc1);
+  item_mma<T>(w, vt, vrow, li, lq, ns, two, acc0, acc1);
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int j = g0 + 16 * t + li;
@@ -555,7 +632,8 @@ __global__ __launch_bounds__(kTBlock) void tile_residual(const ProjBatch pb) {
   }
   __syncthreads();
   if (!s_last) return;  // uniform
-  norms_and_gate<kTBlock>(p, B, pb.gate, pb.eps, reinterpret_cast<float2*>(&vt[0][0][0]), reinterpret_cast<int*>(&vt[1][0][0]));
+  norms_and_gate<kTBlock>(p, B, pb.gate, pb.eps, reinterpret_cast<float2*>(vt),
+                          reinterpret_cast<int*>(reinterpret_cast<float2*>(vt) + kTBlock));
 }
 
 }  // namespace
@@ -569,6 +647,13 @@ bool tile_project_shape_ok(int64_t d, int64_t k, int64_t B, int udtype) {
 }
 
 static int tile_slab_rows(int64_t) { return kPSteps * kStepCols; }
+
+// A residual launch of up to one and a half workgroups per compute unit asks for more than half of a unit's LDS, so that
+// the residual workgroups, which come first, have a unit each and the images the next free one: MLP pair of 4096 and 16384
+// columns, rank 256 (320 workgroups), 4 tokens 69.4 us against 70.0, 16 tokens 70.6 against 71.5.  With more, two share
+// a unit: a block at rank 200, 8 tokens (512 workgroups) 41.9 us against 46.4; the pair with 128 tokens 116.8 against 124.8.
+constexpr int kFewItems = 384;
+constexpr size_t kWholeUnit = 84 * 1024;
 
 size_t tile_project_ws(int64_t d, int64_t k, int64_t B) {
   const int a_slabs = (int)ceil_div(d, tile_slab_rows(d));
@@ -596,7 +681,7 @@ hipError_t tile_proj_reduce_launch(const ProjBatch& pb, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s) {
+hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s, TileImgBatch& ib) {
   if (pb.n == 0 || pb.B == 0) return hipSuccess;
   const int rounds = (int)ceil_div(pb.B, kRoundTok);
   int ta = 0, tb = 0;
@@ -610,14 +695,29 @@ hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, f
   pb.norms = with_norms ? 1 : 0;
   pb.gate = with_gate ? 1 : 0;
   pb.eps = eps;
+  int imgs = 0, max_k = 0;
+  for (int i = 0; i < ib.n; ++i) {
+    ib.t[i].blk_begin = imgs;
+    imgs += (int)ceil_div(ib.t[i].m, kItemRows) * rounds;
+  }
+  for (int i = 0; i < pb.n; ++i) max_k = std::max(max_k, pb.t[i].k);  // (an image's rank is that of its input)
+  const int vrow = (int)align_up((size_t)max_k, kStepCols) + 8;
   hipError_t err = hipSuccess;
   auto launch = [&](auto terms) {
     constexpr int T = decltype(terms)::value;
+    constexpr size_t kScratch = kTBlock * sizeof(float2) + 16;  // norms_and_gate
+    size_t smem = std::max((size_t)T * kRoundTok * vrow * sizeof(uint16_t), kScratch);
+    if (tb + imgs <= kFewItems) smem = std::max(smem, kWholeUnit);
+    static const hipError_t attr =  // more than the default 64 KB at the largest ranks
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_residual<T>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            std::max(T * kRoundTok * kVRow * (int)sizeof(uint16_t), (int)kWholeUnit));
+    err = attr;
+    if (err != hipSuccess) return;
     if (pb.B <= 32) tile_proj_partial<1, T><<<ta, kPBlock, 0, s>>>(pb);
     else if (pb.B <= 64) tile_proj_partial<2, T><<<ta, kPBlock, 0, s>>>(pb);
     else tile_proj_partial<4, T><<<ta, kPBlock, 0, s>>>(pb);
     err = tile_proj_reduce_launch(pb, s);
-    tile_residual<T><<<tb, kTBlock, 0, s>>>(pb);
+    tile_residual<T><<<tb + imgs, kTBlock, smem, s>>>(pb, ib, vrow);
   };
   if (pb.t[0].tile == 3) launch(std::integral_constant<int, 3>{});
   else launch(std::integral_constant<int, 2>{});
@@ -640,7 +740,14 @@ size_t tile_part_bytes(int64_t m, int64_t d, int64_t B) {
 // activations (themselves a single term)
 int tile_rows_terms(const LinBatch& lb, int group) {
   const LinGroup& g = lb.g[group];
-  return (!lb.dense && g.k % kStepCols) || ((lb.dense || g.wx) && g.xdtype != GSI_F32) ? 3 : 2;
+  return tile_image_terms(lb.dense ? 0 : g.k, lb.dense || g.wx, g.xdtype);
+}
+int tile_image_terms(int64_t k, bool reads_x, int xdtype) { return k % kStepCols || (reads_x && xdtype != GSI_F32) ? 3 : 2; }
+
+// what the image items of tile_rows need of a map whose input's C they read
+bool tile_image_ok(int64_t m, int64_t k, const void* M, const void* C, const void* Y) {
+  return m % 4 == 0 && k % 8 == 0 && k <= kSliceCols && m * k * 2 < (1ll << 32) && reinterpret_cast<uintptr_t>(M) % 16 == 0 &&
+         reinterpret_cast<uintptr_t>(C) % 16 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0;
 }
 
 bool tile_rows_ok(const LinBatch& lb, int wdtype) {
@@ -670,7 +777,7 @@ hipError_t tile_rows_launch(LinBatch& lb, hipStream_t s) {
   int total = 0, max_m = 0;
   for (int i = 0; i < lb.n; ++i) {
     lb.blk_begin2[i] = total;
-    if (!lb.dense) total += (int)(ceil_div(lb.t[i].m, kItemRows) * ceil_div(lb.B, kRoundTok));
+    if (!lb.dense && !lb.t[i].img_done) total += (int)(ceil_div(lb.t[i].m, kItemRows) * ceil_div(lb.B, kRoundTok));
   }
   lb.tile_split = total;  // image items below, weight items from here on
   for (int i = 0; i < lb.n; ++i) {

@@ -17,26 +17,27 @@ __device__ __forceinline__ float4 load_act4(const void* p, int dtype, int64_t i)
 
 // |r|, |x| per token from the row blocks' shares, then the gate and the ordered list of fired tokens
 // (Eq. (gate); Algorithm 1, line 4), by the NB threads of one workgroup.  NB / 32 threads share a token
-// (NB / 128 beyond 32 tokens): each adds its part of the shares in order, the part sums are then added in order.
+// (NB / 64 beyond 32 tokens, NB / 128 beyond 64): each adds its part of the shares in order, the part sums are then added in order.
 // red: NB float2, wave_count: two ints of LDS.
 template <int NB>
 __device__ __forceinline__ void norms_and_gate(const ProjTask& p, int B, int do_gate, float eps, float2* red,
                                                int* wave_count) {
-  const int slots = B <= 32 ? 32 : kMaxTok, parts = NB / slots;
+  const int slots = B <= 32 ? 32 : B <= 64 ? 64 : kMaxTok, parts = NB / slots;
   const int t = threadIdx.x % slots, part = threadIdx.x / slots;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int per = (p.b_slabs + parts - 1) / parts;
   const int s_begin = part * per, s_end = min(p.b_slabs, s_begin + per);
+  constexpr int kFlight = 16;  // requests in flight: one round trip for 128 row blocks of up to 64 tokens
   float sr = 0.f, sx = 0.f;
   const float2* src = reinterpret_cast<const float2*>(p.part_n) + min(t, B - 1);
-  for (int s0 = s_begin; s0 < s_end; s0 += 8) {
-    unsigned long long q[8];  // (|r|^2, |x|^2) shares, read past the caches: other workgroups of this launch wrote them
+  for (int s0 = s_begin; s0 < s_end; s0 += kFlight) {
+    unsigned long long q[kFlight];  // (|r|^2, |x|^2) shares, read past the caches: other workgroups of this launch wrote them
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < kFlight; ++u)
       q[u] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(src + (int64_t)min(s0 + u, p.b_slabs - 1) * B),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < kFlight; ++u)
       if (s0 + u < s_end) { sr += __uint_as_float((unsigned)q[u]); sx += __uint_as_float((unsigned)(q[u] >> 32)); }
   }
   red[part * slots + t] = float2{sr, sx};
