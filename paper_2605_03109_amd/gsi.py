@@ -182,9 +182,15 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+def _device() -> int:
+    """torch.cuda.current_device() without its initialisation check where torch is initialised."""
+    return torch._C._cuda_getDevice() if torch.cuda.is_initialized() else torch.cuda.current_device()
+
+
 def _stream(stream=None) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    # the raw handle of the current stream, without a Stream object per call: three calls of one fp32 map, one token, are
+    # bound by the host and take 38.6 us with the object, 26.5 us without
+    return torch._C._cuda_getCurrentRawStream(_device()) if stream is None else stream.cuda_stream
 
 
 def to_device(a: np.ndarray, dtype: str, device="cuda") -> torch.Tensor:
@@ -208,7 +214,7 @@ def workspace(nbytes: int, device=None) -> Optional[torch.Tensor]:
     """A cached device byte buffer of at least ``nbytes`` (device memory plumbing only)."""
     if nbytes == 0:
         return None
-    dev = torch.cuda.current_device() if device is None else torch.device(device).index or 0
+    dev = _device() if device is None else torch.device(device).index or 0
     have = _ws_cache.get((dev, 0))
     if have is None or have.numel() < nbytes:
         have = torch.empty(max(nbytes, 1 << 20), dtype=torch.uint8, device=f"cuda:{dev}")
