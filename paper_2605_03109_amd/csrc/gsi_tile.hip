@@ -507,7 +507,7 @@ __global__ __launch_bounds__(256) void tile_proj_reduce(const ProjBatch pb) {
 // Image terms y = M c of a call's maps ride behind the residual workgroups (ib): both need c alone.  By itself the
 // residual is short of work and bound by latency (160 workgroups of 128 rows for an MLP pair), and in front of the W
 // items, where gated_linear alone still has them, the image items take the places of workgroups that stream weights.
-// The pair of 4096 and 16384 columns, rank 256, 64 tokens: this launch 17.8 -> 20.6 us, the W items 62.6 -> 50 us; the call
+// The pair of 4096 and 16384 columns, rank 256, 64 tokens: this launch 17.8 -> 20.6 us, the W items 62.6 -> 53 us; the call
 // 97.5 -> 93.6 us (20 tokens: 75.5 -> 73.7, 128: 125.3 -> 116.8; a block at rank 200, 24 tokens: 54.1 -> 47.2).
 // LDS holds the operand of the launch's largest rank only (vrow), so that the short items of small ranks share a unit.
 template <int TI>
