@@ -136,12 +136,16 @@ size_t gsi_workspace_bytes(int which_call, int64_t m, int64_t d, int64_t k, int6
   return call_ws_bytes(which_call, m, d, k, B, true);
 }
 
-// does the workspace of a stand-alone call have the full size?  (GSI_OK: at least the smaller one)
+// Does a call bring a workspace that it can use, of the full size?  (NULL or unaligned memory is none, whatever size is
+// named for it: a call that needed no workspace before has to be served without one.)
+static bool full_ws(const void* ws, size_t ws_bytes, size_t full_bytes) {
+  return full_bytes == 0 || (ws && aligned(ws, 256) && ws_bytes >= full_bytes);
+}
+// ... of a stand-alone call (GSI_OK: at least the smaller size)
 static int check_call_ws(const char* fn, int which_call, int64_t m, int64_t d, int64_t k, int64_t B, const void* ws,
                          size_t ws_bytes, bool& full) {
-  full = ws_bytes >= call_ws_bytes(which_call, m, d, k, B, true) && aligned(ws, 256);
-  return full ? check_ws(fn, ws, ws_bytes, call_ws_bytes(which_call, m, d, k, B, true))
-              : check_ws(fn, ws, ws_bytes, call_ws_bytes(which_call, m, d, k, B, false));
+  full = full_ws(ws, ws_bytes, call_ws_bytes(which_call, m, d, k, B, true));
+  return full ? GSI_OK : check_ws(fn, ws, ws_bytes, call_ws_bytes(which_call, m, d, k, B, false));
 }
 
 // D[M,N] = A[M,K] B[N,K]^T (unsplit unless the caller adds a workspace)
@@ -860,8 +864,9 @@ int gsi_dense_stack(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_de
     }
   }
   if (B == 0) return GSI_OK;
-  const bool full = ws_bytes >= dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true);
-  if (int rc = check_ws(fn, ws, ws_bytes, dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, full))) return rc;
+  const bool full = full_ws(ws, ws_bytes, dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true));
+  if (!full)
+    if (int rc = check_ws(fn, ws, ws_bytes, dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, false))) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   std::vector<float*> part(n_maps, nullptr);
   {
@@ -967,10 +972,9 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
       if (!aligned(mp.M_scale, 4)) return fail(GSI_ERR_ALIGN, "%s: maps[%d].M_scale is not aligned to 4 bytes", fn, j);
     }
   }
-  const size_t need_any = stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true);
-  const bool full = ws_bytes >= need_any;  // (else the smaller workspace: see project_ws_bytes)
-  if (int rc = check_ws(fn, ws, ws_bytes, full ? need_any : stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, false)))
-    return rc;
+  const bool full = full_ws(ws, ws_bytes, stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true));
+  if (!full)  // (the smaller workspace: see project_ws_bytes)
+    if (int rc = check_ws(fn, ws, ws_bytes, stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, false))) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
 
   // Bookkeeping of the call lives in thread-local vectors that keep their capacity from call to call: after the
