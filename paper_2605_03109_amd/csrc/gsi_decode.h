@@ -145,7 +145,8 @@ inline bool rank_pow2(int64_t k, int udtype) {
 // batch of 2..128 tokens whose shape the matrix-core kernel takes)
 bool decode_linear_ok(int64_t m, int64_t d, int64_t k, int wdtype, const void* W, const void* M, int64_t B = 2);
 
-// full: with what the decode batches of fp32 storage take on the matrix cores (else the FMA kernels run them)
+// full: with what decode batches of fp32 storage, and of bf16 ranks that are no multiple of 64, take on the matrix cores
+// (else the FMA kernels run them)
 size_t decode_project_ws(int64_t d, int64_t k, int64_t B, int udtype, bool full);
 // fills d, k, slab geometry and the two workspace pointers of a task whose other fields are set
 void decode_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws, bool full);

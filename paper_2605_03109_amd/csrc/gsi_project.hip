@@ -466,6 +466,12 @@ ProjGeom proj_geom(int64_t d, int64_t k, int udtype) {
 }
 }  // namespace
 
+// bf16 decode batches on the matrix cores; with the smaller workspace the ranks that they took when it was sized
+// (their row slabs are finer than those of the FMA kernels, which ranks of 8, 16 and 32 columns took then)
+static bool tile_of_ws(int64_t d, int64_t k, int64_t B, int udtype, bool full) {
+  return tile_project_shape_ok(d, k, B, udtype) && (full || k % 64 == 0);
+}
+
 size_t decode_project_ws(int64_t d, int64_t k, int64_t B, int udtype, bool full) {
   const ProjGeom g = proj_geom(d, k, udtype);
   int s_rows = 0, s_slabs = 0;
@@ -475,7 +481,7 @@ size_t decode_project_ws(int64_t d, int64_t k, int64_t B, int udtype, bool full)
   // (B == 1: twice, for the low parts of the partials that the single-pass gate keeps)
   size_t need = align_up(part_slabs * B * k * 4 * (B == 1 ? 2 : 1), 256) +
                 align_up(std::max((size_t)g.b_slabs * B * 2 * 4, sizeof(double) * kGateDoubles), 256);
-  if (tile_project_shape_ok(d, k, B, udtype)) need = std::max(need, tile_project_ws(d, k, B));
+  if (tile_of_ws(d, k, B, udtype, full)) need = std::max(need, tile_project_ws(d, k, B));
   if (full && f32_project_shape_ok(d, k, B, udtype)) need = std::max(need, f32_project_ws(d, k, B));
   return need;
 }
@@ -488,7 +494,7 @@ void decode_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws,
     t.tile = kTileF32;
     return;
   }
-  if (tile_project_shape_ok(d, k, B, t.udtype) && reinterpret_cast<uintptr_t>(t.X) % 16 == 0 &&
+  if (tile_of_ws(d, k, B, t.udtype, full) && reinterpret_cast<uintptr_t>(t.X) % 16 == 0 &&
       reinterpret_cast<uintptr_t>(t.C) % 16 == 0 && reinterpret_cast<uintptr_t>(t.R) % 16 == 0) {
     tile_project_fill(t, d, k, B, ws);
     t.tile = tile_proj_terms(k, t.xdtype);

@@ -47,3 +47,16 @@ def test_no_workspace_at_a_ragged_rank(gsi, k, B, ws):
     # where a workspace was needed it still is
     assert _project(gsi, 1024, 64, B, gsi.GSI_BF16, gsi.GSI_F32, ws, BIG) == (
         gsi.GSI_ERR_WORKSPACE if ws is None else gsi.GSI_ERR_ALIGN)
+
+
+# (d, k, B): the size that gsi_workspace_bytes named while ranks of 8, 16 and 32 columns ran on the FMA kernels
+FORMER = {(4096, 32, 64): 147456, (16384, 32, 128): 655360, (65536, 32, 128): 1048576, (16384, 8, 2): 2304}
+
+
+@pytest.mark.parametrize("shape", sorted(FORMER))
+def test_former_sizes_of_small_ranks(gsi, shape):
+    d, k, B = shape
+    for xdtype in (gsi.GSI_F32, gsi.GSI_BF16):
+        assert _project(gsi, d, k, B, gsi.GSI_BF16, xdtype, ADDR, FORMER[shape]) == gsi.GSI_ERR_HIP, gsi.last_error()
+        assert _project(gsi, d, k, B, gsi.GSI_BF16, xdtype, ADDR, FORMER[shape] - 256) == gsi.GSI_ERR_WORKSPACE
+    assert gsi.workspace_bytes(gsi.CALL_PROJECT, 0, d, k, B) > FORMER[shape]
