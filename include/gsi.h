@@ -244,7 +244,11 @@ enum { GSI_MAP_IMAGE_FP8 = 1 };
  * input: gsi_project + gsi_gate once; for each map: gsi_gated_linear on its input's c, r and fired
  * list.  `maps` and `inputs` are HOST arrays (read during the call only).  Inputs with src_map >= 0
  * are processed after the map that produces them.  Results are identical to issuing the separate
- * calls in that order.  ws: gsi_layer_stack_workspace_bytes(). */
+ * calls in that order.  ws: gsi_layer_stack_workspace_bytes().
+ * A map's Y may lie over the X of an external input (src_map -1): every X is read before it is overwritten.  Where the
+ * maps read x as well (GSI_INPUT_SLOW_PATH_WX), a map whose Y lies over such an X runs behind the other maps; it may not lie
+ * over the X of its own input then, nor two such maps over each other's.  With GSI_INPUT_FUSED_KERNEL and in a plan
+ * no Y may lie over an X. */
 int gsi_layer_stack(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int32_t n_inputs,
                     int64_t B, float eps, void* ws, size_t ws_bytes, void* stream);
 
@@ -298,7 +302,8 @@ int gsi_layer_stack_timed(const gsi_map_desc* maps, int32_t n_maps, const gsi_in
 /* Dense baseline for a whole stack: Y = W X for every map, all maps in one launch (Section 3.1,
  * the computation the method replaces).  Uses only W, Y, m, wdtype, input_id of each map and X, d,
  * xdtype of each input (src_map must be -1).  ws: device workspace of at least
- * gsi_dense_stack_workspace_bytes(...) bytes (0 for a single token: ws may then be NULL). */
+ * gsi_dense_stack_workspace_bytes(...) bytes (0 for a single token: ws may then be NULL).  A map whose Y lies over the X
+ * of another input runs behind the maps of the others, on its own; Y may not lie over the map's own X. */
 int gsi_dense_stack(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int32_t n_inputs,
                     int64_t B, void* ws, size_t ws_bytes, void* stream);
 

@@ -5,6 +5,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "gsi_decode.h"
@@ -526,6 +527,28 @@ static gsi::GemmProb mfma_dense_prob(const void* W, const void* X, int64_t m, in
   return g;
 }
 
+// Address ranges of the activations of some inputs, and whether a map's output lies over one of them.
+namespace {
+struct Spans {
+  std::vector<std::pair<uintptr_t, uintptr_t>> v;  // sorted by begin; second: the furthest end up to here
+  void clear() { v.clear(); }
+  void add(const gsi_input_desc& in, int64_t B) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(in.X);
+    v.emplace_back(x, x + (uintptr_t)B * in.d * gsi::elem_size(in.xdtype));
+  }
+  void close() {
+    std::sort(v.begin(), v.end());
+    for (size_t i = 1; i < v.size(); ++i) v[i].second = std::max(v[i].second, v[i - 1].second);
+  }
+  bool under(const gsi_map_desc& mp, int64_t B) const {
+    const uintptr_t y = reinterpret_cast<uintptr_t>(mp.Y), end = y + (uintptr_t)B * mp.m * sizeof(float);
+    // (the first range that begins at or behind the output's end)
+    const auto it = std::lower_bound(v.begin(), v.end(), std::make_pair(end, (uintptr_t)0));
+    return it != v.begin() && std::prev(it)->second > y;
+  }
+};
+}  // namespace
+
 static void clear(gsi::LinBatch& lb, int64_t B) {
   std::memset(&lb, 0, sizeof(lb));
   lb.B = (int)B;
@@ -877,44 +900,54 @@ int gsi_dense_stack(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_de
       off += pb;
     }
   }
-  std::vector<char> done(n_maps, 0);
-  for (int xdt = 0; xdt < 2; ++xdt) {  // prefill-sized batches: the matrix-core products of all maps in one launch
-    std::vector<gsi::GemmProb> pr;
-    for (int j = 0; j < n_maps; ++j) {
-      const gsi_map_desc& mp = maps[j];
-      const gsi_input_desc& in = inputs[mp.input_id];
-      if (in.xdtype != xdt || !mfma_dense_path(mp.W, in.X, mp.m, in.d, B, mp.wdtype, mp.Y)) continue;
-      pr.push_back(mfma_dense_prob(mp.W, in.X, mp.m, in.d, B, mp.Y, part[j], full));
-      done[j] = 1;
-    }
-    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s); e != hipSuccess)
-      return hip_fail(e, fn);
-  }
-  for (int dt = 0; dt < 2; ++dt) {
-    LinBatcher bt;
-    bt.wdtype = dt; bt.s = s;
-    bt.reset(B, 1);
-    for (int j = 0; j < n_maps; ++j) {
-      const gsi_map_desc& mp = maps[j];
-      const gsi_input_desc& in = inputs[mp.input_id];
-      if (done[j] || mp.wdtype != dt || !gsi::decode_linear_ok(mp.m, in.d, 0, mp.wdtype, mp.W, nullptr, B) ||
-          !aligned(in.X, 16) || !long_batch_ok(in.d, B, mp.Y, true, in.X, in.xdtype))
-        continue;
-      gsi::LinGroup gd;
-      std::memset(&gd, 0, sizeof(gd));
-      gd.X = in.X; gd.xdtype = in.xdtype; gd.d = (int)in.d;
-      if (hipError_t e = bt.add(mp.input_id, gd, mp.W, nullptr, mp.Y, mp.m, false, part[j]); e != hipSuccess)
+  // A map whose Y lies over an x of the call has launches of its own, behind those that read it.
+  std::vector<char> done(n_maps, 0), late(n_maps, 0);
+  Spans xs;
+  for (int i = 0; i < n_inputs; ++i) xs.add(inputs[i], B);
+  xs.close();
+  for (int j = 0; j < n_maps; ++j) late[j] = xs.under(maps[j], B);
+  for (int only = -1; only < n_maps; ++only) {
+    if (only >= 0 && !late[only]) continue;
+    auto now = [&](int j) { return !done[j] && (only < 0 ? !late[j] : j == only); };
+    for (int xdt = 0; xdt < 2; ++xdt) {  // prefill-sized batches: the matrix-core products of all maps in one launch
+      std::vector<gsi::GemmProb> pr;
+      for (int j = 0; j < n_maps; ++j) {
+        if (!now(j)) continue;
+        const gsi_map_desc& mp = maps[j];
+        const gsi_input_desc& in = inputs[mp.input_id];
+        if (in.xdtype != xdt || !mfma_dense_path(mp.W, in.X, mp.m, in.d, B, mp.wdtype, mp.Y)) continue;
+        pr.push_back(mfma_dense_prob(mp.W, in.X, mp.m, in.d, B, mp.Y, part[j], full));
+        done[j] = 1;
+      }
+      if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s); e != hipSuccess)
         return hip_fail(e, fn);
-      done[j] = 1;
     }
-    if (hipError_t e = bt.flush(); e != hipSuccess) return hip_fail(e, fn);
-  }
-  for (int j = 0; j < n_maps; ++j) {
-    if (done[j]) continue;
-    const gsi_map_desc& mp = maps[j];
-    const gsi_input_desc& in = inputs[mp.input_id];
-    hipError_t e = gsi::generic_dense_linear(mp.W, in.X, mp.m, in.d, B, mp.wdtype, in.xdtype, mp.Y, s);
-    if (e != hipSuccess) return hip_fail(e, fn);
+    for (int dt = 0; dt < 2; ++dt) {
+      LinBatcher bt;
+      bt.wdtype = dt; bt.s = s;
+      bt.reset(B, 1);
+      for (int j = 0; j < n_maps; ++j) {
+        const gsi_map_desc& mp = maps[j];
+        const gsi_input_desc& in = inputs[mp.input_id];
+        if (!now(j) || mp.wdtype != dt || !gsi::decode_linear_ok(mp.m, in.d, 0, mp.wdtype, mp.W, nullptr, B) ||
+            !aligned(in.X, 16) || !long_batch_ok(in.d, B, mp.Y, true, in.X, in.xdtype))
+          continue;
+        gsi::LinGroup gd;
+        std::memset(&gd, 0, sizeof(gd));
+        gd.X = in.X; gd.xdtype = in.xdtype; gd.d = (int)in.d;
+        if (hipError_t e = bt.add(mp.input_id, gd, mp.W, nullptr, mp.Y, mp.m, false, part[j]); e != hipSuccess)
+          return hip_fail(e, fn);
+        done[j] = 1;
+      }
+      if (hipError_t e = bt.flush(); e != hipSuccess) return hip_fail(e, fn);
+    }
+    for (int j = 0; j < n_maps; ++j) {
+      if (!now(j)) continue;
+      const gsi_map_desc& mp = maps[j];
+      const gsi_input_desc& in = inputs[mp.input_id];
+      hipError_t e = gsi::generic_dense_linear(mp.W, in.X, mp.m, in.d, B, mp.wdtype, in.xdtype, mp.Y, s);
+      if (e != hipSuccess) return hip_fail(e, fn);
+    }
   }
   return GSI_OK;
 }
@@ -984,7 +1017,8 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
     std::vector<float*> part;
     std::vector<int> mode, mode_separate, part_ncb, ready, mready;
     std::vector<gsi::ProjTask> ptask;
-    std::vector<char> map_fused, in_done, map_done, img_done, gate_inline;
+    std::vector<char> map_fused, in_done, map_done, img_done, gate_inline, late;
+    Spans wave_x;
   };
   static thread_local Scratch sc;
   std::vector<size_t>& ws_off = sc.ws_off;
@@ -1121,22 +1155,30 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
   gate_inline.assign(n_inputs, 0);
   part_ncb.assign(n_inputs, 1);
   int remaining = n_inputs + n_maps;
-  // An image term that rides in a launch of its inputs' residuals is written while the x of the inputs of that wave are
-  // still read: a Y that lies over one of them waits for the launch of the weight term.
-  auto clear_of_inputs = [&](const gsi_map_desc& mp, const std::vector<int>& wave) {
-    const uintptr_t y0 = reinterpret_cast<uintptr_t>(mp.Y), y1 = y0 + (uintptr_t)B * mp.m * sizeof(float);
-    for (int i : wave) {
-      const uintptr_t x0 = reinterpret_cast<uintptr_t>(inputs[i].X);
-      if (y0 < x0 + (uintptr_t)B * inputs[i].d * gsi::elem_size(inputs[i].xdtype) && x0 < y1) return false;
-    }
-    return true;
-  };
+  // Outputs that lie over activations of the call.  An image term that rides in a launch of its inputs' projections is
+  // written while the x of the inputs of that wave are still read: a Y that lies over one of them waits for the launch of
+  // the weight term.  Under GSI_INPUT_SLOW_PATH_WX the maps read x as well: a map whose Y lies over such an x runs in a
+  // wave of its own, when nothing else is ready.  (A plan's launches are fixed, and so is a fused input's.)
+  Spans& wave_x = sc.wave_x;
+  std::vector<char>& late = sc.late;
+  late.assign(n_maps, 0);
+  if (!plan && B > 0) {
+    wave_x.clear();
+    for (int i = 0; i < n_inputs; ++i)
+      if (inputs[i].src_map < 0 && (inputs[i].flags & GSI_INPUT_SLOW_PATH_WX)) wave_x.add(inputs[i], B);
+    wave_x.close();
+    for (int j = 0; j < n_maps && !wave_x.v.empty(); ++j) late[j] = wave_x.under(maps[j], B);
+  }
+  auto may_ride = [&](int j) { return plan || !(late[j] || wave_x.under(maps[j], B)); };
   while (remaining > 0) {
     int progressed = 0;
     std::vector<int>& ready = sc.ready;
     ready.clear();
     for (int i = 0; i < n_inputs; ++i)
       if (!in_done[i] && (inputs[i].src_map < 0 || map_done[inputs[i].src_map])) ready.push_back(i);
+    wave_x.clear();
+    for (int i : ready) wave_x.add(inputs[i], B);
+    wave_x.close();
     // fused chunks: ready inputs of one dtype and rank are packed, with their maps, into chunks as long as a
     // chunk fits one launch's registers and scratch; up to kFusedMaxChunks chunks share a launch
     if (B == 1) {
@@ -1230,7 +1272,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
           const bool wx = (in.flags & GSI_INPUT_SLOW_PATH_WX) != 0;
           if (mp.input_id != i || mp.wdtype != dt || !part[j] || !wx_vector_ok(in) ||
               !gsi::decode_linear_ok(mp.m, in.d, in.k, mp.wdtype, mp.W, mp.M, B) ||
-              !gsi::tile_image_ok(mp.m, in.k, mp.M, in.C, mp.Y) || !clear_of_inputs(mp, ready))
+              !gsi::tile_image_ok(mp.m, in.k, mp.M, in.C, mp.Y) || !may_ride(j))
             continue;
           ib.t[ib.n++] = gsi::TileImg{mp.M, in.C, mp.Y, (int)mp.m, (int)in.k, gsi::tile_image_terms(in.k, wx, in.xdtype), 0};
           img_done[j] = 1;
@@ -1302,7 +1344,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
           t.r_rows_x = r_rows | (in.xdtype << 16) | ((in.flags & GSI_INPUT_SLOW_PATH_WX) ? 1 << 20 : 0);
           t.gw_off = (int)(reinterpret_cast<char*>(pt.part_n) - reinterpret_cast<char*>(pt.part_c));
           for (int j = 0; j < n_maps; ++j) {
-            if (maps[j].input_id != i || maps[j].wdtype != dt || img_done[j]) continue;
+            if (maps[j].input_id != i || maps[j].wdtype != dt || img_done[j] || !may_ride(j)) continue;
             gsi::TabMap tm;
             std::memset(&tm, 0, sizeof(tm));
             tm.M = maps[j].M; tm.Y = maps[j].Y;
@@ -1376,7 +1418,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
               gsi::stage_set_res_xcd_order(a, res, t.b_slabs / t.s_slabs);
           }
           for (int j = 0; j < n_maps && a.ni < gsi::kMaxLinTasks; ++j) {
-            if (maps[j].input_id != i || maps[j].wdtype != dt || img_done[j]) continue;
+            if (maps[j].input_id != i || maps[j].wdtype != dt || img_done[j] || !may_ride(j)) continue;
             gsi::stage_add_img(a, res, maps[j].M, maps[j].Y,
                                (maps[j].flags & GSI_MAP_IMAGE_FP8) ? maps[j].M_scale : nullptr, (int)maps[j].m);
             img_done[j] = 1;
@@ -1403,7 +1445,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
           const gsi_map_desc& mp = maps[j];
           if (mp.input_id != i || img_done[j]) continue;
           if (!mfma_gated_path(mp.W, mp.M, in.C, in.R, in.d, in.k, B, mp.wdtype, mp.m, mp.Y) || !wx_vector_ok(in) ||
-              !clear_of_inputs(mp, ready))
+              !may_ride(j))
             continue;
           riders.push_back(ImageRider{(int)min.size(), mp.M, mp.Y, mp.m});
           img_done[j] = 1;
@@ -1437,6 +1479,8 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
     std::vector<int>& mready = sc.mready;
     mready.clear();
     for (int j = 0; j < n_maps; ++j)
+      if (!map_done[j] && in_done[maps[j].input_id] == 1 && !late[j]) mready.push_back(j);
+    for (int j = 0; ready.empty() && mready.empty() && j < n_maps; ++j)
       if (!map_done[j] && in_done[maps[j].input_id] == 1) mready.push_back(j);
     // single token, more inputs or maps than one launch's arguments describe: one weight-streaming launch over
     // a descriptor table uploaded to the workspace
