@@ -155,6 +155,15 @@ __device__ __forceinline__ void weights_clear_tail(uint4 (&w)[kSteps], int lq, i
     if (s == ns - 1 && dead) w[s] = uint4{0u, 0u, 0u, 0u};
 }
 
+// Sum of the head's products plus that of the remainders', which count only where the first is finite: an infinite weight
+// times a remainder of either sign, or of zero, would make a NaN of the infinity that the fp32 product is.
+__device__ __forceinline__ f32x4 add_tails(const f32x4& head, const f32x4& tails) {
+  f32x4 s;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) s[e] = head[e] + (fabsf(head[e]) <= 3.402823466e38f ? tails[e] : 0.f);
+  return s;
+}
+
 // acc0 / acc1 = the item's weights times the staged tokens 0 .. 15 / 16 .. 31.  Three terms: the head's products of even
 // and odd steps and those of the two remainders have accumulators of their own, so that fewer large partial sums are
 // rounded (the residual's error against 64 bits is then the FMA kernel's, 2.7e-6 at rank 128; 3.6e-6 with one).
@@ -202,8 +211,8 @@ __device__ __forceinline__ void item_mma(const uint4 (&w)[kSteps], const uint16_
   acc0 = acc[0][0];
   acc1 = acc[1][0];
   if constexpr (NA == 3) {
-    acc0 = (acc0 + acc[0][1]) + acc[0][2];
-    acc1 = (acc1 + acc[1][1]) + acc[1][2];
+    acc0 = add_tails(acc0 + acc[0][1], acc[0][2]);
+    acc1 = add_tails(acc1 + acc[1][1], acc[1][2]);
   }
 }
 
@@ -422,9 +431,12 @@ __global__ __launch_bounds__(kPBlock) void tile_proj_partial(const ProjBatch pb)
   };
   const int terms = p.xdtype == GSI_F32 ? T : 1;  // uniform
 
-  f32x4 acc[kTiles];
+  constexpr int NA = T == 3 ? 2 : 1;  // three terms: the remainders have a sum of their own (add_tails)
+  f32x4 acc[kTiles][NA];
 #pragma unroll
-  for (int t = 0; t < kTiles; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+    for (int q = 0; q < NA; ++q) acc[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};
   commit(0, 0);
 #pragma unroll
   for (int s = 0; s < kPSteps; ++s) {
@@ -444,9 +456,11 @@ __global__ __launch_bounds__(kPBlock) void tile_proj_partial(const ProjBatch pb)
         if (t < ntile) {  // uniform
 #pragma unroll
           for (int q = 0; q < T; ++q)
-            if (q < terms)
-              acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, *reinterpret_cast<const bf16x8*>(&xt[q][buf][16 * t + li][8 * lq]),
-                                                               acc[t], 0, 0, 0);
+            if (q < terms) {
+              f32x4& s16 = acc[t][NA == 2 && q > 0 ? 1 : 0];
+              s16 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, *reinterpret_cast<const bf16x8*>(&xt[q][buf][16 * t + li][8 * lq]),
+                                                            s16, 0, 0, 0);
+            }
         }
       }
       if (s + 1 < kPSteps && s + 1 < steps) commit(s + 1, buf ^ 1);
@@ -458,7 +472,8 @@ __global__ __launch_bounds__(kPBlock) void tile_proj_partial(const ProjBatch pb)
     const int tok = 16 * t + li;
     if (t < ntile && tok < B && cg * kPCols + 16 * wave + 4 * lq < k) {
       float* dst = p.part_c + ((int64_t)slab * B + tok) * k + cg * kPCols + 16 * wave + 4 * lq;
-      *reinterpret_cast<float4*>(dst) = float4{acc[t][0], acc[t][1], acc[t][2], acc[t][3]};
+      const f32x4 c = NA == 2 ? add_tails(acc[t][0], acc[t][NA - 1]) : acc[t][0];
+      *reinterpret_cast<float4*>(dst) = float4{c[0], c[1], c[2], c[3]};
     }
   }
 }
