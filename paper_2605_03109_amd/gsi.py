@@ -9,7 +9,8 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import Dict, List, Optional, Sequence, Tuple
+import threading
+from typing import List, Optional, Sequence, Tuple
 
 import numpy as np
 import torch
@@ -207,18 +208,33 @@ def bits_of(t: torch.Tensor) -> np.ndarray:
     return t.detach().cpu().numpy()
 
 
-_ws_cache: Dict[Tuple[int, int], torch.Tensor] = {}
+_WS_KEPT = 8                  # buffers that a thread keeps
+_ws_local = threading.local()  # {(device, raw stream): buffer} in order of use, one table per thread
 
 
-def workspace(nbytes: int, device=None) -> Optional[torch.Tensor]:
-    """A cached device byte buffer of at least ``nbytes`` (device memory plumbing only)."""
+def workspace(nbytes: int, device=None, stream=None) -> Optional[torch.Tensor]:
+    """A device byte buffer of at least ``nbytes`` for a call on ``stream`` (None: the current one).
+
+    A call's kernels leave partial sums and completion counters there, so calls that may overlap never share one: every
+    thread keeps a buffer per stream, allocated on that stream (what an outgrown or dropped buffer gives back is
+    used again behind the stream's work only).  Under capture the buffer is the graph's and is not kept."""
     if nbytes == 0:
         return None
+    if stream is not None:
+        if not isinstance(stream, torch.cuda.Stream):
+            stream = torch.cuda.ExternalStream(stream.cuda_stream)
+        with torch.cuda.stream(stream):
+            return workspace(nbytes, device)
     dev = _device() if device is None else torch.device(device).index or 0
-    have = _ws_cache.get((dev, 0))
+    if torch.cuda.is_current_stream_capturing():
+        return torch.empty(nbytes, dtype=torch.uint8, device=f"cuda:{dev}")
+    kept, key = _ws_local.__dict__, (dev, torch._C._cuda_getCurrentRawStream(dev))
+    have = kept.pop(key, None)
     if have is None or have.numel() < nbytes:
         have = torch.empty(max(nbytes, 1 << 20), dtype=torch.uint8, device=f"cuda:{dev}")
-        _ws_cache[(dev, 0)] = have
+        while len(kept) >= _WS_KEPT:
+            del kept[next(iter(kept))]
+    kept[key] = have
     return have
 
 
@@ -226,10 +242,11 @@ def workspace_bytes(which: int, m: int = 0, d: int = 0, k: int = 0, B: int = 0) 
     return int(lib.gsi_workspace_bytes(which, m, d, k, B))
 
 
-def _ws_args(ws: Optional[torch.Tensor], need: int):
+def _ws_args(ws: Optional[torch.Tensor], need: int, stream=None):
+    """(pointer, bytes, the tensor that the caller holds until its call is enqueued)"""
     if ws is None:
-        ws = workspace(need)
-    return (None, 0) if ws is None else (ws.data_ptr(), ws.numel() * ws.element_size())
+        ws = workspace(need, stream=stream)
+    return (None, 0, None) if ws is None else (ws.data_ptr(), ws.numel() * ws.element_size(), ws)
 
 
 # ----------------------------------------------------------------------------------------------
@@ -242,7 +259,7 @@ def build_image(W: torch.Tensor, U: torch.Tensor, M: Optional[torch.Tensor] = No
         raise ValueError("W[m,d] and U[d,k] must agree in d and dtype")
     if M is None:
         M = torch.empty((m, k), dtype=W.dtype, device=W.device)
-    wsp, wsn = _ws_args(ws, workspace_bytes(CALL_BUILD_IMAGE, m, d, k, 0))
+    wsp, wsn, held = _ws_args(ws, workspace_bytes(CALL_BUILD_IMAGE, m, d, k, 0), stream)
     _check(lib.gsi_build_image(_ptr(W), _ptr(U), _ptr(M), m, d, k, dtype_code(W), wsp, wsn, _stream(stream)))
     return M
 
@@ -267,7 +284,7 @@ def extend_basis(U: torch.Tensor, k_cur: torch.Tensor, R: torch.Tensor, rnorm: t
         if W.dtype != U.dtype or M.dtype != U.dtype or tuple(M.shape) != (W.shape[0], K) or W.shape[1] != d:
             raise ValueError("maps must be (W[m,d], M[m,K]) in the basis' dtype")
         em[j].W, em[j].M, em[j].m = _ptr(W), _ptr(M), W.shape[0]
-    wsp, wsn = _ws_args(ws, int(lib.gsi_extend_basis_workspace_bytes(d, K)))
+    wsp, wsn, held = _ws_args(ws, int(lib.gsi_extend_basis_workspace_bytes(d, K)), stream)
     _check(lib.gsi_extend_basis(_ptr(U), d, K, dtype_code(U), _ptr(k_cur), _ptr(R), _ptr(rnorm), _ptr(xnorm), float(tau),
                                 em, len(maps), _ptr(gram), _ptr(extended), wsp, wsn, _stream(stream)))
     return extended
@@ -333,7 +350,7 @@ def project(U: torch.Tensor, X: torch.Tensor, C=None, R=None, rnorm=None, xnorm=
     R = torch.empty((B, d), **f32) if R is None else R
     rnorm = torch.empty((B,), **f32) if rnorm is None else rnorm
     xnorm = torch.empty((B,), **f32) if xnorm is None else xnorm
-    wsp, wsn = _ws_args(ws, workspace_bytes(CALL_PROJECT, 0, d, k, B))
+    wsp, wsn, held = _ws_args(ws, workspace_bytes(CALL_PROJECT, 0, d, k, B), stream)
     _check(lib.gsi_project(_ptr(U), _ptr(X), d, k, B, dtype_code(U), dtype_code(X), _ptr(C), _ptr(R), _ptr(rnorm),
                            _ptr(xnorm), wsp, wsn, _stream(stream)))
     return C, R, rnorm, xnorm
@@ -357,7 +374,7 @@ def gated_linear(W, M, C, R, fired_idx, n_fired, Y=None, ws=None, stream=None):
     if M.shape[0] != m or C.shape[1] != k or tuple(R.shape) != (B, d) or M.dtype != W.dtype:
         raise ValueError("inconsistent shapes/dtypes for gated_linear")
     Y = torch.empty((B, m), dtype=torch.float32, device=W.device) if Y is None else Y
-    wsp, wsn = _ws_args(ws, workspace_bytes(CALL_GATED_LINEAR, m, d, k, B))
+    wsp, wsn, held = _ws_args(ws, workspace_bytes(CALL_GATED_LINEAR, m, d, k, B), stream)
     _check(lib.gsi_gated_linear(_ptr(W), _ptr(M), _ptr(C), _ptr(R), _ptr(fired_idx), _ptr(n_fired), m, d, k, B,
                                 dtype_code(W), _ptr(Y), GSI_F32, wsp, wsn, _stream(stream)))
     return Y
@@ -369,7 +386,7 @@ def dense_linear(W, X, Y=None, ws=None, stream=None):
     if X.shape[1] != d:
         raise ValueError("W[m,d] and X[B,d] must agree in d")
     Y = torch.empty((B, m), dtype=torch.float32, device=W.device) if Y is None else Y
-    wsp, wsn = _ws_args(ws, workspace_bytes(CALL_DENSE_LINEAR, m, d, 0, B))
+    wsp, wsn, held = _ws_args(ws, workspace_bytes(CALL_DENSE_LINEAR, m, d, 0, B), stream)
     _check(lib.gsi_dense_linear(_ptr(W), _ptr(X), m, d, B, dtype_code(W), dtype_code(X), _ptr(Y), wsp, wsn,
                                 _stream(stream)))
     return Y
