@@ -183,15 +183,20 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+# The current device and the raw handle of its current stream without a Stream object and an initialisation check per
+# call, where this torch has the functions for it: three calls of one fp32 map, one token, are bound by the host (passes
+# back to back: 38.6 us with the object, 32.5 us without)
+_get_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+_raw_stream = (getattr(torch._C, "_cuda_getCurrentRawStream", None)
+               or (lambda device: torch.cuda.current_stream(device).cuda_stream))
+
+
 def _device() -> int:
-    """torch.cuda.current_device() without its initialisation check where torch is initialised."""
-    return torch._C._cuda_getDevice() if torch.cuda.is_initialized() else torch.cuda.current_device()
+    return _get_device() if torch.cuda.is_initialized() else torch.cuda.current_device()
 
 
 def _stream(stream=None) -> int:
-    # the raw handle of the current stream, without a Stream object per call: three calls of one fp32 map, one token, are
-    # bound by the host and take 38.6 us with the object, 26.5 us without
-    return torch._C._cuda_getCurrentRawStream(_device()) if stream is None else stream.cuda_stream
+    return _raw_stream(_device()) if stream is None else stream.cuda_stream
 
 
 def to_device(a: np.ndarray, dtype: str, device="cuda") -> torch.Tensor:
@@ -228,7 +233,7 @@ def workspace(nbytes: int, device=None, stream=None) -> Optional[torch.Tensor]:
     dev = _device() if device is None else torch.device(device).index or 0
     if torch.cuda.is_current_stream_capturing():
         return torch.empty(nbytes, dtype=torch.uint8, device=f"cuda:{dev}")
-    kept, key = _ws_local.__dict__, (dev, torch._C._cuda_getCurrentRawStream(dev))
+    kept, key = _ws_local.__dict__, (dev, _raw_stream(dev))
     have = kept.pop(key, None)
     if have is None or have.numel() < nbytes:
         have = torch.empty(max(nbytes, 1 << 20), dtype=torch.uint8, device=f"cuda:{dev}")
