@@ -616,10 +616,11 @@ hipError_t scratch_ptr(unsigned char** out, int* cus) {
 template <class T>
 hipError_t launch_as(const FusedArgs& a, unsigned grid, size_t smem, unsigned char* sc, hipStream_t s, hipEvent_t e0,
                      hipEvent_t e1) {
-  static const hipError_t attr =  // more than the default 64 KB of dynamic LDS
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_token<T>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (kFusedMaxCols + kFusedBlock + kFusedMaxD) * (int)sizeof(float));
-  if (attr != hipSuccess) return attr;
+  static LdsLimit lds;  // more than the default 64 KB of dynamic LDS
+  if (hipError_t e = lds.allow(reinterpret_cast<const void*>(&fused_token<T>),
+                               (kFusedMaxCols + kFusedBlock + kFusedMaxD) * (int)sizeof(float));
+      e != hipSuccess)
+    return e;
   if (e0 && e1) {  // the events take the dispatch's own start and stop timestamps
     hipExtLaunchKernelGGL((fused_token<T>), dim3(grid), dim3(kFusedBlock), smem, s, e0, e1, 0, a, sc);
   } else {

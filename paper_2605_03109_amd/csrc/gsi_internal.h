@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/gsi.h"
+#include "gsi_lds_limit.h"
 
 namespace gsi {
 

@@ -239,22 +239,12 @@ hipError_t decode_linear_launch(LinBatch& lb, int wdtype, hipStream_t s, hipEven
   }
   const size_t smem = tile_smem(lb);
   // one activation vector of up to kMaxLinD floats beside the kernels' static LDS: more than the default 64 KB
-  static const hipError_t attr = [] {
-    const int bytes = kMaxLinD * (int)sizeof(float);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dense_rows<BF16>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dense_rows<F32>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gated_rows<BF16>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gated_rows<F32>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  static LdsLimit lds[4];
+  const int which = (lb.dense ? 0 : 2) + (wdtype == GSI_BF16 ? 0 : 1);
+  void (*const kernels[4])(const LinBatch) = {dense_rows<BF16>, dense_rows<F32>, gated_rows<BF16>, gated_rows<F32>};
+  if (hipError_t e = lds[which].allow(reinterpret_cast<const void*>(kernels[which]), kMaxLinD * (int)sizeof(float)); e != hipSuccess)
     return e;
-  }();
-  if (attr != hipSuccess) return attr;
-  if (lb.dense) {
-    if (wdtype == GSI_BF16) dense_rows<BF16><<<total, kBlock, smem, s>>>(lb);
-    else dense_rows<F32><<<total, kBlock, smem, s>>>(lb);
-  } else {
-    if (wdtype == GSI_BF16) gated_rows<BF16><<<total, kBlock, smem, s>>>(lb);
-    else gated_rows<F32><<<total, kBlock, smem, s>>>(lb);
-  }
+  kernels[which]<<<total, kBlock, smem, s>>>(lb);
   return hipGetLastError();
 }
 

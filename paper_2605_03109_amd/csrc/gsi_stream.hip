@@ -217,10 +217,11 @@ int num_cus() {
 
 template <class T, bool DENSE, bool TAIL, bool NT, bool LONG>
 hipError_t launch_one(const LinBatch& lb, unsigned grid, size_t smem, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  static const hipError_t attr =  // the kernel may use more than the default 64 KB of dynamic LDS
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&stream_rows<T, DENSE, TAIL, NT, LONG>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (kMaxLinD + kMaxSumK) * (int)sizeof(float));
-  if (attr != hipSuccess) return attr;
+  static LdsLimit lds;  // the kernel may use more than the default 64 KB of dynamic LDS
+  if (hipError_t e = lds.allow(reinterpret_cast<const void*>(&stream_rows<T, DENSE, TAIL, NT, LONG>),
+                               (kMaxLinD + kMaxSumK) * (int)sizeof(float));
+      e != hipSuccess)
+    return e;
   if (e0 && e1) {  // the events take the dispatch's own start and stop timestamps
     hipExtLaunchKernelGGL((stream_rows<T, DENSE, TAIL, NT, LONG>), dim3(grid), dim3(kBlock), smem, s, e0, e1, 0, lb);
   } else {
@@ -277,10 +278,10 @@ hipError_t upload_launch(const void* src, size_t bytes, void* dst, hipStream_t s
 template <class T, bool TAIL, bool NT, bool LONG>
 static hipError_t launch_fired(const FiredIn* ins, const FiredMap* maps, int n_in, unsigned grid, size_t smem,
                                hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  static const hipError_t attr =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&stream_fired<T, TAIL, NT, LONG>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLinD * (int)sizeof(float));
-  if (attr != hipSuccess) return attr;
+  static LdsLimit lds;
+  if (hipError_t e = lds.allow(reinterpret_cast<const void*>(&stream_fired<T, TAIL, NT, LONG>), kMaxLinD * (int)sizeof(float));
+      e != hipSuccess)
+    return e;
   if (e0 && e1) hipExtLaunchKernelGGL((stream_fired<T, TAIL, NT, LONG>), dim3(grid), dim3(kBlock), smem, s, e0, e1, 0, ins, maps, n_in);
   else stream_fired<T, TAIL, NT, LONG><<<grid, kBlock, smem, s>>>(ins, maps, n_in);
   return hipGetLastError();

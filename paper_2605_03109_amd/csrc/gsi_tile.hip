@@ -723,15 +723,15 @@ hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, f
     constexpr size_t kScratch = kTBlock * sizeof(float2) + 16;  // norms_and_gate
     size_t smem = std::max((size_t)T * kRoundTok * vrow * sizeof(uint16_t), kScratch);
     if (tb + imgs <= kFewItems) smem = std::max(smem, kWholeUnit);
-    static const hipError_t attr =  // more than the default 64 KB at the largest ranks
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_residual<T>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            std::max(T * kRoundTok * kVRow * (int)sizeof(uint16_t), (int)kWholeUnit));
-    err = attr;
+    static LdsLimit lds;  // more than the default 64 KB at the largest ranks
+    err = lds.allow(reinterpret_cast<const void*>(&tile_residual<T>),
+                    std::max(T * kRoundTok * kVRow * (int)sizeof(uint16_t), (int)kWholeUnit));
     if (err != hipSuccess) return;
     if (pb.B <= 32) tile_proj_partial<1, T><<<ta, kPBlock, 0, s>>>(pb);
     else if (pb.B <= 64) tile_proj_partial<2, T><<<ta, kPBlock, 0, s>>>(pb);
     else tile_proj_partial<4, T><<<ta, kPBlock, 0, s>>>(pb);
     err = tile_proj_reduce_launch(pb, s);
+    if (err != hipSuccess) return;
     tile_residual<T><<<tb + imgs, kTBlock, smem, s>>>(pb, ib, vrow);
   };
   if (pb.t[0].tile == 3) launch(std::integral_constant<int, 3>{});
