@@ -20,8 +20,9 @@
 // column u = r2 / |r2| rounded, and each workgroup forms the part it reads from r2 and the shares itself (the same
 // arithmetic everywhere), so none waits for another; the workgroup that reads the new column of U takes u for it.  An
 // extension moves U three times and every W once; operands whose rows are 16-byte aligned are read with 16-byte loads,
-// several in flight per lane.  (s in a launch of its own, the column and U^T u likewise: seven launches of 4 to 5 us around
-// one of 24 us; three maps 4096 x 4096 on a basis of 4096 x 512: 51.7 us, 43.4 us with these four.)
+// several in flight per lane.  Large bases have s added up by a launch of its own (own_sums).  (s, the column and U^T u in
+// launches of their own for every basis: seven launches of 4 to 5 us around one of 24 us; three maps 4096 x 4096 on a
+// basis of 4096 x 512: 46.4 us, 39.5 us with these four, calls replayed from a graph.)
 //
 // Every launch covers ALL bases of a call (one grid dimension is the basis, or the map): a token's pass over the
 // bases of a whole model is these four launches, not four per basis, and what it costs when no basis grows is
@@ -44,9 +45,10 @@ constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / kWave;
 constexpr int kCols = 64;       // columns of U per workgroup in the projections
 constexpr int kRowsPerWg = 32;  // rows of U per workgroup in the residual
-constexpr int kImgPerWave = 4;    // rows of W per wave and turn in the image launch
+constexpr int kImgPerWave = 2;    // rows of W per wave and turn in the image rows
 constexpr int kImgRows = kWaves * kImgPerWave;
-constexpr int kLdsK = 2048;       // ranks whose s the residual workgroups add up themselves (in LDS)
+constexpr int kLdsK = 2048;       // ranks whose s the residual workgroups can add up themselves (in LDS)
+constexpr int kUBytes = 16384;    // block of the stored column that the image workgroups hold in LDS
 constexpr int kFewMaps = 8;     // maps whose records fit the kernel arguments
 constexpr int kSumBlock = 64;   // a wave per workgroup in the slab sums
 
@@ -58,6 +60,25 @@ struct ExtMapArg {  // the maps of an image launch: a device table, or up to kFe
   const ExtMapRec* tab;
   ExtMapRec few[kFewMaps];
 };
+
+// Loads through pointers that a record holds.  The record comes from the table or from the kernel arguments, so that these
+// pointers are generic to the compiler, and a plain load would be a flat one: it counts as an LDS access as well, and
+// every wait is a wait for all of them.
+__device__ __forceinline__ uint4 load_global16(const void* p) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 v = *(const __attribute__((address_space(1))) u32x4*)p;
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint4 load_global16_once(const void* p) {  // (non-temporal)
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4*)p);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float load_global(const float* p) { return *(const __attribute__((address_space(1))) float*)p; }
+__device__ __forceinline__ float4 load_global4(const float* p) {
+  const uint4 v = load_global16(p);
+  return float4{__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+}
 
 struct ExtWs {
   ExtState* st;
@@ -84,7 +105,7 @@ __host__ __device__ __forceinline__ ExtWs ext_ws(const ExtIn& in) {
 __device__ __forceinline__ float ext_inverse(const ExtIn& in, const ExtWs& w, float* sh) {
   const int cand = w.st->cand;  // (requested with the shares, which are not used if it is zero)
   float t = 0.f;
-  for (int q = threadIdx.x; q < in.wgs; q += kBlock) t += w.pn[q];
+  for (int q = threadIdx.x; q < in.wgs; q += kBlock) t += load_global(w.pn + q);
   t = group_sum<kWave>(t);
   if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = t;
   __syncthreads();
@@ -117,7 +138,7 @@ __device__ __forceinline__ void proj_block(const ExtIn& in, const ExtWs& w, cons
   constexpr int RG = kBlock / TPR;      // rows in flight per pass of the workgroup
   __shared__ float sh[RG][kCols + 1];
   const bool use_u = inv != 0.f;
-  auto value = [&](int64_t i) { return use_u ? stored<T>(v[i] * inv) : v[i]; };
+  auto value = [&](int64_t i) { return use_u ? stored<T>(load_global(v + i) * inv) : load_global(v + i); };
   // (a call with many bases launches fewer workgroups per basis than it has slabs: the workgroup takes several)
   for (int slab = slab0; slab < in.slabs; slab += step) {
     const int64_t r0 = (int64_t)slab * in.rows_per_slab;
@@ -136,7 +157,7 @@ __device__ __forceinline__ void proj_block(const ExtIn& in, const ExtWs& w, cons
           for (int q = 0; q < 4; ++q) {  // four rows requested before the first is used; rows past the slab repeat
             const int64_t ii = i + q * RG;  // the last one with weight zero
             const int64_t ic = ii < r1 ? ii : r1 - 1;
-            T::load_vec(U + ic * K + col0, f[q]);
+            T::widen(load_global16(U + ic * K + col0), f[q]);
             wt[q] = ii < r1 ? value(ic) : 0.f;
           }
 #pragma unroll
@@ -201,7 +222,7 @@ __device__ __forceinline__ float slab_sum(const float* __restrict__ part, int sl
   for (int q0 = 0; q0 < slabs; q0 += 16) {
     float v[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = part[(int64_t)min(q0 + u, slabs - 1) * K + j];
+    for (int u = 0; u < 16; ++u) v[u] = load_global(part + (int64_t)min(q0 + u, slabs - 1) * K + j);
 #pragma unroll
     for (int u = 0; u < 16; ++u)
       if (q0 + u < slabs) t += v[u];
@@ -209,11 +230,21 @@ __device__ __forceinline__ float slab_sum(const float* __restrict__ part, int sl
   return t;
 }
 
-// s of bases of more than kLdsK columns (the residual workgroups add up the others themselves)
+// Is s added up by a launch of its own?  Else every residual workgroup adds all slab partials itself: a launch less, but the
+// sums stand before its first product, and slabs x K x 4 bytes come from L2 for every workgroup.  us per extension of a
+// basis with one map, together / in a launch of their own: 16384 x 256 62.0 / 63.8; 4096 x 512 27.8 / 27.5; 16384 x 512
+// 65.6 / 65.0; 65536 x 512 197 / 191; 4096 x 2048 50.2 / 41.0; 16384 x 2048 109 / 100.  The line: 64 KB per
+// workgroup, 64 MB in all.
+__host__ __device__ __forceinline__ bool own_sums(const ExtIn& in) {
+  const int64_t per = in.K * in.slabs;
+  return in.K > kLdsK || per > 16384 || per * in.wgs > (1 << 24);
+}
+
+// s of the bases whose residual workgroups do not add it up themselves
 __global__ __launch_bounds__(kSumBlock) void ext_sum(const ExtArg a) {
   const ExtIn in = a.tab ? a.tab[blockIdx.y] : a.one;
   const ExtWs w = ext_ws(in);
-  if (in.K <= kLdsK || !w.st->cand) return;
+  if (!own_sums(in) || !w.st->cand) return;
   const int64_t j = (int64_t)blockIdx.x * kSumBlock + threadIdx.x;
   if (j >= in.K) return;
   w.sv[j] = slab_sum(w.part, in.slabs, in.K, j);
@@ -244,11 +275,11 @@ __global__ __launch_bounds__(kBlock) void ext_resid(const ExtArg a) {
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
       const int64_t i = r0 + wave + q * kWaves;
-      raw[q] = *reinterpret_cast<const uint4*>(U + (i < d ? i : d - 1) * K + (c < chunks ? c : chunks - 1) * V);
+      raw[q] = load_global16(U + (i < d ? i : d - 1) * K + (c < chunks ? c : chunks - 1) * V);
     }
   };
   if (in.uvec) request((int64_t)blockIdx.x * kRowsPerWg, lane);  // ahead of the sums below
-  if (K <= kLdsK) {  // uniform
+  if (!own_sums(in)) {  // uniform
     for (int64_t j = threadIdx.x; j < K; j += kBlock) ss[j] = slab_sum(w.part, in.slabs, K, j);
     __syncthreads();
     s = ss;
@@ -286,7 +317,7 @@ __global__ __launch_bounds__(kBlock) void ext_resid(const ExtArg a) {
       const float t = group_sum<kWave>(acc[q]);
       const int64_t i = r0 + wave + q * kWaves;
       if (i < r1) {  // uniform
-        const float ra = v[i] - t;
+        const float ra = load_global(v + i) - t;
         if (lane == 0) r2[i] = ra;
         nn = fmaf(ra, ra, nn);  // (every lane holds the same value)
       }
@@ -331,64 +362,90 @@ __device__ __forceinline__ void column_block(const ExtIn& in, const ExtWs& w, fl
     T::store(U, i * in.K + kc, w.r2[i] * inv);
 }
 
-// M[row, kc] = sum_i W[row, i] u[i]: a workgroup takes kImgRows rows of a map a turn, a wave kImgPerWave of them.  A wave
-// keeps its lanes' share of u in registers for a block of columns (2048 in bf16) and streams its rows past it, four
-// 16-byte loads per lane and row, three rows under way (u read again for every row: three bytes of cache traffic for a byte
-// of W, 4.2 TB/s).
-// (Requesting the first rows ahead of the verdict costs more in registers than it hides: 26 us against 24.)
+// M[row, kc] = sum_i W[row, i] u[i]: a workgroup takes kImgRows rows of a map a turn, a wave kImgPerWave of them.  The
+// workgroup keeps a block of u (8192 columns in bf16) in LDS, rounded as it is stored, from turn to turn if it is all of u;
+// a wave streams its rows past it in steps of 128 pieces of 16 bytes, the next three steps' loads under way all the time:
+// from row to row, along the rows and across blocks.
+// Bound by how much a unit has in flight: 109 registers leave four waves per SIMD.  With four rows per wave and the
+// lanes' share of u in registers (163, three waves per SIMD) nothing was under way from one block of columns to the next,
+// and long rows lost.  us per extension, rank 512, so / here / as a launch of its own behind the stored column: three maps
+// 4096 x 4096 39.6 / 39.4 / 46.5, one of 16384 x 4096 48.2 / 42.7 / 53.2, one of 4096 x 16384 65.5 / 56.0 / 60.5, one of
+// 4096 x 65536 197 / 160 / 168.  Other shapes of the ring (rows per wave x loads per step): 2 x 4 and 4 x 2 lose a wave per
+// SIMD (1 to 9 us), 1 x 2 reads u from LDS twice as often (three maps 46.0).
+// (Requesting the first rows ahead of the verdict costs more in registers than it hides.)
 template <class T>
 __device__ __forceinline__ void image_rows_block(const ExtIn& in, const ExtWs& w, const ExtMapRec& p, float inv, int blk, int blocks) {
   using S = typename T::storage;
   constexpr int V = T::kVec;
-  constexpr int NL = 4, NB = 3;  // loads per lane and row, rows under way
+  constexpr int NL = 2;                   // loads per lane and step
+  constexpr int kStep = kWave * NL;       // 16-byte pieces of a step
+  constexpr int kUPieces = kUBytes / 16;  // ... of a block of u
+  static_assert(kUPieces % kStep == 0, "a block is whole steps");
+  __shared__ uint4 us[kUPieces];
   const int64_t d = in.d, K = in.K;
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int kc = w.st->kc;
   const S* W = static_cast<const S*>(p.W);
   const int64_t chunks = d / V;
+  const int steps = (int)((chunks + kStep - 1) / kStep);
+  int64_t held = -1;  // first piece of the block of u in LDS
+#pragma unroll 1
   for (int64_t row_begin = (int64_t)blk * kImgRows; row_begin < p.m; row_begin += (int64_t)blocks * kImgRows) {
     const int64_t row0 = row_begin + wave * kImgPerWave;
-    if (row0 >= p.m) continue;  // (whole waves)
     float acc[kImgPerWave];
 #pragma unroll
     for (int r = 0; r < kImgPerWave; ++r) acc[r] = 0.f;
     if (p.vec) {
-      for (int64_t c0 = 0; c0 < chunks; c0 += (int64_t)kWave * NL) {
-        uint4 raw[NB][NL];
-        auto request = [&](uint4 (&buf)[NL], int r) {  // rows past the matrix and chunks past the row repeat the last one
-          const S* wr = W + (row0 + r < p.m ? row0 + r : p.m - 1) * d;
+      constexpr int kSlots = 4, kAhead = kSlots - 1;  // steps under way: slot f of the ring is row f % kImgPerWave
+      static_assert(kSlots % kImgPerWave == 0, "a slot belongs to a row");
+      uint4 raw[kSlots][NL];
+      // rows past the matrix and pieces past the row repeat the last one (uniform base, 32-bit lane offsets)
+      auto request = [&](int slot, int g, int r) {
+        const char* base = reinterpret_cast<const char*>(W + (row0 + r < p.m ? row0 + r : p.m - 1) * d + (int64_t)g * kStep * V);
+        const int left = (int)(chunks - (int64_t)g * kStep < kStep ? chunks - (int64_t)g * kStep : kStep);
 #pragma unroll
-          for (int q = 0; q < NL; ++q) {
-            const int64_t c = c0 + lane + (int64_t)q * kWave;
-            buf[q] = load_stream16(wr + (c < chunks ? c : chunks - 1) * V);
-          }
-        };
+        for (int q = 0; q < NL; ++q) raw[slot][q] = load_global16_once(base + 16u * (uint32_t)min(lane + q * kWave, left - 1));
+      };
 #pragma unroll
-        for (int r = 0; r < NB - 1; ++r) request(raw[r], r);
-        float u[NL][V];
+      for (int f = 0; f < kAhead; ++f)
+        if (f / kImgPerWave < steps) request(f, f / kImgPerWave, f % kImgPerWave);
+#pragma unroll 1
+      for (int g0 = 0; g0 < steps; g0 += kSlots / kImgPerWave) {
 #pragma unroll
-        for (int q = 0; q < NL; ++q) {
-          const int64_t c = c0 + lane + (int64_t)q * kWave;
-          const float* src = w.r2 + (c < chunks ? c : chunks - 1) * V;
+        for (int f = 0; f < kSlots; ++f) {
+          const int g = g0 + f / kImgPerWave, r = f % kImgPerWave;
+          if (g < steps) {
+            const int64_t c0 = (int64_t)g * kStep;
+            const int in_block = (int)(c0 % kUPieces), left = (int)(chunks - c0 < kStep ? chunks - c0 : kStep);
+            if (r == 0 && in_block == 0 && c0 != held) {
+              held = c0;  // uniform: the next block of u
+              __syncthreads();  // (the one before has been read)
+#pragma unroll 1
+              for (int e = threadIdx.x; e < kUPieces && c0 + e < chunks; e += kBlock) {
+                __align__(16) S t[V];
 #pragma unroll
-          for (int e = 0; e < V; e += 4) {
-            const float4 x = *reinterpret_cast<const float4*>(src + e);
-            u[q][e] = stored<T>(x.x * inv); u[q][e + 1] = stored<T>(x.y * inv);
-            u[q][e + 2] = stored<T>(x.z * inv); u[q][e + 3] = stored<T>(x.w * inv);
-          }
-        }
+                for (int q = 0; q < V; q += 4) {
+                  const float4 x = load_global4(w.r2 + (c0 + e) * V + q);
+                  T::store(t, q, x.x * inv); T::store(t, q + 1, x.y * inv);
+                  T::store(t, q + 2, x.z * inv); T::store(t, q + 3, x.w * inv);
+                }
+                us[e] = *reinterpret_cast<const uint4*>(t);
+              }
+              __syncthreads();
+            }
+            const int nf = f + kAhead, ng = g0 + nf / kImgPerWave;
+            if (ng < steps) request(nf % kSlots, ng, nf % kImgPerWave);
+            __builtin_amdgcn_sched_barrier(0);  // later rows' requests stay ahead of this row's arithmetic
 #pragma unroll
-        for (int r = 0; r < kImgPerWave; ++r) {
-          if (r + NB - 1 < kImgPerWave) request(raw[(r + NB - 1) % NB], r + NB - 1);
-          __builtin_amdgcn_sched_barrier(0);  // later rows' requests stay ahead of this row's arithmetic
+            for (int q = 0; q < NL; ++q) {
+              float f32[V], u[V];
+              T::widen(raw[f][q], f32);
+              T::widen(us[in_block + lane + q * kWave], u);
+              float t = 0.f;
 #pragma unroll
-          for (int q = 0; q < NL; ++q) {
-            float f[V];
-            T::widen(raw[r % NB][q], f);
-            float t = 0.f;
-#pragma unroll
-            for (int e = 0; e < V; ++e) t = fmaf(f[e], u[q][e], t);
-            acc[r] += c0 + lane + (int64_t)q * kWave < chunks ? t : 0.f;
+              for (int e = 0; e < V; ++e) t = fmaf(f32[e], u[e], t);
+              acc[r] += lane + q * kWave < left ? t : 0.f;
+            }
           }
         }
       }
@@ -492,25 +549,30 @@ hipError_t launch_all(const ExtIn* in, int n, const ExtMapRec* maps, int n_maps,
     mtab = reinterpret_cast<const ExtMapRec*>(static_cast<const char*>(table) + ib);
   }
   int64_t K_max = 0, d_max = 0, m_max = 0;
-  int slabs_max = 0, wgs_max = 0, any_gram = 0;
+  int slabs_max = 0, wgs_max = 0, any_gram = 0, any_own = 0;
   for (int i = 0; i < n; ++i) {
     K_max = std::max<int64_t>(K_max, in[i].K);
     d_max = std::max<int64_t>(d_max, in[i].d);
     slabs_max = std::max(slabs_max, in[i].slabs);
     wgs_max = std::max(wgs_max, in[i].wgs);
     any_gram |= in[i].gram != nullptr;
+    any_own |= own_sums(in[i]);
   }
   for (int j = 0; j < n_maps; ++j) m_max = std::max<int64_t>(m_max, maps[j].m);
   // A launch is about kGridCap workgroups at most: every workgroup of a basis that does not grow reads its record and
   // leaves, which is what a token costs nearly always, so a call with many bases gives each fewer workgroups (they
   // take several slabs, row blocks ... in turn; what a workgroup computes per slab or row does not change).
   constexpr int64_t kGridCap = 2048;
+  // image workgroups: of one basis three per compute unit, resident beside the launch's other workgroups; of many, of
+  // which few grow as a rule, up to twice the cap, so that the maps of a basis that grows alone get some of the chip
+  // (48 maps, 85 workgroups each: 63 us when one of 32 bases grows, 173 us with 16 each)
+  const int64_t img_cap = n > 1 ? 2 * kGridCap : 768;
   const int64_t pc = ceil_div(K_max, kCols);
   const dim3 pgrid((unsigned)pc, (unsigned)std::min<int64_t>(slabs_max, std::max<int64_t>(1, kGridCap / (pc * n))), (unsigned)n);
   const dim3 kgrid((unsigned)ceil_div(K_max, kSumBlock), (unsigned)n);
   const int64_t per_basis = std::max<int64_t>(8, kGridCap / n);
   ext_proj<T><<<pgrid, kBlock, 0, s>>>(a, tau);
-  if (K_max > kLdsK) ext_sum<<<kgrid, kSumBlock, 0, s>>>(a);
+  if (any_own) ext_sum<<<kgrid, kSumBlock, 0, s>>>(a);
   ext_resid<T><<<dim3((unsigned)std::min<int64_t>(wgs_max, per_basis), (unsigned)n), kBlock, 0, s>>>(a);
   ExtStore g;
   g.n = n;
@@ -531,7 +593,7 @@ hipError_t launch_all(const ExtIn* in, int n, const ExtMapRec* maps, int n_maps,
         mm = std::max<int64_t>(mm, maps[j0 + q].m);
       }
     }
-    g.img_wgs = g.n_maps > 0 ? (int)std::min<int64_t>(ceil_div(mm, kImgRows), std::max<int64_t>(8, 2 * kGridCap / g.n_maps)) : 0;
+    g.img_wgs = g.n_maps > 0 ? (int)std::min<int64_t>(ceil_div(mm, kImgRows), std::max<int64_t>(8, img_cap / g.n_maps)) : 0;
     if (j0 > 0) g.n = 0;
     const int64_t blocks = (int64_t)g.n * (g.col_wgs + (int64_t)g.pcols * g.pslabs) + (int64_t)g.n_maps * g.img_wgs;
     if (blocks > 0) ext_store<T><<<(unsigned)blocks, kBlock, 0, s>>>(a, ma, g);
