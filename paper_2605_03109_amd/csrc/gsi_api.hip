@@ -556,9 +556,8 @@ static void clear(gsi::LinBatch& lb, int64_t B) {
 
 // A decode batch (2..128 tokens) over an input longer than the linear kernels' LDS vector runs on the matrix-core
 // kernel only: what that kernel needs beyond decode_linear_ok (reads_x: the product reads x, dense or W x form).
-static bool long_batch_ok(int64_t d, int64_t B, const void* Y, bool reads_x, const void* X, int xdtype) {
+static bool long_batch_ok(int64_t d, int64_t B, const void* Y, bool reads_x, const void* X) {
   if (B == 1 || d <= gsi::kMaxLinD) return true;
-  (void)xdtype;
   return aligned(Y, 16) && (!reads_x || aligned(X, 16));
 }
 
@@ -710,7 +709,7 @@ int gsi_dense_linear(const void* W, const void* X, int64_t m, int64_t d, int64_t
     const gsi::GemmProb g = mfma_dense_prob(W, X, m, d, B, Y, (float*)ws, full);
     e = gsi::mfma_gemm_nt(&g, 1, xdtype == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s);
   } else if (gsi::decode_linear_ok(m, d, 0, wdtype, W, nullptr, B) && aligned(X, 16) &&
-             long_batch_ok(d, B, Y, true, X, xdtype)) {
+             long_batch_ok(d, B, Y, true, X)) {
     gsi::LinBatch lb;
     clear(lb, B);
     lb.n = lb.ng = 1;
@@ -930,7 +929,7 @@ int gsi_dense_stack(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_de
         const gsi_map_desc& mp = maps[j];
         const gsi_input_desc& in = inputs[mp.input_id];
         if (!now(j) || mp.wdtype != dt || !gsi::decode_linear_ok(mp.m, in.d, 0, mp.wdtype, mp.W, nullptr, B) ||
-            !aligned(in.X, 16) || !long_batch_ok(in.d, B, mp.Y, true, in.X, in.xdtype))
+            !aligned(in.X, 16) || !long_batch_ok(in.d, B, mp.Y, true, in.X))
           continue;
         gsi::LinGroup gd;
         std::memset(&gd, 0, sizeof(gd));
@@ -1577,7 +1576,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
           continue;  // matrix cores below
         if (!gsi::decode_linear_ok(mp.m, in.d, in.k, mp.wdtype, mp.W, mp.M, B) || !aligned(in.C, 16) ||
             !aligned(in.R, 16) || !wx_vector_ok(in) ||
-            !long_batch_ok(in.d, B, mp.Y, (in.flags & GSI_INPUT_SLOW_PATH_WX) != 0, in.X, in.xdtype))
+            !long_batch_ok(in.d, B, mp.Y, (in.flags & GSI_INPUT_SLOW_PATH_WX) != 0, in.X))
           continue;
         gsi::LinGroup gd;
         std::memset(&gd, 0, sizeof(gd));

@@ -42,8 +42,8 @@ int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool full);
 size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, bool full);
 
 // Products of one launch (n of any number; more than kMaxProbs take several launches).  a_f32: A is 0: bf16; 1: fp32, fed as
-// bf16 head + tail (two passes); 2: fp32, rounded once to bf16.  epi: EPI_STORE_BF16, EPI_STORE_F32, EPI_PROJECTED or
-// EPI_SCATTER; every problem's own epi belongs to it.
+// bf16 head + tail (two passes); 2: fp32, rounded once to bf16.  epi: EPI_STORE_BF16 (A bf16), EPI_STORE_F32 (bf16 or head +
+// tail), EPI_PROJECTED (head + tail) or EPI_SCATTER; every problem's own epi belongs to it.
 hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s);
 
 // Ut[j][i] = U[i][j] for n bf16 matrices U[rows, cols]

@@ -528,14 +528,26 @@ hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int AM>
-hipError_t launch_epi(GemmArgs& g, int epi, int tm, hipStream_t s) {
+// the forms of A that a caller has with each epilogue, and no others
+hipError_t launch_epi(GemmArgs& g, int a_f32, int epi, int tm, hipStream_t s) {
   switch (epi) {
-    case EPI_STORE_BF16: return launch_group<AM, EPI_STORE_BF16>(g, tm, s);
-    case EPI_STORE_F32: return launch_group<AM, EPI_STORE_F32>(g, tm, s);
-    case EPI_PROJECTED: return launch_group<AM, EPI_PROJECTED>(g, tm, s);
-    default: return launch_group<AM, EPI_SCATTER>(g, tm, s);
+    case EPI_STORE_BF16:
+      if (a_f32 == 0) return launch_group<0, EPI_STORE_BF16>(g, tm, s);
+      break;
+    case EPI_STORE_F32:
+      if (a_f32 == 0) return launch_group<0, EPI_STORE_F32>(g, tm, s);
+      if (a_f32 == 1) return launch_group<1, EPI_STORE_F32>(g, tm, s);
+      break;
+    case EPI_PROJECTED:
+      if (a_f32 == 1) return launch_group<1, EPI_PROJECTED>(g, tm, s);
+      break;
+    case EPI_SCATTER:
+      if (a_f32 == 0) return launch_group<0, EPI_SCATTER>(g, tm, s);
+      if (a_f32 == 1) return launch_group<1, EPI_SCATTER>(g, tm, s);
+      if (a_f32 == 2) return launch_group<2, EPI_SCATTER>(g, tm, s);
+      break;
   }
+  return hipErrorInvalidValue;
 }
 
 // rows that a product is sized for: the scatter products run over the fired rows only (a device-side count): a quarter
@@ -614,8 +626,7 @@ hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStr
     if (g.n == 0) break;
     for (int q = 0; q < g.n; ++q) g.p[q].splits = g.p[q].part ? g.p[q].max_splits : 1;
     const int tm = plan_rows(g, epi);
-    const hipError_t e = a_f32 == 2 ? launch_epi<2>(g, epi, tm, s) : a_f32 ? launch_epi<1>(g, epi, tm, s) : launch_epi<0>(g, epi, tm, s);
-    if (e != hipSuccess) return e;
+    if (hipError_t e = launch_epi(g, a_f32, epi, tm, s); e != hipSuccess) return e;
   }
   return hipSuccess;
 }
