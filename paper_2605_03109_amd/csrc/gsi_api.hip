@@ -669,7 +669,7 @@ int gsi_gated_linear(const void* W, const void* M, const float* C, const float* 
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (!mfma_gated_path(W, M, C, R, d, k, B, wdtype, m, Y) && gsi::decode_linear_ok(m, d, k, wdtype, W, M, B) &&
-      aligned(C, 16) && aligned(R, 16) && long_batch_ok(d, B, Y, false, nullptr, 0)) {
+      aligned(C, 16) && aligned(R, 16) && long_batch_ok(d, B, Y, false, nullptr)) {
     LinBatcher bt;
     bt.wdtype = wdtype; bt.s = s;
     bt.reset(B, 0);
