@@ -16,6 +16,8 @@
 
 namespace {
 
+using gsi::WsLevel, gsi::kWsFull, gsi::kWsCoarse, gsi::kWsFirst;
+
 thread_local char g_err[512] = "";
 
 int fail(int code, const char* fmt, ...) {
@@ -63,6 +65,21 @@ int check_ws(const char* fn, const void* ws, size_t have, size_t need) {
   return GSI_OK;
 }
 
+// Which of its sizes does a call's workspace have?  bytes(level): the size of each.  NULL or unaligned memory is none, whatever
+// size is named for it: a call that needed no workspace before has to be served without one.  GSI_OK: at least the first.
+template <class Bytes>
+int check_ws_level(const char* fn, const void* ws, size_t ws_bytes, Bytes bytes, WsLevel& level) {
+  for (WsLevel l : {kWsFull, kWsCoarse}) {
+    const size_t need = bytes(l);
+    if (need == 0 || (ws && aligned(ws, 256) && ws_bytes >= need)) {
+      level = l;
+      return GSI_OK;
+    }
+  }
+  level = kWsFirst;
+  return check_ws(fn, ws, ws_bytes, bytes(kWsFirst));
+}
+
 }  // namespace
 
 extern "C" {
@@ -86,67 +103,57 @@ static bool mfma_image_ok(int64_t m, int64_t d, int64_t k) {
 static bool mfma_batch_ok(int64_t d, int64_t k, int64_t B) {
   return B > kDecodeMaxB && d % 64 == 0 && k % 64 == 0 && B < (1ll << 30) && B * d < (1ll << 31);
 }
-static size_t mfma_project_ws(int64_t d, int64_t k, int64_t B, bool full) {
-  return gsi::align_up((size_t)k * d * 2, 256) + gsi::align_up((size_t)gsi::mfma_res_tiles(d, full) * B * 2 * 4, 256) +
-         gsi::mfma_part_bytes(B, k, d, gsi::EPI_STORE_F32, full);
+static size_t mfma_project_ws(int64_t d, int64_t k, int64_t B, WsLevel level) {
+  return gsi::align_up((size_t)k * d * 2, 256) + gsi::align_up((size_t)gsi::mfma_res_tiles(d, level) * B * 2 * 4, 256) +
+         gsi::mfma_part_bytes(B, k, d, gsi::EPI_COEFF, level);
 }
 // workspace of one linear map of a call with B tokens: partial products of the decode-batch kernel, or of
 // the split contraction of the prefill-sized W term (dense = 1: of the dense product)
-static size_t map_part_bytes(int64_t m, int64_t d, int64_t B, int dense, bool full) {
+static size_t map_part_bytes(int64_t m, int64_t d, int64_t B, int dense, WsLevel level) {
   if (B > kDecodeMaxB)
-    return d % 64 == 0 ? gsi::mfma_part_bytes(B, m, d, dense ? gsi::EPI_STORE_F32 : gsi::EPI_SCATTER_ADD, full) : 0;
+    return d % 64 == 0 ? gsi::mfma_part_bytes(B, m, d, dense ? gsi::EPI_STORE_F32 : gsi::EPI_SCATTER_ADD, level) : 0;
   return gsi::tile_part_bytes(m, d, B);
 }
 
-// Workspaces come in two sizes.  full: what the queries name.  Less: what they named before ranks other than 2^j pieces
-// of 16 bytes had vector kernels (none for those) and prefill-sized products were split as finely as now; a call that
-// brings only that much (a fixed scratch memory it used to fit) is still served, those ranks by the generic kernels.
-static size_t project_ws_bytes(int64_t d, int64_t k, int64_t B, bool full) {
+static size_t project_ws_bytes(int64_t d, int64_t k, int64_t B, WsLevel level) {
   if (d < 1 || k < 1 || k > d || B < 1) return 0;
-  if (B > kDecodeMaxB) return mfma_batch_ok(d, k, B) ? mfma_project_ws(d, k, B, full) : 0;
+  if (B > kDecodeMaxB) return mfma_batch_ok(d, k, B) ? mfma_project_ws(d, k, B, level) : 0;
   // the slab partials of the vector projection kernels; sized for the wider of the two dtypes so
   // that the query does not depend on the dtype (generic kernels need none)
   size_t need = 0;
   for (int dt = 0; dt < 2; ++dt) {
-    if (!gsi::decode_project_ok(d, k, dt, nullptr) || !(full || gsi::rank_pow2(k, dt))) continue;
-    const size_t w = gsi::decode_project_ws(d, k, B, dt, full);
+    if (!gsi::decode_project_ok(d, k, dt, nullptr) || !(level > kWsFirst || gsi::rank_pow2(k, dt))) continue;
+    const size_t w = gsi::decode_project_ws(d, k, B, dt, level > kWsFirst);
     if (w > need) need = w;
   }
   return need;
 }
 
-static size_t call_ws_bytes(int which_call, int64_t m, int64_t d, int64_t k, int64_t B, bool full) {
+static size_t call_ws_bytes(int which_call, int64_t m, int64_t d, int64_t k, int64_t B, WsLevel level) {
   switch (which_call) {
     case GSI_CALL_BUILD_IMAGE:
       // the transposed basis of the matrix-core build (bf16 operands); generic kernels need none
       if (m < 1 || d < 1 || k < 1 || k > d || !mfma_image_ok(m, d, k)) return 0;
-      return gsi::align_up((size_t)k * d * 2, 256) + gsi::mfma_part_bytes(m, k, d, gsi::EPI_STORE_BF16, full);
+      return gsi::align_up((size_t)k * d * 2, 256) + gsi::mfma_part_bytes(m, k, d, gsi::EPI_STORE_BF16, level);
     case GSI_CALL_PROJECT:
-      return project_ws_bytes(d, k, B, full);
+      return project_ws_bytes(d, k, B, level);
     case GSI_CALL_GATED_LINEAR:
     case GSI_CALL_DENSE_LINEAR:
       // partial products of the matrix-core kernels
       if (m < 1 || d < 1 || B < 1) return 0;
-      return map_part_bytes(m, d, B, which_call == GSI_CALL_DENSE_LINEAR, full);
+      return map_part_bytes(m, d, B, which_call == GSI_CALL_DENSE_LINEAR, level);
     default:
       return 0;
   }
 }
 
 size_t gsi_workspace_bytes(int which_call, int64_t m, int64_t d, int64_t k, int64_t B) {
-  return call_ws_bytes(which_call, m, d, k, B, true);
+  return call_ws_bytes(which_call, m, d, k, B, kWsFull);
 }
 
-// Does a call bring a workspace that it can use, of the full size?  (NULL or unaligned memory is none, whatever size is
-// named for it: a call that needed no workspace before has to be served without one.)
-static bool full_ws(const void* ws, size_t ws_bytes, size_t full_bytes) {
-  return full_bytes == 0 || (ws && aligned(ws, 256) && ws_bytes >= full_bytes);
-}
-// ... of a stand-alone call (GSI_OK: at least the smaller size)
 static int check_call_ws(const char* fn, int which_call, int64_t m, int64_t d, int64_t k, int64_t B, const void* ws,
-                         size_t ws_bytes, bool& full) {
-  full = full_ws(ws, ws_bytes, call_ws_bytes(which_call, m, d, k, B, true));
-  return full ? GSI_OK : check_ws(fn, ws, ws_bytes, call_ws_bytes(which_call, m, d, k, B, false));
+                         size_t ws_bytes, WsLevel& level) {
+  return check_ws_level(fn, ws, ws_bytes, [&](WsLevel l) { return call_ws_bytes(which_call, m, d, k, B, l); }, level);
 }
 
 // D[M,N] = A[M,K] B[N,K]^T (unsplit unless the caller adds a workspace)
@@ -172,8 +179,8 @@ int gsi_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d,
   GSI_REQUIRE_ALIGNED(W, es);
   GSI_REQUIRE_ALIGNED(U, es);
   GSI_REQUIRE_ALIGNED(M, es);
-  bool full;
-  if (int rc = check_call_ws("gsi_build_image", GSI_CALL_BUILD_IMAGE, m, d, k, 0, ws, ws_bytes, full)) return rc;
+  WsLevel level;
+  if (int rc = check_call_ws("gsi_build_image", GSI_CALL_BUILD_IMAGE, m, d, k, 0, ws, ws_bytes, level)) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (wdtype == GSI_BF16 && mfma_image_ok(m, d, k) && aligned(W, 16) && aligned(U, 2) && aligned(M, 8)) {
@@ -182,7 +189,7 @@ int gsi_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d,
     e = gsi::mfma_transpose_bf16(&tr, 1, s);
     if (e == hipSuccess) {
       gsi::GemmProb g = gemm_prob(W, d, ws, d, M, k, m, k, d, gsi::EPI_STORE_BF16);
-      g.max_splits = gsi::mfma_splits(m, k, d, gsi::EPI_STORE_BF16, full);
+      g.max_splits = gsi::mfma_splits(m, k, d, gsi::EPI_STORE_BF16, false, level);
       if (g.max_splits > 1)
         g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + gsi::align_up((size_t)k * d * 2, 256));
       e = gsi::mfma_gemm_nt(&g, 1, 0, gsi::EPI_STORE_BF16, s);
@@ -374,15 +381,15 @@ static int check_gated_args(const char* fn, const void* W, const void* M, const 
   return GSI_OK;
 }
 
-static bool project_vector_path(int64_t d, int64_t k, int64_t B, int udtype, const void* U, bool full) {
-  return B <= kDecodeMaxB && gsi::decode_project_ok(d, k, udtype, U) && (full || gsi::rank_pow2(k, udtype));
+static bool project_vector_path(int64_t d, int64_t k, int64_t B, int udtype, const void* U, WsLevel level) {
+  return B <= kDecodeMaxB && gsi::decode_project_ok(d, k, udtype, U) && (level > kWsFirst || gsi::rank_pow2(k, udtype));
 }
 
 static void fill_proj_task(gsi::ProjTask& t, const void* U, const void* X, int64_t d, int64_t k, int64_t B,
-                           int udtype, int xdtype, float* C, float* R, float* rnorm, float* xnorm, void* ws, bool full) {
+                           int udtype, int xdtype, float* C, float* R, float* rnorm, float* xnorm, void* ws, WsLevel level) {
   t.U = U; t.X = X; t.C = C; t.R = R; t.rnorm = rnorm; t.xnorm = xnorm;
   t.udtype = udtype; t.xdtype = xdtype;
-  gsi::decode_project_fill(t, d, k, B, ws, full);
+  gsi::decode_project_fill(t, d, k, B, ws, level > kWsFirst);
 }
 
 // Prefill-sized projections of independent inputs on the matrix cores: C = X U, then R = X - C U^T with per-tile partial
@@ -407,7 +414,7 @@ struct ImageRider {
   int64_t m;
 };
 static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img, int n_img, int64_t B, bool with_gate,
-                               float eps, bool full, hipStream_t s) {
+                               float eps, WsLevel level, hipStream_t s) {
   static thread_local std::vector<gsi::TransposeTask> tr;
   static thread_local std::vector<gsi::GemmProb> pr;
   tr.clear();
@@ -420,10 +427,10 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
       const int64_t d = in[i].d, k = in[i].k;
       if (in[i].xdtype != xdt) continue;
       gsi::GemmProb g = gemm_prob(in[i].X, d, in[i].ws, d, in[i].C, k, B, k, d, gsi::EPI_STORE_F32);
-      g.max_splits = gsi::mfma_splits(B, k, d, gsi::EPI_STORE_F32, full);
+      g.max_splits = gsi::mfma_splits(B, k, d, gsi::EPI_COEFF, xdt == GSI_F32, level);
       if (g.max_splits > 1)
         g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(part_n(i)) +
-                                          gsi::align_up((size_t)gsi::mfma_res_tiles(d, full) * B * 2 * 4, 256));
+                                          gsi::align_up((size_t)gsi::mfma_res_tiles(d, level) * B * 2 * 4, 256));
       pr.push_back(g);
     }
     if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s); e != hipSuccess)
@@ -440,7 +447,7 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
       if (img[q].in == i)
         pr.push_back(gemm_prob(in[i].C, in[i].k, img[q].M, in[i].k, img[q].Y, img[q].m, B, img[q].m, in[i].k, gsi::EPI_STORE_F32));
   }
-  for (gsi::GemmProb& g : pr) g.res_cols = full ? 64 : 128;
+  for (gsi::GemmProb& g : pr) g.res_cols = gsi::mfma_res_cols(level);
   if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), 1, gsi::EPI_PROJECTED, s); e != hipSuccess) return e;
   for (int i = 0; i < n;) {
     gsi::ProjBatch pb;
@@ -448,7 +455,7 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
     pb.B = (int)B;
     for (; i < n && pb.n < gsi::kMaxTasks; ++i) {
       gsi::ProjTask& t = pb.t[pb.n++];
-      t.part_n = part_n(i); t.b_slabs = gsi::mfma_res_tiles(in[i].d, full);
+      t.part_n = part_n(i); t.b_slabs = gsi::mfma_res_tiles(in[i].d, level);
       t.sync = reinterpret_cast<unsigned*>(in[i].ws);
       t.rnorm = in[i].rnorm; t.xnorm = in[i].xnorm;
       t.mask = in[i].mask; t.fired_idx = in[i].fired_idx; t.n_fired = in[i].n_fired;
@@ -481,7 +488,7 @@ struct MfmaMap {
   float* part;
   bool image_done;
 };
-static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, bool full, hipStream_t s) {
+static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, WsLevel level, hipStream_t s) {
   static thread_local std::vector<gsi::GemmProb> pr;
   pr.clear();
   for (int j = 0; j < n; ++j)
@@ -498,7 +505,7 @@ static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, bool full, hip
       const int epi = q.Xwx ? gsi::EPI_SCATTER_STORE : gsi::EPI_SCATTER_ADD;
       gsi::GemmProb g = gemm_prob(q.Xwx ? q.Xwx : q.R, q.d, q.W, q.d, q.Y, q.m, B, q.m, q.d, epi);
       g.row_idx = q.fired_idx; g.n_rows_dev = q.n_fired;
-      g.max_splits = gsi::mfma_splits(B, q.m, q.d, epi, full);
+      g.max_splits = gsi::mfma_splits(B, q.m, q.d, epi, mode == 1, level);
       g.part = g.max_splits > 1 ? q.part : nullptr;
       pr.push_back(g);
     }
@@ -519,10 +526,10 @@ static bool mfma_dense_path(const void* W, const void* X, int64_t m, int64_t d, 
   return wdtype == GSI_BF16 && B > kDecodeMaxB && d % 64 == 0 && m % 4 == 0 && B * m < (1ll << 31) &&
          aligned(W, 16) && aligned(X, 16) && aligned(Y, 16);
 }
-static gsi::GemmProb mfma_dense_prob(const void* W, const void* X, int64_t m, int64_t d, int64_t B, float* Y, float* part,
-                                     bool full) {
+static gsi::GemmProb mfma_dense_prob(const void* W, const void* X, int xdtype, int64_t m, int64_t d, int64_t B, float* Y,
+                                     float* part, WsLevel level) {
   gsi::GemmProb g = gemm_prob(X, d, W, d, Y, m, B, m, d, gsi::EPI_STORE_F32);
-  g.max_splits = gsi::mfma_splits(B, m, d, gsi::EPI_STORE_F32, full);
+  g.max_splits = gsi::mfma_splits(B, m, d, gsi::EPI_STORE_F32, xdtype == GSI_F32, level);
   g.part = g.max_splits > 1 ? part : nullptr;
   return g;
 }
@@ -628,20 +635,20 @@ int gsi_project(const void* U, const void* X, int64_t d, int64_t k, int64_t B, i
                 float* R, float* rnorm, float* xnorm, void* ws, size_t ws_bytes, void* stream) {
   if (int rc = check_project_args("gsi_project", U, X, d, k, B, udtype, xdtype, C, R, rnorm, xnorm)) return rc;
   if (B == 0) return GSI_OK;
-  bool full;
-  if (int rc = check_call_ws("gsi_project", GSI_CALL_PROJECT, 0, d, k, B, ws, ws_bytes, full)) return rc;
+  WsLevel level;
+  if (int rc = check_call_ws("gsi_project", GSI_CALL_PROJECT, 0, d, k, B, ws, ws_bytes, level)) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
-  if (project_vector_path(d, k, B, udtype, U, full)) {
+  if (project_vector_path(d, k, B, udtype, U, level)) {
     gsi::ProjBatch pb;
     std::memset(&pb, 0, sizeof(pb));
     pb.n = 1;
     pb.B = (int)B;
-    fill_proj_task(pb.t[0], U, X, d, k, B, udtype, xdtype, C, R, rnorm, xnorm, ws, full);
+    fill_proj_task(pb.t[0], U, X, d, k, B, udtype, xdtype, C, R, rnorm, xnorm, ws, level);
     e = gsi::decode_project_launch(pb, udtype, true, false, 0.f, s);
   } else if (mfma_project_path(U, X, d, k, B, udtype, xdtype, C, R)) {
     const MfmaInput in{U, X, d, k, xdtype, C, R, rnorm, xnorm, nullptr, nullptr, nullptr, static_cast<char*>(ws)};
-    e = mfma_project(&in, 1, nullptr, 0, B, false, 0.f, full, s);
+    e = mfma_project(&in, 1, nullptr, 0, B, false, 0.f, level, s);
   } else {
     e = gsi::generic_project(U, X, d, k, B, udtype, xdtype, C, R, rnorm, xnorm, s);
   }
@@ -664,8 +671,8 @@ int gsi_gated_linear(const void* W, const void* M, const float* C, const float* 
   if (int rc = check_gated_args("gsi_gated_linear", W, M, C, R, fired_idx, n_fired, m, d, k, B, wdtype, Y, ydtype))
     return rc;
   if (B == 0) return GSI_OK;
-  bool full;
-  if (int rc = check_call_ws("gsi_gated_linear", GSI_CALL_GATED_LINEAR, m, d, k, B, ws, ws_bytes, full)) return rc;
+  WsLevel level;
+  if (int rc = check_call_ws("gsi_gated_linear", GSI_CALL_GATED_LINEAR, m, d, k, B, ws, ws_bytes, level)) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (!mfma_gated_path(W, M, C, R, d, k, B, wdtype, m, Y) && gsi::decode_linear_ok(m, d, k, wdtype, W, M, B) &&
@@ -681,7 +688,7 @@ int gsi_gated_linear(const void* W, const void* M, const float* C, const float* 
     if (e == hipSuccess) e = bt.flush();
   } else if (mfma_gated_path(W, M, C, R, d, k, B, wdtype, m, Y)) {
     const MfmaMap mp{W, M, C, R, nullptr, 0, fired_idx, n_fired, m, d, k, (float*)Y, (float*)ws, false};
-    e = mfma_gated(&mp, 1, B, full, s);
+    e = mfma_gated(&mp, 1, B, level, s);
   } else {
     e = gsi::generic_gated_linear(W, M, C, R, fired_idx, n_fired, m, d, k, B, wdtype, (float*)Y, s);
   }
@@ -701,12 +708,12 @@ int gsi_dense_linear(const void* W, const void* X, int64_t m, int64_t d, int64_t
   GSI_REQUIRE_ALIGNED(W, gsi::elem_size(wdtype));
   GSI_REQUIRE_ALIGNED(X, gsi::elem_size(xdtype));
   GSI_REQUIRE_ALIGNED(Y, 4);
-  bool full;
-  if (int rc = check_call_ws("gsi_dense_linear", GSI_CALL_DENSE_LINEAR, m, d, 0, B, ws, ws_bytes, full)) return rc;
+  WsLevel level;
+  if (int rc = check_call_ws("gsi_dense_linear", GSI_CALL_DENSE_LINEAR, m, d, 0, B, ws, ws_bytes, level)) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (mfma_dense_path(W, X, m, d, B, wdtype, Y)) {
-    const gsi::GemmProb g = mfma_dense_prob(W, X, m, d, B, Y, (float*)ws, full);
+    const gsi::GemmProb g = mfma_dense_prob(W, X, xdtype, m, d, B, Y, (float*)ws, level);
     e = gsi::mfma_gemm_nt(&g, 1, xdtype == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s);
   } else if (gsi::decode_linear_ok(m, d, 0, wdtype, W, nullptr, B) && aligned(X, 16) &&
              long_batch_ok(d, B, Y, true, X)) {
@@ -732,14 +739,14 @@ static bool wx_vector_ok(const gsi_input_desc& in) {
 
 // Is the E4M3 image of this map read as codes?  Only by the single-token vector kernels; every other call
 // expands it (exactly) to the weights' type in the workspace first and runs the map with an ordinary image.
-static bool fp8_codes_read(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B, bool full) {
+static bool fp8_codes_read(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B, WsLevel level) {
   return B == 1 && aligned(mp.M, 16) && in.k % 16 == 0 && in.k <= gsi::kMaxK &&
-         project_vector_path(in.d, in.k, B, in.udtype, in.U, full) &&
+         project_vector_path(in.d, in.k, B, in.udtype, in.U, level) &&
          gsi::decode_linear_ok(mp.m, in.d, in.k, mp.wdtype, mp.W, nullptr, B) && aligned(in.C, 16) && aligned(in.R, 16) &&
          wx_vector_ok(in);
 }
-static size_t fp8_expand_bytes(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B, bool full) {
-  if (!(mp.flags & GSI_MAP_IMAGE_FP8) || B < 1 || mp.m < 1 || in.k < 1 || fp8_codes_read(mp, in, B, full)) return 0;
+static size_t fp8_expand_bytes(const gsi_map_desc& mp, const gsi_input_desc& in, int64_t B, WsLevel level) {
+  if (!(mp.flags & GSI_MAP_IMAGE_FP8) || B < 1 || mp.m < 1 || in.k < 1 || fp8_codes_read(mp, in, B, level)) return 0;
   return gsi::align_up((size_t)mp.m * in.k * gsi::elem_size(mp.wdtype), 256);
 }
 
@@ -752,30 +759,30 @@ static size_t stack_table_bytes(int32_t n_maps, int32_t n_inputs, int64_t B) {
 }
 
 static size_t stack_ws_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int32_t n_inputs,
-                             int64_t B, bool full) {
+                             int64_t B, WsLevel level) {
   if (!inputs || n_inputs < 0) return 0;
   // projections of independent inputs share a launch, so every input has its own region
   size_t need = stack_table_bytes(maps ? n_maps : 0, n_inputs, B);
   for (int i = 0; i < n_inputs; ++i)
-    need += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, full), 256);
+    need += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, level), 256);
   // and so do the maps of a decode batch (partial products of the weight term)
   if (maps)
     for (int j = 0; j < n_maps; ++j) {
       const int id = maps[j].input_id;
-      if (id >= 0 && id < n_inputs) need += map_part_bytes(maps[j].m, inputs[id].d, B, 0, full);
+      if (id >= 0 && id < n_inputs) need += map_part_bytes(maps[j].m, inputs[id].d, B, 0, level);
     }
   // E4M3 images that are not read as codes are expanded to the weights' type
   if (maps)
     for (int j = 0; j < n_maps; ++j) {
       const int id = maps[j].input_id;
-      if (id >= 0 && id < n_inputs) need += fp8_expand_bytes(maps[j], inputs[id], B, full);
+      if (id >= 0 && id < n_inputs) need += fp8_expand_bytes(maps[j], inputs[id], B, level);
     }
   return need;
 }
 
 size_t gsi_layer_stack_workspace_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs,
                                        int32_t n_inputs, int64_t B) {
-  return stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true);
+  return stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsFull);
 }
 
 // What gsi_stack_plan_build leaves in the caller's gsi_stack_plan: the launch shapes of a single-token call whose
@@ -820,8 +827,10 @@ int gsi_layer_stack_static(const gsi_map_desc* maps, int32_t n_maps, const gsi_i
   for (int j = 0; j < n_maps; ++j)
     if (maps[j].input_id < 0 || maps[j].input_id >= n_inputs)
       return fail(GSI_ERR_SHAPE, "%s: maps[%d].input_id = %d out of range", fn, j, maps[j].input_id);
-  const size_t need = B > 0 ? std::min(stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true),
-                                       stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, false)) : 0;
+  size_t need = 0;  // the least of the sizes that such a call is served with
+  if (B > 0)
+    need = std::min({stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsFull), stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsCoarse),
+                     stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsFirst)});
   if (need > have)
     return fail(GSI_ERR_WORKSPACE,
                 "%s: this call needs %zu bytes of scratch, the library's static array holds %zu; use gsi_layer_stack "
@@ -849,19 +858,19 @@ int gsi_layer_stack_timed(const gsi_map_desc* maps, int32_t n_maps, const gsi_in
 }
 
 static size_t dense_stack_ws_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int32_t n_inputs,
-                                   int64_t B, bool full) {
+                                   int64_t B, WsLevel level) {
   if (!maps || !inputs || n_maps < 0 || n_inputs < 0) return 0;
   size_t need = 0;  // partial products of the several-token matrix-core kernel, one region per map
   for (int j = 0; j < n_maps; ++j) {
     const int id = maps[j].input_id;
-    if (id >= 0 && id < n_inputs) need += map_part_bytes(maps[j].m, inputs[id].d, B, 1, full);
+    if (id >= 0 && id < n_inputs) need += map_part_bytes(maps[j].m, inputs[id].d, B, 1, level);
   }
   return need;
 }
 
 size_t gsi_dense_stack_workspace_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs,
                                        int32_t n_inputs, int64_t B) {
-  return dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true);
+  return dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsFull);
 }
 
 int gsi_dense_stack(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int32_t n_inputs,
@@ -886,15 +895,16 @@ int gsi_dense_stack(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_de
     }
   }
   if (B == 0) return GSI_OK;
-  const bool full = full_ws(ws, ws_bytes, dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true));
-  if (!full)
-    if (int rc = check_ws(fn, ws, ws_bytes, dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, false))) return rc;
+  WsLevel level;
+  if (int rc = check_ws_level(fn, ws, ws_bytes, [&](WsLevel l) { return dense_stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, l); },
+                              level))
+    return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   std::vector<float*> part(n_maps, nullptr);
   {
     size_t off = 0;
     for (int j = 0; j < n_maps; ++j) {
-      const size_t pb = map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 1, full);
+      const size_t pb = map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 1, level);
       if (pb) part[j] = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + off);
       off += pb;
     }
@@ -915,7 +925,7 @@ int gsi_dense_stack(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_de
         const gsi_map_desc& mp = maps[j];
         const gsi_input_desc& in = inputs[mp.input_id];
         if (in.xdtype != xdt || !mfma_dense_path(mp.W, in.X, mp.m, in.d, B, mp.wdtype, mp.Y)) continue;
-        pr.push_back(mfma_dense_prob(mp.W, in.X, mp.m, in.d, B, mp.Y, part[j], full));
+        pr.push_back(mfma_dense_prob(mp.W, in.X, in.xdtype, mp.m, in.d, B, mp.Y, part[j], level));
         done[j] = 1;
       }
       if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s); e != hipSuccess)
@@ -1004,9 +1014,9 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
       if (!aligned(mp.M_scale, 4)) return fail(GSI_ERR_ALIGN, "%s: maps[%d].M_scale is not aligned to 4 bytes", fn, j);
     }
   }
-  const bool full = full_ws(ws, ws_bytes, stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, true));
-  if (!full)  // (the smaller workspace: see project_ws_bytes)
-    if (int rc = check_ws(fn, ws, ws_bytes, stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, false))) return rc;
+  WsLevel level;
+  if (int rc = check_ws_level(fn, ws, ws_bytes, [&](WsLevel l) { return stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, l); }, level))
+    return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
 
   // Bookkeeping of the call lives in thread-local vectors that keep their capacity from call to call: after the
@@ -1028,10 +1038,10 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
     size_t off = stack_table_bytes(n_maps, n_inputs, B);
     for (int i = 0; i < n_inputs; ++i) {
       ws_off[i] = off;
-      off += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, full), 256);
+      off += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, level), 256);
     }
     for (int j = 0; j < n_maps; ++j) {
-      const size_t pb = map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 0, full);
+      const size_t pb = map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 0, level);
       if (pb) part[j] = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + off);
       off += pb;
     }
@@ -1044,11 +1054,11 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
   if (B > 0) {
     size_t off = stack_table_bytes(n_maps, n_inputs, B);
     for (int i = 0; i < n_inputs; ++i)
-      off += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, full), 256);
-    for (int j = 0; j < n_maps; ++j) off += map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 0, full);
+      off += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, level), 256);
+    for (int j = 0; j < n_maps; ++j) off += map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 0, level);
     for (int j = 0; j < n_maps; ++j) {
       const gsi_input_desc& in = inputs[maps[j].input_id];
-      const size_t bytes = fp8_expand_bytes(maps[j], in, B, full);
+      const size_t bytes = fp8_expand_bytes(maps[j], in, B, level);
       if (!bytes) continue;
       if (expanded.empty()) expanded.assign(maps, maps + n_maps);
       void* tmp = reinterpret_cast<char*>(ws) + off;
@@ -1076,10 +1086,10 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
   for (int i = 0; i < n_inputs; ++i) {
     const gsi_input_desc& in = inputs[i];
     std::memset(&ptask[i], 0, sizeof(gsi::ProjTask));
-    if (B == 0 || !project_vector_path(in.d, in.k, B, in.udtype, in.U, full)) continue;
+    if (B == 0 || !project_vector_path(in.d, in.k, B, in.udtype, in.U, level)) continue;
     mode[i] = kVecGate;
     fill_proj_task(ptask[i], in.U, in.X, in.d, in.k, B, in.udtype, in.xdtype, in.C, in.R, in.rnorm, in.xnorm,
-                   reinterpret_cast<char*>(ws) + ws_off[i], full);
+                   reinterpret_cast<char*>(ws) + ws_off[i], level);
     ptask[i].mask = in.mask; ptask[i].fired_idx = in.fired_idx; ptask[i].n_fired = in.n_fired;
     if (B != 1) continue;
     int readers = 0;
@@ -1453,7 +1463,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
                                 in.n_fired, reinterpret_cast<char*>(ws) + ws_off[i]});
       }
       if (!min.empty())
-        if (hipError_t e = mfma_project(min.data(), (int)min.size(), riders.data(), (int)riders.size(), B, true, eps, full, s);
+        if (hipError_t e = mfma_project(min.data(), (int)min.size(), riders.data(), (int)riders.size(), B, true, eps, level, s);
             e != hipSuccess)
           return hip_fail(e, fn);
     }
@@ -1611,7 +1621,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
         map_done[j] = 2;
       }
       if (!mm.empty())
-        if (hipError_t e = mfma_gated(mm.data(), (int)mm.size(), B, full, s); e != hipSuccess) return hip_fail(e, fn);
+        if (hipError_t e = mfma_gated(mm.data(), (int)mm.size(), B, level, s); e != hipSuccess) return hip_fail(e, fn);
     }
     for (int j : mready) {
       const gsi_map_desc& mp = maps[j];

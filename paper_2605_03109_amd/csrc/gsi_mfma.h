@@ -7,7 +7,7 @@ namespace gsi {
 // What becomes of A B^T.  EPI_RESIDUAL and EPI_STORE_F32 problems share launches (EPI_PROJECTED: a residual and the image
 // rows beside it), and so do EPI_SCATTER_ADD and EPI_SCATTER_STORE (EPI_SCATTER).
 enum { EPI_STORE_BF16 = 0, EPI_STORE_F32 = 1, EPI_RESIDUAL = 2, EPI_SCATTER_ADD = 3, EPI_SCATTER_STORE = 4,
-       EPI_PROJECTED = 5, EPI_SCATTER = 6 };
+       EPI_PROJECTED = 5, EPI_SCATTER = 6, EPI_COEFF = 7 };
 
 // One product D = A B^T of a launch: A[M,K] (bf16, or fp32 fed as bf16), B[N,K] bf16, both row-major.
 struct GemmProb {
@@ -35,11 +35,10 @@ struct GemmArgs {
 };
 static_assert(sizeof(GemmArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
-// How many ways the contraction of an M x N x K problem is split, and the workspace that takes.  full: the
-// caller's workspace has the size that the queries name; else only what they named while tiles had one size (a fixed
-// scratch memory that a call used to fit), and the product is split less.
-int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool full);
-size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, bool full);
+// How many ways the contraction of an M x N x K product is split, and the workspace that takes (whatever the form of its
+// operand).  epi: of the problem, or EPI_COEFF for the product of a projection.  two_term: A is fed as head + tail.
+int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool two_term, WsLevel level);
+size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, WsLevel level);
 
 // Products of one launch (n of any number; more than kMaxProbs take several launches).  a_f32: A is 0: bf16; 1: fp32, fed as
 // bf16 head + tail (two passes); 2: fp32, rounded once to bf16.  epi: EPI_STORE_BF16 (A bf16), EPI_STORE_F32 (bf16 or head +
@@ -54,7 +53,8 @@ struct TransposeTask {
   int blk_begin;  // filled at launch
 };
 hipError_t mfma_transpose_bf16(TransposeTask* tasks, int n, hipStream_t s);
-// column tiles of the residual GEMM = partial norms per token (full: see mfma_splits)
-int mfma_res_tiles(int64_t d, bool full);
+// columns per partial norm of the residual GEMM, and its partial norms per token
+inline int mfma_res_cols(WsLevel level) { return level > kWsFirst ? 64 : 128; }
+inline int mfma_res_tiles(int64_t d, WsLevel level) { return (int)ceil_div(d, mfma_res_cols(level)); }
 
 }  // namespace gsi

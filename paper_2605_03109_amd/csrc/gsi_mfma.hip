@@ -566,13 +566,22 @@ constexpr int kMaxSplits = 32;
 // rows) than there are units are cut into parts of 4096 columns, which makes the products of a block alike; those of so few
 // tiles (less than an eighth of the units) that even their parts are less than a quarter of the chip, and image builds,
 // which are alone in their launch, are cut further, down to 512 columns.  Measured, GEMM + sums of the partials: projections of a block, 2048 tokens:
-// parts of 4096 columns 85 + 7 us, 2048: 91 + 15, 1024: 108 + 25; its W r products 326 + 16, 326 + 54, 381 + 93; the
-// projections of the pair at 333 tokens 105 + 5, 59 + 5, 34 + 5; an image of 4096 x 4096 x 256: 57, 33 + 6, 22 + 7.
-int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool full) {
+// parts of 4096 columns 85 + 7 us, 2048: 91 + 15, 1024: 108 + 25; the projections of the pair at 333 tokens 105 + 5, 59 + 5,
+// 34 + 5; an image of 4096 x 4096 x 256: 57, 33 + 6, 22 + 7.
+// Products of up to half the units are cut again while their parts fit the chip at once, down to 1024 columns (512 for an
+// eighth of the units): a workgroup takes 0.75 us per 64 columns, 1.5 us with a two-term operand, however few there are.  In
+// eight at most; a two-term contraction of 8192 columns and more even beyond the chip.  Scatter products of more than one row
+// tile are cut so in two, or until half the chip has a part: others of their block share the launch.  The
+// coefficients of a projection are cut so only with a two-term operand.  Measured, us per call without / with this second cut
+// (calls replayed from a graph): 129 x 4096 x 4096 48 / 23, two-term 97 / 36; 512 rows 50 / 33, 101 / 47; 1024 rows 53 / 50,
+// 104 / 77; W r of 4096 x 4096 with 205 of 1024 rows fired 78 / 42; the projection of 2048 fp32 tokens, 4096 x 512
+// 141 / 77; the block of 2048 tokens 742 / 730 (its W r launch 295 + 15 / 268 + 31).  Slower with it: W r over rows that
+// all fire, where a quarter is expected (257 rows x 16384 x 4096 88 / 104).
+int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool two_term, WsLevel level) {
   if (epi == EPI_RESIDUAL) return 1;
   const int64_t m = rows_expected(M, epi), nk = ceil_div(K, BK);
   int s = 1;
-  if (!full) {
+  if (level == kWsFirst) {
     const int64_t tiles = ceil_div(std::max<int64_t>(m, 256), 256) * ceil_div(N, BN);
     while (s < 8 && tiles * s < kUnits && nk / (s * 2) >= 4) s *= 2;
     return s;
@@ -581,11 +590,17 @@ int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool full) {
   if (tiles < kUnits) s = (int)std::min<int64_t>(ceil_div(nk, kMaxDepth), kMaxSplits);
   const int64_t want = epi == EPI_STORE_BF16 ? kUnits : tiles < kUnits / 8 ? kUnits / 4 : 0;
   while (s * 2 <= kMaxSplits && tiles * s < want && nk / (s * 2) >= kMinDepth) s *= 2;
+  if (level == kWsCoarse || epi == EPI_STORE_BF16 || (epi == EPI_COEFF && !two_term)) return s;
+  const bool shares = (epi == EPI_SCATTER_ADD || epi == EPI_SCATTER_STORE) && m > 128;
+  const int64_t room = two_term && nk >= 2 * kMaxDepth ? 2 * kUnits : kUnits;
+  while (s < 8 && tiles * s * 2 <= (shares && s > 1 ? kUnits / 2 : room) &&
+         nk / (s * 2) >= (tiles * s > kUnits / 8 ? 2 * kMinDepth : kMinDepth))
+    s *= 2;
   return s;
 }
 
-size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, bool full) {
-  const int s = mfma_splits(M, N, K, epi, full);
+size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, WsLevel level) {
+  const int s = std::max(mfma_splits(M, N, K, epi, false, level), mfma_splits(M, N, K, epi, true, level));
   return s > 1 ? align_up((size_t)s * M * N * sizeof(float), 256) : 0;
 }
 
@@ -611,7 +626,7 @@ int plan_rows(const GemmArgs& g, int epi) {
     }
     cost[t] = std::max(total / kUnits, longest) + 0.5 * longest;
   }
-  return cost[1] <= cost[0] ? 128 : 256;
+  return cost[1] < cost[0] ? 128 : 256;
 }
 
 }  // namespace
@@ -645,7 +660,5 @@ hipError_t mfma_transpose_bf16(TransposeTask* tasks, int n, hipStream_t s) {
   }
   return hipSuccess;
 }
-
-int mfma_res_tiles(int64_t d, bool full) { return (int)ceil_div(d, full ? 64 : 128); }
 
 }  // namespace gsi
