@@ -663,7 +663,7 @@ bool tile_project_shape_ok(int64_t d, int64_t k, int64_t B, int udtype) {
 
 static int tile_slab_rows(int64_t) { return kPSteps * kStepCols; }
 
-// A residual launch of up to one and a half workgroups per compute unit asks for more than half of a unit's LDS, so that
+// A residual launch with images, of up to one and a half workgroups per compute unit, asks for more than half of a unit's LDS, so that
 // the residual workgroups, which come first, have a unit each and the images the next free one: MLP pair of 4096 and 16384
 // columns, rank 256 (320 workgroups), 4 tokens 69.4 us against 70.0, 16 tokens 70.6 against 71.5.  With more, two share
 // a unit: a block at rank 200, 8 tokens (512 workgroups) 41.9 us against 46.4; the pair with 128 tokens 116.8 against 124.8.
@@ -722,7 +722,7 @@ hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, f
     constexpr int T = decltype(terms)::value;
     constexpr size_t kScratch = kTBlock * sizeof(float2) + 16;  // norms_and_gate
     size_t smem = std::max((size_t)T * kRoundTok * vrow * sizeof(uint16_t), kScratch);
-    if (tb + imgs <= kFewItems) smem = std::max(smem, kWholeUnit);
+    if (imgs > 0 && tb + imgs <= kFewItems) smem = std::max(smem, kWholeUnit);
     static LdsLimit lds;  // more than the default 64 KB at the largest ranks
     err = lds.allow(reinterpret_cast<const void*>(&tile_residual<T>),
                     std::max(T * kRoundTok * kVRow * (int)sizeof(uint16_t), (int)kWholeUnit));
