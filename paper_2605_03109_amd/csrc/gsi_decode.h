@@ -193,6 +193,7 @@ hipError_t f32_rows_launch(LinBatch& lb, hipStream_t s);
 hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s, TileImgBatch& ib);
 bool tile_rows_shape_ok(int64_t m, int64_t d, int64_t k, int64_t B, int wdtype);
 bool tile_rows_ok(const LinBatch& lb, int wdtype);
+bool tile_rows_longer(const LinBatch& lb, int task);  // the FMA kernel is the shorter way for this map
 hipError_t tile_rows_launch(LinBatch& lb, hipStream_t s);
 
 // ---- single token: projection, residual, image rows and gate as stages of one kernel (gsi_stage.hip) -------

@@ -218,6 +218,8 @@ static bool f32_rows_ok(const LinBatch& lb, int wdtype) {
 bool decode_linear_fits(const LinBatch& lb, int wdtype) {
   if (f32_rows_ok(lb, wdtype)) return true;
   if (lb.B == 1) return stream_smem_bytes(lb) <= (size_t)kMaxLinD * sizeof(float);
+  for (int i = 1; i < lb.n; ++i)  // (a map takes the same kernel in whatever launch)
+    if (tile_rows_longer(lb, i) != tile_rows_longer(lb, 0)) return false;
   if (tile_rows_ok(lb, wdtype)) {  // one number of operand terms per launch
     for (int i = 1; i < lb.ng; ++i)
       if (tile_rows_terms(lb, i) != tile_rows_terms(lb, 0)) return false;

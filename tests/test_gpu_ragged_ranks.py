@@ -89,3 +89,20 @@ def test_infinite_and_nan_activations_stay_in_their_token(gsi, pu):
     u = dg.U[17].float()
     assert torch.equal(res["C"][3][u != 0], (torch.sign(u) * float("inf"))[u != 0])  # one infinite term: c is infinite
     assert torch.isnan(res["C"][11]).all() and torch.isinf(res["xnorm"][3]) and torch.isnan(res["xnorm"][11])
+
+
+@pytest.mark.parametrize("d,m", [(768, 3072), (2048, 8192), (2080, 512), (2048, 8196)])
+def test_dense_products_of_two_bf16_tokens(gsi, pu, d, m):
+    """Both sides of the rule that gives short rows to the FMA kernel; a stack of both kinds equals its separate products."""
+    g = torch.Generator(device="cuda").manual_seed(d + m)
+    X = torch.randn(2, d, generator=g, device="cuda").to(torch.bfloat16)
+    Ws = [(torch.randn(r, d, generator=g, device="cuda") / d**0.5).to(torch.bfloat16) for r in (m, 64, 8200)]
+    st = gsi.LayerStack([{"U": torch.zeros(d, 64, dtype=torch.bfloat16, device="cuda"), "X": X}],
+                        [{"W": W, "M": torch.zeros(W.shape[0], 64, dtype=torch.bfloat16, device="cuda"), "input_id": 0} for W in Ws],
+                        2, 0.1)
+    st.run_dense()
+    torch.cuda.synchronize()
+    for W, t in zip(Ws, st.maps_t):
+        ref = X.double() @ W.double().T
+        assert pu.rel_l2_rows(t["Y"].cpu().double().numpy(), ref.cpu().numpy()).max() <= 1e-6
+        assert torch.equal(t["Y"], gsi.dense_linear(W, X))
