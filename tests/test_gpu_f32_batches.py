@@ -54,20 +54,23 @@ def test_f32_batches(gsi, pu, d, k, m, T, nf, xdtype):
 
 
 def test_f32_batch_with_the_smaller_workspace(gsi, pu):
-    """A call that brings less than the query names, but what calls of its shape once asked for, takes the FMA kernels."""
-    d, k, m, T = 768, 64, 300, 16
+    """A call that brings less than the query names, but what calls of its shape once asked for, takes the FMA kernels;
+    one step less was refused and is."""
+    d, k, m, T, full, former = 768, 64, 300, 16, 26368, 26112
     w = wl.tiny(d, k, m, T, 4, seed=52000, wdtype="f32")
     dg, og = pu.DeviceGroup(w, w.groups[0]), pu.OracleGroup(w, w.groups[0])
-    need = gsi.workspace_bytes(gsi.CALL_PROJECT, 0, d, k, T)
-    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    assert gsi.workspace_bytes(gsi.CALL_PROJECT, 0, d, k, T) == full
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
     out = [torch.empty(s, device="cuda") for s in ((T, k), (T, d), (T,), (T,))]
     s = torch.cuda.current_stream().cuda_stream
-    rc = gsi.lib.gsi_project(dg.U.data_ptr(), dg.X.data_ptr(), d, k, T, 0, 0, *[o.data_ptr() for o in out], ws.data_ptr(),
-                             need - 256, s)
+
+    def call(nbytes):
+        return gsi.lib.gsi_project(dg.U.data_ptr(), dg.X.data_ptr(), d, k, T, 0, 0, *[o.data_ptr() for o in out],
+                                   ws.data_ptr(), nbytes, s)
+
+    assert call(former - 256) == gsi.GSI_ERR_WORKSPACE
+    assert call(former) == gsi.GSI_OK, gsi.last_error()
     torch.cuda.synchronize()
     ref = og.run()
-    if rc == gsi.GSI_OK:
-        assert pu.rel_l2_rows(out[0].cpu().double().numpy(), ref["C"]).max() <= 1e-5
-        assert np.abs(out[2].cpu().double().numpy() - ref["rnorm"]).max() <= 1e-5 * ref["xnorm"].max()
-    else:  # (the two sizes may coincide for a shape)
-        assert rc == gsi.GSI_ERR_WORKSPACE
+    assert pu.rel_l2_rows(out[0].cpu().double().numpy(), ref["C"]).max() <= 1e-5
+    assert np.abs(out[2].cpu().double().numpy() - ref["rnorm"]).max() <= 1e-5 * ref["xnorm"].max()
