@@ -33,7 +33,11 @@
  *     rank, which changes no result); inputs of up to 65536 elements, a multiple
  *     of 8 (bf16) / 4 (fp32), for one token per call; for 2 .. 128 tokens per call bf16 storage and
  *     d a multiple of 128 (else the vector kernels up to d = 16384, d a
- *     multiple of 32 for the maps); more than 128 tokens: bf16 storage, d and k multiples of 64.
+ *     multiple of 32 for the maps), or fp32 storage, d a multiple of 4; more than 128 tokens: bf16 storage, d and k
+ *     multiples of 64.
+ *   - A workspace of less than gsi_workspace_bytes(), but of a size that it named in an earlier version, is accepted and
+ *     served by the kernels (or the coarser split of a product) of that version.  NULL, or memory that is not aligned to
+ *     256 bytes, counts as none where a call needs none.
  */
 #ifndef GSI_H
 #define GSI_H
@@ -108,7 +112,7 @@ int gsi_gate(const float* rnorm, const float* xnorm, int64_t B, float eps, uint8
  * in `wdtype`; C, R fp32; fired_idx / n_fired are the device outputs of gsi_gate; Y[B,m] fp32
  * (`ydtype` must be GSI_F32).  ws: GSI_CALL_GATED_LINEAR (partial products of the several-token kernels).
  * Arithmetic by call size (bf16 weights): one token -- fp32 FMA on widened weights; 2..128 tokens -- MFMA
- * with c and r fed as bf16 head + tail (nothing rounded to 8 bits); more than 128 tokens -- MFMA GEMM with
+ * with c and r fed as sums of two or three bf16 terms (nothing rounded to 8 bits); more than 128 tokens -- MFMA GEMM with
  * c as head + tail and r rounded once to bf16 (its term is scaled by the residual ratio). */
 int gsi_gated_linear(const void* W, const void* M, const float* C, const float* R, const int32_t* fired_idx,
                      const int32_t* n_fired, int64_t m, int64_t d, int64_t k, int64_t B, int wdtype, void* Y,

@@ -22,11 +22,11 @@
 // extension moves U three times and every W once; operands whose rows are 16-byte aligned are read with 16-byte loads,
 // several in flight per lane.  Large bases have s added up by a launch of its own (own_sums).  (s, the column and U^T u in
 // launches of their own for every basis: seven launches of 4 to 5 us around one of 24 us; three maps 4096 x 4096 on a
-// basis of 4096 x 512: 46.4 us, 39.5 us with these four, calls replayed from a graph.)
+// basis of 4096 x 384, 256 columns in use: 46.7 us, 35.6 us with these four, calls replayed from a graph.)
 //
 // Every launch covers ALL bases of a call (one grid dimension is the basis, or the map): a token's pass over the
-// bases of a whole model is these four launches, not four per basis, and what it costs when no basis grows is
-// four nearly empty launches.  The records of a call with several bases sit in a table in the workspace (copied
+// bases of a whole model is these launches, not as many per basis, and what it costs when no basis grows is
+// four or five nearly empty ones.  The records of a call with several bases sit in a table in the workspace (copied
 // there by the call); a call with one basis carries its record in the kernel arguments.
 #include <hip/hip_runtime.h>
 

@@ -25,7 +25,7 @@
 // A launch takes the products of all inputs, or of all maps, of a call (GemmProb): one product of a block is 64 to 512
 // tiles, one or two rounds of the 256 compute units with a ramp and a tail of its own.  The row tile is chosen
 // for the whole launch (plan_rows).  A block's prefill, 2048 tokens at rank 512: 36 launches 1007 us, 7 launches
-// 747 us; the pair 4096 / 16384, 333 tokens at rank 256: 14 launches 438 us, 7 launches 173 us.
+// 730 us; the pair 4096 / 16384, 333 tokens at rank 256: 14 launches 438 us, 7 launches 162 us.
 // Problems with few output tiles split the contraction; the partial sums go to the workspace
 // and a second kernel adds them in split order and applies the epilogue.
 // The residual and image products are short (the rank) with long epilogues (every output row of a block: 0.5 GB), so they
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
         if (row[q] < Mrows && col < N)  // N is a multiple of 4 here (checked on the host)
           *reinterpret_cast<float4*>(pdst + (int64_t)row[q] * N + col) = val[q];
     } else if (EPI == EPI_PROJECTED && g.epi == EPI_RESIDUAL) {
-      // r = x - acc; R written; per row the sums of r^2 and x^2 over this wave's 128 columns
+      // r = x - acc; R written; per row the sums of r^2 and x^2 over this wave's columns (128; 64 with tiles of 128 rows)
       float4 x[kReads];
 #pragma unroll
       for (int q = 0; q < kReads; ++q) {
@@ -609,7 +609,8 @@ namespace {
 // Row tile of a launch: the one with the least estimated time.  A workgroup takes its k-tiles and the time of about six
 // more for its first loads and its epilogue; a tile of 128 rows takes 0.6 of the time of one of 256 (the same right-hand
 // tile, half the products); the launch lasts as long as the work spread over the units, or its longest workgroup, and about
-// half of that workgroup again for the tail.
+// half of that workgroup again for the tail.  (Work is spread evenly here; tiles of 256 rows hold a unit each and run in
+// whole rounds, so between one round and a few the estimate is low for them.)
 int plan_rows(const GemmArgs& g, int epi) {
   // (the norm shares of a residual are per 64 columns with tiles of 128 rows, per 128 with 256)
   if (epi == EPI_PROJECTED) return g.p[0].res_cols == 64 ? 128 : 256;

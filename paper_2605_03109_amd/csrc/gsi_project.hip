@@ -339,7 +339,7 @@ __global__ __launch_bounds__(kBlock) void proj_norms(const ProjBatch pb, int do_
 // sixteenth of the slab shares each (one memory round trip up to 128 slabs; neighbouring threads read neighbouring tokens),
 // the sixteen sums are added in order.  The workgroup of an input that finishes last (a counter that the launch before
 // cleared; norms are written through and read coherently) decides all its tokens and writes the ordered list of the fired
-// ones.  Four inputs of 2048 tokens: 7 us, against 47 us for a launch of norms (a thread per token) and one of the gate per
+// ones.  Four inputs of 2048 tokens: 10 us, against 47 us for a launch of norms (a thread per token) and one of the gate per
 // input; a batch of 333 tokens had one workgroup per input, with a token per wave and strided loads: 68 us each.
 constexpr int kNormTok = 64, kNormParts = 16, kNormBlock = kNormTok * kNormParts;
 __global__ __launch_bounds__(kNormBlock) void norms_tokens(const ProjBatch pb, int do_gate, float eps) {

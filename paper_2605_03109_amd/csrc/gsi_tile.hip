@@ -14,11 +14,13 @@
 // Items of one matrix that cover different column slices write partial sums to the workspace, and a
 // second kernel adds them in slice order, so results do not vary from run to run.
 //
-// Terms of an fp32 operand: two (relative remainder 2^-17) for ranks of 64 * 2^j columns and fp32 activations.  Other
-// ranks (any multiple of 8 up to 512) and bf16 activations take three (2^-25, the fp32 value itself): these calls ran
-// on fp32 FMAs before, and with two terms the residual, whose parts cancel to a few percent, was 2e-5 .. 5e-5 off
-// instead of 3e-6 .. 2e-5.  The kernels are bound by memory and latency, the third MFMA costs nothing that shows.
-// Measured: a block of d = 2560, rank 128, 23 bf16 tokens 174 us on the FMA kernels, 66 us on these.
+// Terms of an fp32 operand: two (relative remainder 2^-17) or three (2^-25, the fp32 value itself).  The projection and the
+// residual take two for ranks of 64 * 2^j columns and fp32 activations, else three; image and weight rows take three only at
+// ranks that are no multiple of 32 columns, or where the weight rows read bf16 activations.  What takes three ran on fp32
+// FMAs before, and with two the residual, whose parts cancel to a few percent, was 2e-5 .. 5e-5 off instead of 3e-6 .. 2e-5.
+// Three terms cost weight rows half of their places: 97.5 KB of LDS and 164 registers, one workgroup per unit, against 65 KB
+// and 126, two per unit.
+// Measured: a block of d = 2560, rank 128, 23 bf16 tokens 174 us on the FMA kernels, 64 us on these.
 #include <algorithm>
 #include <type_traits>
 
@@ -522,8 +524,9 @@ __global__ __launch_bounds__(256) void tile_proj_reduce(const ProjBatch pb) {
 // Image terms y = M c of a call's maps ride behind the residual workgroups (ib): both need c alone.  By itself the
 // residual is short of work and bound by latency (160 workgroups of 128 rows for an MLP pair), and in front of the W
 // items, where gated_linear alone still has them, the image items take the places of workgroups that stream weights.
-// The pair of 4096 and 16384 columns, rank 256, 64 tokens: this launch 17.8 -> 20.6 us, the W items 62.6 -> 53 us; the call
-// 97.5 -> 93.6 us (20 tokens: 75.5 -> 73.7, 128: 125.3 -> 116.8; a block at rank 200, 24 tokens: 54.1 -> 47.2).
+// The pair of 4096 and 16384 columns, rank 256, 64 tokens: this launch 17.8 -> 20.6 us, the W items 62.6 -> 53 us; calls one
+// after the other, us each: 97.5 -> 93.6 (20 tokens: 75.5 -> 73.7, 128: 125.3 -> 116.8; a block at rank 200, 24 tokens:
+// 54.1 -> 47.2).  With other work between the calls they take 3 to 5 us more.
 // LDS holds the operand of the launch's largest rank only (vrow), so that the short items of small ranks share a unit.
 template <int TI>
 __device__ __forceinline__ void image_item(const TileImg& p, int item, int B, uint16_t* vt, int vrow, int wave,
@@ -665,7 +668,8 @@ static int tile_slab_rows(int64_t) { return kPSteps * kStepCols; }
 
 // A residual launch with images, of up to one and a half workgroups per compute unit, asks for more than half of a unit's LDS, so that
 // the residual workgroups, which come first, have a unit each and the images the next free one: MLP pair of 4096 and 16384
-// columns, rank 256 (320 workgroups), 4 tokens 69.4 us against 70.0, 16 tokens 70.6 against 71.5.  With more, two share
+// columns, rank 256 (320 workgroups), calls one after the other, 4 tokens 69.4 us each against 70.0, 16 tokens
+// 70.6 against 71.5.  With more, two share
 // a unit: a block at rank 200, 8 tokens (512 workgroups) 41.9 us against 46.4; the pair with 128 tokens 116.8 against 124.8.
 constexpr int kFewItems = 384;
 constexpr size_t kWholeUnit = 84 * 1024;
