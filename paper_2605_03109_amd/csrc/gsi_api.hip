@@ -164,7 +164,7 @@ static gsi::GemmProb gemm_prob(const void* A, int64_t lda, const void* B, int64_
   g.A = A; g.B = B; g.D = D;
   g.lda = (int)lda; g.ldb = (int)ldb; g.ldd = (int)ldd;
   g.M = (int)M; g.N = (int)N; g.K = (int)K;
-  g.epi = epi; g.max_splits = 1;
+  g.epi = epi; g.max_splits = 1; g.row_tiles = 0;
   return g;
 }
 
@@ -506,7 +506,8 @@ static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, WsLevel level,
       gsi::GemmProb g = gemm_prob(q.Xwx ? q.Xwx : q.R, q.d, q.W, q.d, q.Y, q.m, B, q.m, q.d, epi);
       g.row_idx = q.fired_idx; g.n_rows_dev = q.n_fired;
       g.max_splits = gsi::mfma_splits(B, q.m, q.d, epi, mode == 1, level);
-      g.part = g.max_splits > 1 ? q.part : nullptr;
+      g.row_tiles = gsi::mfma_follow(B, q.d, epi, g.max_splits, level);
+      g.part = g.max_splits > 1 || g.row_tiles ? q.part : nullptr;
       pr.push_back(g);
     }
     if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), mode, gsi::EPI_SCATTER, s); e != hipSuccess) return e;

@@ -19,14 +19,15 @@ struct GemmProb {
   unsigned* sync;             // ... and a counter that the launch clears for the norm kernel behind it (may be null)
   const int32_t* row_idx;     // optional: row i of A is A[row_idx[i]], and (scatter) row i of D is D[row_idx[i]]
   const int32_t* n_rows_dev;  // optional: device count of valid rows (<= M)
-  float* part;                // split contraction: workspace [splits][M][N] of partial sums, or null (then no split)
+  float* part;                // split contraction: workspace [splits][rows][N] of partial sums, or null (then no split)
   int lda, ldb, ldd;
   int M, N, K;                // K a multiple of 64; M * N below 2^31
   int epi;
   int xdtype;
   int max_splits;             // in: splits of the contraction that `part` has room for (mfma_splits), 1 without it
+  int row_tiles;              // in: tiles of 128 rows that max_splits is meant for, where it follows the count (mfma_follow), or 0
   int res_cols;               // EPI_PROJECTED: columns per partial norm, 64 or 128 (the same in every problem)
-  int splits, col_tiles, blk_begin;  // filled at launch
+  int splits, col_tiles, blk_begin, min_parts;  // filled at launch
 };
 constexpr int kMaxProbs = 24;
 struct GemmArgs {
@@ -38,6 +39,9 @@ static_assert(sizeof(GemmArgs) <= 4096, "kernel arguments are limited to 4 KB");
 // How many ways the contraction of an M x N x K product is split, and the workspace that takes (whatever the form of its
 // operand).  epi: of the problem, or EPI_COEFF for the product of a projection.  two_term: A is fed as head + tail.
 int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool two_term, WsLevel level);
+// ... and whether the split of a product over a device-side count of rows follows that count: the tiles of 128 rows that
+// mfma_splits (splits) expects, or 0.
+int mfma_follow(int64_t M, int64_t K, int epi, int splits, WsLevel level);
 size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, WsLevel level);
 
 // Products of one launch (n of any number; more than kMaxProbs take several launches).  a_f32: A is 0: bf16; 1: fp32, fed as

@@ -184,6 +184,26 @@ __device__ __forceinline__ void mma(const Ops<AM, TM>& o, f32x16 (&acc)[kAF][Geo
   }
 }
 
+// Parts of the contraction of a product over `rows` rows (a device-side count).  It is sized for row_tiles tiles of 128
+// rows.  With fewer, the same number of workgroups: each tile is cut into more parts (the workgroups of the row tiles that
+// are not there take them).  With more, fewer parts, down to min_parts, as long as they fill the chip: what is cut for
+// nothing writes partial sums for nothing.  Tiles of 128 rows whatever the launch's tile: the order of a sum is the product's
+// and the count's own.  W r beside the image term, us a call, parts fixed / following the count: 16384 x 4096, 102 of 2048
+// rows 137 / 102, all of 512 rows 167 / 106; 4096 x 16384, 51 of 1024 rows 75 / 52; a block, 2048 tokens that all fire
+// 1480 / 1414, 102 fired 644 / 632.  A product whose expected rows take one part has the launch of the sums all the same:
+// 16384 x 4096, 410 of 2048 rows 139 / 143.
+constexpr int kUnits = 256;      // compute units: one workgroup each
+constexpr int kMaxDepth = 64;    // k-tiles of 64 columns per workgroup, where a product has fewer tiles than the chip units
+constexpr int kFewParts = 8;
+constexpr int kMinDepth = 8;     // k-tiles that a split keeps at least
+__device__ __forceinline__ int parts_for(const GemmProb& g, int rows) {
+  if (!g.row_tiles) return g.splits;
+  const int tiles = (rows + 127) / 128, want = g.splits * g.row_tiles;
+  if (tiles <= g.row_tiles) return min(max(g.splits, min(kFewParts, g.K / (BK * kMinDepth))), want / tiles);
+  const int fit = max(want, (g.row_tiles > 1 ? kUnits / 2 : kUnits) / g.col_tiles) / tiles;
+  return min(g.splits, max(g.min_parts, fit));
+}
+
 template <int AM, int EPI, int TM>
 __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm_nt(const GemmArgs args) {
   using G = Geo<AM, TM>;
@@ -197,8 +217,6 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
     if ((int)blockIdx.x >= args.p[q].blk_begin) pi = q;
   const GemmProb& g = args.p[pi];
   const int local = blockIdx.x - g.blk_begin;
-  const int row_tiles = (g.M + TM - 1) / TM;
-  const int tile_n = local % g.col_tiles, tile_m = (local / g.col_tiles) % row_tiles, split = local / (g.col_tiles * row_tiles);
   if constexpr (EPI == EPI_PROJECTED) {
     if (local == 0 && threadIdx.x == 0 && g.sync) *g.sync = 0u;
   }
@@ -207,7 +225,11 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
     const int nd = g.n_rows_dev[0];
     Mrows = nd < Mrows ? nd : Mrows;
   }
-  if (tile_m * TM >= Mrows) return;  // uniform
+  if (Mrows <= 0) return;  // uniform, as the next one
+  const int splits = EPI == EPI_SCATTER ? parts_for(g, Mrows) : g.splits;
+  const int row_tiles = ((EPI == EPI_SCATTER && g.row_tiles ? Mrows : g.M) + TM - 1) / TM;
+  const int tile_n = local % g.col_tiles, tile_m = (local / g.col_tiles) % row_tiles, split = local / (g.col_tiles * row_tiles);
+  if (tile_m * TM >= Mrows || split >= splits) return;
   const int N = g.N;
   void* const Dmat = g.D;
   const int64_t lda = g.lda, ldb = g.ldb, ldd = g.ldd;
@@ -219,7 +241,6 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
 
   // k-tiles of this split
   const int nk = g.K / G::BKT;  // K is a multiple of 64
-  const int splits = g.splits;
   const int kt0 = (int)(((int64_t)nk * split) / splits), kt1 = (int)(((int64_t)nk * (split + 1)) / splits);
 
   // staging pointers: a thread's unit u is tile row tid / CPR + RPP u, 8 columns at 8 (tid % CPR); rows past the
@@ -327,7 +348,7 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
   constexpr int kSR = 8, kSLD = WTN + 4;  // strip rows, padded strip stride (floats)
   float* strip = reinterpret_cast<float*>(lds) + wave * (kSR * kSLD);
   const bool partial = splits > 1;
-  float* const pdst = partial ? g.part + (int64_t)split * g.M * N : nullptr;
+  float* const pdst = partial ? g.part + (int64_t)split * Mrows * N : nullptr;
   // a lane reads four columns of one row, the wave kRL rows at a time
   constexpr int kLR = WTN / 4, kRL = kWave / kLR, kReads = kSR / kRL;  // lanes per strip row, rows per read, reads per strip
   const int er = lane / kLR, ec = 4 * (lane % kLR);
@@ -427,25 +448,28 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
 template <int EPI>
 __global__ __launch_bounds__(256) void splitk_finish(const GemmArgs args) {
   const GemmProb& g = args.p[blockIdx.y];
-  if (g.splits <= 1) return;
+  if (g.splits <= 1 && !g.row_tiles) return;
   int Mrows = g.M;
   if (g.n_rows_dev) {
     const int nd = g.n_rows_dev[0];
     Mrows = nd < Mrows ? nd : Mrows;
   }
+  if (Mrows <= 0) return;
+  const int splits = EPI == EPI_SCATTER ? parts_for(g, Mrows) : g.splits;
+  if (splits <= 1) return;
   const int n4 = g.N >> 2;
-  const int64_t total = (int64_t)Mrows * n4, stride = (int64_t)g.M * g.N;
+  const int64_t total = (int64_t)Mrows * n4, stride = (int64_t)Mrows * g.N;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     const int row = (int)(e / n4), col = 4 * (int)(e - (int64_t)row * n4);
     const float* src = g.part + (int64_t)row * g.N + col;
     float4 s = float4{0.f, 0.f, 0.f, 0.f};
-    for (int z0 = 0; z0 < g.splits; z0 += 8) {
+    for (int z0 = 0; z0 < splits; z0 += 8) {
       float4 q[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) q[u] = *reinterpret_cast<const float4*>(src + (int64_t)min(z0 + u, g.splits - 1) * stride);
+      for (int u = 0; u < 8; ++u) q[u] = *reinterpret_cast<const float4*>(src + (int64_t)min(z0 + u, splits - 1) * stride);
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (z0 + u < g.splits) { s.x += q[u].x; s.y += q[u].y; s.z += q[u].z; s.w += q[u].w; }
+        if (z0 + u < splits) { s.x += q[u].x; s.y += q[u].y; s.z += q[u].z; s.w += q[u].w; }
     }
     if constexpr (EPI == EPI_STORE_BF16) {
       uint2 o;
@@ -514,9 +538,9 @@ hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
     p.col_tiles = (int)ceil_div(p.N, BN);
     p.blk_begin = (int)blocks;
     blocks += (int64_t)p.col_tiles * ceil_div(p.M, tm) * p.splits;
-    if (p.splits > 1) {
+    if (p.splits > 1 || p.row_tiles) {
       split = true;
-      most = std::max(most, (int64_t)p.M * (p.N / 4));
+      most = std::max(most, (int64_t)(p.row_tiles && p.splits == 1 ? std::min(p.M, 128 * p.row_tiles) : p.M) * (p.N / 4));
     }
   }
   if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
@@ -554,15 +578,13 @@ hipError_t launch_epi(GemmArgs& g, int a_f32, int epi, int tm, hipStream_t s) {
 int64_t rows_expected(int64_t M, int epi) {
   return (epi == EPI_SCATTER_ADD || epi == EPI_SCATTER_STORE) ? std::max<int64_t>(std::min<int64_t>(M, 128), M / 4) : M;
 }
-constexpr int kUnits = 256;      // compute units: one workgroup each
-constexpr int kMaxDepth = 64;    // k-tiles of 64 columns per workgroup, where a product has fewer tiles than the chip units
-constexpr int kMinDepth = 8;     // k-tiles that a split keeps at least
 constexpr int kMaxSplits = 32;
 
 }  // namespace
 
 // The split is a property of the product alone, so that a product gives the same bits in whatever launch it runs (the
-// row tile, which plan_rows chooses for a launch, does not change the order of a sum).  Products of fewer tiles (of 128
+// row tile, which plan_rows chooses for a launch, does not change the order of a sum), and over a device-side count of rows
+// of that count (parts_for).  Products of fewer tiles (of 128
 // rows) than there are units are cut into parts of 4096 columns, which makes the products of a block alike; those of so few
 // tiles (less than an eighth of the units) that even their parts are less than a quarter of the chip, and image builds,
 // which are alone in their launch, are cut further, down to 512 columns.  Measured, GEMM + sums of the partials: projections of a block, 2048 tokens:
@@ -575,8 +597,7 @@ constexpr int kMaxSplits = 32;
 // coefficients of a projection are cut so only with a two-term operand.  Measured, us per call without / with this second cut
 // (calls replayed from a graph): 129 x 4096 x 4096 48 / 23, two-term 97 / 36; 512 rows 50 / 33, 101 / 47; 1024 rows 53 / 50,
 // 104 / 77; W r of 4096 x 4096 with 205 of 1024 rows fired 78 / 42; the projection of 2048 fp32 tokens, 4096 x 512
-// 141 / 77; the block of 2048 tokens 742 / 730 (its W r launch 295 + 15 / 268 + 31).  Slower with it: W r over rows that
-// all fire, where a quarter is expected (257 rows x 16384 x 4096 88 / 104).
+// 141 / 77; the block of 2048 tokens 742 / 730 (its W r launch 295 + 15 / 268 + 31).
 int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool two_term, WsLevel level) {
   if (epi == EPI_RESIDUAL) return 1;
   const int64_t m = rows_expected(M, epi), nk = ceil_div(K, BK);
@@ -601,7 +622,15 @@ int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool two_term, WsLevel
 
 size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, WsLevel level) {
   const int s = std::max(mfma_splits(M, N, K, epi, false, level), mfma_splits(M, N, K, epi, true, level));
-  return s > 1 ? align_up((size_t)s * M * N * sizeof(float), 256) : 0;
+  const int64_t rows = s > 1 ? s * M : 128 * mfma_follow(M, K, epi, 1, level);
+  return align_up((size_t)rows * N * sizeof(float), 256);
+}
+
+// Nothing to follow: one tile in one part, or a contraction too short to cut.
+int mfma_follow(int64_t M, int64_t K, int epi, int splits, WsLevel level) {
+  if (level != kWsFull || (epi != EPI_SCATTER_ADD && epi != EPI_SCATTER_STORE) || K < 2 * kMinDepth * BK) return 0;
+  const int t = (int)ceil_div(rows_expected(M, epi), 128);
+  return t * splits > 1 ? t : 0;
 }
 
 namespace {
@@ -640,7 +669,11 @@ hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStr
     for (; i < n && g.n < kMaxProbs; ++i)
       if (probs[i].M > 0 && probs[i].N > 0) g.p[g.n++] = probs[i];
     if (g.n == 0) break;
-    for (int q = 0; q < g.n; ++q) g.p[q].splits = g.p[q].part ? g.p[q].max_splits : 1;
+    for (int q = 0; q < g.n; ++q) {
+      g.p[q].splits = g.p[q].part ? g.p[q].max_splits : 1;
+      if (!g.p[q].part) g.p[q].row_tiles = 0;
+      g.p[q].min_parts = std::min(g.p[q].splits, (int)ceil_div(g.p[q].K, BK * kMaxDepth));
+    }
     const int tm = plan_rows(g, epi);
     if (hipError_t e = launch_epi(g, a_f32, epi, tm, s); e != hipSuccess) return e;
   }

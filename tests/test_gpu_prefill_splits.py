@@ -58,3 +58,42 @@ def test_former_workspaces(d, m, B, sizes):
         rc, Y = _dense(gsi, W, X, nbytes)
         assert rc == gsi.GSI_OK, (nbytes, gsi.last_error())
         assert (Y.double() - want).abs().max() <= bar
+
+
+# counts below, at and above the rows that a product is sized for, one row tile and several: the parts of the contraction
+# follow the count, and their sums stay inside the workspace that the query names (33 to 512 rows are sized as one tile of
+# 128, 2048 as four; 640 as two)
+@pytest.mark.parametrize("d,k,m,B", [(1024, 64, 260, 129), (4096, 64, 1000, 257), (2560, 128, 5000, 300), (4096, 64, 8192, 640),
+                                     (4096, 64, 10240, 2048), (8192, 64, 260, 1000)])
+def test_fired_counts(d, k, m, B):
+    from paper_2605_03109_amd import gsi
+
+    g = torch.Generator(device="cuda").manual_seed(d + m + B)
+    R, C = torch.randn(B, d, generator=g, device="cuda"), torch.randn(B, k, generator=g, device="cuda")
+    W = (torch.randn(m, d, generator=g, device="cuda") / d**0.5).to(torch.bfloat16)
+    M = (torch.randn(m, k, generator=g, device="cuda") / k**0.5).to(torch.bfloat16)
+    need = gsi.workspace_bytes(gsi.CALL_GATED_LINEAR, m, d, k, B)
+    guard = 4 * need + (64 << 20)  # what parts of a row tile more than there is would reach
+    ws = torch.full((need + guard,), 0x5A, dtype=torch.uint8, device="cuda")
+    base, wr = C.double() @ M.double().T, R.to(torch.bfloat16).double() @ W.double().T
+    # 32-bit sums of d exact products, and of k products of operands of 16 mantissa bits: 2^-16 of the norms that bound them
+    bar = 2.0**-16 * (C.double().norm(dim=1).max() * M.double().norm(dim=1).max() + R.double().norm(dim=1).max() * W.double().norm(dim=1).max())
+    for n in sorted({0, 1, 127, 128, 129, B // 4, B // 2, B - 1, B}):
+        print(f"case fired count d={d} m={m} B={B} fired={n}", flush=True)
+        fired = torch.randperm(B, generator=g, device="cuda")[:n].sort().values
+        idx = torch.zeros(B, dtype=torch.int32, device="cuda")
+        idx[:n] = fired.int()
+        want = base.clone()
+        want[fired] += wr[fired]
+        count = torch.tensor([n], dtype=torch.int32, device="cuda")
+        ys = []
+        for _ in range(2):
+            Y = torch.full((B, m), float("nan"), device="cuda")
+            rc = gsi.lib.gsi_gated_linear(W.data_ptr(), M.data_ptr(), C.data_ptr(), R.data_ptr(), idx.data_ptr(), count.data_ptr(),
+                                          m, d, k, B, gsi.GSI_BF16, Y.data_ptr(), gsi.GSI_F32, ws.data_ptr(), need,
+                                          torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            assert rc == gsi.GSI_OK, gsi.last_error()
+            ys.append(Y)
+        assert torch.equal(ys[0], ys[1]) and (ys[0].double() - want).abs().max() <= bar
+        assert bool((ws[need:] == 0x5A).all())
