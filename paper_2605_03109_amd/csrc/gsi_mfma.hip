@@ -656,7 +656,7 @@ int plan_rows(const GemmArgs& g, int epi) {
     }
     cost[t] = std::max(total / kUnits, longest) + 0.5 * longest;
   }
-  return cost[1] < cost[0] ? 128 : 256;
+  return cost[1] < 0.999 * cost[0] ? 128 : 256;  // (a tie up to rounding: 256; dense fp32, 2048 x 4096 x 16384: 514 / 496 us)
 }
 
 }  // namespace
