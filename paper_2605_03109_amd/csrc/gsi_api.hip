@@ -1396,8 +1396,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
           for (int q = 0; q < set_size(g); ++q) total += ptask[member(g, q)].s_slabs;
           for (int q = 0; q < set_size(g); ++q) {
             const int i = member(g, q);
-            int ncb = 1;
-            while (total * ncb < 384 && inputs[i].k / (ncb * 2) >= 64 && (inputs[i].k / (ncb * 2)) % 64 == 0) ncb *= 2;
+            const int ncb = gsi::stage_col_blocks(total, inputs[i].k, dt);
             part_ncb[i] = ncb;
             gsi::stage_add_part(a, ptask[i], sp ? inputs[i].gram : nullptr, ncb);
           }

@@ -431,7 +431,7 @@ bool decode_project_ok(int64_t d, int64_t k, int udtype, const void* U) {
   if (k % V) return false;
   // Pieces per row: one wave at most.  A rank whose pieces are no power of two leaves some lanes idle (k = 200: 7 of
   // 32), which costs far less than the generic kernels' serial sums: a block of d = 4096, k = 200, one token 6.71 ms on
-  // those, 19.8 us here (k = 256: 17.6 us).
+  // those, 17.0 us here (k = 256: 17.6 us).
   if (k / V > kWave) return false;
   if (k > kMaxK || d > (int64_t)kPartSlabs * kStageMaxRows) return false;  // 32 slabs of 2048 rows at most
   return (reinterpret_cast<uintptr_t>(U) % 16) == 0;
@@ -543,7 +543,9 @@ hipError_t decode_project_launch(ProjBatch& pb, int udtype, bool with_norms, boo
     // one token: the staged kernel, first the partial projections, then residuals
     StageArgs a;
     stage_clear(a, eps);
-    for (int i = 0; i < pb.n; ++i) stage_add_part(a, pb.t[i]);
+    int slabs = 0;
+    for (int i = 0; i < pb.n; ++i) slabs += pb.t[i].s_slabs;
+    for (int i = 0; i < pb.n; ++i) stage_add_part(a, pb.t[i], nullptr, stage_col_blocks(slabs, pb.t[i].k, udtype));
     if (hipError_t e = stage_launch(a, udtype, s); e != hipSuccess) return e;
     stage_clear(a, eps);
     for (int i = 0; i < pb.n; ++i) stage_add_res(a, pb.t[i], false);

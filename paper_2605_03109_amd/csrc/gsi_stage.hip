@@ -90,15 +90,16 @@ __device__ __forceinline__ void partial_block(const StagePart& p, int local, flo
                                               float* __restrict__ xs, double* __restrict__ dsh) {
   constexpr int V = T::kVec;
   using S = typename T::storage;
-  // A small call splits the columns of U into ncb blocks of w = k / ncb (a workgroup then reads w-wide pieces of its
-  // rows), so that a few inputs still give the chip hundreds of workgroups; a large call takes whole rows (ncb = 1).
+  // A small call splits the columns of U into ncb blocks of as many 16-byte pieces, give or take one (a workgroup then
+  // reads w-wide pieces of its rows), so that a few inputs still give the chip hundreds of workgroups; a large call takes
+  // whole rows (ncb = 1).
   const int d = p.d, k = p.k_rows & 0xffff, prow = p.k_rows >> 16;
   const int slabs = p.slabs_x & 0xffff, ncb = max(1, (p.slabs_x >> 20) & 0xff);
-  const int slab = local % slabs, col0 = (local / slabs) * (k / ncb);
-  const int w = k / ncb;
+  const int slab = local % slabs, cb = local / slabs;
+  const int p0 = cb * (k / V) / ncb, pieces = (cb + 1) * (k / V) / ncb - p0;
+  const int col0 = p0 * V, w = pieces * V;
   // lanes per row piece: the power of two that covers its 16-byte pieces, one wave at most.  Surplus lanes of a rank
   // that is none (k = 200: 25 of 32 lanes) repeat the last piece and are left out of the sums.
-  const int pieces = w / V;
   const int lsh = pieces <= 1 ? 0 : 32 - __builtin_clz(pieces - 1);
   const int cpr = 1 << lsh;
   const int rps = kBlock >> lsh;  // rows per step
@@ -639,6 +640,17 @@ void stage_geom(int64_t d, int64_t k, int udtype, int& rows, int& slabs, bool fi
   if (r < 8 * rps) r = 8 * rps;
   rows = (int)(ceil_div(r, rps) * rps);
   slabs = (int)ceil_div(d, rows);
+}
+
+// The columns of every basis of a launch are halved until the launch has a workgroup and a half per compute unit, or a
+// block would be narrower than 48 columns (96 bytes of a row in bf16).  A rank is cut between any two 16-byte pieces: a
+// block at rank 200, 32 slabs per input, in four blocks of 48 and 56 columns instead of one: the partial projections
+// 8.6 -> 6.4 us (rank 256, four blocks of 64: 6.1 us).
+int stage_col_blocks(int slabs, int64_t k, int udtype) {
+  const int V = udtype == GSI_BF16 ? 8 : 4;
+  int ncb = 1;
+  while (slabs * ncb < 384 && ncb < 128 && (k / V) / (ncb * 2) * V >= 48) ncb *= 2;
+  return ncb;
 }
 
 void stage_clear(StageArgs& a, float eps) {
