@@ -674,6 +674,12 @@ hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStr
       if (!g.p[q].part) g.p[q].row_tiles = 0;
       g.p[q].min_parts = std::min(g.p[q].splits, (int)ceil_div(g.p[q].K, BK * kMaxDepth));
     }
+    // The products with the longest parts first: workgroups hold a unit each and go out in order, and what is long and
+    // comes last runs on a part of the chip.  (W r of the pair 4096 / 16384, 50 of 333 rows fired: 256 parts of 16 k-tiles,
+    // and 128 of 32 that came last: 79.5 -> 72.4 us.)
+    std::stable_sort(g.p, g.p + g.n, [](const GemmProb& x, const GemmProb& y) {
+      return (int64_t)x.K * y.splits > (int64_t)y.K * x.splits;
+    });
     const int tm = plan_rows(g, epi);
     if (hipError_t e = launch_epi(g, a_f32, epi, tm, s); e != hipSuccess) return e;
   }
