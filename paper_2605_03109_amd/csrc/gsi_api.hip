@@ -678,6 +678,11 @@ int gsi_gated_linear(const void* W, const void* M, const float* C, const float* 
   hipError_t e;
   if (!mfma_gated_path(W, M, C, R, d, k, B, wdtype, m, Y) && gsi::decode_linear_ok(m, d, k, wdtype, W, M, B) &&
       aligned(C, 16) && aligned(R, 16) && long_batch_ok(d, B, Y, false, nullptr)) {
+    if (B == 1) {
+      const gsi::OneMap one{W, M, C, R, n_fired, (float*)Y, (int)m, (int)d, (int)k};
+      e = gsi::gated_one_launch(one, wdtype, s);
+      return e == hipSuccess ? GSI_OK : hip_fail(e, "gsi_gated_linear");
+    }
     LinBatcher bt;
     bt.wdtype = wdtype; bt.s = s;
     bt.reset(B, 0);
@@ -685,7 +690,7 @@ int gsi_gated_linear(const void* W, const void* M, const float* C, const float* 
     std::memset(&gd, 0, sizeof(gd));
     gd.C = C; gd.R = R; gd.fired_idx = fired_idx; gd.n_fired = n_fired;
     gd.d = (int)d; gd.k = (int)k;
-    e = bt.add(0, gd, W, M, (float*)Y, m, B == 1, gsi::tile_part_bytes(m, d, B) ? (float*)ws : nullptr);
+    e = bt.add(0, gd, W, M, (float*)Y, m, false, gsi::tile_part_bytes(m, d, B) ? (float*)ws : nullptr);
     if (e == hipSuccess) e = bt.flush();
   } else if (mfma_gated_path(W, M, C, R, d, k, B, wdtype, m, Y)) {
     const MfmaMap mp{W, M, C, R, nullptr, 0, fired_idx, n_fired, m, d, k, (float*)Y, (float*)ws, false};

@@ -34,7 +34,7 @@ struct ProjTask {
   int32_t* n_fired;
   float* part_c;       // [a_slabs][B][k]  partial projections, one per row slab
   float* part_n;       // [b_slabs][B][2]  partial |r|^2, |x|^2, one per residual slab
-  unsigned* sync;      // decode batch on the matrix cores: finished residual workgroups of this input
+  unsigned* sync;      // finished residual workgroups of this input (decode batch on the matrix cores, or one token's projection)
   int d, k;
   int a_rows, a_slabs, a_cblocks;  // partial projection: rows per slab, slabs, column blocks
   int b_rows, b_slabs;             // residual: rows per slab, slabs
@@ -296,6 +296,8 @@ void stage_add_img(StageArgs& a, int res, const void* M, float* Y, const float* 
 // residual task `res` walks its slabs in the XCD order of the partial projection (r residual slabs per partial slab)
 void stage_set_res_xcd_order(StageArgs& a, int res, int r);
 void stage_add_gate(StageArgs& a, const ProjTask& t);
+// projection of one token and one input, norms included: two launches whose arguments are this input's alone
+hipError_t stage_project_one(const ProjTask& t, int dtype, hipStream_t s);
 // e0 / e1 (optional): events that take the start / stop timestamps of the dispatch
 hipError_t stage_launch(StageArgs& a, int dtype, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 
@@ -394,6 +396,17 @@ hipError_t stream_fired_geom(int n_in, const FiredIn* host_ins, const FiredMap* 
 hipError_t stream_fired_run(const void* table, const FiredGeom& g, hipStream_t s, hipEvent_t e0 = nullptr,
                             hipEvent_t e1 = nullptr);
 
+// One token, one map (gsi_gated_linear): image term and W r in one launch
+struct OneMap {
+  const void* W;
+  const void* M;
+  const float* C;
+  const float* R;
+  const int32_t* n_fired;
+  float* Y;
+  int m, d, k;
+};
+hipError_t gated_one_launch(const OneMap& g, int wdtype, hipStream_t s);
 // single-token persistent kernel (gsi_stream.hip)
 size_t stream_smem_bytes(const LinBatch& lb);
 hipError_t stream_rows_launch(LinBatch& lb, int wdtype, hipStream_t s, hipEvent_t e0 = nullptr,

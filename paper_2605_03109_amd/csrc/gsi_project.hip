@@ -514,6 +514,8 @@ void decode_project_fill(ProjTask& t, int64_t d, int64_t k, int64_t B, void* ws,
   const size_t part_slabs = (size_t)std::max(g.a_slabs, std::max(t.s_slabs, f_slabs));
   t.part_c = reinterpret_cast<float*>(ws);
   t.part_n = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + align_up(part_slabs * B * k * 4 * (B == 1 ? 2 : 1), 256));
+  // (one token: the low parts, behind the partials, are the single-pass gate's, which has no counter)
+  t.sync = B == 1 ? reinterpret_cast<unsigned*>(t.part_c + part_slabs * k) : nullptr;
 }
 
 hipError_t decode_norms_launch(const ProjBatch& pb, bool with_gate, float eps, hipStream_t s) {
@@ -540,6 +542,7 @@ hipError_t decode_project_launch(ProjBatch& pb, int udtype, bool with_norms, boo
                                  hipStream_t s, const TileImgBatch* img) {
   if (pb.n == 0 || pb.B == 0) return hipSuccess;
   if (pb.B == 1) {
+    if (pb.n == 1 && with_norms && !with_gate) return stage_project_one(pb.t[0], udtype, s);
     // one token: the staged kernel, first the partial projections, then residuals
     StageArgs a;
     stage_clear(a, eps);
