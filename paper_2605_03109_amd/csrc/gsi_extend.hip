@@ -22,7 +22,7 @@
 // extension moves U three times and every W once; operands whose rows are 16-byte aligned are read with 16-byte loads,
 // several in flight per lane.  Large bases have s added up by a launch of its own (own_sums).  (s, the column and U^T u in
 // launches of their own for every basis: seven launches of 4 to 5 us around one of 24 us; three maps 4096 x 4096 on a
-// basis of 4096 x 384, 256 columns in use: 46.7 us, 35.6 us with these four, calls replayed from a graph.)
+// basis of 4096 x 384, 256 columns in use: 46.7 us, 35.0 us with these four (a basis of 4096 x 512), calls replayed from a graph.)
 //
 // Every launch covers ALL bases of a call (one grid dimension is the basis, or the map): a token's pass over the
 // bases of a whole model is these launches, not as many per basis, and what it costs when no basis grows is
@@ -56,6 +56,13 @@ struct ExtArg {  // the bases of a launch: a device table, or (tab == null) the 
   const ExtIn* tab;
   ExtIn one;
 };
+// Where the record is, is known at compile time: chosen at run time, every field of it would be a flat load of its own, and
+// so every load through its pointers.
+template <bool TAB>
+__device__ __forceinline__ ExtIn ext_record(const ExtArg& a, int i) {
+  if constexpr (TAB) return a.tab[i];
+  else return a.one;
+}
 struct ExtMapArg {  // the maps of an image launch: a device table, or up to kFewMaps records
   const ExtMapRec* tab;
   ExtMapRec few[kFewMaps];
@@ -75,6 +82,11 @@ __device__ __forceinline__ uint4 load_global16_once(const void* p) {  // (non-te
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ float load_global(const float* p) { return *(const __attribute__((address_space(1))) float*)p; }
+__device__ __forceinline__ float2 load_global2(const float* p) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  const f32x2 v = *(const __attribute__((address_space(1))) f32x2*)p;
+  return float2{v.x, v.y};
+}
 __device__ __forceinline__ float4 load_global4(const float* p) {
   const uint4 v = load_global16(p);
   return float4{__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
@@ -101,11 +113,14 @@ __host__ __device__ __forceinline__ ExtWs ext_ws(const ExtIn& in) {
 }
 
 // the candidate's norm: every workgroup of a basis adds the shares of |r2|^2 in the same fixed order; 1 / |r2|, or 0 when
-// the basis does not grow
-__device__ __forceinline__ float ext_inverse(const ExtIn& in, const ExtWs& w, float* sh) {
-  const int cand = w.st->cand;  // (requested with the shares, which are not used if it is zero)
-  float t = 0.f;
-  for (int q = threadIdx.x; q < in.wgs; q += kBlock) t += load_global(w.pn + q);
+// the basis does not grow.  first: the thread's first share (ext_first_share), requested earlier.
+__device__ __forceinline__ float ext_first_share(const ExtIn& in, const ExtWs& w) {
+  return load_global(w.pn + min((int)threadIdx.x, in.wgs - 1));
+}
+__device__ __forceinline__ float ext_inverse(const ExtIn& in, const ExtWs& w, float* sh, float first) {
+  const int cand = w.st->cand;  // (the shares are not used if it is zero)
+  float t = (int)threadIdx.x < in.wgs ? first : 0.f;
+  for (int q = threadIdx.x + kBlock; q < in.wgs; q += kBlock) t += load_global(w.pn + q);
   t = group_sum<kWave>(t);
   if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = t;
   __syncthreads();
@@ -199,9 +214,9 @@ __device__ __forceinline__ void proj_block(const ExtIn& in, const ExtWs& w, cons
 
 // Partials of s = U^T r (grid: column blocks x slabs x bases); every workgroup forms the candidate verdict from the
 // token's norms and the column counter, the first one of a basis records it.
-template <class T>
+template <class T, bool TAB>
 __global__ __launch_bounds__(kBlock) void ext_proj(const ExtArg a, float tau) {
-  const ExtIn in = a.tab ? a.tab[blockIdx.z] : a.one;
+  const ExtIn in = ext_record<TAB>(a, blockIdx.z);
   const ExtWs w = ext_ws(in);
   if ((int64_t)blockIdx.x * kCols >= in.K || (int)blockIdx.y >= in.slabs) return;  // (the grid is sized for the largest basis)
   const int k = in.k_cur[0];
@@ -230,6 +245,23 @@ __device__ __forceinline__ float slab_sum(const float* __restrict__ part, int sl
   return t;
 }
 
+// ... of columns j and j + 1 (K even, the partials 8-byte aligned), all of up to 32 slabs requested at once
+__device__ __forceinline__ float2 slab_sum2(const float* __restrict__ part, int slabs, int64_t K, int64_t j) {
+  float2 t = float2{0.f, 0.f};
+  for (int q0 = 0; q0 < slabs; q0 += 32) {
+    float2 v[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) v[u] = load_global2(part + (int64_t)min(q0 + u, slabs - 1) * K + j);
+#pragma unroll
+    for (int u = 0; u < 32; ++u)
+      if (q0 + u < slabs) {
+        t.x += v[u].x;
+        t.y += v[u].y;
+      }
+  }
+  return t;
+}
+
 // Is s added up by a launch of its own?  Else every residual workgroup adds all slab partials itself: a launch less, but the
 // sums stand before its first product, and slabs x K x 4 bytes come from L2 for every workgroup.  us per extension of a
 // basis with one map, together / in a launch of their own: 16384 x 256 62.0 / 63.8; 4096 x 512 27.8 / 27.5; 16384 x 512
@@ -241,8 +273,9 @@ __host__ __device__ __forceinline__ bool own_sums(const ExtIn& in) {
 }
 
 // s of the bases whose residual workgroups do not add it up themselves
+template <bool TAB>
 __global__ __launch_bounds__(kSumBlock) void ext_sum(const ExtArg a) {
-  const ExtIn in = a.tab ? a.tab[blockIdx.y] : a.one;
+  const ExtIn in = ext_record<TAB>(a, blockIdx.y);
   const ExtWs w = ext_ws(in);
   if (!own_sums(in) || !w.st->cand) return;
   const int64_t j = (int64_t)blockIdx.x * kSumBlock + threadIdx.x;
@@ -252,10 +285,10 @@ __global__ __launch_bounds__(kSumBlock) void ext_sum(const ExtArg a) {
 
 // r2[i] = r[i] - sum_j U[i, j] s[j], a wave per row (two rows at a time); pn[workgroup] = the workgroup's share
 // of |r2|^2
-template <class T>
+template <class T, bool TAB>
 __global__ __launch_bounds__(kBlock) void ext_resid(const ExtArg a) {
   using S = typename T::storage;
-  const ExtIn in = a.tab ? a.tab[blockIdx.y] : a.one;
+  const ExtIn in = ext_record<TAB>(a, blockIdx.y);
   const ExtWs w = ext_ws(in);
   if ((int)blockIdx.x >= in.wgs || !w.st->cand) return;
   const int64_t d = in.d, K = in.K;
@@ -280,7 +313,12 @@ __global__ __launch_bounds__(kBlock) void ext_resid(const ExtArg a) {
   };
   if (in.uvec) request((int64_t)blockIdx.x * kRowsPerWg, lane);  // ahead of the sums below
   if (!own_sums(in)) {  // uniform
-    for (int64_t j = threadIdx.x; j < K; j += kBlock) ss[j] = slab_sum(w.part, in.slabs, K, j);
+    if (K % 2 == 0) {
+      for (int64_t j = 2 * threadIdx.x; j < K; j += 2 * kBlock)
+        *reinterpret_cast<float2*>(ss + j) = slab_sum2(w.part, in.slabs, K, j);
+    } else {
+      for (int64_t j = threadIdx.x; j < K; j += kBlock) ss[j] = slab_sum(w.part, in.slabs, K, j);
+    }
     __syncthreads();
     s = ss;
   }
@@ -366,7 +404,10 @@ __device__ __forceinline__ void column_block(const ExtIn& in, const ExtWs& w, fl
 // workgroup keeps a block of u (8192 columns in bf16) in LDS, rounded as it is stored, from turn to turn if it is all of u;
 // a wave streams its rows past it in steps of 128 pieces of 16 bytes, the next three steps' loads under way all the time:
 // from row to row, along the rows and across blocks.
-// Bound by how much a unit has in flight: 109 registers leave four waves per SIMD.  With four rows per wave and the
+// Bound by how much a unit has in flight: 119 registers leave four waves per SIMD.  Three maps 4096 x 4096 beside the rest of
+// the launch 25.1 us, 21.8 with the first block of r2 requested beside the norm's shares, the image workgroups first (the
+// launch has 16 more than the chip has places, and they waited for the last) and one basis' record read as an argument.
+// With four rows per wave and the
 // lanes' share of u in registers (163, three waves per SIMD) nothing was under way from one block of columns to the next,
 // and long rows lost.  us per extension, rank 512, so / here / as a launch of its own behind the stored column: three maps
 // 4096 x 4096 39.6 / 39.4 / 46.5, one of 16384 x 4096 48.2 / 42.7 / 53.2, one of 4096 x 16384 65.5 / 56.0 / 60.5, one of
@@ -374,7 +415,7 @@ __device__ __forceinline__ void column_block(const ExtIn& in, const ExtWs& w, fl
 // SIMD (1 to 9 us), 1 x 2 reads u from LDS twice as often (three maps 46.0).
 // (Requesting the first rows ahead of the verdict costs more in registers than it hides.)
 template <class T>
-__device__ __forceinline__ void image_rows_block(const ExtIn& in, const ExtWs& w, const ExtMapRec& p, float inv, int blk, int blocks) {
+__device__ __forceinline__ void image_rows_block(const ExtIn& in, const ExtWs& w, const ExtMapRec& p, int blk, int blocks, float* sh) {
   using S = typename T::storage;
   constexpr int V = T::kVec;
   constexpr int NL = 2;                   // loads per lane and step
@@ -389,6 +430,37 @@ __device__ __forceinline__ void image_rows_block(const ExtIn& in, const ExtWs& w
   const int64_t chunks = d / V;
   const int steps = (int)((chunks + kStep - 1) / kStep);
   int64_t held = -1;  // first piece of the block of u in LDS
+  // The first block of r2 is requested with the shares of its norm, so that the rows wait for one round trip, not two.
+  constexpr int kUPer = kUPieces / kBlock;
+  float4 head[kUPer][V / 4];
+  const float first = ext_first_share(in, w);
+  if (p.vec) {
+#pragma unroll
+    for (int e = 0; e < kUPer; ++e) {
+      if (e > 0 && e * kBlock >= chunks) break;  // uniform
+#pragma unroll
+      for (int q = 0; q < V / 4; ++q)
+        head[e][q] = load_global4(w.r2 + min((int64_t)(threadIdx.x + e * kBlock), chunks - 1) * V + 4 * q);
+    }
+  }
+  const float inv = ext_inverse(in, w, sh, first);
+  if (inv == 0.f) return;  // uniform
+  if (p.vec) {
+#pragma unroll
+    for (int e = 0; e < kUPer; ++e) {
+      if (e > 0 && e * kBlock >= chunks) break;
+      __align__(16) S t[V];
+#pragma unroll
+      for (int q = 0; q < V / 4; ++q) {
+        const float4 x = head[e][q];
+        T::store(t, 4 * q, x.x * inv); T::store(t, 4 * q + 1, x.y * inv);
+        T::store(t, 4 * q + 2, x.z * inv); T::store(t, 4 * q + 3, x.w * inv);
+      }
+      us[threadIdx.x + e * kBlock] = *reinterpret_cast<const uint4*>(t);
+    }
+    held = 0;
+    __syncthreads();
+  }
 #pragma unroll 1
   for (int64_t row_begin = (int64_t)blk * kImgRows; row_begin < p.m; row_begin += (int64_t)blocks * kImgRows) {
     const int64_t row0 = row_begin + wave * kImgPerWave;
@@ -465,49 +537,49 @@ __device__ __forceinline__ void image_rows_block(const ExtIn& in, const ExtWs& w
   }
 }
 
-// What needs the stored column: workgroups of three kinds, told apart by their index: n bases x col_wgs columns, n bases x
-// (pcols x pslabs) partials of U^T u, maps x img_wgs image rows.
+// What needs the stored column: workgroups of three kinds, told apart by their index: maps x img_wgs image rows, n bases x
+// col_wgs columns, n bases x (pcols x pslabs) partials of U^T u.
 struct ExtStore {
   int col_wgs, pcols, pslabs, img_wgs, n, n_maps;
 };
-template <class T>
+template <class T, bool TAB>
 __global__ __launch_bounds__(kBlock) void ext_store(const ExtArg a, const ExtMapArg ma, const ExtStore g) {
   __shared__ float sh[kWaves];
   int b = blockIdx.x;
+  if (b < g.n_maps * g.img_wgs) {  // the images first: the launch lasts as long as they do
+    const ExtMapRec p = TAB ? ma.tab[b / g.img_wgs] : ma.few[b / g.img_wgs];
+    const int blk = b % g.img_wgs;
+    if ((int64_t)blk * kImgRows >= p.m) return;
+    const ExtIn in = ext_record<TAB>(a, p.in);
+    const ExtWs w = ext_ws(in);
+    if (!w.st->cand) return;
+    image_rows_block<T>(in, w, p, blk, g.img_wgs, sh);
+    return;
+  }
+  b -= g.n_maps * g.img_wgs;
   if (b < g.n * g.col_wgs) {
     const int blk = b % g.col_wgs;
-    const ExtIn in = a.tab ? a.tab[b / g.col_wgs] : a.one;
+    const ExtIn in = ext_record<TAB>(a, b / g.col_wgs);
     if (blk > 0 && (int64_t)blk * kBlock >= in.d) return;
     const ExtWs w = ext_ws(in);
-    column_block<T>(in, w, ext_inverse(in, w, sh), blk, g.col_wgs);
+    column_block<T>(in, w, ext_inverse(in, w, sh, ext_first_share(in, w)), blk, g.col_wgs);
     return;
   }
   b -= g.n * g.col_wgs;
   const int per = g.pcols * g.pslabs;
-  if (b < g.n * per) {
-    const ExtIn in = a.tab ? a.tab[b / per] : a.one;
-    const int cb = b % per % g.pcols, slab = b % per / g.pcols;
-    if (!in.gram || (int64_t)cb * kCols >= in.K || slab >= in.slabs) return;
-    const ExtWs w = ext_ws(in);
-    if (!w.st->cand) return;
-    const float inv = ext_inverse(in, w, sh);
-    if (inv != 0.f) proj_block<T>(in, w, w.r2, inv, w.st->kc, cb, slab, g.pslabs);
-    return;
-  }
-  b -= g.n * per;
-  const ExtMapRec p = ma.tab ? ma.tab[b / g.img_wgs] : ma.few[b / g.img_wgs];
-  const int blk = b % g.img_wgs;
-  if ((int64_t)blk * kImgRows >= p.m) return;
-  const ExtIn in = a.tab ? a.tab[p.in] : a.one;
+  const ExtIn in = ext_record<TAB>(a, b / per);
+  const int cb = b % per % g.pcols, slab = b % per / g.pcols;
+  if (!in.gram || (int64_t)cb * kCols >= in.K || slab >= in.slabs) return;
   const ExtWs w = ext_ws(in);
   if (!w.st->cand) return;
-  const float inv = ext_inverse(in, w, sh);
-  if (inv != 0.f) image_rows_block<T>(in, w, p, inv, blk, g.img_wgs);
+  const float inv = ext_inverse(in, w, sh, ext_first_share(in, w));
+  if (inv != 0.f) proj_block<T>(in, w, w.r2, inv, w.st->kc, cb, slab, g.pslabs);
 }
 
 // E[j, kc] = E[kc, j] = (U^T u)[j] - (j == kc), the projection over the extended basis added over its slabs
+template <bool TAB>
 __global__ __launch_bounds__(kSumBlock) void ext_gram(const ExtArg a) {
-  const ExtIn in = a.tab ? a.tab[blockIdx.y] : a.one;
+  const ExtIn in = ext_record<TAB>(a, blockIdx.y);
   const ExtWs w = ext_ws(in);
   if (!in.gram || !w.st->ext) return;
   const int64_t K = in.K;
@@ -532,12 +604,12 @@ Geom geom(int64_t d) {
   return g;
 }
 
-template <class T>
+template <class T, bool TAB>
 hipError_t launch_all(const ExtIn* in, int n, const ExtMapRec* maps, int n_maps, float tau, void* table, hipStream_t s) {
   ExtArg a;
   std::memset(&a, 0, sizeof(a));
   const ExtMapRec* mtab = nullptr;
-  if (n == 1) {
+  if (!TAB) {
     a.one = in[0];
   } else {  // the records go to the table in the workspace: bases first, then maps
     const size_t ib = align_up((size_t)n * sizeof(ExtIn), 256), mb = align_up((size_t)n_maps * sizeof(ExtMapRec), 256);
@@ -571,9 +643,9 @@ hipError_t launch_all(const ExtIn* in, int n, const ExtMapRec* maps, int n_maps,
   const dim3 pgrid((unsigned)pc, (unsigned)std::min<int64_t>(slabs_max, std::max<int64_t>(1, kGridCap / (pc * n))), (unsigned)n);
   const dim3 kgrid((unsigned)ceil_div(K_max, kSumBlock), (unsigned)n);
   const int64_t per_basis = std::max<int64_t>(8, kGridCap / n);
-  ext_proj<T><<<pgrid, kBlock, 0, s>>>(a, tau);
-  if (any_own) ext_sum<<<kgrid, kSumBlock, 0, s>>>(a);
-  ext_resid<T><<<dim3((unsigned)std::min<int64_t>(wgs_max, per_basis), (unsigned)n), kBlock, 0, s>>>(a);
+  ext_proj<T, TAB><<<pgrid, kBlock, 0, s>>>(a, tau);
+  if (any_own) ext_sum<TAB><<<kgrid, kSumBlock, 0, s>>>(a);
+  ext_resid<T, TAB><<<dim3((unsigned)std::min<int64_t>(wgs_max, per_basis), (unsigned)n), kBlock, 0, s>>>(a);
   ExtStore g;
   g.n = n;
   g.col_wgs = (int)std::min<int64_t>(ceil_div(d_max, kBlock), std::max<int64_t>(1, per_basis / 8));
@@ -596,9 +668,9 @@ hipError_t launch_all(const ExtIn* in, int n, const ExtMapRec* maps, int n_maps,
     g.img_wgs = g.n_maps > 0 ? (int)std::min<int64_t>(ceil_div(mm, kImgRows), std::max<int64_t>(8, img_cap / g.n_maps)) : 0;
     if (j0 > 0) g.n = 0;
     const int64_t blocks = (int64_t)g.n * (g.col_wgs + (int64_t)g.pcols * g.pslabs) + (int64_t)g.n_maps * g.img_wgs;
-    if (blocks > 0) ext_store<T><<<(unsigned)blocks, kBlock, 0, s>>>(a, ma, g);
+    if (blocks > 0) ext_store<T, TAB><<<(unsigned)blocks, kBlock, 0, s>>>(a, ma, g);
   }
-  if (any_gram) ext_gram<<<kgrid, kSumBlock, 0, s>>>(a);
+  if (any_gram) ext_gram<TAB><<<kgrid, kSumBlock, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -632,8 +704,11 @@ void extend_fill_map(ExtMapRec& mp, int64_t d, int udtype) {
 hipError_t extend_many(const ExtIn* in, int n, const ExtMapRec* maps, int n_maps, int udtype, float tau, void* table,
                        hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  return udtype == GSI_BF16 ? launch_all<BF16>(in, n, maps, n_maps, tau, table, s)
-                            : launch_all<F32>(in, n, maps, n_maps, tau, table, s);
+  if (n == 1)
+    return udtype == GSI_BF16 ? launch_all<BF16, false>(in, n, maps, n_maps, tau, table, s)
+                              : launch_all<F32, false>(in, n, maps, n_maps, tau, table, s);
+  return udtype == GSI_BF16 ? launch_all<BF16, true>(in, n, maps, n_maps, tau, table, s)
+                            : launch_all<F32, true>(in, n, maps, n_maps, tau, table, s);
 }
 
 }  // namespace gsi
