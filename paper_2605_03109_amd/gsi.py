@@ -8,6 +8,7 @@ kernels; there is no fallback: if ``libgsi.so`` is missing, importing this modul
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import threading
 from typing import List, Optional, Sequence, Tuple
@@ -243,6 +244,7 @@ def workspace(nbytes: int, device=None, stream=None) -> Optional[torch.Tensor]:
     return have
 
 
+@functools.lru_cache(maxsize=4096)  # (of the sizes alone; 0.1 us instead of 0.5 for a known call)
 def workspace_bytes(which: int, m: int = 0, d: int = 0, k: int = 0, B: int = 0) -> int:
     return int(lib.gsi_workspace_bytes(which, m, d, k, B))
 
