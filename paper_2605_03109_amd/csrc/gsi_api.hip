@@ -184,15 +184,17 @@ int gsi_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d,
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (wdtype == GSI_BF16 && mfma_image_ok(m, d, k) && aligned(W, 16) && aligned(U, 2) && aligned(M, 8)) {
-    // matrix cores: M = W (U^T)^T with the basis transposed once into the workspace
+    // matrix cores; the basis is transposed on its way to LDS, or, where its rows are no whole 8-byte pieces, once into the
+    // workspace
+    const bool as_stored = aligned(U, 8);
     gsi::TransposeTask tr{U, ws, (int)d, (int)k, 0};
-    e = gsi::mfma_transpose_bf16(&tr, 1, s);
+    e = as_stored ? hipSuccess : gsi::mfma_transpose_bf16(&tr, 1, s);
     if (e == hipSuccess) {
-      gsi::GemmProb g = gemm_prob(W, d, ws, d, M, k, m, k, d, gsi::EPI_STORE_BF16);
+      gsi::GemmProb g = gemm_prob(W, d, as_stored ? U : ws, as_stored ? k : d, M, k, m, k, d, gsi::EPI_STORE_BF16);
       g.max_splits = gsi::mfma_splits(m, k, d, gsi::EPI_STORE_BF16, false, level);
       if (g.max_splits > 1)
         g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + gsi::align_up((size_t)k * d * 2, 256));
-      e = gsi::mfma_gemm_nt(&g, 1, 0, gsi::EPI_STORE_BF16, s);
+      e = gsi::mfma_gemm_nt(&g, 1, 0, gsi::EPI_STORE_BF16, s, as_stored);
     }
   } else {
     e = gsi::generic_build_image(W, U, M, m, d, k, wdtype, s);
@@ -417,23 +419,30 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
                                float eps, WsLevel level, hipStream_t s) {
   static thread_local std::vector<gsi::TransposeTask> tr;
   static thread_local std::vector<gsi::GemmProb> pr;
+  // The basis is transposed on its way to LDS, which a k-tile pays for with more and smaller loads; bf16 activations of many
+  // tokens (whose operand needs no conversion, and whose row tiles are many) have it transposed once instead.  us, projection
+  // of one token batch over 4096 and 16384 columns with small maps, as stored / transposed first: rank 256, bf16, 200 tokens
+  // 53 / 57, 1024 101 / 101, 2048 168 / 162; rank 64, 2048 136 / 127; fp32, rank 256, 200 55 / 60, 1024 124 / 126,
+  // 2048 184 / 195.
+  auto as_stored = [&](int i) { return in[i].xdtype == GSI_F32 || B <= 1024; };
   tr.clear();
-  for (int i = 0; i < n; ++i) tr.push_back(gsi::TransposeTask{in[i].U, in[i].ws, (int)in[i].d, (int)in[i].k, 0});
-  if (hipError_t e = gsi::mfma_transpose_bf16(tr.data(), n, s); e != hipSuccess) return e;
+  for (int i = 0; i < n; ++i)
+    if (!as_stored(i)) tr.push_back(gsi::TransposeTask{in[i].U, in[i].ws, (int)in[i].d, (int)in[i].k, 0});
+  if (hipError_t e = gsi::mfma_transpose_bf16(tr.data(), (int)tr.size(), s); e != hipSuccess) return e;
   auto part_n = [&](int i) { return reinterpret_cast<float*>(in[i].ws + gsi::align_up((size_t)in[i].k * in[i].d * 2, 256)); };
   for (int xdt = 0; xdt < 2; ++xdt) {
     pr.clear();
     for (int i = 0; i < n; ++i) {
       const int64_t d = in[i].d, k = in[i].k;
       if (in[i].xdtype != xdt) continue;
-      gsi::GemmProb g = gemm_prob(in[i].X, d, in[i].ws, d, in[i].C, k, B, k, d, gsi::EPI_STORE_F32);
+      gsi::GemmProb g = gemm_prob(in[i].X, d, as_stored(i) ? in[i].U : in[i].ws, as_stored(i) ? k : d, in[i].C, k, B, k, d, gsi::EPI_STORE_F32);
       g.max_splits = gsi::mfma_splits(B, k, d, gsi::EPI_COEFF, xdt == GSI_F32, level);
       if (g.max_splits > 1)
         g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(part_n(i)) +
                                           gsi::align_up((size_t)gsi::mfma_res_tiles(d, level) * B * 2 * 4, 256));
       pr.push_back(g);
     }
-    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s); e != hipSuccess)
+    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s, xdt == GSI_F32 || B <= 1024); e != hipSuccess)
       return e;
   }
   pr.clear();
@@ -441,7 +450,7 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
     gsi::GemmProb g = gemm_prob(in[i].C, in[i].k, in[i].U, in[i].k, in[i].R, in[i].d, B, in[i].d, in[i].k, gsi::EPI_RESIDUAL);
     g.X = in[i].X; g.xdtype = in[i].xdtype;
     g.part_n = part_n(i);
-    g.sync = reinterpret_cast<unsigned*>(in[i].ws);  // (the transposed basis is not read any more)
+    g.sync = reinterpret_cast<unsigned*>(in[i].ws);  // (a transposed basis is not read any more)
     pr.push_back(g);
     for (int q = 0; q < n_img; ++q)
       if (img[q].in == i)

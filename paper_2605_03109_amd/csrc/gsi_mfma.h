@@ -47,7 +47,8 @@ size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, WsLevel level);
 // Products of one launch (n of any number; more than kMaxProbs take several launches).  a_f32: A is 0: bf16; 1: fp32, fed as
 // bf16 head + tail (two passes); 2: fp32, rounded once to bf16.  epi: EPI_STORE_BF16 (A bf16), EPI_STORE_F32 (bf16 or head +
 // tail), EPI_PROJECTED (head + tail) or EPI_SCATTER; every problem's own epi belongs to it.
-hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s);
+// b_rows: B is stored [K, N] (ldb elements a row, whole 8-byte pieces) and transposed on its way (EPI_STORE_BF16, EPI_STORE_F32).
+hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s, bool b_rows = false);
 
 // Ut[j][i] = U[i][j] for n bf16 matrices U[rows, cols]
 struct TransposeTask {

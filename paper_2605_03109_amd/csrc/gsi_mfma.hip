@@ -30,8 +30,10 @@
 // and a second kernel adds them in split order and applies the epilogue.
 // The residual and image products are short (the rank) with long epilogues (every output row of a block: 0.5 GB), so they
 // run on tiles of 128 rows, two workgroups per unit: one's epilogue beside the other's products.
-// Operands that are N-contiguous in memory (U as the right factor of W U and X U) are transposed
-// once into the workspace.
+// A right operand that is N-contiguous in memory (U as the factor of W U and X U) is transposed on its way to LDS: a thread
+// has four columns of BKT / 8 rows, packs two rows into a word and writes four columns.  Where that costs more than it saves
+// (many row tiles of bf16 activations: mfma_project), or its rows are no whole 8-byte pieces, it is transposed once into
+// the workspace.  The six images of a block (4096 / 16384, rank 256): a launch of 5 us each less.
 #include <algorithm>
 
 #include "gsi_device.h"
@@ -48,6 +50,7 @@ constexpr int WTM = 64;                         // rows of a wave tile
 constexpr int kThreads = 512;
 constexpr int kAF = WTM / 32;                   // A fragments per wave
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // a native vector: loads and stores of it are
                                                               // instructions, not aggregate copies
 
@@ -56,8 +59,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // a native vector:
 // Geometry of a staged k-tile by mode.  The head + tail form keeps two tiles of A per stage, so its k-tile is 32
 // columns deep (two MFMA steps of two passes each: as many MFMAs between barriers as the 64-deep tile of the
 // other modes) and two stages still fit in LDS.
-// TM: rows of the workgroup tile, 256 or 128 (eight waves 4 x 2 or 2 x 4, each 64 x 128 or 64 x 64).
-template <int AM, int TM>
+// TM: rows of the workgroup tile, 256, 128 or 64 (eight waves 4 x 2, 2 x 4 or 1 x 8, each 64 x 128, 64 x 64 or 64 x 32).
+// BT: the right operand is stored with the contraction along its rows (the basis, U[l][j]): it is transposed on its way to LDS.
+template <int AM, int TM, bool BT>
 struct Geo {
   static constexpr int BKT = AM == 1 ? 32 : 64;          // columns of a k-tile
   static constexpr int LD = BKT + 8;                     // padded LDS row stride, bf16 elements (80 or 144 bytes:
@@ -69,18 +73,28 @@ struct Geo {
   static constexpr int NA = TM / RPP;                    // ... and of A
   static constexpr int NP = AM == 1 ? 2 : 1;             // LDS tiles of A per stage
   static constexpr int kATile = TM * LD;                 // elements of one LDS tile of A
-  static constexpr int kStage = (NP * TM + BN) * LD;     // elements of one stage
-  static constexpr int WN = TM == 256 ? 2 : 4;           // waves side by side
+  static constexpr int kBPad = BT ? 3 * 32 : 0;          // see b_row
+  static constexpr int kStage = (NP * TM + BN) * LD + kBPad;  // elements of one stage
+  static constexpr int WN = TM == 256 ? 2 : TM == 128 ? 4 : 8;  // waves side by side
   static constexpr int WTN = BN / WN;                    // columns of a wave tile
   static constexpr int kBF = WTN / 32;                   // B fragments per wave
   static_assert(NU == KS, "one staging unit of B per MFMA step");
 };
 
-template <int AM, int TM>
+template <int AM, int TM, bool BT>
 struct Stage {
-  u32x4 a[Geo<AM, TM>::NA][AM ? 2 : 1];
-  u32x4 b[Geo<AM, TM>::NU];
+  u32x4 a[Geo<AM, TM, BT>::NA][AM ? 2 : 1];
+  u32x4 b[Geo<AM, TM, BT>::NU];  // BT: rows 2 u and 2 u + 1 of the thread's, four columns each
 };
+
+// LDS row of column n of the right operand's tile.  Transposed, a thread has four neighbouring columns: those of one
+// remainder modulo four are kept together, so that neighbouring threads write neighbouring rows, and the four groups lie 64
+// bytes further apart than their rows, so that sixteen neighbouring columns are read from distinct banks.
+template <int AM, int TM, bool BT>
+__device__ __forceinline__ int b_row(int n) {
+  using G = Geo<AM, TM, BT>;
+  return BT ? (n & 3) * (BN / 4 * G::LD + 32) + (n >> 2) * G::LD : n * G::LD;
+}
 
 // 8 fp32 -> 8 bf16 (RNE), and the bf16 of what is left
 __device__ __forceinline__ u32x4 round8(const u32x4& x0, const u32x4& x1, u32x4* tail) {
@@ -101,31 +115,47 @@ __device__ __forceinline__ u32x4 round8(const u32x4& x0, const u32x4& x1, u32x4*
                (uint32_t)h[4] | ((uint32_t)h[5] << 16), (uint32_t)h[6] | ((uint32_t)h[7] << 16)};
 }
 
+// A transposed right operand: bytes per row of it, and the lane's offset in a row (its rows' addresses are uniform)
+struct BSrc {
+  int64_t row;
+  uint32_t lane;
+};
 // requests unit u of k-tile kt of both operands (unit u of a thread: tile row tid / CPR + RPP u, columns
-// 8 (tid % CPR) .. + 8; the pointers already point at that row and column of k-tile 0)
-template <int AM, int TM>
-__device__ __forceinline__ void issue_unit(Stage<AM, TM>& st, int u, const char* const (&ap)[Geo<AM, TM>::NA],
-                                           const char* const (&bp)[Geo<AM, TM>::NU], int kt) {
-  using G = Geo<AM, TM>;
+// 8 (tid % CPR) .. + 8; the pointers already point at that row and column of k-tile 0).  A transposed right operand's units
+// are needed together and requested with the last: wave w has rows BKT / 8 * w .. of a k-tile, a lane four columns.
+template <int AM, int TM, bool BT>
+__device__ __forceinline__ void issue_unit(Stage<AM, TM, BT>& st, int u, const char* const (&ap)[Geo<AM, TM, BT>::NA],
+                                           const char* const (&bp)[Geo<AM, TM, BT>::NU], int kt, const BSrc& bs) {
+  using G = Geo<AM, TM, BT>;
   constexpr int ES = AM ? 4 : 2;
   if (u < G::NA) {
     const char* p = ap[u] + (int64_t)kt * G::BKT * ES;
     st.a[u][0] = *reinterpret_cast<const u32x4*>(p);
     if constexpr (AM != 0) st.a[u][1] = *reinterpret_cast<const u32x4*>(p + 16);
   }
-  st.b[u] = *reinterpret_cast<const u32x4*>(bp[u] + (int64_t)kt * G::BKT * 2);
-}
-template <int AM, int TM>
-__device__ __forceinline__ void issue(Stage<AM, TM>& st, const char* const (&ap)[Geo<AM, TM>::NA],
-                                      const char* const (&bp)[Geo<AM, TM>::NU], int kt) {
+  if constexpr (!BT) {
+    st.b[u] = *reinterpret_cast<const u32x4*>(bp[u] + (int64_t)kt * G::BKT * 2);
+  } else if (u == G::NU - 1) {
+    const char* p = bp[0] + (int64_t)kt * G::BKT * bs.row;
 #pragma unroll
-  for (int u = 0; u < Geo<AM, TM>::NU; ++u) issue_unit<AM, TM>(st, u, ap, bp, kt);
+    for (int r = 0; r < 2 * G::NU; ++r) {
+      const u32x2 x = *reinterpret_cast<const u32x2*>(p + r * bs.row + bs.lane);
+      st.b[r >> 1][2 * (r & 1)] = x[0];
+      st.b[r >> 1][2 * (r & 1) + 1] = x[1];
+    }
+  }
+}
+template <int AM, int TM, bool BT>
+__device__ __forceinline__ void issue(Stage<AM, TM, BT>& st, const char* const (&ap)[Geo<AM, TM, BT>::NA],
+                                      const char* const (&bp)[Geo<AM, TM, BT>::NU], int kt, const BSrc& bs) {
+#pragma unroll
+  for (int u = 0; u < Geo<AM, TM, BT>::NU; ++u) issue_unit<AM, TM, BT>(st, u, ap, bp, kt, bs);
 }
 
 // writes unit u of the staged k-tile to the LDS stage at `stage` as bf16 (fp32 A: rounded, or head and tail tiles)
-template <int AM, int TM>
-__device__ __forceinline__ void commit_unit(const Stage<AM, TM>& st, int u, uint16_t* stage, int tid) {
-  using G = Geo<AM, TM>;
+template <int AM, int TM, bool BT>
+__device__ __forceinline__ void commit_unit(const Stage<AM, TM, BT>& st, int u, uint16_t* stage, int tid) {
+  using G = Geo<AM, TM, BT>;
   const int off = ((tid / G::CPR) + G::RPP * u) * G::LD + 8 * (tid % G::CPR);
   if (u < G::NA) {
     u32x4* d0 = reinterpret_cast<u32x4*>(stage + off);
@@ -139,30 +169,48 @@ __device__ __forceinline__ void commit_unit(const Stage<AM, TM>& st, int u, uint
       *reinterpret_cast<u32x4*>(stage + G::kATile + off) = tail;
     }
   }
-  *reinterpret_cast<u32x4*>(stage + G::NP * G::kATile + off) = st.b[u];
-}
-template <int AM, int TM>
-__device__ __forceinline__ void commit(const Stage<AM, TM>& st, uint16_t* stage, int tid) {
+  uint16_t* bs = stage + G::NP * G::kATile;
+  if constexpr (!BT) {
+    *reinterpret_cast<u32x4*>(bs + off) = st.b[u];
+  } else {  // columns 4 (tid % 64) + j: all of the thread's rows, two in a word; unit u writes its share of the four
+    constexpr int R = 2 * G::NU, per = 4 / G::NU;
+    const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll
-  for (int u = 0; u < Geo<AM, TM>::NU; ++u) commit_unit<AM, TM>(st, u, stage, tid);
+    for (int j = per * u; j < per * (u + 1); ++j) {
+      uint32_t w[R / 2];
+#pragma unroll
+      for (int q = 0; q < R / 2; ++q) {
+        const uint32_t lo = st.b[q][j >> 1], hi = st.b[q][2 + (j >> 1)];  // rows 2 q and 2 q + 1
+        w[q] = (j & 1) ? (lo >> 16) | (hi & 0xffff0000u) : (lo & 0xffffu) | (hi << 16);
+      }
+      uint16_t* d = bs + b_row<AM, TM, BT>(4 * lane + j) + R * wave;
+      if constexpr (R == 8) *reinterpret_cast<u32x4*>(d) = u32x4{w[0], w[1], w[2], w[3]};
+      else *reinterpret_cast<u32x2*>(d) = u32x2{w[0], w[1]};
+    }
+  }
+}
+template <int AM, int TM, bool BT>
+__device__ __forceinline__ void commit(const Stage<AM, TM, BT>& st, uint16_t* stage, int tid) {
+#pragma unroll
+  for (int u = 0; u < Geo<AM, TM, BT>::NU; ++u) commit_unit<AM, TM, BT>(st, u, stage, tid);
 }
 
 // The MFMA operands of one step (16 columns of the k-tile) of a wave: lane half lh takes one half of the tile's
 // columns, eight per step (both operands in the same order, so the order of the contraction index does not
 // matter)
-template <int AM, int TM>
+template <int AM, int TM, bool BT>
 struct Ops {
   bf16x8 a[kAF];
   bf16x8 al[AM == 1 ? kAF : 1];
-  bf16x8 b[Geo<AM, TM>::kBF];
+  bf16x8 b[Geo<AM, TM, BT>::kBF];
 };
-template <int AM, int TM>
-__device__ __forceinline__ void read_ops(Ops<AM, TM>& o, const uint16_t* stage, int wm, int wn, int lc, int lh, int j) {
-  using G = Geo<AM, TM>;
+template <int AM, int TM, bool BT>
+__device__ __forceinline__ void read_ops(Ops<AM, TM, BT>& o, const uint16_t* stage, int wm, int wn, int lc, int lh, int j) {
+  using G = Geo<AM, TM, BT>;
   const int col = (G::BKT / 2) * lh + 8 * j;
   const uint16_t* Bq = stage + G::NP * G::kATile;
 #pragma unroll
-  for (int n = 0; n < G::kBF; ++n) o.b[n] = *reinterpret_cast<const bf16x8*>(Bq + (G::WTN * wn + 32 * n + lc) * G::LD + col);
+  for (int n = 0; n < G::kBF; ++n) o.b[n] = *reinterpret_cast<const bf16x8*>(Bq + b_row<AM, TM, BT>(G::WTN * wn + 32 * n + lc) + col);
 #pragma unroll
   for (int i = 0; i < kAF; ++i) {
     const int off = (WTM * wm + 32 * i + lc) * G::LD + col;
@@ -170,9 +218,9 @@ __device__ __forceinline__ void read_ops(Ops<AM, TM>& o, const uint16_t* stage, 
     if constexpr (AM == 1) o.al[i] = *reinterpret_cast<const bf16x8*>(stage + G::kATile + off);
   }
 }
-template <int AM, int TM>
-__device__ __forceinline__ void mma(const Ops<AM, TM>& o, f32x16 (&acc)[kAF][Geo<AM, TM>::kBF]) {
-  constexpr int kBF = Geo<AM, TM>::kBF;
+template <int AM, int TM, bool BT>
+__device__ __forceinline__ void mma(const Ops<AM, TM, BT>& o, f32x16 (&acc)[kAF][Geo<AM, TM, BT>::kBF]) {
+  constexpr int kBF = Geo<AM, TM, BT>::kBF;
 #pragma unroll
   for (int i = 0; i < kAF; ++i) {
 #pragma unroll
@@ -204,9 +252,9 @@ __device__ __forceinline__ int parts_for(const GemmProb& g, int rows) {
   return min(g.splits, max(g.min_parts, fit));
 }
 
-template <int AM, int EPI, int TM>
+template <int AM, int EPI, int TM, bool BT>
 __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm_nt(const GemmArgs args) {
-  using G = Geo<AM, TM>;
+  using G = Geo<AM, TM, BT>;
   constexpr int WTN = G::WTN, kBF = G::kBF;
   // two stages, each the tile(s) of A followed by the tile of B
   __shared__ __align__(16) uint16_t lds[2 * G::kStage];
@@ -254,8 +302,13 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
     if (g.row_idx) grow = g.row_idx[grow];
     ap[u] = reinterpret_cast<const char*>(g.A) + ((int64_t)grow * lda + 8 * (tid % G::CPR)) * ES;
   }
+  BSrc bsrc{0, 0u};
+  if constexpr (BT) {  // columns past the end repeat the last four
+    bsrc = BSrc{ldb * 2, 2u * (uint32_t)min(tile_n * BN + 4 * lane, N - 4)};
+    bp[0] = reinterpret_cast<const char*>(g.B) + (int64_t)(G::BKT / 8) * wave * bsrc.row;
+  }
 #pragma unroll
-  for (int u = 0; u < G::NU; ++u) {
+  for (int u = 0; !BT && u < G::NU; ++u) {
     int grow = tile_n * BN + (tid / G::CPR) + G::RPP * u;
     grow = grow < N ? grow : N - 1;
     bp[u] = reinterpret_cast<const char*>(g.B) + ((int64_t)grow * ldb + 8 * (tid % G::CPR)) * 2;
@@ -275,10 +328,10 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
     // One barrier per tile, before the last step: by then every wave has written its share of the next stage
     // and has the last step's operands in registers, so the first operands of the next tile are read behind
     // the last step's MFMAs.  Past the range the last tile is requested (and staged) again and never used.
-    Stage<AM, TM> st;
-    issue<AM, TM>(st, ap, bp, kt0);
-    commit<AM, TM>(st, lds, tid);
-    issue<AM, TM>(st, ap, bp, kt0 + 1 < kt1 ? kt0 + 1 : kt0);
+    Stage<AM, TM, BT> st;
+    issue<AM, TM, BT>(st, ap, bp, kt0, bsrc);
+    commit<AM, TM, BT>(st, lds, tid);
+    issue<AM, TM, BT>(st, ap, bp, kt0 + 1 < kt1 ? kt0 + 1 : kt0, bsrc);
     __syncthreads();
     if constexpr (AM == 1 && TM == 128) {
       // two workgroups per compute unit (one's epilogue beside the other's products): operands are read step by step, the
@@ -286,32 +339,44 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
       const char* pa = ap[0] + (int64_t)(kt0 + 1 < kt1 ? kt0 + 1 : kt0) * G::BKT * ES;  // the k-tile requested last
       const char* pb[G::NU];
 #pragma unroll
-      for (int u = 0; u < G::NU; ++u) pb[u] = bp[u] + (int64_t)(kt0 + 1 < kt1 ? kt0 + 1 : kt0) * G::BKT * 2;
+      for (int u = 0; u < (BT ? 1 : G::NU); ++u) pb[u] = bp[u] + (int64_t)(kt0 + 1 < kt1 ? kt0 + 1 : kt0) * G::BKT * 2 * (BT ? ldb : 1);
       static_assert(G::NA == 1, "one staging unit of A per thread");
       int cur = 0;
       for (int kt = kt0; kt < kt1; ++kt) {
         const int step = kt + 2 < kt1 ? G::BKT : 0;
 #pragma unroll
         for (int j = 0; j < G::KS; ++j) {
-          Ops<AM, TM> o;
-          read_ops<AM, TM>(o, lds + cur, wm, wn, lc, lh, j);
-          mma<AM, TM>(o, acc);
-          commit_unit<AM, TM>(st, j, lds + (G::kStage - cur), tid);
+          Ops<AM, TM, BT> o;
+          read_ops<AM, TM, BT>(o, lds + cur, wm, wn, lc, lh, j);
+          mma<AM, TM, BT>(o, acc);
+          commit_unit<AM, TM, BT>(st, j, lds + (G::kStage - cur), tid);
           if (j == 0) {
             pa += step * ES;
             st.a[0][0] = *reinterpret_cast<const u32x4*>(pa);
             st.a[0][1] = *reinterpret_cast<const u32x4*>(pa + 16);
           }
-          pb[j] += step * 2;
-          st.b[j] = *reinterpret_cast<const u32x4*>(pb[j]);
+          if constexpr (BT) {
+            if (j == G::KS - 1) {
+              pb[0] += step * bsrc.row;
+#pragma unroll
+              for (int r = 0; r < 2 * G::NU; ++r) {
+                const u32x2 x = *reinterpret_cast<const u32x2*>(pb[0] + r * bsrc.row + bsrc.lane);
+                st.b[r >> 1][2 * (r & 1)] = x[0];
+                st.b[r >> 1][2 * (r & 1) + 1] = x[1];
+              }
+            }
+          } else {
+            pb[j] += step * 2;
+            st.b[j] = *reinterpret_cast<const u32x4*>(pb[j]);
+          }
           __builtin_amdgcn_sched_barrier(0);
         }
         cur = G::kStage - cur;
         __syncthreads();
       }
     } else {
-      Ops<AM, TM> o[2];
-      read_ops<AM, TM>(o[0], lds, wm, wn, lc, lh, 0);
+      Ops<AM, TM, BT> o[2];
+      read_ops<AM, TM, BT>(o[0], lds, wm, wn, lc, lh, 0);
       for (int kt = kt0; kt < kt1; ++kt) {
         uint16_t* cur = lds + ((kt - kt0) & 1) * G::kStage;
         uint16_t* nxt = lds + (((kt - kt0) & 1) ^ 1) * G::kStage;
@@ -319,19 +384,19 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
 #pragma unroll
         for (int j = 0; j < G::KS; ++j) {
           if (j + 1 < G::KS) {
-            read_ops<AM, TM>(o[(j + 1) & 1], cur, wm, wn, lc, lh, j + 1);
+            read_ops<AM, TM, BT>(o[(j + 1) & 1], cur, wm, wn, lc, lh, j + 1);
           } else {
             __syncthreads();
-            read_ops<AM, TM>(o[(j + 1) & 1], nxt, wm, wn, lc, lh, 0);
+            read_ops<AM, TM, BT>(o[(j + 1) & 1], nxt, wm, wn, lc, lh, 0);
           }
-          mma<AM, TM>(o[j & 1], acc);
+          mma<AM, TM, BT>(o[j & 1], acc);
           if (j + 1 < G::KS) {
             // a unit behind every step but the last two, which share the step before the barrier
-            commit_unit<AM, TM>(st, j, nxt, tid);
-            issue_unit<AM, TM>(st, j, ap, bp, kt2);
+            commit_unit<AM, TM, BT>(st, j, nxt, tid);
+            issue_unit<AM, TM, BT>(st, j, ap, bp, kt2, bsrc);
             if (j + 2 == G::KS) {
-              commit_unit<AM, TM>(st, j + 1, nxt, tid);
-              issue_unit<AM, TM>(st, j + 1, ap, bp, kt2);
+              commit_unit<AM, TM, BT>(st, j + 1, nxt, tid);
+              issue_unit<AM, TM, BT>(st, j + 1, ap, bp, kt2, bsrc);
             }
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -528,7 +593,7 @@ __global__ __launch_bounds__(256) void transpose_bf16(const TransposeArgs a) {
   }
 }
 
-template <int AM, int EPI>
+template <int AM, int EPI, bool BT>
 hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
   int64_t blocks = 0;
   bool split = false;
@@ -544,31 +609,37 @@ hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
     }
   }
   if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
-  if (tm == 128) gemm_nt<AM, EPI, 128><<<(unsigned)blocks, kThreads, 0, s>>>(g);
-  else gemm_nt<AM, EPI, 256><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+  if (tm == 256) {
+    gemm_nt<AM, EPI, 256, BT><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+  } else if (tm == 128) {
+    gemm_nt<AM, EPI, 128, BT><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+  } else {
+    if constexpr (EPI == EPI_STORE_BF16) gemm_nt<AM, EPI, 64, BT><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+  }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if constexpr (EPI != EPI_PROJECTED)
     if (split) splitk_finish<EPI><<<dim3((unsigned)std::min<int64_t>(ceil_div(most, 256), 4096), (unsigned)g.n), 256, 0, s>>>(g);
   return hipGetLastError();
 }
 
-// the forms of A that a caller has with each epilogue, and no others
-hipError_t launch_epi(GemmArgs& g, int a_f32, int epi, int tm, hipStream_t s) {
+// the forms of the operands that a caller has with each epilogue, and no others
+hipError_t launch_epi(GemmArgs& g, int a_f32, int epi, bool bt, int tm, hipStream_t s) {
   switch (epi) {
     case EPI_STORE_BF16:
-      if (a_f32 == 0) return launch_group<0, EPI_STORE_BF16>(g, tm, s);
+      if (a_f32 == 0) return bt ? launch_group<0, EPI_STORE_BF16, true>(g, tm, s) : launch_group<0, EPI_STORE_BF16, false>(g, tm, s);
       break;
     case EPI_STORE_F32:
-      if (a_f32 == 0) return launch_group<0, EPI_STORE_F32>(g, tm, s);
-      if (a_f32 == 1) return launch_group<1, EPI_STORE_F32>(g, tm, s);
+      if (a_f32 == 0) return bt ? launch_group<0, EPI_STORE_F32, true>(g, tm, s) : launch_group<0, EPI_STORE_F32, false>(g, tm, s);
+      if (a_f32 == 1) return bt ? launch_group<1, EPI_STORE_F32, true>(g, tm, s) : launch_group<1, EPI_STORE_F32, false>(g, tm, s);
       break;
     case EPI_PROJECTED:
-      if (a_f32 == 1) return launch_group<1, EPI_PROJECTED>(g, tm, s);
+      if (a_f32 == 1 && !bt) return launch_group<1, EPI_PROJECTED, false>(g, tm, s);
       break;
     case EPI_SCATTER:
-      if (a_f32 == 0) return launch_group<0, EPI_SCATTER>(g, tm, s);
-      if (a_f32 == 1) return launch_group<1, EPI_SCATTER>(g, tm, s);
-      if (a_f32 == 2) return launch_group<2, EPI_SCATTER>(g, tm, s);
+      if (bt) break;
+      if (a_f32 == 0) return launch_group<0, EPI_SCATTER, false>(g, tm, s);
+      if (a_f32 == 1) return launch_group<1, EPI_SCATTER, false>(g, tm, s);
+      if (a_f32 == 2) return launch_group<2, EPI_SCATTER, false>(g, tm, s);
       break;
   }
   return hipErrorInvalidValue;
@@ -580,6 +651,12 @@ int64_t rows_expected(int64_t M, int epi) {
 }
 constexpr int kMaxSplits = 32;
 
+// Images of fewer 128-row tiles than units run on tiles of 64 rows.  Alone in their launch, they are cut until the chip is
+// full, and what the parts write and the sums read back is a good part of the time: half the rows, half the parts.  4096 x
+// 4096 x 256: eight parts of 32 tiles 19.5 + 7.7 us behind a transposition of 4.8, four of 64 tiles 22.2 + 5.4 with the
+// transposition inside.
+bool image_rows64(int64_t M, int64_t N) { return ceil_div(M, 128) * ceil_div(N, BN) < kUnits; }
+
 }  // namespace
 
 // The split is a property of the product alone, so that a product gives the same bits in whatever launch it runs (the
@@ -589,7 +666,7 @@ constexpr int kMaxSplits = 32;
 // tiles (less than an eighth of the units) that even their parts are less than a quarter of the chip, and image builds,
 // which are alone in their launch, are cut further, down to 512 columns.  Measured, GEMM + sums of the partials: projections of a block, 2048 tokens:
 // parts of 4096 columns 85 + 7 us, 2048: 91 + 15, 1024: 108 + 25; the projections of the pair at 333 tokens 105 + 5, 59 + 5,
-// 34 + 5; an image of 4096 x 4096 x 256: 57, 33 + 6, 22 + 7.
+// 34 + 5; an image of 4096 x 4096 x 256: 57, 33 + 6, 22 + 7 (on tiles of 128 rows).
 // Products of up to half the units are cut again while their parts fit the chip at once, down to 1024 columns (512 for an
 // eighth of the units): a workgroup takes 0.75 us per 64 columns, 1.5 us with a two-term operand, however few there are.  In
 // eight at most; a two-term contraction of 8192 columns and more even beyond the chip.  Scatter products of more than one row
@@ -611,6 +688,12 @@ int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool two_term, WsLevel
   if (tiles < kUnits) s = (int)std::min<int64_t>(ceil_div(nk, kMaxDepth), kMaxSplits);
   const int64_t want = epi == EPI_STORE_BF16 ? kUnits : tiles < kUnits / 8 ? kUnits / 4 : 0;
   while (s * 2 <= kMaxSplits && tiles * s < want && nk / (s * 2) >= kMinDepth) s *= 2;
+  if (epi == EPI_STORE_BF16 && image_rows64(M, N)) {  // (never more parts than tiles of 128 rows had)
+    const int64_t tiles64 = ceil_div(M, 64) * ceil_div(N, BN);
+    int t = 1;
+    while (t < s && tiles64 * t < kUnits) t *= 2;
+    return std::min(s, t);
+  }
   if (level == kWsCoarse || epi == EPI_STORE_BF16 || (epi == EPI_COEFF && !two_term)) return s;
   const bool shares = (epi == EPI_SCATTER_ADD || epi == EPI_SCATTER_STORE) && m > 128;
   const int64_t room = two_term && nk >= 2 * kMaxDepth ? 2 * kUnits : kUnits;
@@ -643,6 +726,7 @@ namespace {
 int plan_rows(const GemmArgs& g, int epi) {
   // (the norm shares of a residual are per 64 columns with tiles of 128 rows, per 128 with 256)
   if (epi == EPI_PROJECTED) return g.p[0].res_cols == 64 ? 128 : 256;
+  if (epi == EPI_STORE_BF16 && image_rows64(g.p[0].M, g.p[0].N)) return 64;  // (a launch holds one image)
   double cost[2];
   for (int t = 0; t < 2; ++t) {
     const int tm = t ? 128 : 256;
@@ -661,7 +745,7 @@ int plan_rows(const GemmArgs& g, int epi) {
 
 }  // namespace
 
-hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s) {
+hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s, bool b_rows) {
   GemmArgs g;
   int i = 0;
   while (i < n) {
@@ -681,7 +765,7 @@ hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStr
       return (int64_t)x.K * y.splits > (int64_t)y.K * x.splits;
     });
     const int tm = plan_rows(g, epi);
-    if (hipError_t e = launch_epi(g, a_f32, epi, tm, s); e != hipSuccess) return e;
+    if (hipError_t e = launch_epi(g, a_f32, epi, b_rows, tm, s); e != hipSuccess) return e;
   }
   return hipSuccess;
 }
