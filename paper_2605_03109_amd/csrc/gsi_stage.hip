@@ -57,6 +57,17 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return v;
 }
 
+// ... of three values at once, each in the same order
+__device__ __forceinline__ void wave_sum3_f64(double& x, double& y, double& z) {
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const double a = __shfl_xor(x, o, kWave), b = __shfl_xor(y, o, kWave), c = __shfl_xor(z, o, kWave);
+    x += a;
+    y += b;
+    z += c;
+  }
+}
+
 // Eq. (gate) from the single-pass shares of one input: gw = [slabs shares of |x|^2][kGramBlocks shares of
 // c^T E c][|c|^2].  Called by whole waves: the lanes load the shares side by side (a few memory latencies in all,
 // not one per share), the sums run in a fixed order (lane-strided, then a butterfly over the wave), so every wave
@@ -64,12 +75,11 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 __device__ __forceinline__ bool single_pass_gate(const double* __restrict__ gw, int slabs, float eps, float& rn,
                                                  float& xn) {
   const int lane = threadIdx.x % kWave;
-  double a = 0.0;
-  for (int s = lane; s < slabs; s += kWave) a += gw[s];
+  double x2 = 0.0;
   const double v = lane < kGramBlocks + kC2Shares ? gw[slabs + lane] : 0.0;
-  const double x2 = wave_sum_f64(a);
-  const double q = wave_sum_f64(lane < kGramBlocks ? v : 0.0);
-  const double c2 = wave_sum_f64(lane >= kGramBlocks ? v : 0.0);
+  for (int s = lane; s < slabs; s += kWave) x2 += gw[s];
+  double q = lane < kGramBlocks ? v : 0.0, c2 = lane >= kGramBlocks ? v : 0.0;
+  wave_sum3_f64(x2, q, c2);
   const double r2 = x2 - c2 + q;
   rn = (float)sqrt(r2 > 0.0 ? r2 : 0.0);
   xn = (float)sqrt(x2);
@@ -538,17 +548,21 @@ __global__ __launch_bounds__(kBlock) void one_residual(const StageRes p, float* 
 }
 
 // ---- the same stages over a table in device memory (many inputs, single-pass gate) ------------------------------
-// first-workgroup table of n tasks staged in LDS, then a binary search: the task that holds workgroup b
-__device__ __forceinline__ int find_in_table(const int* __restrict__ begin, int n, int b, int* __restrict__ sh) {
-  for (int i = threadIdx.x; i < n; i += kBlock) sh[i] = begin[i];
-  __syncthreads();
-  int lo = 0, hi = n - 1;  // begin[0] = 0 <= b
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (sh[mid] <= b) lo = mid;
-    else hi = mid - 1;
+// The task that holds workgroup b, from the first-workgroup table of n <= 4096 tasks (ascending, begin[0] = 0): every wave
+// compares 64 entries spread over the table, then the entries between two of them; two loads, no LDS and no barrier.
+// first: the task's first workgroup.
+__device__ __forceinline__ int find_in_table(const int* __restrict__ begin, int n, int b, int& first) {
+  const int lane = threadIdx.x % kWave;
+  const int step = (n + kWave - 1) / kWave;
+  int base = 0, v = begin[min(lane * step, n - 1)];
+  int q = __popcll(__ballot(lane * step < n && v <= b)) - 1;
+  if (step > 1) {  // uniform
+    base = q * step;
+    v = begin[min(base + lane, n - 1)];
+    q = __popcll(__ballot(lane < step && base + lane < n && v <= b)) - 1;
   }
-  return __builtin_amdgcn_readfirstlane(lo);
+  first = __builtin_amdgcn_readlane(v, q);
+  return __builtin_amdgcn_readfirstlane(base + q);
 }
 
 template <class T, bool NT>
@@ -557,15 +571,15 @@ __global__ __launch_bounds__(kBlock) void table_partial(const TabIn* __restrict_
   __shared__ __align__(16) float lds[kBlock * 8];
   __shared__ float xs[kStageMaxRows];
   __shared__ double dsh[2 * kWaves];
-  __shared__ int tab[kMaxTabIn];
   const int b = blockIdx.x;
-  const int i = find_in_table(pbegin, n_in, b, tab);
+  int first;
+  const int i = find_in_table(pbegin, n_in, b, first);
   const TabIn& in = ins[i];
   StagePart p;
   p.U = in.U; p.X = in.X; p.part_c = in.part_c; p.d = in.d; p.k_rows = in.k_rows;
   p.slabs_x = (in.slabs & 0xffff) | (((in.r_rows_x >> 16) & 0xf) << 16);
   p.x2_off = in.gw_off;
-  partial_block<T, NT>(p, b - tab[i], lds, xs, dsh);
+  partial_block<T, NT>(p, b - first, lds, xs, dsh);
 }
 
 // c = the partials added in slab order: a workgroup per (input, 64 columns); its four waves take every fourth slab
@@ -573,12 +587,12 @@ __global__ __launch_bounds__(kBlock) void table_partial(const TabIn* __restrict_
 __global__ __launch_bounds__(kBlock) void table_cred(const TabIn* __restrict__ ins, const int* __restrict__ cbegin,
                                                      int n_in) {
   __shared__ double sh[kWaves][kWave];
-  __shared__ int tab[kMaxTabIn];
-  const int i = find_in_table(cbegin, n_in, blockIdx.x, tab);
+  int first;
+  const int i = find_in_table(cbegin, n_in, blockIdx.x, first);
   const TabIn& in = ins[i];
   const int k = in.k_rows & 0xffff, slabs = in.slabs & 0xffff;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int cblk = blockIdx.x - tab[i];
+  const int cblk = blockIdx.x - first;
   const int j = cblk * kWave + lane;
   double s = 0.0;
   if (j < k) {
@@ -635,23 +649,23 @@ __global__ __launch_bounds__(kBlock) void table_rows(const TabIn* __restrict__ i
   __shared__ __align__(16) float lds[kBlock * 8];
   __shared__ float xs[kStageMaxRows];
   __shared__ float nr[kWaves], nx[kWaves];
-  __shared__ int tab[kMaxTabMaps];
-  int b = blockIdx.x;
+  int b = blockIdx.x, first;
   if (b >= r_total) {
     b -= r_total;
-    const int j = find_in_table(ibegin, n_maps, b, tab);
+    const int j = find_in_table(ibegin, n_maps, b, first);
     const TabMap& mp = maps[j];
-    if (mp.gw) {  // W x form of the slow path: a fired input's rows are left to the weight kernel
-      float rn, xn;
-      if (single_pass_gate(mp.gw, mp.slabs, eps, rn, xn)) return;
-    }
     ImgTask t;
     t.M = mp.M; t.Y = mp.Y; t.part_c = nullptr; t.C = mp.C; t.scale = mp.scale;
-    t.m = mp.m; t.k = mp.k; t.a_slabs = 0; t.blk_begin = tab[j];
-    image_block<T, kTabImgItems, NT>(t, b - t.blk_begin, lds);
+    t.m = mp.m; t.k = mp.k; t.a_slabs = 0; t.blk_begin = first;
+    const double* gw = mp.gw;
+    const int slabs = mp.slabs;
+    image_block<T, kTabImgItems, NT>(t, b - first, lds, [&]() {  // W x form of the slow path: a fired input's rows are the weight kernel's
+      float rn, xn;
+      return gw && single_pass_gate(gw, slabs, eps, rn, xn);
+    });
     return;
   }
-  const int i = find_in_table(rbegin, n_in, b, tab);
+  const int i = find_in_table(rbegin, n_in, b, first);
   const TabIn& in = ins[i];
   StageGate g;
   g.part_n = reinterpret_cast<const float*>(reinterpret_cast<const char*>(in.part_c) + in.gw_off);
@@ -663,7 +677,7 @@ __global__ __launch_bounds__(kBlock) void table_rows(const TabIn* __restrict__ i
   p.d = in.d; p.k_rows = (in.k_rows & 0xffff) | ((in.r_rows_x & 0xffff) << 16);
   p.slabs_x = (in.slabs >> 16) | ((in.slabs & 0xff) << 16) | (((in.r_rows_x >> 16) & 0xf) << 24);
   p.gate = 1;
-  residual_block<T>(p, &g, eps, b - tab[i], lds, xs, nr, nx);
+  residual_block<T>(p, &g, eps, b - first, lds, xs, nr, nx);
 }
 
 }  // namespace
