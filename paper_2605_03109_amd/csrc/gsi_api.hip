@@ -185,8 +185,9 @@ int gsi_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d,
   hipError_t e;
   if (wdtype == GSI_BF16 && mfma_image_ok(m, d, k) && aligned(W, 16) && aligned(U, 2) && aligned(M, 8)) {
     // matrix cores; the basis is transposed on its way to LDS, or, where its rows are no whole 8-byte pieces, once into the
-    // workspace
-    const bool as_stored = aligned(U, 8);
+    // workspace, and for large images too: every row tile pays for the first.  us, transposed first / as stored: 4096 x 4096 x
+    // 256 33 / 28, x 512 39 / 36; 16384 x 4096 x 256 55 / 55, x 512 78 / 82; 14720 x 4096 x 288 81 / 87.
+    const bool as_stored = aligned(U, 8) && gsi::mfma_image_work(m, k, d) <= 8192;
     gsi::TransposeTask tr{U, ws, (int)d, (int)k, 0};
     e = as_stored ? hipSuccess : gsi::mfma_transpose_bf16(&tr, 1, s);
     if (e == hipSuccess) {

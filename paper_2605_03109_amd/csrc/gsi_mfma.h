@@ -42,6 +42,8 @@ int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool two_term, WsLevel
 // ... and whether the split of a product over a device-side count of rows follows that count: the tiles of 128 rows that
 // mfma_splits (splits) expects, or 0.
 int mfma_follow(int64_t M, int64_t K, int epi, int splits, WsLevel level);
+// work of an image build: its tiles of 128 rows times its k-tiles
+inline int64_t mfma_image_work(int64_t m, int64_t k, int64_t d) { return ceil_div(m, 128) * ceil_div(k, 256) * ceil_div(d, 64); }
 size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, WsLevel level);
 
 // Products of one launch (n of any number; more than kMaxProbs take several launches).  a_f32: A is 0: bf16; 1: fp32, fed as

@@ -32,7 +32,7 @@
 // run on tiles of 128 rows, two workgroups per unit: one's epilogue beside the other's products.
 // A right operand that is N-contiguous in memory (U as the factor of W U and X U) is transposed on its way to LDS: a thread
 // has four columns of BKT / 8 rows, packs two rows into a word and writes four columns.  Where that costs more than it saves
-// (many row tiles of bf16 activations: mfma_project), or its rows are no whole 8-byte pieces, it is transposed once into
+// (many row tiles of bf16 activations: mfma_project; large images: gsi_build_image), or its rows are no whole 8-byte pieces, it is transposed once into
 // the workspace.  The six images of a block (4096 / 16384, rank 256): a launch of 5 us each less.
 #include <algorithm>
 
@@ -651,11 +651,11 @@ int64_t rows_expected(int64_t M, int epi) {
 }
 constexpr int kMaxSplits = 32;
 
-// Images of fewer 128-row tiles than units run on tiles of 64 rows.  Alone in their launch, they are cut until the chip is
-// full, and what the parts write and the sums read back is a good part of the time: half the rows, half the parts.  4096 x
-// 4096 x 256: eight parts of 32 tiles 19.5 + 7.7 us behind a transposition of 4.8, four of 64 tiles 22.2 + 5.4 with the
-// transposition inside.
-bool image_rows64(int64_t M, int64_t N) { return ceil_div(M, 128) * ceil_div(N, BN) < kUnits; }
+// Small images run on tiles of 64 rows: they are cut until the chip is full, and what the parts write and the sums read back is
+// a good part of the time: half the rows, half the parts.  us, tiles of 128 / 64 rows, at rank 64 and 256: 1024 x 1024
+// 15 / 13, 16 / 14; 2176 x 2176 17 / 15, 21 / 18; 4096 x 4096 20 / 22, 28 / 26; 4096 x 14720 39 / 50, 50 / 56; at rank 512, 1024 x 1024
+// 17 / 15, 2176 x 2176 22 / 28.
+bool image_rows64(int64_t M, int64_t N, int64_t K) { return mfma_image_work(M, N, K) <= 640; }
 
 }  // namespace
 
@@ -688,7 +688,7 @@ int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool two_term, WsLevel
   if (tiles < kUnits) s = (int)std::min<int64_t>(ceil_div(nk, kMaxDepth), kMaxSplits);
   const int64_t want = epi == EPI_STORE_BF16 ? kUnits : tiles < kUnits / 8 ? kUnits / 4 : 0;
   while (s * 2 <= kMaxSplits && tiles * s < want && nk / (s * 2) >= kMinDepth) s *= 2;
-  if (epi == EPI_STORE_BF16 && image_rows64(M, N)) {  // (never more parts than tiles of 128 rows had)
+  if (epi == EPI_STORE_BF16 && image_rows64(M, N, K)) {  // (never more parts than tiles of 128 rows had)
     const int64_t tiles64 = ceil_div(M, 64) * ceil_div(N, BN);
     int t = 1;
     while (t < s && tiles64 * t < kUnits) t *= 2;
@@ -726,7 +726,7 @@ namespace {
 int plan_rows(const GemmArgs& g, int epi) {
   // (the norm shares of a residual are per 64 columns with tiles of 128 rows, per 128 with 256)
   if (epi == EPI_PROJECTED) return g.p[0].res_cols == 64 ? 128 : 256;
-  if (epi == EPI_STORE_BF16 && image_rows64(g.p[0].M, g.p[0].N)) return 64;  // (a launch holds one image)
+  if (epi == EPI_STORE_BF16 && image_rows64(g.p[0].M, g.p[0].N, g.p[0].K)) return 64;  // (a launch holds one image)
   double cost[2];
   for (int t = 0; t < 2; ++t) {
     const int tm = t ? 128 : 256;

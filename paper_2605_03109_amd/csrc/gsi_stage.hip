@@ -261,18 +261,18 @@ __device__ __forceinline__ void cred_block(const StageCRed& p) {
 __device__ __forceinline__ double sum_partials_f64(const float* __restrict__ pc, int k, int slabs) {
   double s = 0.0;
   const float* __restrict__ lo = pc + (int64_t)slabs * k;
-  int sl = 0;
-  for (; sl + 16 <= slabs; sl += 16) {
+  for (int s0 = 0; s0 < slabs; s0 += 16) {  // sixteen slabs requested together (past the last, that one again)
     float h[16], l[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-      h[q] = pc[(int64_t)(sl + q) * k];
-      l[q] = lo[(int64_t)(sl + q) * k];
+      const int64_t at = (int64_t)min(s0 + q, slabs - 1) * k;
+      h[q] = pc[at];
+      l[q] = lo[at];
     }
 #pragma unroll
-    for (int q = 0; q < 16; ++q) s += (double)h[q] + (double)l[q];
+    for (int q = 0; q < 16; ++q)
+      if (s0 + q < slabs) s += (double)h[q] + (double)l[q];
   }
-  for (; sl < slabs; ++sl) s += (double)pc[(int64_t)sl * k] + (double)lo[(int64_t)sl * k];
   return s;
 }
 
