@@ -206,7 +206,7 @@ struct StagePart {        // partial projection c = U^T x of one input over row 
   float* part_c;          // [slabs][k]
   int d;
   int k_rows;             // k | rows per slab << 16
-  int slabs_x;            // slabs | xdtype << 16 | column blocks << 20 (0 or 1: whole rows)
+  int slabs_x;            // slabs | xdtype << 16 | log2 of the column blocks << 20 (0: whole rows)
   int x2_off;             // single-pass gate: byte offset from part_c of the slab shares of |x|^2 (doubles); else 0
 };
 
@@ -287,7 +287,7 @@ void stage_clear(StageArgs& a, float eps);
 // E (single-pass gate): the input's cached U^T U - I, else null
 // column blocks for the partial projections of a launch whose inputs have `slabs` row slabs together
 int stage_col_blocks(int slabs, int64_t k, int udtype);
-// ncb: column blocks (stage_col_blocks): more, narrower workgroups for small calls
+// ncb: column blocks, a power of two (stage_col_blocks): more, narrower workgroups for small calls
 void stage_add_part(StageArgs& a, const ProjTask& t, const float* E = nullptr, int ncb = 1);
 void stage_add_cred(StageArgs& a, const ProjTask& t, const float* E = nullptr);
 // returns its index; single-pass gate: the residual workgroups evaluate and publish the gate themselves

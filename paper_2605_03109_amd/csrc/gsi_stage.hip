@@ -100,13 +100,13 @@ __device__ __forceinline__ void partial_block(const StagePart& p, int local, flo
                                               float* __restrict__ xs, double* __restrict__ dsh) {
   constexpr int V = T::kVec;
   using S = typename T::storage;
-  // A small call splits the columns of U into ncb blocks of as many 16-byte pieces, give or take one (a workgroup then
+  // A small call splits the columns of U into 2^lcb blocks of as many 16-byte pieces, give or take one (a workgroup then
   // reads w-wide pieces of its rows), so that a few inputs still give the chip hundreds of workgroups; a large call takes
-  // whole rows (ncb = 1).
+  // whole rows (lcb = 0).
   const int d = p.d, k = p.k_rows & 0xffff, prow = p.k_rows >> 16;
-  const int slabs = p.slabs_x & 0xffff, ncb = max(1, (p.slabs_x >> 20) & 0xff);
+  const int slabs = p.slabs_x & 0xffff, lcb = (p.slabs_x >> 20) & 0xff;
   const int slab = local % slabs, cb = local / slabs;
-  const int p0 = cb * (k / V) / ncb, pieces = (cb + 1) * (k / V) / ncb - p0;
+  const int p0 = cb * (k / V) >> lcb, pieces = ((cb + 1) * (k / V) >> lcb) - p0;
   const int col0 = p0 * V, w = pieces * V;
   // lanes per row piece: the power of two that covers its 16-byte pieces, one wave at most.  Surplus lanes of a rank
   // that is none (k = 200: 25 of 32 lanes) repeat the last piece and are left out of the sums.
@@ -720,7 +720,7 @@ void stage_clear(StageArgs& a, float eps) {
 void stage_add_part(StageArgs& a, const ProjTask& t, const float* E, int ncb) {
   StagePart& p = a.a[a.na++];
   p.U = t.U; p.X = t.X; p.part_c = t.part_c;
-  p.d = t.d; p.k_rows = t.k | (t.s_rows << 16); p.slabs_x = t.s_slabs | (t.xdtype << 16) | (ncb << 20);
+  p.d = t.d; p.k_rows = t.k | (t.s_rows << 16); p.slabs_x = t.s_slabs | (t.xdtype << 16) | (__builtin_ctz(ncb) << 20);
   p.x2_off = E ? (int)(reinterpret_cast<char*>(t.part_n) - reinterpret_cast<char*>(t.part_c)) : 0;
 }
 
@@ -764,7 +764,7 @@ hipError_t stage_launch(StageArgs& a, int dtype, hipStream_t s, hipEvent_t e0, h
   int ta = 0, tb = 0, ti = 0;
   for (int i = 0; i < a.na; ++i) {
     a.a_begin[i] = ta;
-    ta += (a.a[i].slabs_x & 0xffff) * std::max(1, (a.a[i].slabs_x >> 20) & 0xff);
+    ta += (a.a[i].slabs_x & 0xffff) << ((a.a[i].slabs_x >> 20) & 0xff);
   }
   for (int i = 0; i < a.nb; ++i) {
     a.b_begin[i] = tb;
