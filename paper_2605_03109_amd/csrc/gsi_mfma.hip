@@ -252,6 +252,24 @@ __device__ __forceinline__ int parts_for(const GemmProb& g, int rows) {
   return min(g.splits, max(g.min_parts, fit));
 }
 
+// What an epilogue writes or reads once goes past the caches: a batch's rows of R and Y are far more than an XCD's L2 holds, at
+// most the fired ones are read again, and what they displaced were the operands of the tiles beside them.  The sums of the
+// parts and x likewise.  (C stays: the next launch reads it.)  us a call, before / now: a block of 2048 tokens at rank 512 725 / 685 (R and
+// Y alone 694), the pair at 333 tokens 150 / 142 (143); 2048 x 5120, rank 512, 1500 fp32 tokens 224 / 185.  Partial sums written
+// the same way: no difference.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_once(float* p, const float4& v) {
+  __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4*>(p));
+}
+__device__ __forceinline__ float4 load_once(const float* p) {
+  const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+  return float4{v[0], v[1], v[2], v[3]};
+}
+__device__ __forceinline__ uint2 load_once8(const uint16_t* p) {
+  const u32x2 v = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
+  return uint2{v[0], v[1]};
+}
+
 template <int AM, int EPI, int TM, bool BT>
 __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm_nt(const GemmArgs args) {
   using G = Geo<AM, TM, BT>;
@@ -453,9 +471,9 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
         x[q] = float4{0.f, 0.f, 0.f, 0.f};
         if (row[q] < Mrows && col < N) {
           if (g.xdtype == GSI_F32) {
-            x[q] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(g.X) + (int64_t)row[q] * ldd + col);
+            x[q] = load_once(reinterpret_cast<const float*>(g.X) + (int64_t)row[q] * ldd + col);
           } else {
-            const uint2 xb = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(g.X) + (int64_t)row[q] * ldd + col);
+            const uint2 xb = load_once8(reinterpret_cast<const uint16_t*>(g.X) + (int64_t)row[q] * ldd + col);
             x[q] = float4{bf16_lo(xb.x), bf16_hi(xb.x), bf16_lo(xb.y), bf16_hi(xb.y)};
           }
         }
@@ -466,7 +484,7 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
         const float4 r = float4{x[q].x - val[q].x, x[q].y - val[q].y, x[q].z - val[q].z, x[q].w - val[q].w};
         float sr = 0.f, sx = 0.f;
         if (live) {
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(Dmat) + (int64_t)row[q] * ldd + col) = r;
+          store_once(reinterpret_cast<float*>(Dmat) + (int64_t)row[q] * ldd + col, r);
           sr = fmaf(r.x, r.x, fmaf(r.y, r.y, fmaf(r.z, r.z, r.w * r.w)));
           sx = fmaf(x[q].x, x[q].x, fmaf(x[q].y, x[q].y, fmaf(x[q].z, x[q].z, x[q].w * x[q].w)));
         }
@@ -488,7 +506,9 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
             o.y = (uint32_t)f32_to_bf16_bits(val[q].z) | ((uint32_t)f32_to_bf16_bits(val[q].w) << 16);
             *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(Dmat) + (int64_t)row[q] * ldd + col) = o;
           } else if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_PROJECTED) {
-            *reinterpret_cast<float4*>(reinterpret_cast<float*>(Dmat) + (int64_t)row[q] * ldd + col) = val[q];
+            float* const dp = reinterpret_cast<float*>(Dmat) + (int64_t)row[q] * ldd + col;
+            if constexpr (EPI == EPI_PROJECTED) store_once(dp, val[q]);
+            else *reinterpret_cast<float4*>(dp) = val[q];
           } else {  // scatter: one workgroup owns an output element, so the update is ordered
             const int drow = g.row_idx ? g.row_idx[row[q]] : row[q];
             float4* dp = reinterpret_cast<float4*>(reinterpret_cast<float*>(Dmat) + (int64_t)drow * ldd + col);
@@ -531,7 +551,7 @@ __global__ __launch_bounds__(256) void splitk_finish(const GemmArgs args) {
     for (int z0 = 0; z0 < splits; z0 += 8) {
       float4 q[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) q[u] = *reinterpret_cast<const float4*>(src + (int64_t)min(z0 + u, splits - 1) * stride);
+      for (int u = 0; u < 8; ++u) q[u] = load_once(src + (int64_t)min(z0 + u, splits - 1) * stride);
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         if (z0 + u < splits) { s.x += q[u].x; s.y += q[u].y; s.z += q[u].z; s.w += q[u].w; }
