@@ -54,7 +54,8 @@ __device__ __forceinline__ float load_old(const float* p) {
 // (ld = d for a whole matrix W[m, d]; a block of columns of a longer row otherwise); xs = the staged vector
 // (d floats, LDS).
 // whole: the product replaces y (dense baseline, W x form of the slow path); else it is added to y.
-// TAIL: d / kVec is not a multiple of 64 * kLU (loads clamped, surplus products dropped).
+// TAIL: d / kVec is not a multiple of 64 * kLU (loads clamped, surplus products dropped).  It is a property of a launch, so both
+// forms add the same products in the same order: a row has the same bits beside whatever other maps.
 template <class T, bool TAIL, bool COHERENT, bool NT = false>
 __device__ __forceinline__ void stream_map_rows(const typename T::storage* __restrict__ W, float* __restrict__ Y,
                                                 int m, int d, int64_t ld, const float* __restrict__ xs, bool whole,
@@ -90,7 +91,7 @@ __device__ __forceinline__ void stream_map_rows(const typename T::storage* __res
           float w[V], xv[V];
           buf[q].widen(w);
           lds_vec<V>(xp + q * kWave * V, xv);
-          acc = dotv<V>(w, xv, acc);
+          acc += dotv<V>(w, xv, 0.f);
         }
         const bool last = sg == nseg - 1;
         const float sum = group_sum<kWave>(acc);
