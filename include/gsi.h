@@ -248,7 +248,9 @@ enum { GSI_MAP_IMAGE_FP8 = 1 };
  * input: gsi_project + gsi_gate once; for each map: gsi_gated_linear on its input's c, r and fired
  * list.  `maps` and `inputs` are HOST arrays (read during the call only).  Inputs with src_map >= 0
  * are processed after the map that produces them.  Results are identical to issuing the separate
- * calls in that order.  ws: gsi_layer_stack_workspace_bytes().
+ * calls in that order, bit for bit, but for one token's inputs with GSI_INPUT_GATE_SINGLE_PASS or GSI_INPUT_FUSED_KERNEL and
+ * for more than 16 of its inputs of one storage type at a time: their c is added up in another order.
+ * ws: gsi_layer_stack_workspace_bytes().
  * A map's Y may lie over the X of an external input (src_map -1): every X is read before it is overwritten.  Where the
  * maps read x as well (GSI_INPUT_SLOW_PATH_WX), a map whose Y lies over such an X runs behind the other maps; it may not lie
  * over the X of its own input then, nor two such maps over each other's.  With GSI_INPUT_FUSED_KERNEL and in a plan

@@ -1406,15 +1406,13 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
       for (int g = 0; g < nsets + 2 + sum_stage - (sp || inline_gate ? 1 : 0); ++g) {
         gsi::StageArgs a;
         gsi::stage_clear(a, eps);
-        {  // a set with few slabs splits the columns of its bases so that the launch still fills the chip
-          int total = 0;
-          for (int q = 0; q < set_size(g); ++q) total += ptask[member(g, q)].s_slabs;
-          for (int q = 0; q < set_size(g); ++q) {
-            const int i = member(g, q);
-            const int ncb = gsi::stage_col_blocks(total, inputs[i].k, dt);
-            part_ncb[i] = ncb;
-            gsi::stage_add_part(a, ptask[i], sp ? inputs[i].gram : nullptr, ncb);
-          }
+        int total = 0;
+        for (int q = 0; q < set_size(g); ++q) total += ptask[member(g, q)].s_slabs;
+        for (int q = 0; q < set_size(g); ++q) {
+          const int i = member(g, q);
+          part_ncb[i] = sum_stage ? gsi::stage_set_col_blocks(total, inputs[i].k, dt)
+                                  : gsi::stage_col_blocks(ptask[i].s_slabs, ptask[i].s_rows, inputs[i].k, dt);
+          gsi::stage_add_part(a, ptask[i], sp ? inputs[i].gram : nullptr, part_ncb[i]);
         }
         if (sum_stage)
           for (int q = 0; q < set_size(g - 1); ++q) {

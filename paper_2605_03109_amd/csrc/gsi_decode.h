@@ -285,8 +285,10 @@ static_assert(sizeof(StageArgs) <= 4096, "kernel arguments are limited to 4 KB")
 void stage_geom(int64_t d, int64_t k, int udtype, int& rows, int& slabs, bool fine = false);
 void stage_clear(StageArgs& a, float eps);
 // E (single-pass gate): the input's cached U^T U - I, else null
-// column blocks for the partial projections of a launch whose inputs have `slabs` row slabs together
-int stage_col_blocks(int slabs, int64_t k, int udtype);
+// column blocks for the partial projection of an input of `slabs` slabs of `rows` rows ...
+int stage_col_blocks(int slabs, int rows, int64_t k, int udtype);
+// ... and of the inputs of a launch, `slabs` slabs together, whose partials a sum stage adds
+int stage_set_col_blocks(int slabs, int64_t k, int udtype);
 // ncb: column blocks, a power of two (stage_col_blocks): more, narrower workgroups for small calls
 void stage_add_part(StageArgs& a, const ProjTask& t, const float* E = nullptr, int ncb = 1);
 void stage_add_cred(StageArgs& a, const ProjTask& t, const float* E = nullptr);

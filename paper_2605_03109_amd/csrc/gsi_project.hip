@@ -546,9 +546,8 @@ hipError_t decode_project_launch(ProjBatch& pb, int udtype, bool with_norms, boo
     // one token: the staged kernel, first the partial projections, then residuals
     StageArgs a;
     stage_clear(a, eps);
-    int slabs = 0;
-    for (int i = 0; i < pb.n; ++i) slabs += pb.t[i].s_slabs;
-    for (int i = 0; i < pb.n; ++i) stage_add_part(a, pb.t[i], nullptr, stage_col_blocks(slabs, pb.t[i].k, udtype));
+    for (int i = 0; i < pb.n; ++i)
+      stage_add_part(a, pb.t[i], nullptr, stage_col_blocks(pb.t[i].s_slabs, pb.t[i].s_rows, pb.t[i].k, udtype));
     if (hipError_t e = stage_launch(a, udtype, s); e != hipSuccess) return e;
     stage_clear(a, eps);
     for (int i = 0; i < pb.n; ++i) stage_add_res(a, pb.t[i], false);

@@ -701,15 +701,30 @@ void stage_geom(int64_t d, int64_t k, int udtype, int& rows, int& slabs, bool fi
   slabs = (int)ceil_div(d, rows);
 }
 
-// The columns of every basis of a launch are halved until the launch has a workgroup and a half per compute unit, or a
-// block would be narrower than 48 columns (96 bytes of a row in bf16).  A rank is cut between any two 16-byte pieces: a
-// block at rank 200, 32 slabs per input, in four blocks of 48 and 56 columns instead of one: the partial projections
-// 8.6 -> 6.4 us (rank 256, four blocks of 64: 6.1 us).
-int stage_col_blocks(int slabs, int64_t k, int udtype) {
-  const int V = udtype == GSI_BF16 ? 8 : 4;
+// Column blocks of a basis: it is halved, between any two 16-byte pieces of a row, while `more` asks for it and no block gets
+// narrower than 48 columns (96 bytes of a row in bf16).
+template <class More>
+static int halve_columns(int64_t k, int udtype, More more) {
+  const int64_t V = udtype == GSI_BF16 ? 8 : 4, pieces = k / V;
   int ncb = 1;
-  while (slabs * ncb < 384 && ncb < 128 && (k / V) / (ncb * 2) * V >= 48) ncb *= 2;
+  while (ncb < 128 && pieces / (ncb * 2) * V >= 48 && more(ncb, pieces / ncb)) ncb *= 2;
   return ncb;
+}
+
+// Until the input has 128 workgroups or nearly, and a workgroup no more than 64 KB of the basis: 4096 x 512 in four blocks, 16384 x 512
+// in eight.  The blocks fix the order of the sums, so they follow from the input alone: it has the same coefficients, bit for
+// bit, by itself and in any set.  us a call, whole rows / so: a block of 4096 / 16384 at rank 200 18.1 / 15.4, rank 512 (cut for
+// the launch as a whole, four blocks each) 26.2 / 25.5; the projection of 16384 x 512 24.6 / 17.9; 12 inputs of 4096 at rank 200
+// 15.2 / 16.2, 16 at rank 200 16.9 / 18.8, at 256 19.5 / 20.0, at 512 31.0 / 31.2.
+// (The order of the narrow blocks kept in whole rows, a thread with several groups of rows: 16.3, 18.0, 20.6, 32.2.)
+int stage_col_blocks(int slabs, int rows, int64_t k, int udtype) {
+  return halve_columns(k, udtype, [&](int ncb, int64_t pieces) { return slabs * ncb < 96 || rows * pieces * 16 > 65536; });
+}
+
+// Inputs whose partials a stage of its own adds (other slabs than those of gsi_project): until the launch, `slabs` slabs in all,
+// has a workgroup and a half per compute unit.  Eight blocks of bases 4096 / 16384 at rank 200: 53.1 us, 57.8 with the rule above.
+int stage_set_col_blocks(int slabs, int64_t k, int udtype) {
+  return halve_columns(k, udtype, [&](int ncb, int64_t) { return slabs * ncb < 384; });
 }
 
 void stage_clear(StageArgs& a, float eps) {
@@ -794,7 +809,7 @@ hipError_t stage_launch(StageArgs& a, int dtype, hipStream_t s, hipEvent_t e0, h
 hipError_t stage_project_one(const ProjTask& t, int dtype, hipStream_t s) {
   StageArgs a;  // (the records of the shared launches; only the first of each is set)
   a.na = a.nb = 0;
-  const int ncb = stage_col_blocks(t.s_slabs, t.k, dtype);
+  const int ncb = stage_col_blocks(t.s_slabs, t.s_rows, t.k, dtype);
   stage_add_part(a, t, nullptr, ncb);
   stage_add_res(a, t, false);
   if (dtype == GSI_BF16) {

@@ -6,9 +6,13 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-# widths of whole units of W r beside widths with a rest.  An image that is not 16-byte aligned has the projections run by
-# themselves.
-@pytest.mark.parametrize("k,dtype,widths", [(64, "bf16", (4096, 1024)), (64, "f32", (2048, 768))])
+# column blocks of a call of its own and fewer of them in a larger one: ranks that are cut evenly, raggedly (one piece more in
+# the last block: 264) and not at all; slabs whose rows fill the row groups, or do not (2576: 81 rows), a last slab of few rows
+# (4097); 16 inputs make whole rows, 64 KB of LDS at rank 512; widths of whole units of W r beside widths with a rest.  An
+# image that is not 16-byte aligned has the projections run by themselves.
+@pytest.mark.parametrize("k,dtype,widths", [
+    (200, "bf16", (4096, 1024)), (256, "bf16", (4096, 16384)), (512, "bf16", (4096, 2048)), (264, "bf16", (4097, 2576)),
+    (128, "bf16", (1032, 4096)), (64, "bf16", (4096, 1024)), (64, "f32", (2048, 768)), (256, "f32", (2048, 2577)), (252, "f32", (4096,)), (100, "f32", (1160,))])
 @pytest.mark.parametrize("n,odd_image", [(2, False), (4, False), (6, False), (9, False), (12, False), (16, False), (6, True), (16, True)])
 def test_stack_of_one_token(k, dtype, widths, n, odd_image):
     from paper_2605_03109_amd import gsi
