@@ -44,22 +44,41 @@ def hipcc() -> str:
 NO_SCRATCH = {"gsi_fused.hip": ("fused_token",), "gsi_stage.hip": ("proj_stage", "table_partial", "table_cred", "table_gram", "table_rows")}
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJ, os.path.basename(src).replace(".hip", ".o"))
+# Waves per SIMD that launches of these kernels count on: workgroups of a whole call resident at once.
+MIN_WAVES = {"gsi_stage.hip": {"proj_stage": 5, "one_partial": 5, "table_partial": 5, "table_rows": 6}}
+
+
+def check_resources(name: str, remarks: str) -> int:
+    """Holds the compiler's resource remarks of one source against NO_SCRATCH and MIN_WAVES; the kernels it looked at."""
+    scratch, waves = NO_SCRATCH.get(name, ()), MIN_WAVES.get(name, {})
+    kernel, seen = None, set()
+    for line in remarks.splitlines():
+        if "Function Name:" in line:
+            kernel = line.split("Function Name:")[1].split()[0]
+        elif kernel and "ScratchSize [bytes/lane]:" in line and any(w in kernel for w in scratch):
+            n = int(line.split("ScratchSize [bytes/lane]:")[1].split()[0])
+            seen.add(kernel)
+            if n != 0:
+                raise RuntimeError(f"{name}: kernel {kernel} spills registers ({n} bytes of scratch per lane)")
+        elif kernel and "Occupancy [waves/SIMD]:" in line:
+            n = int(line.split("Occupancy [waves/SIMD]:")[1].split()[0])
+            for w, want in waves.items():
+                if w in kernel:
+                    seen.add(kernel)
+                    if n < want:
+                        raise RuntimeError(f"{name}: kernel {kernel} runs {n} waves per SIMD instead of {want}")
+    return len(seen)
+
+
+def _compile(src: str, obj: str | None = None) -> str:
+    name = os.path.basename(src)
+    obj = obj or os.path.join(OBJ, name.replace(".hip", ".o"))
     cmd = [hipcc(), *HIPCC_FLAGS, "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")
-    want = NO_SCRATCH.get(os.path.basename(src))
-    if want:
-        name = None
-        for line in r.stderr.splitlines():
-            if "Function Name:" in line:
-                name = line.split("Function Name:")[1].strip()
-            elif "ScratchSize [bytes/lane]:" in line and name and any(w in name for w in want):
-                n = int(line.split("ScratchSize [bytes/lane]:")[1].split()[0])
-                if n != 0:
-                    raise RuntimeError(f"{src}: kernel {name} spills registers ({n} bytes of scratch per lane)")
+    if check_resources(name, r.stderr) == 0 and (name in NO_SCRATCH or name in MIN_WAVES):
+        raise RuntimeError(f"{src}: no resource remark of the kernels that are to be checked")
     return obj
 
 

@@ -258,25 +258,47 @@ __device__ __forceinline__ void cred_block(const StageCRed& p) {
 // a lane the 16-byte pieces lane, lane + 64, ... of it.
 // c_j to double precision: high and low parts of the slab partials ([slabs][k] each, low parts behind the high
 // parts), slab order fixed
-__device__ __forceinline__ double sum_partials_f64(const float* __restrict__ pc, int k, int slabs) {
+// AHEAD: sixteen slabs requested together (past the last, that one again), for launches of these sums alone.  In proj_stage
+// their registers would cost every role a wave per SIMD (107 instead of 88: a block of 5120 / 20480 at rank 256, explicit gate, 1280
+// workgroups: 19.7 -> 22.0 us), and a shorter batch of the kind is slower than the plain loop (single-pass gate, block of
+// 4096 / 16384 at rank 512, eight: 46.4 us, plain 42.0).
+template <bool AHEAD>
+__device__ __forceinline__ double sum_partials_f64(const float* __restrict__ pc, int j, int k, int slabs) {
   double s = 0.0;
-  const float* __restrict__ lo = pc + (int64_t)slabs * k;
-  for (int s0 = 0; s0 < slabs; s0 += 16) {  // sixteen slabs requested together (past the last, that one again)
-    float h[16], l[16];
+  if constexpr (AHEAD) {
+    for (int s0 = 0; s0 < slabs; s0 += 16) {
+      float h[16], l[16];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int64_t at = (int64_t)min(s0 + q, slabs - 1) * k;
-      h[q] = pc[at];
-      l[q] = lo[at];
+      for (int q = 0; q < 16; ++q) {  // (row addresses are uniform, a lane's offset is its column)
+        const int sl = min(s0 + q, slabs - 1);
+        h[q] = (pc + sl * k)[(unsigned)j];
+        l[q] = (pc + (slabs + sl) * k)[(unsigned)j];
+      }
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+        if (s0 + q < slabs) s += (double)h[q] + (double)l[q];
     }
+  } else {
+    pc += j;
+    const float* __restrict__ lo = pc + (int64_t)slabs * k;
+    int sl = 0;
+    for (; sl + 8 <= slabs; sl += 8) {
+      float h[8], l[8];
 #pragma unroll
-    for (int q = 0; q < 16; ++q)
-      if (s0 + q < slabs) s += (double)h[q] + (double)l[q];
+      for (int q = 0; q < 8; ++q) {
+        h[q] = pc[(int64_t)(sl + q) * k];
+        l[q] = lo[(int64_t)(sl + q) * k];
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s += (double)h[q] + (double)l[q];
+    }
+    for (; sl < slabs; ++sl) s += (double)pc[(int64_t)sl * k] + (double)lo[(int64_t)sl * k];
   }
   return s;
 }
 
 // c_ready: C already holds the sums (a launch before this one added the partials)
+template <bool AHEAD>
 __device__ __forceinline__ void gram_block(const StageCRed& p, double* __restrict__ gw, bool c_ready, int blk,
                                            float* __restrict__ cs, double* __restrict__ dsh) {
   const int k = p.k_slabs & 0xffff, slabs = p.k_slabs >> 16;
@@ -286,7 +308,7 @@ __device__ __forceinline__ void gram_block(const StageCRed& p, double* __restric
     for (int j = threadIdx.x; j < k; j += kBlock) cs[j] = p.C[j];
   } else {
     for (int j = threadIdx.x; j < k; j += kBlock) {
-      const double cd = sum_partials_f64(p.part_c + j, k, slabs);
+      const double cd = sum_partials_f64<AHEAD>(p.part_c, j, k, slabs);
       const float c = (float)cd;
       cs[j] = c;
       if (blk == 0) {
@@ -496,7 +518,7 @@ __global__ __launch_bounds__(kBlock) void proj_stage(const StageArgs a) {
   if (a.gram) {
     if (b < a.ncr * kGramBlocks) {
       const StageCRed& p = a.cr[b / kGramBlocks];
-      gram_block(p, reinterpret_cast<double*>(reinterpret_cast<char*>(const_cast<float*>(p.part_c)) + p.gw_off), false,
+      gram_block<false>(p, reinterpret_cast<double*>(reinterpret_cast<char*>(const_cast<float*>(p.part_c)) + p.gw_off), false,
                  b % kGramBlocks, lds, dsh);
     }
     return;
@@ -627,8 +649,10 @@ __global__ __launch_bounds__(kBlock) void table_cred(const TabIn* __restrict__ i
 }
 
 // merged: no launch added the partials before this one; every workgroup adds them itself (fixed order) and the first
-// of an input writes C and |c|^2
-__global__ __launch_bounds__(kBlock) void table_gram(const TabIn* __restrict__ ins, int merged) {
+// of an input writes C and |c|^2.  WAVES: per SIMD; with eight, fewer of the partials are requested together.  us a call from a plan, five /
+// eight waves: a block at rank 64 13.8 / 14.0, at rank 128 15.8 / 16.1, 32 layers at rank 64 (2048 workgroups) 40.1 / 38.9.
+template <int WAVES>
+__global__ __launch_bounds__(kBlock, WAVES) void table_gram(const TabIn* __restrict__ ins, int merged) {
   __shared__ __align__(16) float lds[kMaxK];
   __shared__ double dsh[2 * kWaves];
   const TabIn& in = ins[blockIdx.x / kGramBlocks];
@@ -636,7 +660,7 @@ __global__ __launch_bounds__(kBlock) void table_gram(const TabIn* __restrict__ i
   p.part_c = merged ? in.part_c : nullptr; p.C = in.C; p.E = in.E;
   p.k_slabs = (in.k_rows & 0xffff) | ((in.slabs & 0xffff) << 16);
   p.gw_off = 0;
-  gram_block(p, reinterpret_cast<double*>(reinterpret_cast<char*>(in.part_c) + in.gw_off), !merged, blockIdx.x % kGramBlocks,
+  gram_block<true>(p, reinterpret_cast<double*>(reinterpret_cast<char*>(in.part_c) + in.gw_off), !merged, blockIdx.x % kGramBlocks,
              lds, dsh);
 }
 
@@ -903,8 +927,13 @@ hipError_t stage_table_launch(const void* table, const StageTableGeom& g, float 
     table_cred<<<(unsigned)g.tc, kBlock, 0, s>>>(d_ins, d_cb, n_in);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
-  if (ev(1)) hipExtLaunchKernelGGL(table_gram, dim3((unsigned)n_in * kGramBlocks), dim3(kBlock), 0, s, e0, e1, 0, d_ins, g.merge);
-  else table_gram<<<(unsigned)n_in * kGramBlocks, kBlock, 0, s>>>(d_ins, g.merge);
+  auto gram = [&](auto kern) {
+    const unsigned grid = (unsigned)n_in * kGramBlocks;
+    if (ev(1)) hipExtLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, e0, e1, 0, d_ins, g.merge);
+    else kern<<<grid, kBlock, 0, s>>>(d_ins, g.merge);
+  };
+  if (g.merge && n_in * kGramBlocks <= 5 * 256) gram(table_gram<5>);  // (all resident with five waves)
+  else gram(table_gram<8>);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   // 3. gates, residuals of fired inputs, image rows
   const unsigned grid = (unsigned)(g.ti + g.tr);
