@@ -45,7 +45,11 @@ NO_SCRATCH = {"gsi_fused.hip": ("fused_token",), "gsi_stage.hip": ("proj_stage",
 
 
 # Waves per SIMD that launches of these kernels count on: workgroups of a whole call resident at once.
-MIN_WAVES = {"gsi_stage.hip": {"proj_stage": 5, "one_partial": 5, "table_partial": 5, "table_rows": 6}}
+MIN_WAVES = {
+    "gsi_stage.hip": {"proj_stage": 5, "one_partial": 5, "table_partial": 5, "table_rows": 6},
+    # two-term operand, tiles of 128 rows, no transposition: two workgroups of eight waves per compute unit
+    "gsi_mfma.hip": {f"gemm_ntILi1ELi{epi}ELi128ELb0E": 4 for epi in (1, 5, 6)},
+}
 
 
 def check_resources(name: str, remarks: str) -> int:

@@ -416,8 +416,15 @@ struct ImageRider {
   float* Y;
   int64_t m;
 };
-static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img, int n_img, int64_t B, bool with_gate,
-                               float eps, WsLevel level, hipStream_t s) {
+// Do the rows of R and Y of a call go past the caches?  If they, x and the weights, which are read beside them, are more than the
+// 256 MB of the memory-side cache (store_row in gsi_mfma.hip has both sides measured), and no Y is the input of another
+// projection of the call.
+static bool passes_caches(int64_t bytes) { return bytes > (256ll << 20); }
+static int64_t rows_bytes(int64_t B, int64_t n) { return B * n * 4; }           // ... of R or Y
+static int64_t weight_bytes(int64_t m, int64_t d) { return m * d * 2; }         // (bf16)
+// map_bytes: weights and Y of the maps that read the inputs; again: a projection of the call reads one of these Y
+static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img, int n_img, int64_t map_bytes, bool again,
+                               int64_t B, bool with_gate, float eps, WsLevel level, hipStream_t s) {
   static thread_local std::vector<gsi::TransposeTask> tr;
   static thread_local std::vector<gsi::GemmProb> pr;
   // The basis is transposed on its way to LDS, which a k-tile pays for with more and smaller loads; bf16 activations of many
@@ -447,6 +454,9 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
       return e;
   }
   pr.clear();
+  int64_t bytes = map_bytes;
+  for (int i = 0; i < n; ++i) bytes += rows_bytes(B, in[i].d) + B * in[i].d * (int64_t)gsi::elem_size(in[i].xdtype);
+  const int once = again || !passes_caches(bytes) ? 0 : map_bytes > 0 ? 2 : 1;
   for (int i = 0; i < n; ++i) {
     gsi::GemmProb g = gemm_prob(in[i].C, in[i].k, in[i].U, in[i].k, in[i].R, in[i].d, B, in[i].d, in[i].k, gsi::EPI_RESIDUAL);
     g.X = in[i].X; g.xdtype = in[i].xdtype;
@@ -458,7 +468,7 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
         pr.push_back(gemm_prob(in[i].C, in[i].k, img[q].M, in[i].k, img[q].Y, img[q].m, B, img[q].m, in[i].k, gsi::EPI_STORE_F32));
   }
   for (gsi::GemmProb& g : pr) g.res_cols = gsi::mfma_res_cols(level);
-  if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), 1, gsi::EPI_PROJECTED, s); e != hipSuccess) return e;
+  if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), 1, gsi::EPI_PROJECTED, s, false, once); e != hipSuccess) return e;
   for (int i = 0; i < n;) {
     gsi::ProjBatch pb;
     std::memset(&pb, 0, sizeof(pb));
@@ -497,6 +507,7 @@ struct MfmaMap {
   float* Y;
   float* part;
   bool image_done;
+  bool again;        // Y is the input of another projection of the call
 };
 static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, WsLevel level, hipStream_t s) {
   static thread_local std::vector<gsi::GemmProb> pr;
@@ -505,6 +516,14 @@ static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, WsLevel level,
     if (!mp[j].image_done)
       pr.push_back(gemm_prob(mp[j].C, mp[j].k, mp[j].M, mp[j].k, mp[j].Y, mp[j].m, B, mp[j].m, mp[j].k, gsi::EPI_STORE_F32));
   if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), 1, gsi::EPI_STORE_F32, s); e != hipSuccess) return e;
+  int64_t bytes = 0;
+  bool again = false;
+  for (int j = 0; j < n; ++j) {
+    again |= mp[j].again;
+    bytes += weight_bytes(mp[j].m, mp[j].d) + rows_bytes(B, mp[j].m);
+    if (j == 0 || mp[j].R != mp[j - 1].R) bytes += rows_bytes(B, mp[j].d);
+  }
+  const int once = !again && passes_caches(bytes) ? 1 : 0;
   // r enters rounded once to bf16 (mode 2): its term is scaled by the residual ratio, so the rounding (2^-9 relative)
   // adds a few 1e-4 of |y| at most, beside the 1.7e-3 that the bf16 image already costs
   for (int mode = 0; mode < 3; ++mode) {
@@ -520,7 +539,7 @@ static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, WsLevel level,
       g.part = g.max_splits > 1 || g.row_tiles ? q.part : nullptr;
       pr.push_back(g);
     }
-    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), mode, gsi::EPI_SCATTER, s); e != hipSuccess) return e;
+    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), mode, gsi::EPI_SCATTER, s, false, once); e != hipSuccess) return e;
   }
   return hipSuccess;
 }
@@ -659,7 +678,7 @@ int gsi_project(const void* U, const void* X, int64_t d, int64_t k, int64_t B, i
     e = gsi::decode_project_launch(pb, udtype, true, false, 0.f, s);
   } else if (mfma_project_path(U, X, d, k, B, udtype, xdtype, C, R)) {
     const MfmaInput in{U, X, d, k, xdtype, C, R, rnorm, xnorm, nullptr, nullptr, nullptr, static_cast<char*>(ws)};
-    e = mfma_project(&in, 1, nullptr, 0, B, false, 0.f, level, s);
+    e = mfma_project(&in, 1, nullptr, 0, 0, false, B, false, 0.f, level, s);
   } else {
     e = gsi::generic_project(U, X, d, k, B, udtype, xdtype, C, R, rnorm, xnorm, s);
   }
@@ -703,7 +722,7 @@ int gsi_gated_linear(const void* W, const void* M, const float* C, const float* 
     e = bt.add(0, gd, W, M, (float*)Y, m, false, gsi::tile_part_bytes(m, d, B) ? (float*)ws : nullptr);
     if (e == hipSuccess) e = bt.flush();
   } else if (mfma_gated_path(W, M, C, R, d, k, B, wdtype, m, Y)) {
-    const MfmaMap mp{W, M, C, R, nullptr, 0, fired_idx, n_fired, m, d, k, (float*)Y, (float*)ws, false};
+    const MfmaMap mp{W, M, C, R, nullptr, 0, fired_idx, n_fired, m, d, k, (float*)Y, (float*)ws, false, false};
     e = mfma_gated(&mp, 1, B, level, s);
   } else {
     e = gsi::generic_gated_linear(W, M, C, R, fired_idx, n_fired, m, d, k, B, wdtype, (float*)Y, s);
@@ -1195,6 +1214,11 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
     for (int j = 0; j < n_maps && !wave_x.v.empty(); ++j) late[j] = wave_x.under(maps[j], B);
   }
   auto may_ride = [&](int j) { return plan || !(late[j] || wave_x.under(maps[j], B)); };
+  auto read_again = [&](int j) {
+    for (int i = 0; i < n_inputs; ++i)
+      if (inputs[i].src_map == j) return true;
+    return false;
+  };
   while (remaining > 0) {
     int progressed = 0;
     std::vector<int>& ready = sc.ready;
@@ -1460,12 +1484,17 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
       static thread_local std::vector<ImageRider> riders;
       min.clear();
       riders.clear();
+      int64_t map_bytes = 0;
+      bool again = false;
       for (int i : ready) {
         const gsi_input_desc& in = inputs[i];
         if (mode[i] != kGeneric || !mfma_project_path(in.U, in.X, in.d, in.k, B, in.udtype, in.xdtype, in.C, in.R)) continue;
         for (int j = 0; j < n_maps; ++j) {
           const gsi_map_desc& mp = maps[j];
-          if (mp.input_id != i || img_done[j]) continue;
+          if (mp.input_id != i) continue;
+          map_bytes += weight_bytes(mp.m, in.d) + rows_bytes(B, mp.m);
+          again |= read_again(j);
+          if (img_done[j]) continue;
           if (!mfma_gated_path(mp.W, mp.M, in.C, in.R, in.d, in.k, B, mp.wdtype, mp.m, mp.Y) || !wx_vector_ok(in) ||
               !may_ride(j))
             continue;
@@ -1476,7 +1505,8 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
                                 in.n_fired, reinterpret_cast<char*>(ws) + ws_off[i]});
       }
       if (!min.empty())
-        if (hipError_t e = mfma_project(min.data(), (int)min.size(), riders.data(), (int)riders.size(), B, true, eps, level, s);
+        if (hipError_t e = mfma_project(min.data(), (int)min.size(), riders.data(), (int)riders.size(), map_bytes, again, B,
+                                        true, eps, level, s);
             e != hipSuccess)
           return hip_fail(e, fn);
     }
@@ -1630,7 +1660,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
             !wx_vector_ok(in))
           continue;
         mm.push_back(MfmaMap{mp.W, mp.M, in.C, in.R, (in.flags & GSI_INPUT_SLOW_PATH_WX) ? in.X : nullptr, in.xdtype, in.fired_idx,
-                             in.n_fired, mp.m, in.d, in.k, mp.Y, part[j], img_done[j] != 0});
+                             in.n_fired, mp.m, in.d, in.k, mp.Y, part[j], img_done[j] != 0, read_again(j)});
         map_done[j] = 2;
       }
       if (!mm.empty())

@@ -50,7 +50,8 @@ size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, WsLevel level);
 // bf16 head + tail (two passes); 2: fp32, rounded once to bf16.  epi: EPI_STORE_BF16 (A bf16), EPI_STORE_F32 (bf16 or head +
 // tail), EPI_PROJECTED (head + tail) or EPI_SCATTER; every problem's own epi belongs to it.
 // b_rows: B is stored [K, N] (ldb elements a row, whole 8-byte pieces) and transposed on its way (EPI_STORE_BF16, EPI_STORE_F32).
-hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s, bool b_rows = false);
+// once: EPI_PROJECTED and EPI_SCATTER: the rows of D go past the caches (1), x of a residual too (2).
+hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s, bool b_rows = false, int once = 0);
 
 // Ut[j][i] = U[i][j] for n bf16 matrices U[rows, cols]
 struct TransposeTask {

@@ -252,25 +252,35 @@ __device__ __forceinline__ int parts_for(const GemmProb& g, int rows) {
   return min(g.splits, max(g.min_parts, fit));
 }
 
-// What an epilogue writes or reads once goes past the caches: a batch's rows of R and Y are far more than an XCD's L2 holds, at
-// most the fired ones are read again, and what they displaced were the operands of the tiles beside them.  The sums of the
-// parts and x likewise.  (C stays: the next launch reads it.)  us a call, before / now: a block of 2048 tokens at rank 512 725 / 685 (R and
-// Y alone 694), the pair at 333 tokens 150 / 142 (143); 2048 x 5120, rank 512, 1500 fp32 tokens 224 / 185.  Partial sums written
-// the same way: no difference.  The fired rows of Y, read and written by the W r products and their sums: 693 / 689, 142 / 139.
+// ONCE: how many of the rows of a launch go past the caches.  1: R and Y as they are written, the fired rows of Y and the partial
+// sums of a scatter product as they are read again; 2: x of a residual as well.  The calls that ask for it read more weights
+// and write more rows than the memory-side cache holds, and what the rows displaced were the operands of the tiles beside
+// them.  us a call, through the caches / past them: a block of 2048 tokens at rank 512, 410 fired 730 / 683; the pair 4096 / 16384, 200
+// tokens, 30 fired 129 / 114, 333 tokens, 50 fired 148 / 129.  Where all of it fits, the products of the fired rows find R and Y there:
+// 4096 x 4096, 1024 tokens that fire 112 / 124, a block of 1024 / 4096, 1000 tokens 126 / 138.  x goes past them where products of the
+// fired rows follow (the pair at 333 tokens 133 / 129, none fired 69 / 72), not in a projection by itself (16384 x 256, 4096 tokens 182 /
+// 193).  The partial sums of images and coefficients are read through the caches (11008 x 1024 x 512 41 / 47).
+// (A property of the launch and not of a problem: chosen at run time per row it took 1 to 2 %.)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void store_once(float* p, const float4& v) {
-  __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4*>(p));
+template <bool PAST>
+__device__ __forceinline__ void store_row(float* p, const float4& v) {
+  if constexpr (PAST) __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4*>(p));
+  else *reinterpret_cast<float4*>(p) = v;
 }
-__device__ __forceinline__ float4 load_once(const float* p) {
+template <bool PAST>
+__device__ __forceinline__ float4 load_row(const float* p) {
+  if constexpr (!PAST) return *reinterpret_cast<const float4*>(p);
   const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
   return float4{v[0], v[1], v[2], v[3]};
 }
-__device__ __forceinline__ uint2 load_once8(const uint16_t* p) {
+template <bool PAST>
+__device__ __forceinline__ uint2 load_row(const uint16_t* p) {
+  if constexpr (!PAST) return *reinterpret_cast<const uint2*>(p);
   const u32x2 v = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
   return uint2{v[0], v[1]};
 }
 
-template <int AM, int EPI, int TM, bool BT>
+template <int AM, int EPI, int TM, bool BT, int ONCE>
 __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm_nt(const GemmArgs args) {
   using G = Geo<AM, TM, BT>;
   constexpr int WTN = G::WTN, kBF = G::kBF;
@@ -471,9 +481,9 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
         x[q] = float4{0.f, 0.f, 0.f, 0.f};
         if (row[q] < Mrows && col < N) {
           if (g.xdtype == GSI_F32) {
-            x[q] = load_once(reinterpret_cast<const float*>(g.X) + (int64_t)row[q] * ldd + col);
+            x[q] = load_row<ONCE == 2>(reinterpret_cast<const float*>(g.X) + (int64_t)row[q] * ldd + col);
           } else {
-            const uint2 xb = load_once8(reinterpret_cast<const uint16_t*>(g.X) + (int64_t)row[q] * ldd + col);
+            const uint2 xb = load_row<ONCE == 2>(reinterpret_cast<const uint16_t*>(g.X) + (int64_t)row[q] * ldd + col);
             x[q] = float4{bf16_lo(xb.x), bf16_hi(xb.x), bf16_lo(xb.y), bf16_hi(xb.y)};
           }
         }
@@ -484,7 +494,7 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
         const float4 r = float4{x[q].x - val[q].x, x[q].y - val[q].y, x[q].z - val[q].z, x[q].w - val[q].w};
         float sr = 0.f, sx = 0.f;
         if (live) {
-          store_once(reinterpret_cast<float*>(Dmat) + (int64_t)row[q] * ldd + col, r);
+          store_row<ONCE != 0>(reinterpret_cast<float*>(Dmat) + (int64_t)row[q] * ldd + col, r);
           sr = fmaf(r.x, r.x, fmaf(r.y, r.y, fmaf(r.z, r.z, r.w * r.w)));
           sx = fmaf(x[q].x, x[q].x, fmaf(x[q].y, x[q].y, fmaf(x[q].z, x[q].z, x[q].w * x[q].w)));
         }
@@ -507,16 +517,15 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
             *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(Dmat) + (int64_t)row[q] * ldd + col) = o;
           } else if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_PROJECTED) {
             float* const dp = reinterpret_cast<float*>(Dmat) + (int64_t)row[q] * ldd + col;
-            if constexpr (EPI == EPI_PROJECTED) store_once(dp, val[q]);
-            else *reinterpret_cast<float4*>(dp) = val[q];
+            store_row<ONCE != 0>(dp, val[q]);
           } else {  // scatter: one workgroup owns an output element, so the update is ordered
             const int drow = g.row_idx ? g.row_idx[row[q]] : row[q];
-            float4* dp = reinterpret_cast<float4*>(reinterpret_cast<float*>(Dmat) + (int64_t)drow * ldd + col);
+            float* const dp = reinterpret_cast<float*>(Dmat) + (int64_t)drow * ldd + col;
             if (g.epi == EPI_SCATTER_STORE) {
-              store_once(reinterpret_cast<float*>(dp), val[q]);
+              store_row<ONCE != 0>(dp, val[q]);
             } else {
-              const float4 o = load_once(reinterpret_cast<const float*>(dp));
-              store_once(reinterpret_cast<float*>(dp), float4{o.x + val[q].x, o.y + val[q].y, o.z + val[q].z, o.w + val[q].w});
+              const float4 o = load_row<ONCE != 0>(dp);
+              store_row<ONCE != 0>(dp, float4{o.x + val[q].x, o.y + val[q].y, o.z + val[q].z, o.w + val[q].w});
             }
           }
         }
@@ -530,7 +539,7 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
 // Adds the partial sums of a split contraction in split order and applies the epilogue (store / scatter-add).
 // A thread owns four consecutive columns; the blocks stride over the live rows (a device-side count for the
 // scatter-add product), so the launch does not grow with rows that did not fire.
-template <int EPI>
+template <int EPI, int ONCE>
 __global__ __launch_bounds__(256) void splitk_finish(const GemmArgs args) {
   const GemmProb& g = args.p[blockIdx.y];
   if (g.splits <= 1 && !g.row_tiles) return;
@@ -551,7 +560,7 @@ __global__ __launch_bounds__(256) void splitk_finish(const GemmArgs args) {
     for (int z0 = 0; z0 < splits; z0 += 8) {
       float4 q[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) q[u] = load_once(src + (int64_t)min(z0 + u, splits - 1) * stride);
+      for (int u = 0; u < 8; ++u) q[u] = load_row<ONCE != 0>(src + (int64_t)min(z0 + u, splits - 1) * stride);
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         if (z0 + u < splits) { s.x += q[u].x; s.y += q[u].y; s.z += q[u].z; s.w += q[u].w; }
@@ -565,12 +574,12 @@ __global__ __launch_bounds__(256) void splitk_finish(const GemmArgs args) {
       *reinterpret_cast<float4*>(reinterpret_cast<float*>(g.D) + (int64_t)row * g.ldd + col) = s;
     } else {
       const int drow = g.row_idx ? g.row_idx[row] : row;
-      float4* dp = reinterpret_cast<float4*>(reinterpret_cast<float*>(g.D) + (int64_t)drow * g.ldd + col);
+      float* const dp = reinterpret_cast<float*>(g.D) + (int64_t)drow * g.ldd + col;
       if (g.epi == EPI_SCATTER_STORE) {
-        store_once(reinterpret_cast<float*>(dp), s);
+        store_row<ONCE != 0>(dp, s);
       } else {
-        const float4 o = load_once(reinterpret_cast<const float*>(dp));
-        store_once(reinterpret_cast<float*>(dp), float4{o.x + s.x, o.y + s.y, o.z + s.z, o.w + s.w});
+        const float4 o = load_row<ONCE != 0>(dp);
+        store_row<ONCE != 0>(dp, float4{o.x + s.x, o.y + s.y, o.z + s.z, o.w + s.w});
       }
     }
   }
@@ -613,7 +622,7 @@ __global__ __launch_bounds__(256) void transpose_bf16(const TransposeArgs a) {
   }
 }
 
-template <int AM, int EPI, bool BT>
+template <int AM, int EPI, bool BT, int ONCE = 0>
 hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
   int64_t blocks = 0;
   bool split = false;
@@ -630,20 +639,20 @@ hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
   }
   if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
   if (tm == 256) {
-    gemm_nt<AM, EPI, 256, BT><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+    gemm_nt<AM, EPI, 256, BT, ONCE><<<(unsigned)blocks, kThreads, 0, s>>>(g);
   } else if (tm == 128) {
-    gemm_nt<AM, EPI, 128, BT><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+    gemm_nt<AM, EPI, 128, BT, ONCE><<<(unsigned)blocks, kThreads, 0, s>>>(g);
   } else {
-    if constexpr (EPI == EPI_STORE_BF16) gemm_nt<AM, EPI, 64, BT><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+    if constexpr (EPI == EPI_STORE_BF16) gemm_nt<AM, EPI, 64, BT, ONCE><<<(unsigned)blocks, kThreads, 0, s>>>(g);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if constexpr (EPI != EPI_PROJECTED)
-    if (split) splitk_finish<EPI><<<dim3((unsigned)std::min<int64_t>(ceil_div(most, 256), 4096), (unsigned)g.n), 256, 0, s>>>(g);
+    if (split) splitk_finish<EPI, ONCE><<<dim3((unsigned)std::min<int64_t>(ceil_div(most, 256), 4096), (unsigned)g.n), 256, 0, s>>>(g);
   return hipGetLastError();
 }
 
 // the forms of the operands that a caller has with each epilogue, and no others
-hipError_t launch_epi(GemmArgs& g, int a_f32, int epi, bool bt, int tm, hipStream_t s) {
+hipError_t launch_epi(GemmArgs& g, int a_f32, int epi, bool bt, int once, int tm, hipStream_t s) {
   switch (epi) {
     case EPI_STORE_BF16:
       if (a_f32 == 0) return bt ? launch_group<0, EPI_STORE_BF16, true>(g, tm, s) : launch_group<0, EPI_STORE_BF16, false>(g, tm, s);
@@ -653,13 +662,14 @@ hipError_t launch_epi(GemmArgs& g, int a_f32, int epi, bool bt, int tm, hipStrea
       if (a_f32 == 1) return bt ? launch_group<1, EPI_STORE_F32, true>(g, tm, s) : launch_group<1, EPI_STORE_F32, false>(g, tm, s);
       break;
     case EPI_PROJECTED:
-      if (a_f32 == 1 && !bt) return launch_group<1, EPI_PROJECTED, false>(g, tm, s);
-      break;
+      if (a_f32 != 1 || bt) break;
+      if (once == 0) return launch_group<1, EPI_PROJECTED, false>(g, tm, s);
+      return once == 1 ? launch_group<1, EPI_PROJECTED, false, 1>(g, tm, s) : launch_group<1, EPI_PROJECTED, false, 2>(g, tm, s);
     case EPI_SCATTER:
       if (bt) break;
-      if (a_f32 == 0) return launch_group<0, EPI_SCATTER, false>(g, tm, s);
-      if (a_f32 == 1) return launch_group<1, EPI_SCATTER, false>(g, tm, s);
-      if (a_f32 == 2) return launch_group<2, EPI_SCATTER, false>(g, tm, s);
+      if (a_f32 == 0) return once ? launch_group<0, EPI_SCATTER, false, 1>(g, tm, s) : launch_group<0, EPI_SCATTER, false>(g, tm, s);
+      if (a_f32 == 1) return once ? launch_group<1, EPI_SCATTER, false, 1>(g, tm, s) : launch_group<1, EPI_SCATTER, false>(g, tm, s);
+      if (a_f32 == 2) return once ? launch_group<2, EPI_SCATTER, false, 1>(g, tm, s) : launch_group<2, EPI_SCATTER, false>(g, tm, s);
       break;
   }
   return hipErrorInvalidValue;
@@ -765,7 +775,7 @@ int plan_rows(const GemmArgs& g, int epi) {
 
 }  // namespace
 
-hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s, bool b_rows) {
+hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s, bool b_rows, int once) {
   GemmArgs g;
   int i = 0;
   while (i < n) {
@@ -785,7 +795,7 @@ hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStr
       return (int64_t)x.K * y.splits > (int64_t)y.K * x.splits;
     });
     const int tm = plan_rows(g, epi);
-    if (hipError_t e = launch_epi(g, a_f32, epi, b_rows, tm, s); e != hipSuccess) return e;
+    if (hipError_t e = launch_epi(g, a_f32, epi, b_rows, once, tm, s); e != hipSuccess) return e;
   }
   return hipSuccess;
 }
