@@ -40,12 +40,8 @@ __device__ __forceinline__ float sum_partials(const float* __restrict__ pc, int6
 
 // STREAM: the image is larger than the caches keep from one step to the next (many maps in one launch): its rows
 // are loaded non-temporally
-// skip: asked (uniformly) once the rows are requested: nothing is to be done after all
-struct NeverSkip {
-  __device__ __forceinline__ bool operator()() const { return false; }
-};
-template <class T, int ITEMS = kImgItemsPerBlock, bool STREAM = false, class Skip = NeverSkip>
-__device__ __forceinline__ void image_block_as(const ImgTask& t, int local_block, float* __restrict__ cs, Skip skip = Skip()) {
+template <class T, int ITEMS = kImgItemsPerBlock, bool STREAM = false>
+__device__ __forceinline__ void image_block_as(const ImgTask& t, int local_block, float* __restrict__ cs) {
   constexpr int kPerWave = ITEMS / 4;
   constexpr int V = T::kVec;
   using S = typename T::storage;
@@ -81,7 +77,6 @@ __device__ __forceinline__ void image_block_as(const ImgTask& t, int local_block
         rscale[it][u] = t.scale[row < m ? row : m - 1];
       }
   }
-  if (skip()) return;
   for (int j = threadIdx.x; j < k; j += 256) cs[j] = t.part_c ? sum_partials(t.part_c + j, k, t.a_slabs) : t.C[j];
   __syncthreads();
   float cvv[V];
@@ -110,10 +105,10 @@ __device__ __forceinline__ void image_block_as(const ImgTask& t, int local_block
 
 // T: storage of an image in the weights' dtype; a task with row scales holds E4M3 codes instead (Section 7,
 // "Combination with quantization").  The choice is uniform over the workgroup.
-template <class T, int ITEMS = kImgItemsPerBlock, bool STREAM = false, class Skip = NeverSkip>
-__device__ __forceinline__ void image_block(const ImgTask& t, int local_block, float* __restrict__ cs, Skip skip = Skip()) {
-  if (t.scale) image_block_as<FP8, ITEMS, STREAM>(t, local_block, cs, skip);
-  else image_block_as<T, ITEMS, STREAM>(t, local_block, cs, skip);
+template <class T, int ITEMS = kImgItemsPerBlock, bool STREAM = false>
+__device__ __forceinline__ void image_block(const ImgTask& t, int local_block, float* __restrict__ cs) {
+  if (t.scale) image_block_as<FP8, ITEMS, STREAM>(t, local_block, cs);
+  else image_block_as<T, ITEMS, STREAM>(t, local_block, cs);
 }
 
 // workgroups a map needs in an image launch

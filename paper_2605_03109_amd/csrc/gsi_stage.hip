@@ -683,15 +683,16 @@ __global__ __launch_bounds__(kBlock) void table_rows(const TabIn* __restrict__ i
     b -= r_total;
     const int j = find_in_table(ibegin, n_maps, b, first);
     const TabMap& mp = maps[j];
+    // W x form of the slow path: a fired input's rows are the weight kernel's, and its image is not read.  (Rows requested ahead of
+    // the gate: 0.7 us less for eight layers of which no input fires, 6 us more where all 32 fire: 502 / 508.)
+    if (mp.gw) {
+      float rn, xn;
+      if (single_pass_gate(mp.gw, mp.slabs, eps, rn, xn)) return;
+    }
     ImgTask t;
     t.M = mp.M; t.Y = mp.Y; t.part_c = nullptr; t.C = mp.C; t.scale = mp.scale;
     t.m = mp.m; t.k = mp.k; t.a_slabs = 0; t.blk_begin = first;
-    const double* gw = mp.gw;
-    const int slabs = mp.slabs;
-    image_block<T, kTabImgItems, NT>(t, b - first, lds, [&]() {  // W x form of the slow path: a fired input's rows are the weight kernel's
-      float rn, xn;
-      return gw && single_pass_gate(gw, slabs, eps, rn, xn);
-    });
+    image_block<T, kTabImgItems, NT>(t, b - first, lds);
     return;
   }
   const int i = find_in_table(rbegin, n_in, b, first);
