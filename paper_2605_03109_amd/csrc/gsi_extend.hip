@@ -544,15 +544,19 @@ __device__ __forceinline__ void image_rows_block(const ExtIn& in, const ExtWs& w
 }
 
 // What needs the stored column: workgroups of three kinds, told apart by their index: maps x img_wgs image rows, n bases x
-// col_wgs columns, n bases x (pcols x pslabs) partials of U^T u.
+// col_wgs columns, n bases x (pcols x pslabs) partials of U^T u.  The images go first, the launch lasts as long as they do; but
+// behind the others (images_last) where a basis whose rows are no whole 16-byte pieces has partials, which then take longest:
+// 4096 x 250 with three maps of 4096 rows 51.0 us behind the images, 49.7 ahead of them.
 struct ExtStore {
-  int col_wgs, pcols, pslabs, img_wgs, n, n_maps;
+  int col_wgs, pcols, pslabs, img_wgs, n, n_maps, images_last;
 };
 template <class T, bool TAB>
 __global__ __launch_bounds__(kBlock) void ext_store(const ExtArg a, const ExtMapArg ma, const ExtStore g) {
   __shared__ float sh[kWaves];
+  const int images = g.n_maps * g.img_wgs;
   int b = blockIdx.x;
-  if (b < g.n_maps * g.img_wgs) {  // the images first: the launch lasts as long as they do
+  if (g.images_last) b = b < (int)gridDim.x - images ? b + images : b - ((int)gridDim.x - images);
+  if (b < images) {
     const ExtMapRec p = TAB ? ma.tab[b / g.img_wgs] : ma.few[b / g.img_wgs];
     const int blk = b % g.img_wgs;
     if ((int64_t)blk * kImgRows >= p.m) return;
@@ -562,7 +566,7 @@ __global__ __launch_bounds__(kBlock) void ext_store(const ExtArg a, const ExtMap
     image_rows_block<T>(in, w, p, blk, g.img_wgs, sh);
     return;
   }
-  b -= g.n_maps * g.img_wgs;
+  b -= images;
   if (b < g.n * g.col_wgs) {
     const int blk = b % g.col_wgs;
     const ExtIn in = ext_record<TAB>(a, b / g.col_wgs);
@@ -654,6 +658,8 @@ hipError_t launch_all(const ExtIn* in, int n, const ExtMapRec* maps, int n_maps,
   ext_resid<T, TAB><<<dim3((unsigned)std::min<int64_t>(wgs_max, per_basis), (unsigned)n), kBlock, 0, s>>>(a);
   ExtStore g;
   g.n = n;
+  g.images_last = 0;
+  for (int i = 0; i < n; ++i) g.images_last |= in[i].gram && !in[i].uvec;
   g.col_wgs = (int)std::min<int64_t>(ceil_div(d_max, kBlock), std::max<int64_t>(1, per_basis / 8));
   g.pcols = any_gram ? (int)pgrid.x : 0;
   g.pslabs = any_gram ? (int)pgrid.y : 0;
