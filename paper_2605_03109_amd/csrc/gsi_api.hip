@@ -186,8 +186,9 @@ int gsi_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d,
   if (wdtype == GSI_BF16 && mfma_image_ok(m, d, k) && aligned(W, 16) && aligned(U, 2) && aligned(M, 8)) {
     // matrix cores; the basis is transposed on its way to LDS, or, where its rows are no whole 8-byte pieces, once into the
     // workspace, and for large images too: every row tile pays for the first.  us, transposed first / as stored: 4096 x 4096 x
-    // 256 33 / 28, x 512 39 / 36; 16384 x 4096 x 256 55 / 55, x 512 78 / 82; 14720 x 4096 x 288 81 / 87.
-    const bool as_stored = aligned(U, 8) && gsi::mfma_image_work(m, k, d) <= 8192;
+    // 256 28 / 25, 8192 x 4096 x 256 34 / 33 (the limit), 4096 x 4096 x 512 34 / 33 (the limit), 5120 x 4096 x 512 49 / 51, 11008 x
+    // 4096 x 128 42 / 44, 16384 x 4096 x 256 50 / 51, 11008 x 11008 x 256 127 / 136.
+    const bool as_stored = aligned(U, 8) && gsi::mfma_image_work(m, k, d) <= 4096;
     gsi::TransposeTask tr{U, ws, (int)d, (int)k, 0};
     e = as_stored ? hipSuccess : gsi::mfma_transpose_bf16(&tr, 1, s);
     if (e == hipSuccess) {
@@ -428,11 +429,16 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
   static thread_local std::vector<gsi::TransposeTask> tr;
   static thread_local std::vector<gsi::GemmProb> pr;
   // The basis is transposed on its way to LDS, which a k-tile pays for with more and smaller loads; bf16 activations of many
-  // tokens (whose operand needs no conversion, and whose row tiles are many) have it transposed once instead.  us, projection
-  // of one token batch over 4096 and 16384 columns with small maps, as stored / transposed first: rank 256, bf16, 200 tokens
-  // 53 / 57, 1024 101 / 101, 2048 168 / 162; rank 64, 2048 136 / 127; fp32, rank 256, 200 55 / 60, 1024 124 / 126,
-  // 2048 184 / 195.
-  auto as_stored = [&](int i) { return in[i].xdtype == GSI_F32 || B <= 1024; };
+  // tokens (whose operand needs no conversion, and whose row tiles are many) have it transposed once instead.  us, transposed first /
+  // as stored, bf16: one input of 16384 at rank 256, 512 tokens 59 / 57, 768 66 / 63, 1024 82 / 83, 2048 129 / 137; of 4096, 1500
+  // tokens 51 / 49, 4096 99 / 108; a block of 2048 / 8192, 1500 tokens 95 / 91, 2048 113 / 114; of 4096 / 16384, 768 tokens 100 / 94, 2048
+  // 197 / 200.  fp32: a block of 4096 / 16384 at rank 256, 200 tokens 63 / 57, 1024 155 / 145, 2048 258 / 219, at rank 512, 768 167 /
+  // 151, 2048 342 / 342; one input of 16384 at rank 64, 1024 94 / 95 (the worst; 4096 tokens 197 / 193).
+  int64_t longest = 0;
+  for (int i = 0; i < n; ++i)
+    if (in[i].xdtype != GSI_F32) longest = std::max(longest, in[i].d);
+  const bool bf16_stored = B <= (longest <= 8192 ? 1536 : 768);
+  auto as_stored = [&](int i) { return in[i].xdtype == GSI_F32 || bf16_stored; };
   tr.clear();
   for (int i = 0; i < n; ++i)
     if (!as_stored(i)) tr.push_back(gsi::TransposeTask{in[i].U, in[i].ws, (int)in[i].d, (int)in[i].k, 0});
@@ -450,7 +456,8 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
                                           gsi::align_up((size_t)gsi::mfma_res_tiles(d, level) * B * 2 * 4, 256));
       pr.push_back(g);
     }
-    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s, xdt == GSI_F32 || B <= 1024); e != hipSuccess)
+    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s, xdt == GSI_F32 || bf16_stored);
+        e != hipSuccess)
       return e;
   }
   pr.clear();
