@@ -244,7 +244,7 @@ def workspace(nbytes: int, device=None, stream=None) -> Optional[torch.Tensor]:
     return have
 
 
-@functools.lru_cache(maxsize=4096)  # (of the sizes alone; 0.1 us instead of 0.5 for a known call)
+@functools.lru_cache(maxsize=4096, typed=True)  # (of the sizes alone; 0.15 us instead of 1.1 for a known call; 4096.0 is refused behind 4096 too)
 def workspace_bytes(which: int, m: int = 0, d: int = 0, k: int = 0, B: int = 0) -> int:
     return int(lib.gsi_workspace_bytes(which, m, d, k, B))
 
