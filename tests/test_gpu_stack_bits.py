@@ -41,3 +41,28 @@ def test_stack_of_one_token(k, dtype, widths, n, odd_image):
         for a, b in ((C, t["C"]), (R, t["R"]), (rn, t["rnorm"]), (xn, t["xnorm"]), (mask, t["mask"]), (nf, t["n_fired"])):
             assert torch.equal(a, b)
         assert torch.equal(Y, mp["Y"])
+
+
+# many tokens: whether a basis is transposed first follows from the longest input of the call; the order of the sums does not
+@pytest.mark.parametrize("B,xdtype", [(900, "bf16"), (1600, "bf16"), (900, "f32")])
+def test_stack_of_many_tokens(B, xdtype):
+    from paper_2605_03109_amd import gsi
+
+    print(f"case stack bits {B} tokens {xdtype}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(B)
+    inputs, maps = [], []
+    for i, (d, k) in enumerate([(1024, 256), (8256, 64), (4096, 512)]):
+        U = (torch.randn(d, k, generator=g, device="cuda") / d**0.5).bfloat16()
+        W = (torch.randn(136, d, generator=g, device="cuda") / d**0.5).bfloat16()
+        X = torch.randn(B, d, generator=g, device="cuda").to({"bf16": torch.bfloat16, "f32": torch.float32}[xdtype])
+        inputs.append({"U": U, "X": X})
+        maps.append({"W": W, "M": (W.double() @ U.double()).bfloat16(), "input_id": i})
+    st = gsi.layer_stack(inputs, maps, B, 0.9)
+    torch.cuda.synchronize()
+    for t, mp in zip(st.inputs_t, st.maps_t):
+        C, R, rn, xn = gsi.project(t["U"], t["X"])
+        mask, idx, nf = gsi.gate(rn, xn, 0.9)
+        Y = gsi.gated_linear(mp["W"], mp["M"], C, R, idx, nf)
+        torch.cuda.synchronize()
+        for a, b in ((C, t["C"]), (R, t["R"]), (rn, t["rnorm"]), (xn, t["xnorm"]), (mask, t["mask"]), (Y, mp["Y"])):
+            assert torch.equal(a, b)
