@@ -185,10 +185,12 @@ int gsi_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d,
   hipError_t e;
   if (wdtype == GSI_BF16 && mfma_image_ok(m, d, k) && aligned(W, 16) && aligned(U, 2) && aligned(M, 8)) {
     // matrix cores; the basis is transposed on its way to LDS, or, where its rows are no whole 8-byte pieces, once into the
-    // workspace, and for large images too: every row tile pays for the first.  us, transposed first / as stored: 4096 x 4096 x
-    // 256 28 / 25, 8192 x 4096 x 256 34 / 33 (the limit), 4096 x 4096 x 512 34 / 33 (the limit), 5120 x 4096 x 512 49 / 51, 11008 x
-    // 4096 x 128 42 / 44, 16384 x 4096 x 256 50 / 51, 11008 x 11008 x 256 127 / 136.
-    const bool as_stored = aligned(U, 8) && gsi::mfma_image_work(m, k, d) <= 4096;
+    // workspace, and for large images too: every row tile pays for the first.  us, transposed first / as stored, weights that no
+    // cache holds: 4096 x 4096 x 256 30.8 / 27.7, x 512 36.3 / 34.7 (the first limit), 8192 x 4096 x 512 53.3 / 55.7, 11008 x 4096 x 64
+    // 43.5 / 47.3, x 128 47.7 / 50.5, x 256 57.8 / 58.3, 4096 x 11008 x 256 60.3 / 57.2, 16384 x 4096 x 64 47.4 / 50.0, x 256 62.7 / 60.0 (the
+    // second limit: a rank that all but fills the column tile; x 192 57.7 / 57.9), x 512 81.1 / 87.9.
+    const int64_t work = gsi::mfma_image_work(m, k, d);
+    const bool as_stored = aligned(U, 8) && (work <= 4096 || (work <= 8192 && k > 192 && k <= 256));
     gsi::TransposeTask tr{U, ws, (int)d, (int)k, 0};
     e = as_stored ? hipSuccess : gsi::mfma_transpose_bf16(&tr, 1, s);
     if (e == hipSuccess) {

@@ -18,7 +18,7 @@ def _basis(d, k, offset, g):
 # equal to and past a tile; bases that start 8 bytes (as stored) and 2 bytes (transposed first) off
 @pytest.mark.parametrize("m,d,k,offset", [
     (1, 64, 4, 0), (63, 4096, 60, 0), (65, 16384, 256, 0), (4096, 1024, 260, 4), (300, 10240, 512, 0), (16384, 512, 256, 0),
-    (16321, 320, 64, 4), (1024, 5120, 256, 0), (1025, 5120, 256, 4), (300, 13632, 300, 0), (16384, 4096, 256, 0), (16385, 4096, 256, 0), (8192, 4096, 256, 0), (8193, 4096, 256, 0), (33000, 192, 128, 0), (70000, 256, 256, 0), (65, 1024, 68, 1), (33000, 128, 64, 1)])
+    (16321, 320, 64, 4), (1024, 5120, 256, 0), (1025, 5120, 256, 4), (300, 13632, 300, 0), (16384, 4096, 256, 0), (16385, 4096, 256, 0), (8193, 4096, 64, 0), (8193, 4096, 192, 0), (8193, 4096, 200, 0), (33000, 192, 128, 0), (70000, 256, 256, 0), (65, 1024, 68, 1), (33000, 128, 64, 1)])
 def test_images(m, d, k, offset):
     from paper_2605_03109_amd import gsi
 
