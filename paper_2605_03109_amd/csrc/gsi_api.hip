@@ -430,6 +430,9 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
                                int64_t B, bool with_gate, float eps, WsLevel level, hipStream_t s) {
   static thread_local std::vector<gsi::TransposeTask> tr;
   static thread_local std::vector<gsi::GemmProb> pr;
+  int64_t bytes = map_bytes;
+  for (int i = 0; i < n; ++i) bytes += rows_bytes(B, in[i].d) + B * in[i].d * (int64_t)gsi::elem_size(in[i].xdtype);
+  const int once = again || !passes_caches(bytes) ? 0 : map_bytes > 0 ? 2 : 1;
   // The basis is transposed on its way to LDS, which a k-tile pays for with more and smaller loads; bf16 activations of many
   // tokens (whose operand needs no conversion, and whose row tiles are many) have it transposed once instead.  us, transposed first /
   // as stored, bf16: one input of 16384 at rank 256, 512 tokens 59 / 57, 768 66 / 63, 1024 82 / 83, 2048 129 / 137; of 4096, 1500
@@ -458,14 +461,11 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
                                           gsi::align_up((size_t)gsi::mfma_res_tiles(d, level) * B * 2 * 4, 256));
       pr.push_back(g);
     }
-    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s, xdt == GSI_F32 || bf16_stored);
+    if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s, xdt == GSI_F32 || bf16_stored, once == 2 ? 1 : 0);
         e != hipSuccess)
       return e;
   }
   pr.clear();
-  int64_t bytes = map_bytes;
-  for (int i = 0; i < n; ++i) bytes += rows_bytes(B, in[i].d) + B * in[i].d * (int64_t)gsi::elem_size(in[i].xdtype);
-  const int once = again || !passes_caches(bytes) ? 0 : map_bytes > 0 ? 2 : 1;
   for (int i = 0; i < n; ++i) {
     gsi::GemmProb g = gemm_prob(in[i].C, in[i].k, in[i].U, in[i].k, in[i].R, in[i].d, B, in[i].d, in[i].k, gsi::EPI_RESIDUAL);
     g.X = in[i].X; g.xdtype = in[i].xdtype;

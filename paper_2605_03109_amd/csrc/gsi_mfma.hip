@@ -259,7 +259,8 @@ __device__ __forceinline__ int parts_for(const GemmProb& g, int rows) {
 // tokens, 30 fired 129 / 114, 333 tokens, 50 fired 148 / 129.  Where all of it fits, the products of the fired rows find R and Y there:
 // 4096 x 4096, 1024 tokens that fire 112 / 124, a block of 1024 / 4096, 1000 tokens 126 / 138.  x goes past them where products of the
 // fired rows follow (the pair at 333 tokens 133 / 129, none fired 69 / 72), not in a projection by itself (16384 x 256, 4096 tokens 182 /
-// 193).  The partial sums of images and coefficients are read through the caches (11008 x 1024 x 512 41 / 47).
+// 193), and so do the partial sums of such a call's coefficients, as they are added (the same 126.1 / 123.7, rank 512 149.7 / 146.2; a block of
+// 2048 tokens, none fired, 408 / 411); those of images are read through the caches (11008 x 1024 x 512 41 / 47).
 // (A property of the launch and not of a problem: chosen at run time per row it took 1 to 2 %.)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <bool PAST>
@@ -624,6 +625,7 @@ __global__ __launch_bounds__(256) void transpose_bf16(const TransposeArgs a) {
 
 template <int AM, int EPI, bool BT, int ONCE = 0>
 hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
+  constexpr int R = EPI == EPI_STORE_F32 ? 0 : ONCE;  // (coefficients: the next launch reads them)
   int64_t blocks = 0;
   bool split = false;
   int64_t most = 0;
@@ -639,11 +641,11 @@ hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
   }
   if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
   if (tm == 256) {
-    gemm_nt<AM, EPI, 256, BT, ONCE><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+    gemm_nt<AM, EPI, 256, BT, R><<<(unsigned)blocks, kThreads, 0, s>>>(g);
   } else if (tm == 128) {
-    gemm_nt<AM, EPI, 128, BT, ONCE><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+    gemm_nt<AM, EPI, 128, BT, R><<<(unsigned)blocks, kThreads, 0, s>>>(g);
   } else {
-    if constexpr (EPI == EPI_STORE_BF16) gemm_nt<AM, EPI, 64, BT, ONCE><<<(unsigned)blocks, kThreads, 0, s>>>(g);
+    if constexpr (EPI == EPI_STORE_BF16) gemm_nt<AM, EPI, 64, BT, R><<<(unsigned)blocks, kThreads, 0, s>>>(g);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if constexpr (EPI != EPI_PROJECTED)
@@ -658,6 +660,11 @@ hipError_t launch_epi(GemmArgs& g, int a_f32, int epi, bool bt, int once, int tm
       if (a_f32 == 0) return bt ? launch_group<0, EPI_STORE_BF16, true>(g, tm, s) : launch_group<0, EPI_STORE_BF16, false>(g, tm, s);
       break;
     case EPI_STORE_F32:
+      if (once) {
+        if (a_f32 == 0) return bt ? launch_group<0, EPI_STORE_F32, true, 1>(g, tm, s) : launch_group<0, EPI_STORE_F32, false, 1>(g, tm, s);
+        if (a_f32 == 1) return bt ? launch_group<1, EPI_STORE_F32, true, 1>(g, tm, s) : launch_group<1, EPI_STORE_F32, false, 1>(g, tm, s);
+        break;
+      }
       if (a_f32 == 0) return bt ? launch_group<0, EPI_STORE_F32, true>(g, tm, s) : launch_group<0, EPI_STORE_F32, false>(g, tm, s);
       if (a_f32 == 1) return bt ? launch_group<1, EPI_STORE_F32, true>(g, tm, s) : launch_group<1, EPI_STORE_F32, false>(g, tm, s);
       break;
