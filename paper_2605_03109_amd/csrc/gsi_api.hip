@@ -419,10 +419,13 @@ struct ImageRider {
   float* Y;
   int64_t m;
 };
-// Do the rows of R and Y of a call go past the caches?  If they, x and the weights, which are read beside them, are more than the
-// 256 MB of the memory-side cache (store_row in gsi_mfma.hip has both sides measured), and no Y is the input of another
-// projection of the call.
-static bool passes_caches(int64_t bytes) { return bytes > (256ll << 20); }
+// Do the rows of R and Y of a call go past the caches?  If they, x and the weights, which are read beside them, leave the
+// 256 MB of the memory-side cache little room for anything else (store_row in gsi_mfma.hip has both sides of larger and of far
+// smaller calls), and no Y is the input of another projection of the call.  us a call, through the caches / past them, the caller
+// reading every Y behind it: the pair 2944 / 11392, bf16, 500 tokens (196 MB), none fired 83.8 / 86.3, 5 % 114.5 / 115.4, 18 % 129.2 / 123.8;
+// a block of 1280 / 4096, 1800 tokens (186 MB) 111 / 116, 139 / 139, 164 / 171; of 2048 / 8192, 800 tokens (218 MB) 114 / 115, 154 / 145,
+// 173 / 170; the pair 3584 / 12544, 400 tokens (233 MB) 75.9 / 78.0, 113.5 / 112.6, 122.7 / 119.0.
+static bool passes_caches(int64_t bytes) { return bytes > (208ll << 20); }
 static int64_t rows_bytes(int64_t B, int64_t n) { return B * n * 4; }           // ... of R or Y
 static int64_t weight_bytes(int64_t m, int64_t d) { return m * d * 2; }         // (bf16)
 // map_bytes: weights and Y of the maps that read the inputs; again: a projection of the call reads one of these Y

@@ -253,8 +253,8 @@ __device__ __forceinline__ int parts_for(const GemmProb& g, int rows) {
 }
 
 // ONCE: how many of the rows of a launch go past the caches.  1: R and Y as they are written, the fired rows of Y and the partial
-// sums of a scatter product as they are read again; 2: x of a residual as well.  The calls that ask for it read more weights
-// and write more rows than the memory-side cache holds, and what the rows displaced were the operands of the tiles beside
+// sums of a scatter product as they are read again; 2: x of a residual as well.  The calls that ask for it read and write
+// more than the memory-side cache has room for (passes_caches), and what the rows displaced were the operands of the tiles beside
 // them.  us a call, through the caches / past them: a block of 2048 tokens at rank 512, 410 fired 730 / 683; the pair 4096 / 16384, 200
 // tokens, 30 fired 129 / 114, 333 tokens, 50 fired 148 / 129.  Where all of it fits, the products of the fired rows find R and Y there:
 // 4096 x 4096, 1024 tokens that fire 112 / 124, a block of 1024 / 4096, 1000 tokens 126 / 138.  x goes past them where products of the
@@ -363,8 +363,12 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
     issue<AM, TM, BT>(st, ap, bp, kt0 + 1 < kt1 ? kt0 + 1 : kt0, bsrc);
     __syncthreads();
     if constexpr (AM == 1 && TM == 128) {
-      // two workgroups per compute unit (one's epilogue beside the other's products): operands are read step by step, the
-      // other waves of the SIMD cover the reads
+      // Residual and image rows, W r of few rows: two workgroups per compute unit (one's epilogue beside the other's products),
+      // operands are read step by step, the other waves of the SIMD cover the reads.  The form that transposes its right
+      // operand has the same loop but one workgroup per unit (82304 bytes of LDS, 134 registers).  With the column groups'
+      // rows swapped in place of the padding two fit (81920 bytes, 128 registers, four waves per SIMD), which was no faster: us,
+      // coefficients of fp32 tokens, a block of 4096 / 16384, one / two: rank 256, 1024 tokens 148 / 157, 2048 234 / 252, rank 512, 768
+      // tokens (384 workgroups) 164 / 179, 1500 255 / 252, 2048 348 / 345.
       const char* pa = ap[0] + (int64_t)(kt0 + 1 < kt1 ? kt0 + 1 : kt0) * G::BKT * ES;  // the k-tile requested last
       const char* pb[G::NU];
 #pragma unroll
