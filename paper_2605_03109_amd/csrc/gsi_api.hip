@@ -1345,8 +1345,9 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
     }
     // single token: the staged kernel.  Launch g holds the partial projections of set g (up to kMaxTasks
     // independent inputs), the coefficient sums of set g - 1, the residuals and image rows of set g - 2 and the
-    // gates of set g - 3.  A call of one set skips the sum stage (its residual and image workgroups add the
-    // partials themselves: the same function, the same bits).
+    // gates of set g - 3.  A call of one set skips the sum stage: its residual and image workgroups add the
+    // partials themselves, which are cut as gsi_project cuts them, so the bits are those of the separate calls (a sum stage adds
+    // finer slabs, in another order).
     // With the single-pass gate (GSI_INPUT_GATE_SINGLE_PASS and a 16-byte aligned E) the stages are: partial
     // projections and shares of |x|^2 of set g; coefficient sums and shares of c^T E c of set g - 1; image rows
     // and, behind the gate their workgroups evaluate, residuals of set g - 2.

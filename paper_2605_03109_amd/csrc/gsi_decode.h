@@ -284,12 +284,12 @@ static_assert(sizeof(StageArgs) <= 4096, "kernel arguments are limited to 4 KB")
 // residual and image workgroup then adds the partials itself
 void stage_geom(int64_t d, int64_t k, int udtype, int& rows, int& slabs, bool fine = false);
 void stage_clear(StageArgs& a, float eps);
-// E (single-pass gate): the input's cached U^T U - I, else null
 // column blocks for the partial projection of an input of `slabs` slabs of `rows` rows ...
 int stage_col_blocks(int slabs, int rows, int64_t k, int udtype);
 // ... and of the inputs of a launch, `slabs` slabs together, whose partials a sum stage adds
 int stage_set_col_blocks(int slabs, int64_t k, int udtype);
-// ncb: column blocks, a power of two (stage_col_blocks): more, narrower workgroups for small calls
+// E (single-pass gate): the input's cached U^T U - I, else null.  ncb: column blocks, a power of two (stage_col_blocks): more,
+// narrower workgroups for small calls
 void stage_add_part(StageArgs& a, const ProjTask& t, const float* E = nullptr, int ncb = 1);
 void stage_add_cred(StageArgs& a, const ProjTask& t, const float* E = nullptr);
 // returns its index; single-pass gate: the residual workgroups evaluate and publish the gate themselves
@@ -338,7 +338,7 @@ struct TabMap {          // everything an image workgroup needs, so that its loa
   int in;                // index of the input
 };
 constexpr int kTabImgItems = 8;   // items per image workgroup of the table launch (32 KB of M; 16 KB and 64 KB measured the same)
-constexpr int kMaxTabIn = 1024, kMaxTabMaps = 2048;  // (the first-workgroup tables are searched in LDS)
+constexpr int kMaxTabIn = 1024, kMaxTabMaps = 2048;  // (find_in_table bounds them)
 size_t stage_table_bytes(int n_in, int n_maps);
 struct StageTableGeom {   // what the host needs to launch over a table that is already in device memory
   int n_in, n_maps, dtype;

@@ -22,7 +22,7 @@
 // extension moves U three times and every W once; operands whose rows are 16-byte aligned are read with 16-byte loads,
 // several in flight per lane.  Large bases have s added up by a launch of its own (own_sums).  (s, the column and U^T u in
 // launches of their own for every basis: seven launches of 4 to 5 us around one of 24 us; three maps 4096 x 4096 on a
-// basis of 4096 x 384, 256 columns in use: 46.7 us, 35.0 us with these four (a basis of 4096 x 512), calls replayed from a graph.)
+// basis of 4096 x 384, 256 columns in use: 46.7 us, 34.9 us with these four, calls replayed from a graph.)
 //
 // Every launch covers ALL bases of a call (one grid dimension is the basis, or the map): a token's pass over the
 // bases of a whole model is these launches, not as many per basis, and what it costs when no basis grows is

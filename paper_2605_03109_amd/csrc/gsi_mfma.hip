@@ -29,11 +29,12 @@
 // Problems with few output tiles split the contraction; the partial sums go to the workspace
 // and a second kernel adds them in split order and applies the epilogue.
 // The residual and image products are short (the rank) with long epilogues (every output row of a block: 0.5 GB), so they
-// run on tiles of 128 rows, two workgroups per unit: one's epilogue beside the other's products.
+// run on tiles of 128 rows, two workgroups per unit: one's epilogue beside the other's products.  (One per unit where an fp32
+// operand meets a basis as stored, the coefficients of fp32 tokens.)
 // A right operand that is N-contiguous in memory (U as the factor of W U and X U) is transposed on its way to LDS: a thread
 // has four columns of BKT / 8 rows, packs two rows into a word and writes four columns.  Where that costs more than it saves
-// (many row tiles of bf16 activations: mfma_project; large images: gsi_build_image), or its rows are no whole 8-byte pieces, it is transposed once into
-// the workspace.  The six images of a block (4096 / 16384, rank 256): a launch of 5 us each less.
+// (many row tiles of bf16 activations: mfma_project; large images: gsi_build_image), or its rows are no whole 8-byte pieces,
+// it is transposed once into the workspace.  The six images of a block (4096 / 16384, rank 256): a launch of 5 us each less.
 #include <algorithm>
 
 #include "gsi_device.h"

@@ -578,6 +578,7 @@ __global__ __launch_bounds__(kBlock) void one_residual(const StageRes p, float* 
 // The task that holds workgroup b, from the first-workgroup table of n <= 4096 tasks (ascending, begin[0] = 0): every wave
 // compares 64 entries spread over the table, then the entries between two of them; two loads, no LDS and no barrier.
 // first: the task's first workgroup.
+static_assert(kMaxTabIn <= kWave * kWave && kMaxTabMaps <= kWave * kWave, "two steps of a wave");
 __device__ __forceinline__ int find_in_table(const int* __restrict__ begin, int n, int b, int& first) {
   const int lane = threadIdx.x % kWave;
   const int step = (n + kWave - 1) / kWave;
