@@ -55,7 +55,8 @@ __device__ __forceinline__ float load_old(const float* p) {
 // (d floats, LDS).
 // whole: the product replaces y (dense baseline, W x form of the slow path); else it is added to y.
 // TAIL: d / kVec is not a multiple of 64 * kLU (loads clamped, surplus products dropped).  It is a property of a launch, so both
-// forms add the same products in the same order: a row has the same bits beside whatever other maps.
+// forms add the same products in the same order: a row has the same bits beside whatever other maps.  (Not in the fused kernel
+// (COHERENT), whose sums differ from separate calls anyway: a block of 2048 / 8192 that fires 44.7 us, 45.6 so.)
 template <class T, bool TAIL, bool COHERENT, bool NT = false>
 __device__ __forceinline__ void stream_map_rows(const typename T::storage* __restrict__ W, float* __restrict__ Y,
                                                 int m, int d, int64_t ld, const float* __restrict__ xs, bool whole,
@@ -91,7 +92,8 @@ __device__ __forceinline__ void stream_map_rows(const typename T::storage* __res
           float w[V], xv[V];
           buf[q].widen(w);
           lds_vec<V>(xp + q * kWave * V, xv);
-          acc += dotv<V>(w, xv, 0.f);
+          if constexpr (COHERENT) acc = dotv<V>(w, xv, acc);
+          else acc += dotv<V>(w, xv, 0.f);
         }
         const bool last = sg == nseg - 1;
         const float sum = group_sum<kWave>(acc);
