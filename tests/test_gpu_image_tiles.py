@@ -18,7 +18,7 @@ def _basis(d, k, offset, g):
 # equal to and past a tile; bases that start 8 bytes (as stored) and 2 bytes (transposed first) off
 @pytest.mark.parametrize("m,d,k,offset", [
     (1, 64, 4, 0), (63, 4096, 60, 0), (65, 16384, 256, 0), (4096, 1024, 260, 4), (300, 10240, 512, 0), (16384, 512, 256, 0),
-    (16321, 320, 64, 4), (1024, 5120, 256, 0), (1025, 5120, 256, 4), (300, 13632, 300, 0), (16384, 4096, 256, 0), (16385, 4096, 256, 0), (8193, 4096, 64, 0), (8193, 4096, 192, 0), (8193, 4096, 200, 0), (33000, 192, 128, 0), (70000, 256, 256, 0), (65, 1024, 68, 1), (33000, 128, 64, 1)])
+    (16321, 320, 64, 4), (1024, 5120, 256, 0), (1025, 5120, 256, 4), (300, 13632, 300, 0), (16384, 4096, 256, 0), (16385, 4096, 256, 0), (33000, 192, 128, 0), (70000, 256, 256, 0), (65, 1024, 68, 1), (33000, 128, 64, 1)])
 def test_images(m, d, k, offset):
     from paper_2605_03109_amd import gsi
 
@@ -41,7 +41,6 @@ def test_images(m, d, k, offset):
 # the last and the first side of the rule, both activation types, one and two column tiles, a ragged last row tile
 @pytest.mark.parametrize("d,k,B,xdtype", [
     (1024, 64, 129, "bf16"), (1024, 320, 1000, "f32"), (1024, 320, 1024, "bf16"), (1024, 320, 1025, "bf16"), (1088, 192, 1100, "f32"),
-    (1024, 320, 1536, "bf16"), (1024, 320, 1537, "bf16"), (8256, 64, 768, "bf16"), (8256, 64, 769, "bf16"),
     (16384, 512, 200, "bf16"), (4096, 128, 300, "f32")])
 def test_coefficients(d, k, B, xdtype):
     from paper_2605_03109_amd import gsi

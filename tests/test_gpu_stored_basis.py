@@ -1,0 +1,26 @@
+"""Both sides of the lines that decide whether a basis is read as stored or transposed first, against the oracle's tolerances of
+test_gpu_image_tiles."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+pytest.importorskip("torch")
+
+import test_gpu_image_tiles as tiles  # noqa: E402
+
+
+# a work of 4096 and just above it at a rank that ends the first line, at the last rank without and the first with the second
+# line; the second line's last work and just above it
+@pytest.mark.parametrize("m,d,k,offset", [
+    (4096, 4096, 512, 0), (4097, 4096, 512, 0), (8193, 4096, 64, 0), (8193, 4096, 192, 0), (8193, 4096, 200, 0), (16384, 4096, 200, 4),
+    (16385, 4096, 200, 0)])
+def test_images(m, d, k, offset):
+    tiles.test_images(m, d, k, offset)
+
+
+# bf16 tokens: 1536 and one more, and 768 and one more where the input is longer than 8192
+@pytest.mark.parametrize("d,k,B,xdtype", [
+    (1024, 320, 1536, "bf16"), (1024, 320, 1537, "bf16"), (8192, 64, 769, "bf16"), (8256, 64, 768, "bf16"), (8256, 64, 769, "bf16"),
+    (8256, 64, 1540, "f32")])
+def test_coefficients(d, k, B, xdtype):
+    tiles.test_coefficients(d, k, B, xdtype)
