@@ -530,10 +530,10 @@ static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, WsLevel level,
   if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), 1, gsi::EPI_STORE_F32, s); e != hipSuccess) return e;
   int64_t bytes = 0;
   bool again = false;
-  for (int j = 0; j < n; ++j) {
+  for (int j = 0; j < n; ++j) {  // (with x, as the projection of the call counts it)
     again |= mp[j].again;
     bytes += weight_bytes(mp[j].m, mp[j].d) + rows_bytes(B, mp[j].m);
-    if (j == 0 || mp[j].R != mp[j - 1].R) bytes += rows_bytes(B, mp[j].d);
+    if (j == 0 || mp[j].R != mp[j - 1].R) bytes += rows_bytes(B, mp[j].d) + B * mp[j].d * (int64_t)gsi::elem_size(mp[j].xdtype);
   }
   const int once = !again && passes_caches(bytes) ? 1 : 0;
   // r enters rounded once to bf16 (mode 2): its term is scaled by the residual ratio, so the rounding (2^-9 relative)
