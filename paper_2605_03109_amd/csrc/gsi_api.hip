@@ -198,7 +198,7 @@ int gsi_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d,
       g.max_splits = gsi::mfma_splits(m, k, d, gsi::EPI_STORE_BF16, false, level);
       if (g.max_splits > 1)
         g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + gsi::align_up((size_t)k * d * 2, 256));
-      e = gsi::mfma_gemm_nt(&g, 1, 0, gsi::EPI_STORE_BF16, s, as_stored);
+      e = gsi::mfma_gemm_nt(&g, 1, 0, gsi::EPI_STORE_BF16, s, as_stored, m * k <= (1 << 19) ? 1 : 0);  // (store_row)
     }
   } else {
     e = gsi::generic_build_image(W, U, M, m, d, k, wdtype, s);

@@ -261,7 +261,9 @@ __device__ __forceinline__ int parts_for(const GemmProb& g, int rows) {
 // 4096 x 4096, 1024 tokens that fire 112 / 124, a block of 1024 / 4096, 1000 tokens 126 / 138.  x goes past them where products of the
 // fired rows follow (the pair at 333 tokens 133 / 129, none fired 69 / 72), not in a projection by itself (16384 x 256, 4096 tokens 182 /
 // 193), and so do the partial sums of such a call's coefficients, as they are added (the same 126.1 / 123.7, rank 512 149.7 / 146.2; a block of
-// 2048 tokens, none fired, 408 / 411); those of images are read through the caches (11008 x 1024 x 512 41 / 47).
+// 2048 tokens, none fired, 408 / 411); those of images of more than 2^19 elements are read through the caches, weights that no cache
+// holds: 11008 x 1024 x 512 41.5 / 48.7, 16384 x 1024 x 128 22.4 / 25.1, 3072 x 3072 x 256 24.1 / 24.3; smaller ones past them: 2048 x 2048 x
+// 256 18.7 / 16.7, 3072 x 3072 x 128 23.7 / 22.6, 1024 x 4096 x 256 17.8 / 17.1, 8192 x 4096 x 64 28.8 / 28.7.
 // (A property of the launch and not of a problem: chosen at run time per row it took 1 to 2 %.)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <bool PAST>
@@ -630,7 +632,7 @@ __global__ __launch_bounds__(256) void transpose_bf16(const TransposeArgs a) {
 
 template <int AM, int EPI, bool BT, int ONCE = 0>
 hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
-  constexpr int R = EPI == EPI_STORE_F32 ? 0 : ONCE;  // (coefficients: the next launch reads them)
+  constexpr int R = EPI == EPI_STORE_F32 || EPI == EPI_STORE_BF16 ? 0 : ONCE;  // (the next launch reads coefficients; images stay)
   int64_t blocks = 0;
   bool split = false;
   int64_t most = 0;
@@ -662,7 +664,9 @@ hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
 hipError_t launch_epi(GemmArgs& g, int a_f32, int epi, bool bt, int once, int tm, hipStream_t s) {
   switch (epi) {
     case EPI_STORE_BF16:
-      if (a_f32 == 0) return bt ? launch_group<0, EPI_STORE_BF16, true>(g, tm, s) : launch_group<0, EPI_STORE_BF16, false>(g, tm, s);
+      if (a_f32 != 0) break;
+      if (once) return bt ? launch_group<0, EPI_STORE_BF16, true, 1>(g, tm, s) : launch_group<0, EPI_STORE_BF16, false, 1>(g, tm, s);
+      return bt ? launch_group<0, EPI_STORE_BF16, true>(g, tm, s) : launch_group<0, EPI_STORE_BF16, false>(g, tm, s);
       break;
     case EPI_STORE_F32:
       if (once) {
