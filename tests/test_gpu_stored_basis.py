@@ -13,7 +13,9 @@ import test_gpu_image_tiles as tiles  # noqa: E402
 # line; the second line's last work and just above it
 @pytest.mark.parametrize("m,d,k,offset", [
     (4096, 4096, 512, 0), (4097, 4096, 512, 0), (8193, 4096, 64, 0), (8193, 4096, 192, 0), (8193, 4096, 200, 0), (16384, 4096, 200, 4),
-    (16385, 4096, 200, 0)])
+    (16385, 4096, 200, 0),
+    # 2^19 elements, whose parts are added past the caches, and just above
+    (8192, 4096, 64, 0), (2048, 2048, 256, 0), (2049, 2048, 256, 0)])
 def test_images(m, d, k, offset):
     tiles.test_images(m, d, k, offset)
 
