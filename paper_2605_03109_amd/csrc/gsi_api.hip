@@ -16,7 +16,7 @@
 
 namespace {
 
-using gsi::WsLevel, gsi::kWsFull, gsi::kWsCoarse, gsi::kWsFirst;
+using gsi::WsLevel, gsi::kWsFull, gsi::kWsFine, gsi::kWsCoarse, gsi::kWsFirst;
 
 thread_local char g_err[512] = "";
 
@@ -69,7 +69,7 @@ int check_ws(const char* fn, const void* ws, size_t have, size_t need) {
 // size is named for it: a call that needed no workspace before has to be served without one.  GSI_OK: at least the first.
 template <class Bytes>
 int check_ws_level(const char* fn, const void* ws, size_t ws_bytes, Bytes bytes, WsLevel& level) {
-  for (WsLevel l : {kWsFull, kWsCoarse}) {
+  for (WsLevel l : {kWsFull, kWsFine, kWsCoarse}) {
     const size_t need = bytes(l);
     if (need == 0 || (ws && aligned(ws, 256) && ws_bytes >= need)) {
       level = l;
@@ -107,12 +107,26 @@ static size_t mfma_project_ws(int64_t d, int64_t k, int64_t B, WsLevel level) {
   return gsi::align_up((size_t)k * d * 2, 256) + gsi::align_up((size_t)gsi::mfma_res_tiles(d, level) * B * 2 * 4, 256) +
          gsi::mfma_part_bytes(B, k, d, gsi::EPI_COEFF, level);
 }
+// The W term of a prefill-sized call on tiles of 256 rows, its fired rows laid out as bf16 first: where more than one tile of 128
+// rows is to be expected (a quarter of the tokens).  With fewer the weights are what is waited for, and a launch more costs:
+// the pair 4096 / 16384 at rank 256, 50 of 333 tokens fired 136 / 143 us; a block at rank 512, 410 of 2048 672 / 633.
+static bool wide_scatter_ok(int64_t d, int64_t B, WsLevel level) {
+  return level == kWsFull && B > 512 && d >= 64 && d % 64 == 0 && gsi::wide_ok(d) && B < (1ll << 30) && B * d < (1ll << 31);
+}
 // workspace of one linear map of a call with B tokens: partial products of the decode-batch kernel, or of
 // the split contraction of the prefill-sized W term (dense = 1: of the dense product)
 static size_t map_part_bytes(int64_t m, int64_t d, int64_t B, int dense, WsLevel level) {
-  if (B > kDecodeMaxB)
-    return d % 64 == 0 ? gsi::mfma_part_bytes(B, m, d, dense ? gsi::EPI_STORE_F32 : gsi::EPI_SCATTER_ADD, level) : 0;
+  if (B > kDecodeMaxB) {
+    if (d % 64 != 0) return 0;
+    if (dense) return gsi::mfma_part_bytes(B, m, d, gsi::EPI_STORE_F32, level);
+    const size_t part = gsi::mfma_part_bytes(B, m, d, gsi::EPI_SCATTER_ADD, level);
+    return wide_scatter_ok(d, B, level) ? std::max(part, gsi::wide_part_bytes(B, m, d)) : part;
+  }
   return gsi::tile_part_bytes(m, d, B);
+}
+// ... and of an input whose fired rows are laid out as bf16 for the W term of its maps
+static size_t rounded_rows_bytes(int64_t d, int64_t B, WsLevel level) {
+  return wide_scatter_ok(d, B, level) ? gsi::align_up((size_t)B * d * 2, 256) : 0;
 }
 
 static size_t project_ws_bytes(int64_t d, int64_t k, int64_t B, WsLevel level) {
@@ -141,7 +155,8 @@ static size_t call_ws_bytes(int which_call, int64_t m, int64_t d, int64_t k, int
     case GSI_CALL_DENSE_LINEAR:
       // partial products of the matrix-core kernels
       if (m < 1 || d < 1 || B < 1) return 0;
-      return map_part_bytes(m, d, B, which_call == GSI_CALL_DENSE_LINEAR, level);
+      return map_part_bytes(m, d, B, which_call == GSI_CALL_DENSE_LINEAR, level) +
+             (which_call == GSI_CALL_GATED_LINEAR ? rounded_rows_bytes(d, B, level) : 0);
     default:
       return 0;
   }
@@ -518,11 +533,13 @@ struct MfmaMap {
   int64_t m, d, k;
   float* Y;
   float* part;
+  uint16_t* rounded; // room for the fired rows of R as bf16 (one per input), or null: they are rounded on their way to LDS
   bool image_done;
   bool again;        // Y is the input of another projection of the call
 };
 static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, WsLevel level, hipStream_t s) {
   static thread_local std::vector<gsi::GemmProb> pr;
+  static thread_local std::vector<gsi::RoundTask> rt;
   pr.clear();
   for (int j = 0; j < n; ++j)
     if (!mp[j].image_done)
@@ -538,11 +555,27 @@ static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, WsLevel level,
   const int once = !again && passes_caches(bytes) ? 1 : 0;
   // r enters rounded once to bf16 (mode 2): its term is scaled by the residual ratio, so the rounding (2^-9 relative)
   // adds a few 1e-4 of |y| at most, beside the 1.7e-3 that the bf16 image already costs
+  pr.clear();
+  rt.clear();
+  for (int j = 0; j < n; ++j) {
+    const MfmaMap& q = mp[j];
+    if (q.Xwx || !q.rounded) continue;
+    if (std::none_of(rt.begin(), rt.end(), [&](const gsi::RoundTask& t) { return t.out == q.rounded; }))
+      rt.push_back(gsi::RoundTask{q.R, q.rounded, q.fired_idx, q.n_fired, (int)B, (int)q.d});
+    gsi::GemmProb g = gemm_prob(q.rounded, q.d, q.W, q.d, q.Y, q.m, B, q.m, q.d, gsi::EPI_SCATTER_ADD);
+    g.row_idx = q.fired_idx; g.n_rows_dev = q.n_fired;
+    g.max_splits = gsi::wide_splits(B, q.m, q.d);
+    g.row_tiles = gsi::wide_follow(B, q.d, g.max_splits);
+    g.part = g.max_splits > 1 || g.row_tiles ? q.part : nullptr;
+    pr.push_back(g);
+  }
+  if (hipError_t e = gsi::wide_round_rows(rt.data(), (int)rt.size(), once != 0, s); e != hipSuccess) return e;
+  if (hipError_t e = gsi::wide_scatter(pr.data(), (int)pr.size(), once != 0, s); e != hipSuccess) return e;
   for (int mode = 0; mode < 3; ++mode) {
     pr.clear();
     for (int j = 0; j < n; ++j) {
       const MfmaMap& q = mp[j];
-      if (mode != (!q.Xwx ? 2 : q.xdtype == GSI_F32 ? 1 : 0)) continue;
+      if (mode != (!q.Xwx ? 2 : q.xdtype == GSI_F32 ? 1 : 0) || (!q.Xwx && q.rounded)) continue;
       const int epi = q.Xwx ? gsi::EPI_SCATTER_STORE : gsi::EPI_SCATTER_ADD;
       gsi::GemmProb g = gemm_prob(q.Xwx ? q.Xwx : q.R, q.d, q.W, q.d, q.Y, q.m, B, q.m, q.d, epi);
       g.row_idx = q.fired_idx; g.n_rows_dev = q.n_fired;
@@ -734,7 +767,9 @@ int gsi_gated_linear(const void* W, const void* M, const float* C, const float* 
     e = bt.add(0, gd, W, M, (float*)Y, m, false, gsi::tile_part_bytes(m, d, B) ? (float*)ws : nullptr);
     if (e == hipSuccess) e = bt.flush();
   } else if (mfma_gated_path(W, M, C, R, d, k, B, wdtype, m, Y)) {
-    const MfmaMap mp{W, M, C, R, nullptr, 0, fired_idx, n_fired, m, d, k, (float*)Y, (float*)ws, false, false};
+    uint16_t* const rounded = rounded_rows_bytes(d, B, level)
+                                  ? reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + map_part_bytes(m, d, B, 0, level)) : nullptr;
+    const MfmaMap mp{W, M, C, R, nullptr, 0, fired_idx, n_fired, m, d, k, (float*)Y, (float*)ws, rounded, false, false};
     e = mfma_gated(&mp, 1, B, level, s);
   } else {
     e = gsi::generic_gated_linear(W, M, C, R, fired_idx, n_fired, m, d, k, B, wdtype, (float*)Y, s);
@@ -805,6 +840,15 @@ static size_t stack_table_bytes(int32_t n_maps, int32_t n_inputs, int64_t B) {
              : 0;
 }
 
+// fired rows of an input as bf16, if a map that reads it has a W r term on the matrix cores
+static size_t input_rounded_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int i, int64_t B,
+                                  WsLevel level) {
+  if (inputs[i].flags & GSI_INPUT_SLOW_PATH_WX) return 0;
+  for (int j = 0; j < n_maps; ++j)
+    if (maps[j].input_id == i && maps[j].wdtype == GSI_BF16) return rounded_rows_bytes(inputs[i].d, B, level);
+  return 0;
+}
+
 static size_t stack_ws_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int32_t n_inputs,
                              int64_t B, WsLevel level) {
   if (!inputs || n_inputs < 0) return 0;
@@ -818,6 +862,8 @@ static size_t stack_ws_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi
       const int id = maps[j].input_id;
       if (id >= 0 && id < n_inputs) need += map_part_bytes(maps[j].m, inputs[id].d, B, 0, level);
     }
+  // fired rows as bf16, a region per input
+  for (int i = 0; maps && i < n_inputs; ++i) need += input_rounded_bytes(maps, n_maps, inputs, i, B, level);
   // E4M3 images that are not read as codes are expanded to the weights' type
   if (maps)
     for (int j = 0; j < n_maps; ++j) {
@@ -876,8 +922,8 @@ int gsi_layer_stack_static(const gsi_map_desc* maps, int32_t n_maps, const gsi_i
       return fail(GSI_ERR_SHAPE, "%s: maps[%d].input_id = %d out of range", fn, j, maps[j].input_id);
   size_t need = 0;  // the least of the sizes that such a call is served with
   if (B > 0)
-    need = std::min({stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsFull), stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsCoarse),
-                     stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsFirst)});
+    need = std::min({stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsFull), stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsFine),
+                     stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsCoarse), stack_ws_bytes(maps, n_maps, inputs, n_inputs, B, kWsFirst)});
   if (need > have)
     return fail(GSI_ERR_WORKSPACE,
                 "%s: this call needs %zu bytes of scratch, the library's static array holds %zu; use gsi_layer_stack "
@@ -1071,6 +1117,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
   struct Scratch {
     std::vector<size_t> ws_off;
     std::vector<float*> part;
+    std::vector<uint16_t*> rounded;
     std::vector<int> mode, mode_separate, part_ncb, ready, mready;
     std::vector<gsi::ProjTask> ptask;
     std::vector<char> map_fused, in_done, map_done, img_done, gate_inline, late;
@@ -1079,8 +1126,11 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
   static thread_local Scratch sc;
   std::vector<size_t>& ws_off = sc.ws_off;
   std::vector<float*>& part = sc.part;
+  std::vector<uint16_t*>& rounded = sc.rounded;
+  size_t expand_off = 0;
   ws_off.assign(n_inputs, 0);
   part.assign(n_maps, nullptr);
+  rounded.assign(n_inputs, nullptr);
   {
     size_t off = stack_table_bytes(n_maps, n_inputs, B);
     for (int i = 0; i < n_inputs; ++i) {
@@ -1092,6 +1142,12 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
       if (pb) part[j] = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + off);
       off += pb;
     }
+    for (int i = 0; i < n_inputs; ++i) {
+      const size_t rb = input_rounded_bytes(maps, n_maps, inputs, i, B, level);
+      if (rb) rounded[i] = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + off);
+      off += rb;
+    }
+    expand_off = off;
   }
 
   // E4M3 images that no kernel of this call reads as codes (several tokens, or shapes the single-token vector
@@ -1099,10 +1155,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
   // as maps with an ordinary image.
   std::vector<gsi_map_desc> expanded;
   if (B > 0) {
-    size_t off = stack_table_bytes(n_maps, n_inputs, B);
-    for (int i = 0; i < n_inputs; ++i)
-      off += gsi::align_up(project_ws_bytes(inputs[i].d, inputs[i].k, B, level), 256);
-    for (int j = 0; j < n_maps; ++j) off += map_part_bytes(maps[j].m, inputs[maps[j].input_id].d, B, 0, level);
+    size_t off = expand_off;
     for (int j = 0; j < n_maps; ++j) {
       const gsi_input_desc& in = inputs[maps[j].input_id];
       const size_t bytes = fp8_expand_bytes(maps[j], in, B, level);
@@ -1673,7 +1726,7 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
             !wx_vector_ok(in))
           continue;
         mm.push_back(MfmaMap{mp.W, mp.M, in.C, in.R, (in.flags & GSI_INPUT_SLOW_PATH_WX) ? in.X : nullptr, in.xdtype, in.fired_idx,
-                             in.n_fired, mp.m, in.d, in.k, mp.Y, part[j], img_done[j] != 0, read_again(j)});
+                             in.n_fired, mp.m, in.d, in.k, mp.Y, part[j], rounded[mp.input_id], img_done[j] != 0, read_again(j)});
         map_done[j] = 2;
       }
       if (!mm.empty())

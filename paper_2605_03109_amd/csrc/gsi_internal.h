@@ -14,10 +14,10 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align_up(size_t a, size_t b) { return (a + b - 1) / b * b; }
 
 // Workspaces that a call can bring.  kWsFull: what the queries name.  The others are what they named before, and a call that
-// brings only that much (a fixed scratch memory that it used to fit) is still served: kWsCoarse, while prefill-sized products
-// were split less; kWsFirst, while tiles had one size as well, and only ranks of 2^j pieces of 16 bytes, and
+// brings only that much (a fixed scratch memory that it used to fit) is still served: kWsFine, while no operand of a prefill-sized
+// product was laid out as bf16 first; kWsCoarse, while such products were split less; kWsFirst, while tiles had one size as well, and only ranks of 2^j pieces of 16 bytes, and
 // decode batches of bf16 storage, ran on vector and matrix-core kernels (the others take the kernels they took then).
-enum WsLevel { kWsFirst = 0, kWsCoarse = 1, kWsFull = 2 };
+enum WsLevel { kWsFirst = 0, kWsCoarse = 1, kWsFine = 2, kWsFull = 3 };
 
 // ---- generic kernels: any shape, element-wise access ---------------------------------------------
 hipError_t generic_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d, int64_t k, int wdtype,

@@ -25,7 +25,8 @@ struct GemmProb {
   int epi;
   int xdtype;
   int max_splits;             // in: splits of the contraction that `part` has room for (mfma_splits), 1 without it
-  int row_tiles;              // in: tiles of 128 rows that max_splits is meant for, where it follows the count (mfma_follow), or 0
+  int row_tiles;              // in: tiles of tile_rows rows that max_splits is meant for, where it follows the count (mfma_follow), or 0
+  int tile_rows;              // in: 128 (256: wide_scatter)
   int res_cols;               // EPI_PROJECTED: columns per partial norm, 64 or 128 (the same in every problem)
   int splits, col_tiles, blk_begin, min_parts;  // filled at launch
 };
@@ -52,6 +53,25 @@ size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, WsLevel level);
 // b_rows: B is stored [K, N] (ldb elements a row, whole 8-byte pieces) and transposed on its way (EPI_STORE_BF16, EPI_STORE_F32).
 // once: EPI_PROJECTED and EPI_SCATTER: the rows of D go past the caches (1), x of a residual too (2).
 hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStream_t s, bool b_rows = false, int once = 0);
+
+// Products of the fired rows (EPI_SCATTER_ADD) whose A is bf16, the fired rows one after the other (gsi_wide.hip).
+struct RoundTask {
+  const float* R;
+  uint16_t* out;              // [rows, d]: the fired rows of R, rounded
+  const int32_t* fired_idx;
+  const int32_t* n_fired;
+  int rows, d;                // d a multiple of 8
+};
+hipError_t wide_round_rows(const RoundTask* tasks, int n, bool once, hipStream_t s);
+hipError_t wide_scatter(const GemmProb* probs, int n, bool once, hipStream_t s);
+// the split of such a product, the row tiles it is meant for, and the workspace of its partial sums
+int wide_splits(int64_t M, int64_t N, int64_t K);
+int wide_follow(int64_t M, int64_t K, int splits);
+size_t wide_part_bytes(int64_t M, int64_t N, int64_t K);
+inline bool wide_ok(int64_t K) { return K <= (1 << 22); }  // (offsets in a tile of 256 rows are 32 bits)
+inline int64_t wide_rows_expected(int64_t M) { return M < 512 ? (M < 128 ? M : 128) : M / 4; }
+// adds the partial sums of the products of a launch
+hipError_t mfma_finish_scatter(const GemmArgs& g, bool once, hipStream_t s);
 
 // Ut[j][i] = U[i][j] for n bf16 matrices U[rows, cols]
 struct TransposeTask {

@@ -38,22 +38,17 @@
 #include <algorithm>
 
 #include "gsi_device.h"
-#include "gsi_mfma.h"
+#include "gsi_mfma_device.h"
 
 namespace gsi {
 namespace {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
-constexpr int BN = 256, BK = 64;                // BK: the host's unit of the contraction (K is a multiple of it)
+constexpr int BN = 256;
 constexpr int WTM = 64;                         // rows of a wave tile
 constexpr int kThreads = 512;
 constexpr int kAF = WTM / 32;                   // A fragments per wave
-
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // a native vector: loads and stores of it are
-                                                              // instructions, not aggregate copies
 
 // AM: how the A operand is stored and fed: 0 bf16; 1 fp32, split into bf16 head + tail (two LDS tiles, two
 // MFMA passes); 2 fp32, rounded once to bf16.
@@ -231,57 +226,6 @@ __device__ __forceinline__ void mma(const Ops<AM, TM, BT>& o, f32x16 (&acc)[kAF]
       for (int n = 0; n < kBF; ++n) acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.al[i], o.b[n], acc[i][n], 0, 0, 0);
     }
   }
-}
-
-// Parts of the contraction of a product over `rows` rows (a device-side count).  It is sized for row_tiles tiles of 128
-// rows.  With fewer, the same number of workgroups: each tile is cut into more parts (the workgroups of the row tiles that
-// are not there take them).  With more, fewer parts, down to min_parts, as long as they fill the chip: what is cut for
-// nothing writes partial sums for nothing.  Tiles of 128 rows whatever the launch's tile: the order of a sum is the product's
-// and the count's own.  W r beside the image term, us a call, parts fixed / following the count: 16384 x 4096, 102 of 2048
-// rows 137 / 102, all of 512 rows 167 / 106; 4096 x 16384, 51 of 1024 rows 75 / 52; a block, 2048 tokens that all fire
-// 1480 / 1414, 102 fired 644 / 632.  A product whose expected rows take one part has the launch of the sums all the same:
-// 16384 x 4096, 410 of 2048 rows 139 / 143.
-constexpr int kUnits = 256;      // compute units: one workgroup each
-constexpr int kMaxDepth = 64;    // k-tiles of 64 columns per workgroup, where a product has fewer tiles than the chip units
-constexpr int kFewParts = 8;
-constexpr int kMinDepth = 8;     // k-tiles that a split keeps at least
-__device__ __forceinline__ int parts_for(const GemmProb& g, int rows) {
-  if (!g.row_tiles) return g.splits;
-  const int tiles = (rows + 127) / 128, want = g.splits * g.row_tiles;
-  if (tiles <= g.row_tiles) return min(max(g.splits, min(kFewParts, g.K / (BK * kMinDepth))), want / tiles);
-  const int fit = max(want, (g.row_tiles > 1 ? kUnits / 2 : kUnits) / g.col_tiles) / tiles;
-  return min(g.splits, max(g.min_parts, fit));
-}
-
-// ONCE: how many of the rows of a launch go past the caches.  1: R and Y as they are written, the fired rows of Y and the partial
-// sums of a scatter product as they are read again; 2: x of a residual as well.  The calls that ask for it read and write
-// more than the memory-side cache has room for (passes_caches), and what the rows displaced were the operands of the tiles beside
-// them.  us a call, through the caches / past them: a block of 2048 tokens at rank 512, 410 fired 730 / 683; the pair 4096 / 16384, 200
-// tokens, 30 fired 129 / 114, 333 tokens, 50 fired 148 / 129.  Where all of it fits, the products of the fired rows find R and Y there:
-// 4096 x 4096, 1024 tokens that fire 112 / 124, a block of 1024 / 4096, 1000 tokens 126 / 138.  x goes past them where products of the
-// fired rows follow (the pair at 333 tokens 133 / 129, none fired 69 / 72), not in a projection by itself (16384 x 256, 4096 tokens 182 /
-// 193), and so do the partial sums of such a call's coefficients, as they are added (the same 126.1 / 123.7, rank 512 149.7 / 146.2; a block of
-// 2048 tokens, none fired, 408 / 411); those of images of more than 2^19 elements are read through the caches, weights that no cache
-// holds: 11008 x 1024 x 512 41.5 / 48.7, 16384 x 1024 x 128 22.4 / 25.1, 3072 x 3072 x 256 24.1 / 24.3; smaller ones past them: 2048 x 2048 x
-// 256 18.7 / 16.7, 3072 x 3072 x 128 23.7 / 22.6, 1024 x 4096 x 256 17.8 / 17.1, 8192 x 4096 x 64 28.8 / 28.7.
-// (A property of the launch and not of a problem: chosen at run time per row it took 1 to 2 %.)
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <bool PAST>
-__device__ __forceinline__ void store_row(float* p, const float4& v) {
-  if constexpr (PAST) __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4*>(p));
-  else *reinterpret_cast<float4*>(p) = v;
-}
-template <bool PAST>
-__device__ __forceinline__ float4 load_row(const float* p) {
-  if constexpr (!PAST) return *reinterpret_cast<const float4*>(p);
-  const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
-  return float4{v[0], v[1], v[2], v[3]};
-}
-template <bool PAST>
-__device__ __forceinline__ uint2 load_row(const uint16_t* p) {
-  if constexpr (!PAST) return *reinterpret_cast<const uint2*>(p);
-  const u32x2 v = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
-  return uint2{v[0], v[1]};
 }
 
 template <int AM, int EPI, int TM, bool BT, int ONCE>
@@ -630,21 +574,28 @@ __global__ __launch_bounds__(256) void transpose_bf16(const TransposeArgs a) {
   }
 }
 
+// of the sums of a launch's parts: a thread per four elements of the largest result, up to a limit
+dim3 finish_grid(const GemmArgs& g) {
+  int64_t most = 1;
+  for (int i = 0; i < g.n; ++i) {
+    const GemmProb& p = g.p[i];
+    if (p.splits > 1 || p.row_tiles)
+      most = std::max(most, (int64_t)(p.row_tiles && p.splits == 1 ? std::min(p.M, p.tile_rows * p.row_tiles) : p.M) * (p.N / 4));
+  }
+  return dim3((unsigned)std::min<int64_t>(ceil_div(most, 256), 4096), (unsigned)g.n);
+}
+
 template <int AM, int EPI, bool BT, int ONCE = 0>
 hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
   constexpr int R = EPI == EPI_STORE_F32 || EPI == EPI_STORE_BF16 ? 0 : ONCE;  // (the next launch reads coefficients; images stay)
   int64_t blocks = 0;
   bool split = false;
-  int64_t most = 0;
   for (int i = 0; i < g.n; ++i) {
     GemmProb& p = g.p[i];
     p.col_tiles = (int)ceil_div(p.N, BN);
     p.blk_begin = (int)blocks;
     blocks += (int64_t)p.col_tiles * ceil_div(p.M, tm) * p.splits;
-    if (p.splits > 1 || p.row_tiles) {
-      split = true;
-      most = std::max(most, (int64_t)(p.row_tiles && p.splits == 1 ? std::min(p.M, 128 * p.row_tiles) : p.M) * (p.N / 4));
-    }
+    split |= p.splits > 1 || p.row_tiles;
   }
   if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
   if (tm == 256) {
@@ -656,7 +607,7 @@ hipError_t launch_group(GemmArgs& g, int tm, hipStream_t s) {
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if constexpr (EPI != EPI_PROJECTED)
-    if (split) splitk_finish<EPI, ONCE><<<dim3((unsigned)std::min<int64_t>(ceil_div(most, 256), 4096), (unsigned)g.n), 256, 0, s>>>(g);
+    if (split) splitk_finish<EPI, ONCE><<<finish_grid(g), 256, 0, s>>>(g);
   return hipGetLastError();
 }
 
@@ -757,9 +708,40 @@ size_t mfma_part_bytes(int64_t M, int64_t N, int64_t K, int epi, WsLevel level) 
 
 // Nothing to follow: one tile in one part, or a contraction too short to cut.
 int mfma_follow(int64_t M, int64_t K, int epi, int splits, WsLevel level) {
-  if (level != kWsFull || (epi != EPI_SCATTER_ADD && epi != EPI_SCATTER_STORE) || K < 2 * kMinDepth * BK) return 0;
+  if (level < kWsFine || (epi != EPI_SCATTER_ADD && epi != EPI_SCATTER_STORE) || K < 2 * kMinDepth * BK) return 0;
   const int t = (int)ceil_div(rows_expected(M, epi), 128);
   return t * splits > 1 ? t : 0;
+}
+
+// The same for products on tiles of 256 rows over the fired rows (gsi_wide.hip): parts of 4096 columns where a product has fewer
+// tiles than the chip units, and cut further, down to 1024 columns (512 for an eighth of the units), while the parts of one row
+// tile fit the chip and those of several half of it.
+int wide_splits(int64_t M, int64_t N, int64_t K) {
+  const int64_t m = wide_rows_expected(M), nk = ceil_div(K, BK), tiles = ceil_div(m, 256) * ceil_div(N, BN);
+  int64_t s = tiles < kUnits ? std::min<int64_t>(ceil_div(nk, kMaxDepth), kMaxSplits) : 1;
+  while (s * 2 <= kMaxSplits && tiles * s < (tiles < kUnits / 8 ? kUnits / 4 : 0) && nk / (s * 2) >= kMinDepth) s *= 2;
+  const int64_t room = m > 256 ? kUnits / 4 : kUnits;
+  while (s < 8 && tiles * s * 2 <= room && nk / (s * 2) >= (tiles * s > kUnits / 8 ? 2 * kMinDepth : kMinDepth)) s *= 2;
+  return (int)s;
+}
+int wide_follow(int64_t M, int64_t K, int splits) {
+  if (K < 2 * kMinDepth * BK) return 0;
+  const int t = (int)ceil_div(wide_rows_expected(M), 256);
+  return t * splits > 1 ? t : 0;
+}
+size_t wide_part_bytes(int64_t M, int64_t N, int64_t K) {
+  const int s = wide_splits(M, N, K);
+  const int64_t rows = std::max<int64_t>(s > 1 ? s * M : 0, 256 * s * (int64_t)wide_follow(M, K, s));
+  return align_up((size_t)rows * N * sizeof(float), 256);
+}
+
+hipError_t mfma_finish_scatter(const GemmArgs& g, bool once, hipStream_t s) {
+  bool split = false;
+  for (int i = 0; i < g.n; ++i) split |= g.p[i].splits > 1 || g.p[i].row_tiles;
+  if (!split) return hipSuccess;
+  if (once) splitk_finish<EPI_SCATTER, 1><<<finish_grid(g), 256, 0, s>>>(g);
+  else splitk_finish<EPI_SCATTER, 0><<<finish_grid(g), 256, 0, s>>>(g);
+  return hipGetLastError();
 }
 
 namespace {
@@ -802,6 +784,7 @@ hipError_t mfma_gemm_nt(const GemmProb* probs, int n, int a_f32, int epi, hipStr
     for (int q = 0; q < g.n; ++q) {
       g.p[q].splits = g.p[q].part ? g.p[q].max_splits : 1;
       if (!g.p[q].part) g.p[q].row_tiles = 0;
+      g.p[q].tile_rows = 128;
       g.p[q].min_parts = std::min(g.p[q].splits, (int)ceil_div(g.p[q].K, BK * kMaxDepth));
     }
     // The products with the longest parts first: workgroups hold a unit each and go out in order, and what is long and

@@ -1,0 +1,329 @@
+// Prefill-sized products whose operands are bf16 in memory: from there to LDS without registers, 256 x 256 tiles.
+//
+// D = A B^T, both operands K-contiguous.  A workgroup of eight waves has a tile of 256 x 256; a k-tile is 64 columns, two of
+// them in LDS (128 KB, one workgroup per compute unit).  The tile of each operand lies there as two halves of 128 rows.  A wave
+// owns 64 rows and 32 columns of each pair of halves (waves 2 x 4), so a k-tile is four steps, one pair of halves each: A0 B0,
+// A0 B1, A1 B1, A1 B0, sixteen v_mfma_f32_16x16x32_bf16 a step.  Four waves are half a step behind the other four: one wave of
+// a SIMD reads its operands from LDS while the other one's products run (a barrier between the halves of a step keeps them
+// so; all eight in step: 1188 TFLOP/s in place of 1372).  In every step a thread requests the two 16-byte pieces of a half two
+// k-tiles ahead, into the half that was read last, and waits for those that the next step reads: six halves, 96 KB a unit, are
+// always on their way.
+// In LDS a row of a half is 128 bytes, its 16-byte piece c at c ^ (row / 2 % 8): sixteen rows of one piece, which a read of 128
+// bits takes at a time, lie in distinct banks (c ^ row % 8: 1200 in place of 1354 TFLOP/s).  The loads write LDS in lane order,
+// so it is the lane that loads another piece of its row.
+// What bounds it is the power of the matrix cores: 8192^3 1467 TFLOP/s on random operands, 2022 on zeros; 32 x 32 x 16
+// products 1251 and 1883.  2048 x 16384 x 4096: 1395 TFLOP/s (gemm_nt, whose operands go through registers: 1004).
+//
+// The loads are inline assembly: they write no register, and the compiler, which would wait for all of them before every read
+// of LDS, does not see them.  Every wait for them is written here; the compiler's own counts can only wait for more.
+#include <algorithm>
+
+#include "gsi_mfma_device.h"
+
+namespace gsi {
+namespace {
+
+typedef __attribute__((address_space(3))) char lds_char;
+
+constexpr int kWideThreads = 512;
+constexpr int kWideTile = 256;
+constexpr int kHalf = 128 * 128;       // bytes of a half: 128 rows of 64 columns
+constexpr int kWideStage = 4 * kHalf;  // A0 A1 B0 B1
+
+// a buffer resource over `bytes` bytes: what lies behind them reads as zero
+__device__ __forceinline__ u32x4 buffer_of(const void* p, uint64_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu),
+               (uint32_t)__builtin_amdgcn_readfirstlane(bytes > 0xffffffffull ? 0xffffffffu : (uint32_t)bytes), 0x00020000u};
+}
+// 16 bytes per lane from buffer + voff + soff to LDS at lds + 16 * lane
+__device__ __forceinline__ void load_to_lds(uint32_t lds, const u32x4& buffer, uint32_t voff, uint32_t soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(buffer), "s"(soff)
+               : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {  // all but the N requested last
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Sums of a wave: [h][g][i][j][v]: row 128 h + 32 i + 16 wm + lane % 16 of the tile, column 128 g + 32 wn + 16 j + 4 (lane / 16) + v
+// (the columns of B are the first operand of the products, so that a lane has four neighbouring columns of a row).
+typedef f32x4 WideAcc[2][2][4][2];
+
+// The sums of one tile over the k-tiles kt0 .. kt1 (at least one).  a, b: buffers over the rows of the tile; rows: how many A and
+// B have (at least one; the last stands in for those past it, whose sums mean nothing); N0, N1: row fragments of 16 of each half
+// that the wave multiplies (its own: the barriers are the same for all).  Every wave has passed the last barrier of the loop when it returns, and no load is on its way.
+template <int N0, int N1>
+__device__ __forceinline__ void wide_loop(char* lds, const u32x4& a, int64_t lda, int a_rows, const u32x4& b, int64_t ldb, int b_rows, int kt0,
+                                          int kt1, WideAcc& acc) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = w >> 2, wn = w & 3, lc = lane & 15, lq = lane >> 4;
+  const int nk = kt1 - kt0;
+  // requests: a wave has rows 8 w .. and 64 + 8 w .. of every half, eight lanes a row
+  uint32_t va[2][2], vb[2][2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int row = 64 * q + 8 * w + (lane >> 3);
+      const uint32_t piece = 16u * ((lane & 7) ^ ((row >> 1) & 7));
+      va[h][q] = (uint32_t)(min(128 * h + row, a_rows - 1) * lda * 2) + piece;
+      vb[h][q] = (uint32_t)(min(128 * h + row, b_rows - 1) * ldb * 2) + piece;
+    }
+  const uint32_t to = (uint32_t)(uintptr_t)(lds_char*)lds + w * 1024;
+  // which: 0 B0, 1 A0, 2 B1, 3 A1, the order in which they are read; past the range the last k-tile again, never read
+  auto request = [&](int kt, int stage, int which) {
+    const uint32_t soff = (uint32_t)(kt0 + min(kt, nk - 1)) * 128u;
+    const uint32_t dst = to + stage * kWideStage + ((which & 1) ? 0 : 2 * kHalf) + (which >> 1) * kHalf;
+    const int h = which >> 1;
+    if (which & 1) {
+      load_to_lds(dst, a, va[h][0], soff);
+      load_to_lds(dst + kHalf / 2, a, va[h][1], soff);
+    } else {
+      load_to_lds(dst, b, vb[h][0], soff);
+      load_to_lds(dst + kHalf / 2, b, vb[h][1], soff);
+    }
+  };
+  uint32_t oa[2], ob[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int piece = 16 * ((4 * k + lq) ^ (lc >> 1));
+    oa[k] = (16 * wm + lc) * 128 + piece;
+    ob[k] = 2 * kHalf + (32 * wn + lc) * 128 + piece;
+  }
+#pragma unroll
+  for (int f = 0; f < 32; ++f) acc[f >> 4][(f >> 3) & 1][(f >> 1) & 3][f & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 ra[4][2], rb0[2][2][2], rb1[2][2];
+  auto read_a = [&](int stage, int h) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int i = 0; i < (h ? N1 : N0); ++i) ra[i][k] = *reinterpret_cast<const bf16x8*>(lds + stage * kWideStage + oa[k] + h * kHalf + i * 4096);
+  };
+  auto read_b = [&](int stage, int g, bf16x8 (&x)[2][2]) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) x[j][k] = *reinterpret_cast<const bf16x8*>(lds + stage * kWideStage + ob[k] + g * kHalf + j * 2048);
+  };
+  auto products = [&](int h, int g, const bf16x8 (&x)[2][2]) {
+    const int n = h ? N1 : N0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int i = 0; i < n; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[h][g][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[j][k], ra[i][k], acc[h][g][i][j], 0, 0, 0);
+  };
+  // A step: operands read and the next request out, then, behind the barrier that lets the other four waves read, the
+  // products.  What has been read is in registers before that barrier: behind it its half may be overwritten.
+  auto step = [&](int h, int g, const bf16x8 (&x)[2][2]) {
+    wait_loads<12>();
+    wait_lds();
+    barrier();
+    products(h, g, x);
+    barrier();
+  };
+  for (int q = 0; q < 4; ++q) request(0, 0, q);
+  for (int q = 0; q < 4; ++q) request(1, 1, q);
+  wait_loads<12>();  // B0 and A0 of the first k-tile
+  barrier();
+  read_b(0, 0, rb0[0]);
+  wait_lds();
+  barrier();              // the first step requests into that half
+  if (w >= 4) barrier();  // half a step behind
+  auto tile = [&](int t, int stage, bf16x8 (&now)[2][2], bf16x8 (&next)[2][2]) {
+    read_a(stage, 0);
+    request(t + 2, stage, 0);
+    step(0, 0, now);
+    read_b(stage, 1, rb1);
+    request(t + 2, stage, 1);
+    step(0, 1, rb1);
+    read_a(stage, 1);
+    request(t + 2, stage, 2);
+    step(1, 1, rb1);
+    read_b(stage ^ 1, 0, next);
+    request(t + 2, stage, 3);
+    step(1, 0, now);
+  };
+  int t = 0;
+  for (; t + 1 < nk; t += 2) {
+    tile(t, 0, rb0[0], rb0[1]);
+    tile(t + 1, 1, rb0[1], rb0[0]);
+  }
+  if (t < nk) tile(t, 0, rb0[0], rb0[1]);
+  if (w < 4) barrier();
+  wait_loads<0>();
+}
+
+// Scatter products over a device-side count of fired rows: A[i] is the i-th of them (round_rows), D's row is row_idx[i].  The
+// workgroups of a launch are dealt to the pieces (row tile, column tile, part of the contraction) of the products in order, as
+// many as the counts make; the others leave.  The row tiles of a product are of one height, a multiple of 16 rows, and the
+// products of rows past it are left out (410 rows: two of 208).  Row tiles of a column tile are eight workgroups apart, on the
+// same XCD: its L2 reads the weights once.
+template <int ONCE>
+__global__ __launch_bounds__(kWideThreads, 2) void wide_scatter_kernel(const GemmArgs args) {
+  __shared__ __align__(1024) char lds[2 * kWideStage];
+  const int lane = threadIdx.x & 63;
+  // lane q: the pieces of product q
+  int rows = 0, pieces = 0;
+  if (lane < args.n) {
+    const GemmProb& g = args.p[lane];
+    rows = min(g.n_rows_dev[0], g.M);
+    if (rows > 0) pieces = g.col_tiles * ((rows + kWideTile - 1) / kWideTile) * parts_for(g, rows);
+  }
+  int local = blockIdx.x, pi = 0;
+  for (; pi < args.n; ++pi) {
+    const int n = __builtin_amdgcn_readlane(pieces, pi);
+    if (local < n) break;
+    local -= n;
+  }
+  if (pi == args.n) return;
+  const GemmProb& g = args.p[pi];
+  const int Mrows = __builtin_amdgcn_readlane(rows, pi);
+  const int row_tiles = (Mrows + kWideTile - 1) / kWideTile, parts = parts_for(g, Mrows), ct = g.col_tiles;
+  const int split = local / (ct * row_tiles), q = local - split * ct * row_tiles;
+  int tile_m, tile_n;
+  if (ct % 8 == 0) {
+    tile_m = (q >> 3) % row_tiles;
+    tile_n = (q >> 3) / row_tiles * 8 + (q & 7);
+  } else {
+    tile_m = q % row_tiles;
+    tile_n = q / row_tiles;
+  }
+  const int height = 16 * ((Mrows + 16 * row_tiles - 1) / (16 * row_tiles));
+  const int row0 = tile_m * height, a_rows = min(height, Mrows - row0), b_rows = min(kWideTile, g.N - tile_n * kWideTile);
+  if (a_rows <= 0) return;  // (uniform; a few rows more than whole tiles of 16 can leave the last one without any)
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = w >> 2, wn = w & 3;
+  const int frags = (a_rows + 15) / 16;
+  const int n0 = (min(frags, 8) + 1 - wm) / 2, n1 = (max(frags - 8, 0) + 1 - wm) / 2;
+  const int nk = g.K / BK;
+  const int64_t lda = g.lda, ldb = g.ldb, ldd = g.ldd;
+  const u32x4 a = buffer_of(reinterpret_cast<const uint16_t*>(g.A) + row0 * lda, ((a_rows - 1) * lda + g.K) * 2);
+  const u32x4 b = buffer_of(reinterpret_cast<const uint16_t*>(g.B) + (int64_t)tile_n * kWideTile * ldb, ((b_rows - 1) * ldb + g.K) * 2);
+  WideAcc acc;
+  const int kt0 = (int)((int64_t)nk * split / parts), kt1 = (int)((int64_t)nk * (split + 1) / parts);
+  switch (n1) {  // (uniform in a wave)
+    case 4: wide_loop<4, 4>(lds, a, lda, a_rows, b, ldb, b_rows, kt0, kt1, acc); break;
+    case 3: wide_loop<4, 3>(lds, a, lda, a_rows, b, ldb, b_rows, kt0, kt1, acc); break;
+    case 2: wide_loop<4, 2>(lds, a, lda, a_rows, b, ldb, b_rows, kt0, kt1, acc); break;
+    case 1: wide_loop<4, 1>(lds, a, lda, a_rows, b, ldb, b_rows, kt0, kt1, acc); break;
+    default:
+      if (n0 > 2) wide_loop<4, 0>(lds, a, lda, a_rows, b, ldb, b_rows, kt0, kt1, acc);
+      else wide_loop<2, 0>(lds, a, lda, a_rows, b, ldb, b_rows, kt0, kt1, acc);
+  }
+
+  // a lane has 16 bytes of a row, the four lanes of the row and the two fragments j a 128-byte line
+  const int lc = lane & 15, lq = lane >> 4;
+  const int col0 = tile_n * kWideTile + 32 * wn + 4 * lq;
+  const bool partial = parts > 1;
+  float* const base = partial ? g.part + (int64_t)split * Mrows * g.N : reinterpret_cast<float*>(g.D);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (i >= (h ? n1 : n0)) continue;
+      const int r = 128 * h + 32 * i + 16 * wm + lc;
+      const bool live = r < a_rows;
+      const int row = row0 + min(r, a_rows - 1);
+      float* const dst = base + (partial ? (int64_t)row * g.N : (int64_t)g.row_idx[row] * ldd);
+      float4 old[2][2];
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        const int col = col0 + 128 * (f >> 1) + 16 * (f & 1);
+        old[f >> 1][f & 1] = float4{0.f, 0.f, 0.f, 0.f};
+        if (!partial && live && col < g.N) old[f >> 1][f & 1] = load_row<ONCE != 0>(dst + col);
+      }
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        const int col = col0 + 128 * (f >> 1) + 16 * (f & 1);
+        if (!live || col >= g.N) continue;  // N is a multiple of 4
+        const f32x4 s = acc[h][f >> 1][i][f & 1];
+        const float4 o = old[f >> 1][f & 1];
+        if (partial) *reinterpret_cast<float4*>(dst + col) = float4{s[0], s[1], s[2], s[3]};
+        else store_row<ONCE != 0>(dst + col, float4{o.x + s[0], o.y + s[1], o.z + s[2], o.w + s[3]});
+      }
+    }
+}
+
+// The fired rows of R, one after the other, rounded once to bf16.
+constexpr int kMaxRoundTasks = 64;
+struct RoundArgs {
+  RoundTask t[kMaxRoundTasks];
+};
+static_assert(sizeof(RoundArgs) <= 4096, "kernel arguments are limited to 4 KB");
+template <int ONCE>
+__global__ __launch_bounds__(256) void round_rows(const RoundArgs args) {
+  const RoundTask& t = args.t[blockIdx.y];
+  const int n = min(t.n_fired[0], t.rows), d8 = t.d >> 3;
+  const int64_t total = (int64_t)n * d8;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
+    const int row = (int)(e / d8), c = 8 * (int)(e - (int64_t)row * d8);
+    const float* const src = t.R + (int64_t)t.fired_idx[row] * t.d + c;
+    const float4 x = load_row<ONCE != 0>(src), y = load_row<ONCE != 0>(src + 4);
+    const float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+    uint32_t o[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const __bf16 lo = (__bf16)v[2 * q], hi = (__bf16)v[2 * q + 1];
+      o[q] = (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
+    }
+    *reinterpret_cast<u32x4*>(t.out + (int64_t)row * t.d + c) = u32x4{o[0], o[1], o[2], o[3]};
+  }
+}
+
+}  // namespace
+
+hipError_t wide_round_rows(const RoundTask* tasks, int n, bool once, hipStream_t s) {
+  for (int i = 0; i < n;) {
+    RoundArgs a;
+    int c = 0;
+    int64_t most = 0;
+    for (; i < n && c < kMaxRoundTasks; ++i, ++c) {
+      a.t[c] = tasks[i];
+      most = std::max(most, ceil_div((int64_t)wide_rows_expected(tasks[i].rows) * (tasks[i].d / 8), 256));
+    }
+    const dim3 grid((unsigned)std::min<int64_t>(most, 2048), (unsigned)c);
+    if (once) round_rows<1><<<grid, 256, 0, s>>>(a);
+    else round_rows<0><<<grid, 256, 0, s>>>(a);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t wide_scatter(const GemmProb* probs, int n, bool once, hipStream_t s) {
+  for (int i = 0; i < n;) {
+    GemmArgs g;
+    g.n = 0;
+    for (; i < n && g.n < kMaxProbs; ++i) g.p[g.n++] = probs[i];
+    int64_t blocks = 0;
+    for (int q = 0; q < g.n; ++q) {
+      GemmProb& p = g.p[q];
+      p.tile_rows = kWideTile;
+      p.splits = p.max_splits;
+      p.min_parts = std::min(p.splits, (int)ceil_div(p.K, BK * kMaxDepth));
+      p.col_tiles = (int)ceil_div(p.N, kWideTile);
+      // the most pieces that any count makes (parts_for)
+      const int64_t want = p.row_tiles ? (int64_t)p.splits * p.row_tiles : 0, tiles = ceil_div(p.M, kWideTile);
+      blocks += p.col_tiles * (p.row_tiles ? std::max({want, (int64_t)kUnits / p.col_tiles, tiles * p.min_parts}) : tiles * p.splits);
+    }
+    if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
+    std::stable_sort(g.p, g.p + g.n, [](const GemmProb& x, const GemmProb& y) {  // the longest parts first, as in mfma_gemm_nt
+      return (int64_t)x.K * y.splits > (int64_t)y.K * x.splits;
+    });
+    if (once) wide_scatter_kernel<1><<<(unsigned)blocks, kWideThreads, 0, s>>>(g);
+    else wide_scatter_kernel<0><<<(unsigned)blocks, kWideThreads, 0, s>>>(g);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    if (hipError_t e = mfma_finish_scatter(g, once, s); e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+}  // namespace gsi

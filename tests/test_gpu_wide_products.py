@@ -1,0 +1,38 @@
+"""Prefill-sized products whose operands go from memory to LDS without registers, at the edges of their tiles: the W term over the
+fired rows (row tiles of up to 256 rows in steps of 16, column tiles of 256, one k-tile and odd numbers of them, parts)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+# one k-tile; three; an odd number in parts; column tiles by the eight, ragged, less than one
+@pytest.mark.parametrize("d,m,B", [(64, 2048, 513), (192, 516, 600), (1088, 2052, 769), (4160, 40, 1030), (2048, 4096, 4400)])
+def test_fired_rows(d, m, B):
+    from paper_2605_03109_amd import gsi
+
+    k = 64
+    g = torch.Generator(device="cuda").manual_seed(d + m + B)
+    R, C = torch.randn(B, d, generator=g, device="cuda"), torch.randn(B, k, generator=g, device="cuda")
+    W = (torch.randn(m, d, generator=g, device="cuda") / d**0.5).to(torch.bfloat16)
+    M = (torch.randn(m, k, generator=g, device="cuda") / k**0.5).to(torch.bfloat16)
+    need = gsi.workspace_bytes(gsi.CALL_GATED_LINEAR, m, d, k, B)
+    ws = torch.full((2 * need + (16 << 20),), 0x5A, dtype=torch.uint8, device="cuda")
+    base, wr = C.double() @ M.double().T, R.to(torch.bfloat16).double() @ W.double().T
+    # 32-bit sums of d exact products, and of k products of operands of 16 mantissa bits: 2^-16 of the norms that bound them
+    bar = 2.0**-16 * (C.double().norm(dim=1).max() * M.double().norm(dim=1).max() + R.double().norm(dim=1).max() * W.double().norm(dim=1).max())
+    for n in sorted({1, 16, 17, 128, 129, 144, 255, 256, 257, 273, 511, 513, min(B, 4353), B}):
+        print(f"case fired rows d={d} m={m} B={B} fired={n}", flush=True)
+        fired = torch.randperm(B, generator=g, device="cuda")[:n].sort().values
+        idx = torch.zeros(B, dtype=torch.int32, device="cuda")
+        idx[:n] = fired.int()
+        want = base.clone()
+        want[fired] += wr[fired]
+        count = torch.tensor([n], dtype=torch.int32, device="cuda")
+        Y = torch.full((B, m), float("nan"), device="cuda")
+        rc = gsi.lib.gsi_gated_linear(W.data_ptr(), M.data_ptr(), C.data_ptr(), R.data_ptr(), idx.data_ptr(), count.data_ptr(), m, d, k, B,
+                                      gsi.GSI_BF16, Y.data_ptr(), gsi.GSI_F32, ws.data_ptr(), need, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert rc == gsi.GSI_OK, gsi.last_error()
+        assert (Y.double() - want).abs().max() <= bar
+        assert bool((ws[need:] == 0x5A).all())
