@@ -103,13 +103,22 @@ static bool mfma_image_ok(int64_t m, int64_t d, int64_t k) {
 static bool mfma_batch_ok(int64_t d, int64_t k, int64_t B) {
   return B > kDecodeMaxB && d % 64 == 0 && k % 64 == 0 && B < (1ll << 30) && B * d < (1ll << 31);
 }
+// coefficients in two bf16 terms
+static size_t two_term_bytes(int64_t k, int64_t B, WsLevel level) {
+  return level == kWsFull && k > 0 && gsi::wide_ok(k) ? gsi::align_up((size_t)B * k * 4, 256) : 0;
+}
 static size_t mfma_project_ws(int64_t d, int64_t k, int64_t B, WsLevel level) {
   return gsi::align_up((size_t)k * d * 2, 256) + gsi::align_up((size_t)gsi::mfma_res_tiles(d, level) * B * 2 * 4, 256) +
-         gsi::mfma_part_bytes(B, k, d, gsi::EPI_COEFF, level);
+         gsi::mfma_part_bytes(B, k, d, gsi::EPI_COEFF, level) + two_term_bytes(k, B, level);
+}
+// where a projection has them in its workspace (null: nowhere)
+static uint16_t* two_term_rows(void* ws, int64_t d, int64_t k, int64_t B, WsLevel level) {
+  const size_t n = two_term_bytes(k, B, level);
+  return n ? reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + mfma_project_ws(d, k, B, level) - n) : nullptr;
 }
 // The W term of a prefill-sized call on tiles of 256 rows, its fired rows laid out as bf16 first: where more than one tile of 128
 // rows is to be expected (a quarter of the tokens).  With fewer the weights are what is waited for, and a launch more costs:
-// the pair 4096 / 16384 at rank 256, 50 of 333 tokens fired 136 / 143 us; a block at rank 512, 410 of 2048 672 / 633.
+// the pair 4096 / 16384 at rank 256, 50 of 333 tokens fired 136 / 143 us; a block at rank 512, 410 of 2048 687 / 628.
 static bool wide_scatter_ok(int64_t d, int64_t B, WsLevel level) {
   return level == kWsFull && B > 512 && d >= 64 && d % 64 == 0 && gsi::wide_ok(d) && B < (1ll << 30) && B * d < (1ll << 31);
 }
@@ -156,7 +165,7 @@ static size_t call_ws_bytes(int which_call, int64_t m, int64_t d, int64_t k, int
       // partial products of the matrix-core kernels
       if (m < 1 || d < 1 || B < 1) return 0;
       return map_part_bytes(m, d, B, which_call == GSI_CALL_DENSE_LINEAR, level) +
-             (which_call == GSI_CALL_GATED_LINEAR ? rounded_rows_bytes(d, B, level) : 0);
+             (which_call == GSI_CALL_GATED_LINEAR ? rounded_rows_bytes(d, B, level) + (mfma_batch_ok(d, k, B) ? two_term_bytes(k, B, level) : 0) : 0);
     default:
       return 0;
   }
@@ -447,7 +456,7 @@ static int64_t weight_bytes(int64_t m, int64_t d) { return m * d * 2; }         
 static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img, int n_img, int64_t map_bytes, bool again,
                                int64_t B, bool with_gate, float eps, WsLevel level, hipStream_t s) {
   static thread_local std::vector<gsi::TransposeTask> tr;
-  static thread_local std::vector<gsi::GemmProb> pr;
+  static thread_local std::vector<gsi::GemmProb> pr, wide;
   int64_t bytes = map_bytes;
   for (int i = 0; i < n; ++i) bytes += rows_bytes(B, in[i].d) + B * in[i].d * (int64_t)gsi::elem_size(in[i].xdtype);
   const int once = again || !passes_caches(bytes) ? 0 : map_bytes > 0 ? 2 : 1;
@@ -477,6 +486,7 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
       if (g.max_splits > 1)
         g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(part_n(i)) +
                                           gsi::align_up((size_t)gsi::mfma_res_tiles(d, level) * B * 2 * 4, 256));
+      g.Ht = two_term_rows(in[i].ws, d, k, B, level);
       pr.push_back(g);
     }
     if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s, xdt == GSI_F32 || bf16_stored, once == 2 ? 1 : 0);
@@ -484,18 +494,23 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
       return e;
   }
   pr.clear();
+  wide.clear();
   for (int i = 0; i < n; ++i) {
-    gsi::GemmProb g = gemm_prob(in[i].C, in[i].k, in[i].U, in[i].k, in[i].R, in[i].d, B, in[i].d, in[i].k, gsi::EPI_RESIDUAL);
+    const uint16_t* const Ht = two_term_rows(in[i].ws, in[i].d, in[i].k, B, level);
+    const void* const C = Ht ? static_cast<const void*>(Ht) : in[i].C;
+    std::vector<gsi::GemmProb>& to = Ht ? wide : pr;
+    gsi::GemmProb g = gemm_prob(C, in[i].k, in[i].U, in[i].k, in[i].R, in[i].d, B, in[i].d, in[i].k, gsi::EPI_RESIDUAL);
     g.X = in[i].X; g.xdtype = in[i].xdtype;
     g.part_n = part_n(i);
     g.sync = reinterpret_cast<unsigned*>(in[i].ws);  // (a transposed basis is not read any more)
-    pr.push_back(g);
+    to.push_back(g);
     for (int q = 0; q < n_img; ++q)
       if (img[q].in == i)
-        pr.push_back(gemm_prob(in[i].C, in[i].k, img[q].M, in[i].k, img[q].Y, img[q].m, B, img[q].m, in[i].k, gsi::EPI_STORE_F32));
+        to.push_back(gemm_prob(C, in[i].k, img[q].M, in[i].k, img[q].Y, img[q].m, B, img[q].m, in[i].k, gsi::EPI_STORE_F32));
   }
   for (gsi::GemmProb& g : pr) g.res_cols = gsi::mfma_res_cols(level);
   if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), 1, gsi::EPI_PROJECTED, s, false, once); e != hipSuccess) return e;
+  if (hipError_t e = gsi::wide_two_term(wide.data(), (int)wide.size(), once, s); e != hipSuccess) return e;
   for (int i = 0; i < n;) {
     gsi::ProjBatch pb;
     std::memset(&pb, 0, sizeof(pb));
@@ -533,18 +548,28 @@ struct MfmaMap {
   int64_t m, d, k;
   float* Y;
   float* part;
+  uint16_t* Ht;      // room for C in two bf16 terms (one per input), or null: it is split on its way to LDS
   uint16_t* rounded; // room for the fired rows of R as bf16 (one per input), or null: they are rounded on their way to LDS
   bool image_done;
   bool again;        // Y is the input of another projection of the call
 };
 static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, WsLevel level, hipStream_t s) {
-  static thread_local std::vector<gsi::GemmProb> pr;
+  static thread_local std::vector<gsi::GemmProb> pr, wide;
+  static thread_local std::vector<gsi::SplitTask> st;
   static thread_local std::vector<gsi::RoundTask> rt;
   pr.clear();
-  for (int j = 0; j < n; ++j)
-    if (!mp[j].image_done)
-      pr.push_back(gemm_prob(mp[j].C, mp[j].k, mp[j].M, mp[j].k, mp[j].Y, mp[j].m, B, mp[j].m, mp[j].k, gsi::EPI_STORE_F32));
+  wide.clear();
+  st.clear();
+  for (int j = 0; j < n; ++j) {
+    const MfmaMap& q = mp[j];
+    if (q.image_done) continue;
+    if (q.Ht && std::none_of(st.begin(), st.end(), [&](const gsi::SplitTask& t) { return t.Ht == q.Ht; }))
+      st.push_back(gsi::SplitTask{q.C, q.Ht, (int)B, (int)q.k});
+    (q.Ht ? wide : pr).push_back(gemm_prob(q.Ht ? static_cast<const void*>(q.Ht) : q.C, q.k, q.M, q.k, q.Y, q.m, B, q.m, q.k, gsi::EPI_STORE_F32));
+  }
   if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), 1, gsi::EPI_STORE_F32, s); e != hipSuccess) return e;
+  if (hipError_t e = gsi::wide_split_rows(st.data(), (int)st.size(), s); e != hipSuccess) return e;
+  if (hipError_t e = gsi::wide_two_term(wide.data(), (int)wide.size(), 0, s); e != hipSuccess) return e;
   int64_t bytes = 0;
   bool again = false;
   for (int j = 0; j < n; ++j) {  // (with x, as the projection of the call counts it)
@@ -769,7 +794,9 @@ int gsi_gated_linear(const void* W, const void* M, const float* C, const float* 
   } else if (mfma_gated_path(W, M, C, R, d, k, B, wdtype, m, Y)) {
     uint16_t* const rounded = rounded_rows_bytes(d, B, level)
                                   ? reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + map_part_bytes(m, d, B, 0, level)) : nullptr;
-    const MfmaMap mp{W, M, C, R, nullptr, 0, fired_idx, n_fired, m, d, k, (float*)Y, (float*)ws, rounded, false, false};
+    uint16_t* const Ht = two_term_bytes(k, B, level)
+                             ? reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + map_part_bytes(m, d, B, 0, level) + rounded_rows_bytes(d, B, level)) : nullptr;
+    const MfmaMap mp{W, M, C, R, nullptr, 0, fired_idx, n_fired, m, d, k, (float*)Y, (float*)ws, Ht, rounded, false, false};
     e = mfma_gated(&mp, 1, B, level, s);
   } else {
     e = gsi::generic_gated_linear(W, M, C, R, fired_idx, n_fired, m, d, k, B, wdtype, (float*)Y, s);
@@ -1726,7 +1753,8 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
             !wx_vector_ok(in))
           continue;
         mm.push_back(MfmaMap{mp.W, mp.M, in.C, in.R, (in.flags & GSI_INPUT_SLOW_PATH_WX) ? in.X : nullptr, in.xdtype, in.fired_idx,
-                             in.n_fired, mp.m, in.d, in.k, mp.Y, part[j], rounded[mp.input_id], img_done[j] != 0, read_again(j)});
+                             in.n_fired, mp.m, in.d, in.k, mp.Y, part[j],
+                             two_term_rows(static_cast<char*>(ws) + ws_off[mp.input_id], in.d, in.k, B, level), rounded[mp.input_id], img_done[j] != 0, read_again(j)});
         map_done[j] = 2;
       }
       if (!mm.empty())

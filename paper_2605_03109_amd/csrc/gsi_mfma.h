@@ -19,6 +19,7 @@ struct GemmProb {
   unsigned* sync;             // ... and a counter that the launch clears for the norm kernel behind it (may be null)
   const int32_t* row_idx;     // optional: row i of A is A[row_idx[i]], and (scatter) row i of D is D[row_idx[i]]
   const int32_t* n_rows_dev;  // optional: device count of valid rows (<= M)
+  uint16_t* Ht;               // EPI_STORE_F32: D in two bf16 terms as well (wide_two_term), or null
   float* part;                // split contraction: workspace [splits][rows][N] of partial sums, or null (then no split)
   int lda, ldb, ldd;
   int M, N, K;                // K a multiple of 64; M * N below 2^31
@@ -64,6 +65,16 @@ struct RoundTask {
 };
 hipError_t wide_round_rows(const RoundTask* tasks, int n, bool once, hipStream_t s);
 hipError_t wide_scatter(const GemmProb* probs, int n, bool once, hipStream_t s);
+// Products of an operand in two terms: A is Ht, the rows of an fp32 operand as bf16 (of 32 columns the heads, their tails, the
+// next 32 columns: wide_split_rows, or GemmProb::Ht of the product that makes the operand); epi EPI_RESIDUAL or EPI_STORE_F32,
+// K a multiple of 64.
+struct SplitTask {
+  const float* C;
+  uint16_t* Ht;               // [rows, 2 k]
+  int rows, k;                // k a multiple of 32
+};
+hipError_t wide_split_rows(const SplitTask* tasks, int n, hipStream_t s);
+hipError_t wide_two_term(const GemmProb* probs, int n, int once, hipStream_t s);
 // the split of such a product, the row tiles it is meant for, and the workspace of its partial sums
 int wide_splits(int64_t M, int64_t N, int64_t K);
 int wide_follow(int64_t M, int64_t K, int splits);
@@ -82,7 +93,7 @@ struct TransposeTask {
 };
 hipError_t mfma_transpose_bf16(TransposeTask* tasks, int n, hipStream_t s);
 // columns per partial norm of the residual GEMM, and its partial norms per token
-inline int mfma_res_cols(WsLevel level) { return level > kWsFirst ? 64 : 128; }
+inline int mfma_res_cols(WsLevel level) { return level == kWsCoarse || level == kWsFine ? 64 : 128; }
 inline int mfma_res_tiles(int64_t d, WsLevel level) { return (int)ceil_div(d, mfma_res_cols(level)); }
 
 }  // namespace gsi

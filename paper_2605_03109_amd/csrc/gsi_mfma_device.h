@@ -63,5 +63,23 @@ __device__ __forceinline__ uint2 load_row(const uint16_t* p) {
   return uint2{v[0], v[1]};
 }
 
+__device__ __forceinline__ float4 widen_row(const float4& v) { return v; }
+__device__ __forceinline__ float4 widen_row(const uint2& v) { return float4{bf16_lo(v.x), bf16_hi(v.x), bf16_lo(v.y), bf16_hi(v.y)}; }
+
+// four columns of a row in two bf16 terms: the heads at p, the tails 32 elements on
+__device__ __forceinline__ void store_two_terms(uint16_t* p, const float4& v) {
+  const float x[4] = {v.x, v.y, v.z, v.w};
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const __bf16 hb = (__bf16)x[e];
+    h[e] = __builtin_bit_cast(uint16_t, hb);
+    const __bf16 lb = (__bf16)(x[e] - __uint_as_float(h[e] << 16));
+    l[e] = __builtin_bit_cast(uint16_t, lb);
+  }
+  *reinterpret_cast<u32x2*>(p) = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+  *reinterpret_cast<u32x2*>(p + 32) = u32x2{l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
+}
+
 }  // namespace
 }  // namespace gsi

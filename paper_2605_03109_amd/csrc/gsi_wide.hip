@@ -254,6 +254,11 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_scatter_kernel(const Gem
 }
 
 // The fired rows of R, one after the other, rounded once to bf16.
+constexpr int kMaxSplitTasks = 64;
+struct SplitArgs {
+  SplitTask t[kMaxSplitTasks];
+};
+static_assert(sizeof(SplitArgs) <= 4096, "kernel arguments are limited to 4 KB");
 constexpr int kMaxRoundTasks = 64;
 struct RoundArgs {
   RoundTask t[kMaxRoundTasks];
@@ -279,7 +284,269 @@ __global__ __launch_bounds__(256) void round_rows(const RoundArgs args) {
   }
 }
 
+// Products of an operand in two terms: A is fp32 laid out as bf16 head and tail (split_rows), D = head B^T + tail B^T.  The
+// residual and image products of a prefill-sized call: short (the rank) with long epilogues (every row of R and Y), so a
+// workgroup is four waves (2 x 2, 64 x 128 each) with a tile of 128 x 256 and half a compute unit: one's epilogue beside the
+// other's products.  A k-tile is 32 columns: a row of A is 64 bytes of head and 64 of tail, laid out in LDS as in wide_loop, a
+// row of B 64 bytes, whose piece c lies at c ^ {0, 3, 2, 1}[row / 4 % 4].  One read of B serves both terms.  A wave has all the
+// operands of a k-tile in registers before its products, so that the k-tile after the next is requested over it at once.
+// As many workgroups as the chip holds take tile after tile; the first two k-tiles of a tile are requested beside the last
+// two of the one before, and arrive before its epilogue begins.
+// A block of 2048 tokens at rank 512 (275 GFLOP, 0.65 GB of x, R and Y): 310 to 350 us in gemm_nt, 290 here; without the
+// stores 242, the epilogues alone 158.  No bank conflicts; the matrix cores are busy for 65 % of the time at 2.1 GHz (on zeros
+// 270).  A workgroup per tile 304, with x requested strip by strip and a sum of 32 lanes per row 354; raised priority of the
+// waves around their products 290.
+constexpr int kTwoThreads = 256, kTwoRows = 128, kTwoCols = 256, kTwoGroups = 2 * kUnits;
+constexpr int kTwoA = kTwoRows * 128, kTwoStage = kTwoA + kTwoCols * 64;
+constexpr int kTwoStrip = 16 * 64 * 4;  // bytes of a wave's strip: 16 rows of 64 columns
+
+// Eight sums over the 16 lanes of a row: lane l ends with sums 4 (l % 2) + 2 (l / 2 % 2) and the next.
+__device__ __forceinline__ float2 sums_of_row(const float (&s)[8]) {
+  const bool odd = threadIdx.x & 1, two = threadIdx.x & 2;
+  float a[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) a[e] = (odd ? s[e + 4] : s[e]) + dpp_move<0xB1>(odd ? s[e] : s[e + 4]);  // lane ^ 1
+  float t[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    t[e] = (two ? a[e + 2] : a[e]) + dpp_move<0x4E>(two ? a[e] : a[e + 2]);  // lane ^ 2
+    t[e] += dpp_move<0x124>(t[e]);  // row_ror 4: the lanes of the row that hold the same sums
+    t[e] += dpp_move<0x128>(t[e]);  // row_ror 8
+  }
+  return float2{t[0], t[1]};
+}
+
+template <int ONCE>
+__global__ __launch_bounds__(kTwoThreads, 2) void wide_two_term_kernel(const GemmArgs args, const int tiles) {
+  __shared__ __align__(1024) char lds[2 * kTwoStage + 4 * kTwoStrip];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = w >> 1, wn = w & 1, lc = lane & 15, lq = lane >> 4;
+  const uint32_t to = (uint32_t)(uintptr_t)(lds_char*)lds + w * 1024;
+
+  // the tile whose operands are being requested
+  struct Tile {
+    int problem, m, n;
+  };
+  auto tile_of = [&](int b) {
+    Tile t{0, 0, 0};
+    for (int q = 1; q < args.n; ++q)
+      if (b >= args.p[q].blk_begin) t.problem = q;
+    const GemmProb& g = args.p[t.problem];
+    const int local = b - g.blk_begin, row_tiles = (g.M + kTwoRows - 1) / kTwoRows;
+    if (g.col_tiles % 8 == 0) {  // the row tiles of a column tile on one XCD, as in wide_scatter_kernel
+      t.m = (local >> 3) % row_tiles;
+      t.n = (local >> 3) / row_tiles * 8 + (local & 7);
+    } else {
+      t.m = local % row_tiles;
+      t.n = local / row_tiles;
+    }
+    return t;
+  };
+  // a wave requests rows 32 q + 8 w .. + 7 of A and 64 q + 16 w .. + 15 of B; rows past the end read as zero
+  u32x4 a, b;
+  uint32_t va, vb, sa, sb;
+  auto aim = [&](const Tile& t) {
+    const GemmProb& g = args.p[t.problem];
+    const int row0 = t.m * kTwoRows, col0 = t.n * kTwoCols;
+    const int a_rows = min(kTwoRows, g.M - row0), b_rows = min(kTwoCols, g.N - col0);
+    a = buffer_of(reinterpret_cast<const uint16_t*>(g.A) + (int64_t)row0 * 2 * g.K, (int64_t)a_rows * 4 * g.K);
+    b = buffer_of(reinterpret_cast<const uint16_t*>(g.B) + (int64_t)col0 * g.ldb, ((int64_t)(b_rows - 1) * g.ldb + g.K) * 2);
+    sa = 4u * g.K;
+    sb = 2u * g.ldb;
+    int l = lane;
+    asm volatile("" : "+v"(l));  // (what follows from it is not kept in registers over the products)
+    va = (8 * w + (l >> 3)) * sa + 16u * ((l & 7) ^ ((4 * w + (l >> 4)) & 7));
+    vb = (16 * w + (l >> 2)) * sb + 16u * ((l & 3) ^ ((4 - ((l >> 4) & 3)) & 3));
+  };
+  auto request = [&](int kt, int stage) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      load_to_lds(to + stage * kTwoStage + q * 4096, a, va + 32 * q * sa, (uint32_t)kt * 128u);
+      load_to_lds(to + stage * kTwoStage + kTwoA + q * 4096, b, vb + 64 * q * sb, (uint32_t)kt * 64u);
+    }
+  };
+  const char* const pa = lds + (64 * wm + lc) * 128;
+  const char* const pb = lds + kTwoA + (128 * wn + lc) * 64 + 16 * (lq ^ ((4 - (lc >> 2)) & 3));
+  const int head = 16 * (lq ^ (lc >> 1)), tail = 16 * ((4 + lq) ^ (lc >> 1));
+  char* const strip = lds + 2 * kTwoStage + w * kTwoStrip;
+
+  Tile now = tile_of(blockIdx.x);
+  aim(now);
+  request(0, 0);
+  request(1, 1);
+  wait_loads<0>();
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const GemmProb& g = args.p[now.problem];
+    if (tile == g.blk_begin && tid == 0 && g.sync) *g.sync = 0u;
+    const bool more = tile + (int)gridDim.x < tiles;
+    const Tile next = tile_of(more ? tile + (int)gridDim.x : tile);
+    const int nk = g.K / 32;  // K is a multiple of 64: at least two k-tiles
+    f32x4 acc[4][8];
+#pragma unroll
+    for (int f = 0; f < 32; ++f) acc[f >> 3][f & 7] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto ktile = [&](int t, int stage, bool last) {
+      if (t >= 2) {  // all but the next k-tile's (the first two have arrived)
+        if (last && stage == 1 && !more) wait_loads<0>();
+        else wait_loads<8>();
+      }
+      barrier();
+      bf16x8 ah[4], al[4], bb[8];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        al[i] = *reinterpret_cast<const bf16x8*>(pa + stage * kTwoStage + i * 2048 + tail);
+        ah[i] = *reinterpret_cast<const bf16x8*>(pa + stage * kTwoStage + i * 2048 + head);
+      }
+#pragma unroll
+      for (int n = 0; n < 8; ++n) bb[n] = *reinterpret_cast<const bf16x8*>(pb + stage * kTwoStage + n * 1024);
+      if (last && stage == 0) aim(next);
+      wait_lds();
+      barrier();
+      if (!last) request(t + 2, stage);
+      else if (more) request(stage, stage);
+#pragma unroll
+      for (int n = 0; n < 8; ++n)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb[n], al[i], acc[i][n], 0, 0, 0);
+#pragma unroll
+      for (int n = 0; n < 8; ++n)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb[n], ah[i], acc[i][n], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int t = 0; t + 2 < nk; t += 2) {
+      ktile(t, 0, false);
+      ktile(t + 1, 1, false);
+    }
+    ktile(nk - 2, 0, true);
+    ktile(nk - 1, 1, true);
+
+    // A lane has four neighbouring columns of row lc of a fragment; 16 rows of half the wave tile go through its strip (piece c
+    // of a row at c ^ row), so that what touches memory is 256 bytes of a row: row 4 q + lane / 16, columns 4 (lane % 16) ..
+    const int64_t ldd = g.ldd;
+    int el = lane;
+    asm volatile("" : "+v"(el));  // (as above)
+    const int er = el >> 4, ec = 4 * (el & 15);
+    const int row0 = now.m * kTwoRows + 64 * wm, col0 = now.n * kTwoCols + 128 * wn;
+    auto put = [&](int s) {
+#pragma unroll
+      for (int n = 0; n < 4; ++n) *reinterpret_cast<f32x4*>(strip + (el & 15) * 256 + 16 * ((4 * n + er) ^ (el & 15))) = acc[s >> 1][4 * (s & 1) + n];
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // (private to the wave, whose LDS operations execute in order: only the compiler has to be held)
+    auto get = [&](f32x4 (&val)[4]) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) val[q] = *reinterpret_cast<const f32x4*>(strip + (4 * q + er) * 256 + 16 * ((el & 15) ^ (4 * q + er)));
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    };
+    if (g.epi != EPI_RESIDUAL) {
+      wait_loads<0>();  // the next tile's first k-tiles have arrived: no wait counts the stores that follow for them
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        put(s);
+        f32x4 val[4];
+        get(val);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int row = row0 + 16 * (s >> 1) + 4 * q + er, col = col0 + 64 * (s & 1) + ec;
+          if (row < g.M && col < g.N) store_row<ONCE != 0>(reinterpret_cast<float*>(g.D) + (int64_t)row * ldd + col, float4{val[q][0], val[q][1], val[q][2], val[q][3]});
+        }
+      }
+    } else {
+      auto residual = [&](auto element) {  // of x
+        using T = decltype(element);
+        decltype(load_row<false>(static_cast<const T*>(nullptr))) x[2][4];  // x of half a strip, as stored
+        auto request_x = [&](int s) {  // (rows and columns past the end repeat the last)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            x[s & 1][q] = load_row<ONCE == 2>(reinterpret_cast<const T*>(g.X) + (int64_t)min(row0 + 16 * (s >> 1) + 4 * q + er, g.M - 1) * ldd +
+                                              min(col0 + 64 * (s & 1) + ec, g.N - 4));
+        };
+        request_x(0);
+        wait_loads<0>();  // (as above)
+        float sums[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+          const int half = s & 1;
+          put(s);
+          if (s < 7) request_x(s + 1);
+          f32x4 val[4];
+          get(val);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int row = row0 + 16 * (s >> 1) + 4 * q + er, col = col0 + 64 * half + ec;
+            const bool live = row < g.M && col < g.N;
+            const float4 v = widen_row(x[half][q]);
+            const float4 r = float4{v.x - val[q][0], v.y - val[q][1], v.z - val[q][2], v.w - val[q][3]};
+            if (live) store_row<ONCE != 0>(reinterpret_cast<float*>(g.D) + (int64_t)row * ldd + col, r);
+            const float sr = live ? fmaf(r.x, r.x, fmaf(r.y, r.y, fmaf(r.z, r.z, r.w * r.w))) : 0.f;
+            const float sx = live ? fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, v.w * v.w))) : 0.f;
+            sums[2 * q] = half ? sums[2 * q] + sr : sr;
+            sums[2 * q + 1] = half ? sums[2 * q + 1] + sx : sx;
+          }
+          if (half) {
+            const float2 t = sums_of_row(sums);
+            const int row = row0 + 16 * (s >> 1) + 4 * (2 * (el & 1) + ((el >> 1) & 1)) + er;
+            if ((el & 15) < 4 && row < g.M && col0 < g.N) reinterpret_cast<float2*>(g.part_n)[(int64_t)(2 * now.n + wn) * g.M + row] = t;
+          }
+        }
+      };
+      if (g.xdtype == GSI_F32) residual(0.f);
+      else residual(uint16_t{0});
+    }
+    now = next;
+  }
+}
+
+// Ht[row] = the heads of 32 columns of a row of C, their tails, the next 32 columns ...
+__global__ __launch_bounds__(256) void split_rows(const SplitArgs args) {
+  const SplitTask& t = args.t[blockIdx.y];
+  const int64_t total = (int64_t)t.rows * (t.k >> 2);
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x)
+    store_two_terms(t.Ht + 8 * (4 * e / 32 * 8) + 4 * e % 32, *reinterpret_cast<const float4*>(t.C + 4 * e));
+}
+
 }  // namespace
+
+hipError_t wide_split_rows(const SplitTask* tasks, int n, hipStream_t s) {
+  for (int i = 0; i < n;) {
+    SplitArgs a;
+    int c = 0;
+    int64_t most = 0;
+    for (; i < n && c < kMaxSplitTasks; ++i, ++c) {
+      a.t[c] = tasks[i];
+      most = std::max(most, ceil_div((int64_t)tasks[i].rows * (tasks[i].k / 4), 256));
+    }
+    split_rows<<<dim3((unsigned)std::min<int64_t>(most, 2048), (unsigned)c), 256, 0, s>>>(a);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t wide_two_term(const GemmProb* probs, int n, int once, hipStream_t s) {
+  for (int i = 0; i < n;) {
+    GemmArgs g;
+    g.n = 0;
+    int64_t blocks = 0;
+    for (; i < n && g.n < kMaxProbs; ++i) {
+      GemmProb& p = g.p[g.n++];
+      p = probs[i];
+      p.col_tiles = (int)ceil_div(p.N, kTwoCols);
+      p.blk_begin = (int)blocks;
+      blocks += p.col_tiles * ceil_div(p.M, kTwoRows);
+    }
+    if (blocks >= (1ll << 31) - kTwoGroups) return hipErrorInvalidValue;
+    const unsigned groups = (unsigned)std::min<int64_t>(blocks, kTwoGroups);
+    if (once == 0) wide_two_term_kernel<0><<<groups, kTwoThreads, 0, s>>>(g, (int)blocks);
+    else if (once == 1) wide_two_term_kernel<1><<<groups, kTwoThreads, 0, s>>>(g, (int)blocks);
+    else wide_two_term_kernel<2><<<groups, kTwoThreads, 0, s>>>(g, (int)blocks);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 hipError_t wide_round_rows(const RoundTask* tasks, int n, bool once, hipStream_t s) {
   for (int i = 0; i < n;) {

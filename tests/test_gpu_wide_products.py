@@ -36,3 +36,30 @@ def test_fired_rows(d, m, B):
         assert rc == gsi.GSI_OK, gsi.last_error()
         assert (Y.double() - want).abs().max() <= bar
         assert bool((ws[need:] == 0x5A).all())
+
+
+# one token over a row tile; column tiles that are ragged, less than one, by the eight; ranks of two k-tiles, and of six
+@pytest.mark.parametrize("xdtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d,k,m,B", [(64, 64, 260, 129), (320, 64, 1000, 255), (2048, 192, 2048, 256), (4160, 128, 36, 385), (1024, 256, 4100, 1030)])
+def test_two_terms(d, k, m, B, xdtype):
+    from paper_2605_03109_amd import gsi
+
+    g = torch.Generator(device="cuda").manual_seed(d + k + B)
+    U = torch.linalg.qr(torch.randn(d, k, generator=g, device="cuda").double()).Q.to(torch.bfloat16).contiguous()
+    X = torch.randn(B, d, generator=g, device="cuda").to(xdtype)
+    W = (torch.randn(m, d, generator=g, device="cuda") / d**0.5).to(torch.bfloat16)
+    M = (W.double() @ U.double()).to(torch.bfloat16)
+    print(f"case two terms d={d} k={k} m={m} B={B} x {xdtype}", flush=True)
+    st = gsi.LayerStack([{"U": U, "X": X}], [{"W": W, "M": M, "input_id": 0}], B, 2.0)  # no residual is twice its token: none fires
+    st.run()
+    torch.cuda.synchronize()
+    t = st.inputs_t[0]
+    C, x = t["C"].double(), X.double()
+    # of the stored C: 16 mantissa bits of it, 32-bit sums of k products, one subtraction
+    bar = lambda b: 2.0**-16 * C.norm(dim=1)[:, None] * b.double().norm(dim=1)[None, :]
+    assert ((st.maps_t[0]["Y"].double() - C @ M.double().T).abs() <= bar(M)).all()
+    assert ((t["R"].double() - (x - C @ U.double().T)).abs() <= bar(U) + 2.0**-23 * x.abs()).all()
+    # norms of the stored rows: 32-bit sums of d squares
+    for got, rows in ((t["rnorm"], t["R"].double()), (t["xnorm"], x)):
+        assert ((got.double() - rows.norm(dim=1)).abs() <= 2.0**-20 * rows.norm(dim=1)).all()
+    assert int(t["n_fired"][0]) == 0
