@@ -105,7 +105,7 @@ static bool mfma_batch_ok(int64_t d, int64_t k, int64_t B) {
 }
 // coefficients in two bf16 terms
 static size_t two_term_bytes(int64_t k, int64_t B, WsLevel level) {
-  return level == kWsFull && k > 0 && gsi::wide_ok(k) ? gsi::align_up((size_t)B * k * 4, 256) : 0;
+  return level == kWsFull && k > 0 && gsi::wide_ok(k) ? gsi::align_up((size_t)B * gsi::wide_two_term_ld(k) * 2, 256) : 0;
 }
 static size_t mfma_project_ws(int64_t d, int64_t k, int64_t B, WsLevel level) {
   return gsi::align_up((size_t)k * d * 2, 256) + gsi::align_up((size_t)gsi::mfma_res_tiles(d, level) * B * 2 * 4, 256) +
@@ -117,10 +117,14 @@ static uint16_t* two_term_rows(void* ws, int64_t d, int64_t k, int64_t B, WsLeve
   return n ? reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + mfma_project_ws(d, k, B, level) - n) : nullptr;
 }
 // The W term of a prefill-sized call on tiles of 256 rows, its fired rows laid out as bf16 first: where more than one tile of 128
-// rows is to be expected (a quarter of the tokens).  With fewer the weights are what is waited for, and a launch more costs:
-// the pair 4096 / 16384 at rank 256, 50 of 333 tokens fired 136 / 143 us; a block at rank 512, 410 of 2048 687 / 628.
-static bool wide_scatter_ok(int64_t d, int64_t B, WsLevel level) {
-  return level == kWsFull && B > 512 && d >= 64 && d % 64 == 0 && gsi::wide_ok(d) && B < (1ll << 30) && B * d < (1ll << 31);
+// rows is to be expected (a quarter of the tokens) and the weights are not small.  Otherwise the weights are what is waited for,
+// or the launches, and one more costs.  us a call, rows converted on their way / laid out: the pair 4096 / 16384 at rank 256, 50 of 333
+// tokens fired 136 / 143; 128 of 640 185 / 180; 409 of 2048 402 / 352; the pair 1024 / 4096 at rank 64, 204 of 1024 67 / 72; 2048 / 8192 106 /
+// 111; 2560 / 10240 135 / 131; 3072 / 12288 171 / 149; a block of 2048 / 8192 at rank 256, 409 of 2048 305 / 287, 4096 / 16384 at
+// rank 512 687 / 628.
+static bool wide_scatter_ok(int64_t m, int64_t d, int64_t B, WsLevel level) {
+  return level == kWsFull && B > 512 && d >= 64 && d % 64 == 0 && gsi::wide_ok(d) && B < (1ll << 30) && B * d < (1ll << 31) &&
+         std::min(m, d) * B > (1ll << 21);
 }
 // workspace of one linear map of a call with B tokens: partial products of the decode-batch kernel, or of
 // the split contraction of the prefill-sized W term (dense = 1: of the dense product)
@@ -129,13 +133,13 @@ static size_t map_part_bytes(int64_t m, int64_t d, int64_t B, int dense, WsLevel
     if (d % 64 != 0) return 0;
     if (dense) return gsi::mfma_part_bytes(B, m, d, gsi::EPI_STORE_F32, level);
     const size_t part = gsi::mfma_part_bytes(B, m, d, gsi::EPI_SCATTER_ADD, level);
-    return wide_scatter_ok(d, B, level) ? std::max(part, gsi::wide_part_bytes(B, m, d)) : part;
+    return wide_scatter_ok(m, d, B, level) ? std::max(part, gsi::wide_part_bytes(B, m, d)) : part;
   }
   return gsi::tile_part_bytes(m, d, B);
 }
 // ... and of an input whose fired rows are laid out as bf16 for the W term of its maps
-static size_t rounded_rows_bytes(int64_t d, int64_t B, WsLevel level) {
-  return wide_scatter_ok(d, B, level) ? gsi::align_up((size_t)B * d * 2, 256) : 0;
+static size_t rounded_rows_bytes(int64_t m, int64_t d, int64_t B, WsLevel level) {
+  return wide_scatter_ok(m, d, B, level) ? gsi::align_up((size_t)B * d * 2, 256) : 0;
 }
 
 static size_t project_ws_bytes(int64_t d, int64_t k, int64_t B, WsLevel level) {
@@ -165,7 +169,7 @@ static size_t call_ws_bytes(int which_call, int64_t m, int64_t d, int64_t k, int
       // partial products of the matrix-core kernels
       if (m < 1 || d < 1 || B < 1) return 0;
       return map_part_bytes(m, d, B, which_call == GSI_CALL_DENSE_LINEAR, level) +
-             (which_call == GSI_CALL_GATED_LINEAR ? rounded_rows_bytes(d, B, level) + (mfma_batch_ok(d, k, B) ? two_term_bytes(k, B, level) : 0) : 0);
+             (which_call == GSI_CALL_GATED_LINEAR ? rounded_rows_bytes(m, d, B, level) + (mfma_batch_ok(d, k, B) ? two_term_bytes(k, B, level) : 0) : 0);
     default:
       return 0;
   }
@@ -792,10 +796,10 @@ int gsi_gated_linear(const void* W, const void* M, const float* C, const float* 
     e = bt.add(0, gd, W, M, (float*)Y, m, false, gsi::tile_part_bytes(m, d, B) ? (float*)ws : nullptr);
     if (e == hipSuccess) e = bt.flush();
   } else if (mfma_gated_path(W, M, C, R, d, k, B, wdtype, m, Y)) {
-    uint16_t* const rounded = rounded_rows_bytes(d, B, level)
+    uint16_t* const rounded = rounded_rows_bytes(m, d, B, level)
                                   ? reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + map_part_bytes(m, d, B, 0, level)) : nullptr;
     uint16_t* const Ht = two_term_bytes(k, B, level)
-                             ? reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + map_part_bytes(m, d, B, 0, level) + rounded_rows_bytes(d, B, level)) : nullptr;
+                             ? reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + map_part_bytes(m, d, B, 0, level) + rounded_rows_bytes(m, d, B, level)) : nullptr;
     const MfmaMap mp{W, M, C, R, nullptr, 0, fired_idx, n_fired, m, d, k, (float*)Y, (float*)ws, Ht, rounded, false, false};
     e = mfma_gated(&mp, 1, B, level, s);
   } else {
@@ -871,9 +875,10 @@ static size_t stack_table_bytes(int32_t n_maps, int32_t n_inputs, int64_t B) {
 static size_t input_rounded_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int i, int64_t B,
                                   WsLevel level) {
   if (inputs[i].flags & GSI_INPUT_SLOW_PATH_WX) return 0;
+  size_t bytes = 0;
   for (int j = 0; j < n_maps; ++j)
-    if (maps[j].input_id == i && maps[j].wdtype == GSI_BF16) return rounded_rows_bytes(inputs[i].d, B, level);
-  return 0;
+    if (maps[j].input_id == i && maps[j].wdtype == GSI_BF16) bytes = std::max(bytes, rounded_rows_bytes(maps[j].m, inputs[i].d, B, level));
+  return bytes;
 }
 
 static size_t stack_ws_bytes(const gsi_map_desc* maps, int32_t n_maps, const gsi_input_desc* inputs, int32_t n_inputs,
@@ -1754,7 +1759,8 @@ static int layer_stack_impl(const char* fn, const gsi_map_desc* maps, int32_t n_
           continue;
         mm.push_back(MfmaMap{mp.W, mp.M, in.C, in.R, (in.flags & GSI_INPUT_SLOW_PATH_WX) ? in.X : nullptr, in.xdtype, in.fired_idx,
                              in.n_fired, mp.m, in.d, in.k, mp.Y, part[j],
-                             two_term_rows(static_cast<char*>(ws) + ws_off[mp.input_id], in.d, in.k, B, level), rounded[mp.input_id], img_done[j] != 0, read_again(j)});
+                             two_term_rows(static_cast<char*>(ws) + ws_off[mp.input_id], in.d, in.k, B, level),
+                             wide_scatter_ok(mp.m, in.d, B, level) ? rounded[mp.input_id] : nullptr, img_done[j] != 0, read_again(j)});
         map_done[j] = 2;
       }
       if (!mm.empty())

@@ -471,7 +471,7 @@ __global__ __launch_bounds__(kThreads, (AM == 1 && TM == 128 ? 4 : 2)) void gemm
             float* const dp = reinterpret_cast<float*>(Dmat) + (int64_t)row[q] * ldd + col;
             store_row<ONCE != 0>(dp, val[q]);
             if constexpr (EPI == EPI_STORE_F32)
-              if (g.Ht) store_two_terms(g.Ht + (int64_t)row[q] * 2 * N + col / 32 * 64 + col % 32, val[q]);
+              if (g.Ht) store_two_terms(g.Ht, row[q], N, col, val[q]);
           } else {  // scatter: one workgroup owns an output element, so the update is ordered
             const int drow = g.row_idx ? g.row_idx[row[q]] : row[q];
             float* const dp = reinterpret_cast<float*>(Dmat) + (int64_t)drow * ldd + col;
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(256) void splitk_finish(const GemmArgs args) {
       *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(g.D) + (int64_t)row * g.ldd + col) = o;
     } else if constexpr (EPI == EPI_STORE_F32) {
       *reinterpret_cast<float4*>(reinterpret_cast<float*>(g.D) + (int64_t)row * g.ldd + col) = s;
-      if (g.Ht) store_two_terms(g.Ht + (int64_t)row * 2 * g.N + col / 32 * 64 + col % 32, s);
+      if (g.Ht) store_two_terms(g.Ht, row, g.N, col, s);
     } else {
       const int drow = g.row_idx ? g.row_idx[row] : row;
       float* const dp = reinterpret_cast<float*>(g.D) + (int64_t)drow * g.ldd + col;

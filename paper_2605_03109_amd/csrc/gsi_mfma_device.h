@@ -66,8 +66,9 @@ __device__ __forceinline__ uint2 load_row(const uint16_t* p) {
 __device__ __forceinline__ float4 widen_row(const float4& v) { return v; }
 __device__ __forceinline__ float4 widen_row(const uint2& v) { return float4{bf16_lo(v.x), bf16_hi(v.x), bf16_lo(v.y), bf16_hi(v.y)}; }
 
-// four columns of a row in two bf16 terms: the heads at p, the tails 32 elements on
-__device__ __forceinline__ void store_two_terms(uint16_t* p, const float4& v) {
+// four columns of a row of k in two bf16 terms: of 32 columns the heads, then the tails (those past k are not written)
+__device__ __forceinline__ void store_two_terms(uint16_t* Ht, int64_t row, int k, int col, const float4& v) {
+  uint16_t* const p = Ht + row * (64 * ((k + 31) / 32)) + col / 32 * 64 + col % 32;
   const float x[4] = {v.x, v.y, v.z, v.w};
   uint32_t h[4], l[4];
 #pragma unroll

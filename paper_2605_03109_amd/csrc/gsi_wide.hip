@@ -288,7 +288,9 @@ __global__ __launch_bounds__(256) void round_rows(const RoundArgs args) {
 // residual and image products of a prefill-sized call: short (the rank) with long epilogues (every row of R and Y), so a
 // workgroup is four waves (2 x 2, 64 x 128 each) with a tile of 128 x 256 and half a compute unit: one's epilogue beside the
 // other's products.  A k-tile is 32 columns: a row of A is 64 bytes of head and 64 of tail, laid out in LDS as in wide_loop, a
-// row of B 64 bytes, whose piece c lies at c ^ {0, 3, 2, 1}[row / 4 % 4].  One read of B serves both terms.  A wave has all the
+// row of B 64 bytes, whose piece c lies at c ^ {0, 3, 2, 1}[row / 4 % 4].  One read of B serves both terms.  Columns past the rank
+// (the last k-tile of one that is no multiple of 32), like rows past the end, are read as zero: their lanes ask for an address
+// behind the buffer.  A wave has all the
 // operands of a k-tile in registers before its products, so that the k-tile after the next is requested over it at once.
 // As many workgroups as the chip holds take tile after tile; the first two k-tiles of a tile are requested beside the last
 // two of the one before, and arrive before its epilogue begins.
@@ -346,64 +348,78 @@ __global__ __launch_bounds__(kTwoThreads, 2) void wide_two_term_kernel(const Gem
   // a wave requests rows 32 q + 8 w .. + 7 of A and 64 q + 16 w .. + 15 of B; rows past the end read as zero
   u32x4 a, b;
   uint32_t va, vb, sa, sb;
+  int ka;
   auto aim = [&](const Tile& t) {
     const GemmProb& g = args.p[t.problem];
     const int row0 = t.m * kTwoRows, col0 = t.n * kTwoCols;
     const int a_rows = min(kTwoRows, g.M - row0), b_rows = min(kTwoCols, g.N - col0);
-    a = buffer_of(reinterpret_cast<const uint16_t*>(g.A) + (int64_t)row0 * 2 * g.K, (int64_t)a_rows * 4 * g.K);
-    b = buffer_of(reinterpret_cast<const uint16_t*>(g.B) + (int64_t)col0 * g.ldb, ((int64_t)(b_rows - 1) * g.ldb + g.K) * 2);
-    sa = 4u * g.K;
+    ka = g.K;
+    sa = 128u * ((ka + 31) / 32);
     sb = 2u * g.ldb;
+    a = buffer_of(reinterpret_cast<const char*>(g.A) + (int64_t)row0 * sa, (int64_t)a_rows * sa);
+    b = buffer_of(reinterpret_cast<const uint16_t*>(g.B) + (int64_t)col0 * g.ldb, ((int64_t)(b_rows - 1) * g.ldb + g.K) * 2);
     int l = lane;
     asm volatile("" : "+v"(l));  // (what follows from it is not kept in registers over the products)
     va = (8 * w + (l >> 3)) * sa + 16u * ((l & 7) ^ ((4 * w + (l >> 4)) & 7));
     vb = (16 * w + (l >> 2)) * sb + 16u * ((l & 3) ^ ((4 - ((l >> 4) & 3)) & 3));
   };
-  auto request = [&](int kt, int stage) {
+  auto request = [&](int kt, uint32_t stage) {
+    const uint32_t sk = (uint32_t)kt;
+    if (32 * kt + 32 <= ka) {  // (uniform)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      load_to_lds(to + stage * kTwoStage + q * 4096, a, va + 32 * q * sa, (uint32_t)kt * 128u);
-      load_to_lds(to + stage * kTwoStage + kTwoA + q * 4096, b, vb + 64 * q * sb, (uint32_t)kt * 64u);
+      for (int q = 0; q < 4; ++q) {
+        load_to_lds(to + stage + q * 4096, a, va + 32 * q * sa, sk * 128u);
+        load_to_lds(to + stage + kTwoA + q * 4096, b, vb + 64 * q * sb, sk * 64u);
+      }
+    } else {
+      const int rest = ka - 32 * kt;  // columns of the k-tile, a multiple of 8
+      const bool out_a = 8 * (((lane & 7) ^ ((4 * w + (lane >> 4)) & 7)) & 3) >= rest, out_b = 8 * ((lane & 3) ^ ((4 - ((lane >> 4) & 3)) & 3)) >= rest;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        load_to_lds(to + stage + q * 4096, a, out_a ? 0xfffffff0u : va + 32 * q * sa, sk * 128u);
+        load_to_lds(to + stage + kTwoA + q * 4096, b, out_b ? 0xfffffff0u : vb + 64 * q * sb, sk * 64u);
+      }
     }
   };
-  const char* const pa = lds + (64 * wm + lc) * 128;
   const char* const pb = lds + kTwoA + (128 * wn + lc) * 64 + 16 * (lq ^ ((4 - (lc >> 2)) & 3));
-  const int head = 16 * (lq ^ (lc >> 1)), tail = 16 * ((4 + lq) ^ (lc >> 1));
+  const char* const head = lds + (64 * wm + lc) * 128 + 16 * (lq ^ (lc >> 1));
+  const char* const tail = lds + (64 * wm + lc) * 128 + 16 * ((4 + lq) ^ (lc >> 1));
   char* const strip = lds + 2 * kTwoStage + w * kTwoStrip;
 
   Tile now = tile_of(blockIdx.x);
   aim(now);
   request(0, 0);
-  request(1, 1);
+  request(1, kTwoStage);
   wait_loads<0>();
+  uint32_t stage = 0;
   for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const GemmProb& g = args.p[now.problem];
     if (tile == g.blk_begin && tid == 0 && g.sync) *g.sync = 0u;
     const bool more = tile + (int)gridDim.x < tiles;
     const Tile next = tile_of(more ? tile + (int)gridDim.x : tile);
-    const int nk = g.K / 32;  // K is a multiple of 64: at least two k-tiles
+    const int nk = (g.K + 31) / 32;  // two or more
     f32x4 acc[4][8];
 #pragma unroll
     for (int f = 0; f < 32; ++f) acc[f >> 3][f & 7] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto ktile = [&](int t, int stage, bool last) {
+    for (int t = 0; t < nk; ++t) {
       if (t >= 2) {  // all but the next k-tile's (the first two have arrived)
-        if (last && stage == 1 && !more) wait_loads<0>();
-        else wait_loads<8>();
+        if (t + 1 < nk || more) wait_loads<8>();
+        else wait_loads<0>();
       }
       barrier();
       bf16x8 ah[4], al[4], bb[8];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        al[i] = *reinterpret_cast<const bf16x8*>(pa + stage * kTwoStage + i * 2048 + tail);
-        ah[i] = *reinterpret_cast<const bf16x8*>(pa + stage * kTwoStage + i * 2048 + head);
+        al[i] = *reinterpret_cast<const bf16x8*>(tail + stage + i * 2048);
+        ah[i] = *reinterpret_cast<const bf16x8*>(head + stage + i * 2048);
       }
 #pragma unroll
-      for (int n = 0; n < 8; ++n) bb[n] = *reinterpret_cast<const bf16x8*>(pb + stage * kTwoStage + n * 1024);
-      if (last && stage == 0) aim(next);
+      for (int n = 0; n < 8; ++n) bb[n] = *reinterpret_cast<const bf16x8*>(pb + stage + n * 1024);
+      if (t + 2 == nk && more) aim(next);
       wait_lds();
       barrier();
-      if (!last) request(t + 2, stage);
-      else if (more) request(stage, stage);
+      if (t + 2 < nk || more) request(t + 2 < nk ? t + 2 : t + 2 - nk, stage);
+      stage = kTwoStage - stage;
 #pragma unroll
       for (int n = 0; n < 8; ++n)
 #pragma unroll
@@ -413,13 +429,7 @@ __global__ __launch_bounds__(kTwoThreads, 2) void wide_two_term_kernel(const Gem
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb[n], ah[i], acc[i][n], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
-    };
-    for (int t = 0; t + 2 < nk; t += 2) {
-      ktile(t, 0, false);
-      ktile(t + 1, 1, false);
     }
-    ktile(nk - 2, 0, true);
-    ktile(nk - 1, 1, true);
 
     // A lane has four neighbouring columns of row lc of a fragment; 16 rows of half the wave tile go through its strip (piece c
     // of a row at c ^ row), so that what touches memory is 256 bytes of a row: row 4 q + lane / 16, columns 4 (lane % 16) ..
@@ -458,28 +468,29 @@ __global__ __launch_bounds__(kTwoThreads, 2) void wide_two_term_kernel(const Gem
     } else {
       auto residual = [&](auto element) {  // of x
         using T = decltype(element);
-        decltype(load_row<false>(static_cast<const T*>(nullptr))) x[2][4];  // x of half a strip, as stored
+        decltype(load_row<false>(static_cast<const T*>(nullptr))) x[3][4];  // x of three half strips, as stored
         auto request_x = [&](int s) {  // (rows and columns past the end repeat the last)
 #pragma unroll
           for (int q = 0; q < 4; ++q)
-            x[s & 1][q] = load_row<ONCE == 2>(reinterpret_cast<const T*>(g.X) + (int64_t)min(row0 + 16 * (s >> 1) + 4 * q + er, g.M - 1) * ldd +
+            x[s % 3][q] = load_row<ONCE == 2>(reinterpret_cast<const T*>(g.X) + (int64_t)min(row0 + 16 * (s >> 1) + 4 * q + er, g.M - 1) * ldd +
                                               min(col0 + 64 * (s & 1) + ec, g.N - 4));
         };
         request_x(0);
+        request_x(1);
         wait_loads<0>();  // (as above)
         float sums[8];
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
           const int half = s & 1;
           put(s);
-          if (s < 7) request_x(s + 1);
+          if (s < 6) request_x(s + 2);
           f32x4 val[4];
           get(val);
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const int row = row0 + 16 * (s >> 1) + 4 * q + er, col = col0 + 64 * half + ec;
             const bool live = row < g.M && col < g.N;
-            const float4 v = widen_row(x[half][q]);
+            const float4 v = widen_row(x[s % 3][q]);
             const float4 r = float4{v.x - val[q][0], v.y - val[q][1], v.z - val[q][2], v.w - val[q][3]};
             if (live) store_row<ONCE != 0>(reinterpret_cast<float*>(g.D) + (int64_t)row * ldd + col, r);
             const float sr = live ? fmaf(r.x, r.x, fmaf(r.y, r.y, fmaf(r.z, r.z, r.w * r.w))) : 0.f;
@@ -504,9 +515,12 @@ __global__ __launch_bounds__(kTwoThreads, 2) void wide_two_term_kernel(const Gem
 // Ht[row] = the heads of 32 columns of a row of C, their tails, the next 32 columns ...
 __global__ __launch_bounds__(256) void split_rows(const SplitArgs args) {
   const SplitTask& t = args.t[blockIdx.y];
-  const int64_t total = (int64_t)t.rows * (t.k >> 2);
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x)
-    store_two_terms(t.Ht + 8 * (4 * e / 32 * 8) + 4 * e % 32, *reinterpret_cast<const float4*>(t.C + 4 * e));
+  const int k4 = t.k >> 2;
+  const int64_t total = (int64_t)t.rows * k4;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t row = e / k4;
+    store_two_terms(t.Ht, row, t.k, 4 * (int)(e - row * k4), *reinterpret_cast<const float4*>(t.C + 4 * e));
+  }
 }
 
 }  // namespace
