@@ -107,9 +107,15 @@ static bool mfma_batch_ok(int64_t d, int64_t k, int64_t B) {
 static size_t two_term_bytes(int64_t k, int64_t B, WsLevel level) {
   return level == kWsFull && k > 0 && gsi::wide_ok(k) ? gsi::align_up((size_t)B * gsi::wide_two_term_ld(k) * 2, 256) : 0;
 }
+// partial sums of coefficients on the products that read the basis as stored (bf16 activations)
+static bool coeff_basis_ok(int64_t d, int64_t k, WsLevel level) { return level == kWsFull && gsi::basis_ok(d, k); }
+static size_t coeff_part_bytes(int64_t d, int64_t k, int64_t B, WsLevel level) {
+  const int s = coeff_basis_ok(d, k, level) ? gsi::basis_coeff_splits(B, k, d) : 1;
+  return s > 1 ? gsi::align_up((size_t)s * B * k * sizeof(float), 256) : 0;
+}
 static size_t mfma_project_ws(int64_t d, int64_t k, int64_t B, WsLevel level) {
   return gsi::align_up((size_t)k * d * 2, 256) + gsi::align_up((size_t)gsi::mfma_res_tiles(d, level) * B * 2 * 4, 256) +
-         gsi::mfma_part_bytes(B, k, d, gsi::EPI_COEFF, level) + two_term_bytes(k, B, level);
+         std::max(gsi::mfma_part_bytes(B, k, d, gsi::EPI_COEFF, level), coeff_part_bytes(d, k, B, level)) + two_term_bytes(k, B, level);
 }
 // where a projection has them in its workspace (null: nowhere)
 static uint16_t* two_term_rows(void* ws, int64_t d, int64_t k, int64_t B, WsLevel level) {
@@ -156,12 +162,25 @@ static size_t project_ws_bytes(int64_t d, int64_t k, int64_t B, WsLevel level) {
   return need;
 }
 
+// Images on the products that read the basis as stored (gsi_basis.hip), and the workspace of their partial sums: where a part is no
+// longer than 24 k-tiles.  Longer ones are bound by the basis, which every tile of 64 rows reads again.  us, product and sums, on tiles of
+// 128 rows that transpose it on its way / here: 4096 x 4096 x 256 20.0 + 7.8 / 19.3 + 5.4, 16384 x 4096 x 256 50.0 + 7.8 / 54.6, 4096 x 16384 x
+// 256 53.6 + 9.4 / 70.1 + 5.4.
+static bool image_basis_ok(int64_t m, int64_t d, int64_t k, WsLevel level) {
+  return level == kWsFull && k > 128 && gsi::basis_ok(d, k) && d / gsi::basis_splits(m, k, d, 64) <= 1536;
+}
+static size_t image_part_bytes(int64_t m, int64_t d, int64_t k, WsLevel level) {
+  if (!image_basis_ok(m, d, k, level)) return 0;
+  const int s = gsi::basis_splits(m, k, d, 64);
+  return s > 1 ? gsi::align_up((size_t)s * m * k * sizeof(float), 256) : 0;
+}
+
 static size_t call_ws_bytes(int which_call, int64_t m, int64_t d, int64_t k, int64_t B, WsLevel level) {
   switch (which_call) {
     case GSI_CALL_BUILD_IMAGE:
       // the transposed basis of the matrix-core build (bf16 operands); generic kernels need none
       if (m < 1 || d < 1 || k < 1 || k > d || !mfma_image_ok(m, d, k)) return 0;
-      return gsi::align_up((size_t)k * d * 2, 256) + gsi::mfma_part_bytes(m, k, d, gsi::EPI_STORE_BF16, level);
+      return gsi::align_up((size_t)k * d * 2, 256) + std::max(gsi::mfma_part_bytes(m, k, d, gsi::EPI_STORE_BF16, level), image_part_bytes(m, d, k, level));
     case GSI_CALL_PROJECT:
       return project_ws_bytes(d, k, B, level);
     case GSI_CALL_GATED_LINEAR:
@@ -217,6 +236,15 @@ int gsi_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d,
     // cache holds: 4096 x 4096 x 256 30.8 / 27.7, x 512 36.3 / 34.7 (the first limit), 8192 x 4096 x 512 53.3 / 55.7, 11008 x 4096 x 64
     // 43.5 / 47.3, x 128 47.7 / 50.5, x 256 57.8 / 58.3, 4096 x 11008 x 256 60.3 / 57.2, 16384 x 4096 x 64 47.4 / 50.0, x 256 62.7 / 60.0 (the
     // second limit: a rank that all but fills the column tile; x 192 57.7 / 57.9), x 512 81.1 / 87.9.
+    const bool basis = image_basis_ok(m, d, k, level) && aligned(U, 16);
+    if (basis) {
+      gsi::GemmProb g = gemm_prob(W, d, U, k, M, k, m, k, d, gsi::EPI_STORE_BF16);
+      g.max_splits = gsi::basis_splits(m, k, d, 64);
+      if (g.max_splits > 1)
+        g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + gsi::align_up((size_t)k * d * 2, 256));
+      e = gsi::basis_products(&g, 1, gsi::EPI_STORE_BF16, 64, m * k <= (1 << 19) ? 1 : 0, s);
+      return e == hipSuccess ? GSI_OK : hip_fail(e, "gsi_build_image");
+    }
     const int64_t work = gsi::mfma_image_work(m, k, d);
     const bool as_stored = aligned(U, 8) && (work <= 4096 || (work <= 8192 && k > 192 && k <= 256));
     gsi::TransposeTask tr{U, ws, (int)d, (int)k, 0};
@@ -464,8 +492,11 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
   int64_t bytes = map_bytes;
   for (int i = 0; i < n; ++i) bytes += rows_bytes(B, in[i].d) + B * in[i].d * (int64_t)gsi::elem_size(in[i].xdtype);
   const int once = again || !passes_caches(bytes) ? 0 : map_bytes > 0 ? 2 : 1;
-  // The basis is transposed on its way to LDS, which a k-tile pays for with more and smaller loads; bf16 activations of many
-  // tokens (whose operand needs no conversion, and whose row tiles are many) have it transposed once instead.  us, transposed first /
+  // bf16 activations: the products that read the basis as stored (gsi_basis.hip).  us a call, none fired, before / with them: a pair 4096 /
+  // 16384 at rank 64, 200 tokens 50.5 / 48.0; at rank 256, 1024 tokens 117 / 106; at rank 512, 1000 tokens 172 / 147; a block of 2560 /
+  // 10240 at rank 256, 400 tokens 86 / 80.  Others, and calls with a workspace of a former size: the basis is transposed on its way to
+  // LDS, which a k-tile pays for with more and smaller loads; bf16 activations of many tokens (whose operand needs no conversion, and
+  // whose row tiles are many) have it transposed once instead.  us, transposed first /
   // as stored, bf16: one input of 16384 at rank 256, 512 tokens 59 / 57, 768 66 / 63, 1024 82 / 83, 2048 129 / 137; of 4096, 1500
   // tokens 51 / 49, 4096 99 / 108; a block of 2048 / 8192, 1500 tokens 95 / 91, 2048 113 / 114; of 4096 / 16384, 768 tokens 100 / 94, 2048
   // 197 / 200.  fp32: a block of 4096 / 16384 at rank 256, 200 tokens 63 / 57, 1024 155 / 145, 2048 258 / 219, at rank 512, 768 167 /
@@ -474,8 +505,10 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
   for (int i = 0; i < n; ++i)
     if (in[i].xdtype != GSI_F32) longest = std::max(longest, in[i].d);
   const bool bf16_stored = B <= (longest <= 8192 ? 1536 : 768);
-  auto as_stored = [&](int i) { return in[i].xdtype == GSI_F32 || bf16_stored; };
+  auto basis = [&](int i) { return in[i].xdtype != GSI_F32 && coeff_basis_ok(in[i].d, in[i].k, level); };
+  auto as_stored = [&](int i) { return in[i].xdtype == GSI_F32 || bf16_stored || basis(i); };
   tr.clear();
+  wide.clear();
   for (int i = 0; i < n; ++i)
     if (!as_stored(i)) tr.push_back(gsi::TransposeTask{in[i].U, in[i].ws, (int)in[i].d, (int)in[i].k, 0});
   if (hipError_t e = gsi::mfma_transpose_bf16(tr.data(), (int)tr.size(), s); e != hipSuccess) return e;
@@ -486,13 +519,15 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
       const int64_t d = in[i].d, k = in[i].k;
       if (in[i].xdtype != xdt) continue;
       gsi::GemmProb g = gemm_prob(in[i].X, d, as_stored(i) ? in[i].U : in[i].ws, as_stored(i) ? k : d, in[i].C, k, B, k, d, gsi::EPI_STORE_F32);
-      g.max_splits = gsi::mfma_splits(B, k, d, gsi::EPI_COEFF, xdt == GSI_F32, level);
+      g.max_splits = basis(i) ? gsi::basis_coeff_splits(B, k, d) : gsi::mfma_splits(B, k, d, gsi::EPI_COEFF, xdt == GSI_F32, level);
       if (g.max_splits > 1)
         g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(part_n(i)) +
                                           gsi::align_up((size_t)gsi::mfma_res_tiles(d, level) * B * 2 * 4, 256));
       g.Ht = two_term_rows(in[i].ws, d, k, B, level);
-      pr.push_back(g);
+      (basis(i) ? wide : pr).push_back(g);
     }
+    if (hipError_t e = gsi::basis_products(wide.data(), (int)wide.size(), gsi::EPI_STORE_F32, 128, once == 2 ? 1 : 0, s); e != hipSuccess) return e;
+    wide.clear();
     if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s, xdt == GSI_F32 || bf16_stored, once == 2 ? 1 : 0);
         e != hipSuccess)
       return e;

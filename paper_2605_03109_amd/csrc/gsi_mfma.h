@@ -82,7 +82,14 @@ int wide_follow(int64_t M, int64_t K, int splits);
 size_t wide_part_bytes(int64_t M, int64_t N, int64_t K);
 inline bool wide_ok(int64_t K) { return K <= (1 << 22); }  // (offsets in a tile of 256 rows are 32 bits)
 inline int64_t wide_rows_expected(int64_t M) { return M < 512 ? (M < 128 ? M : 128) : M / 4; }
+// Products with a stored basis as the right factor (gsi_basis.hip): D = A B, A[M, K] bf16, B[K, N] bf16 as stored (ldb), K a multiple of
+// 64, N of 8, B 16-byte aligned and below 2 GiB; epi EPI_STORE_BF16 or EPI_STORE_F32 (with Ht).  tm: rows of a tile, 64 or 128.
+hipError_t basis_products(const GemmProb* probs, int n, int epi, int tm, int once, hipStream_t s);
+int basis_splits(int64_t M, int64_t N, int64_t K, int tm);  // of an image
+int basis_coeff_splits(int64_t M, int64_t N, int64_t K);     // of coefficients (tm 128)
+inline bool basis_ok(int64_t K, int64_t N) { return K % 64 == 0 && N % 8 == 0 && K <= (1 << 22) && K * N < (1ll << 30); }
 // adds the partial sums of the products of a launch
+hipError_t mfma_finish_basis(const GemmArgs& g, int epi, bool once, hipStream_t s);
 hipError_t mfma_finish_scatter(const GemmArgs& g, bool once, hipStream_t s);
 
 // Ut[j][i] = U[i][j] for n bf16 matrices U[rows, cols]

@@ -738,6 +738,15 @@ size_t wide_part_bytes(int64_t M, int64_t N, int64_t K) {
   return align_up((size_t)rows * N * sizeof(float), 256);
 }
 
+hipError_t mfma_finish_basis(const GemmArgs& g, int epi, bool once, hipStream_t s) {
+  const dim3 grid = finish_grid(g);
+  if (epi == EPI_STORE_BF16 && once) splitk_finish<EPI_STORE_BF16, 1><<<grid, 256, 0, s>>>(g);
+  else if (epi == EPI_STORE_BF16) splitk_finish<EPI_STORE_BF16, 0><<<grid, 256, 0, s>>>(g);
+  else if (once) splitk_finish<EPI_STORE_F32, 1><<<grid, 256, 0, s>>>(g);
+  else splitk_finish<EPI_STORE_F32, 0><<<grid, 256, 0, s>>>(g);
+  return hipGetLastError();
+}
+
 hipError_t mfma_finish_scatter(const GemmArgs& g, bool once, hipStream_t s) {
   bool split = false;
   for (int i = 0; i < g.n; ++i) split |= g.p[i].splits > 1 || g.p[i].row_tiles;

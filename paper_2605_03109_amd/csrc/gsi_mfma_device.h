@@ -82,5 +82,31 @@ __device__ __forceinline__ void store_two_terms(uint16_t* Ht, int64_t row, int k
   *reinterpret_cast<u32x2*>(p + 32) = u32x2{l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
 }
 
+// Loads from memory straight to LDS are inline assembly: they write no register, and the compiler, which would wait for all of them
+// before every read of LDS, does not see them.  Every wait for them is written out; the compiler's own counts can only wait
+// for more.
+typedef __attribute__((address_space(3))) char lds_char;
+// a buffer resource over `bytes` bytes: what lies behind them reads as zero
+__device__ __forceinline__ u32x4 buffer_of(const void* p, uint64_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu),
+               (uint32_t)__builtin_amdgcn_readfirstlane(bytes > 0xffffffffull ? 0xffffffffu : (uint32_t)bytes), 0x00020000u};
+}
+// 16 bytes per lane from buffer + voff + soff to LDS at lds + 16 * lane
+__device__ __forceinline__ void load_to_lds(uint32_t lds, const u32x4& buffer, uint32_t voff, uint32_t soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(buffer), "s"(soff)
+               : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {  // all but the N requested last
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 }  // namespace
 }  // namespace gsi

@@ -13,9 +13,6 @@
 // so it is the lane that loads another piece of its row.
 // What bounds it is the power of the matrix cores: 8192^3 1467 TFLOP/s on random operands, 2022 on zeros; 32 x 32 x 16
 // products 1251 and 1883.  2048 x 16384 x 4096: 1395 TFLOP/s (gemm_nt, whose operands go through registers: 1004).
-//
-// The loads are inline assembly: they write no register, and the compiler, which would wait for all of them before every read
-// of LDS, does not see them.  Every wait for them is written here; the compiler's own counts can only wait for more.
 #include <algorithm>
 
 #include "gsi_mfma_device.h"
@@ -23,34 +20,10 @@
 namespace gsi {
 namespace {
 
-typedef __attribute__((address_space(3))) char lds_char;
-
 constexpr int kWideThreads = 512;
 constexpr int kWideTile = 256;
 constexpr int kHalf = 128 * 128;       // bytes of a half: 128 rows of 64 columns
 constexpr int kWideStage = 4 * kHalf;  // A0 A1 B0 B1
-
-// a buffer resource over `bytes` bytes: what lies behind them reads as zero
-__device__ __forceinline__ u32x4 buffer_of(const void* p, uint64_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu),
-               (uint32_t)__builtin_amdgcn_readfirstlane(bytes > 0xffffffffull ? 0xffffffffu : (uint32_t)bytes), 0x00020000u};
-}
-// 16 bytes per lane from buffer + voff + soff to LDS at lds + 16 * lane
-__device__ __forceinline__ void load_to_lds(uint32_t lds, const u32x4& buffer, uint32_t voff, uint32_t soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(buffer), "s"(soff)
-               : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_loads() {  // all but the N requested last
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ void barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_barrier" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
 
 // Sums of a wave: [h][g][i][j][v]: row 128 h + 32 i + 16 wm + lane % 16 of the tile, column 128 g + 32 wn + 16 j + 4 (lane / 16) + v
 // (the columns of B are the first operand of the products, so that a lane has four neighbouring columns of a row).
