@@ -134,26 +134,26 @@ __device__ __forceinline__ void stage_commit(const float4 (&v)[2][kHalfVec], boo
 // The weights of a wave's item: rows row (per lane), columns c0 + 32 s + 8 lq .. + 7 for step s.  base: first column of
 // the slice; steps past the slice repeat its last one.  A slice that ends inside a step (a rank that is no multiple of
 // 32, three terms only) has zeros past its end: those lanes read the step's first columns instead and are cleared.
-template <int T>
-__device__ __forceinline__ void weights_issue(uint4 (&w)[kSteps], const char* __restrict__ base, uint32_t row_off, int lq, int ncol,
+template <int T, int N>
+__device__ __forceinline__ void weights_issue(uint4 (&w)[N], const char* __restrict__ base, uint32_t row_off, int lq, int ncol,
                                               int ns) {
   const uint32_t voff = row_off + 16u * lq;
-  if (T == 2 && ns == kSteps) {  // uniform: a whole slice, at constant offsets
+  if (ns == N && (T == 2 || (N < kSteps && ncol % kStepCols == 0))) {  // uniform: a whole slice, at constant offsets
 #pragma unroll
-    for (int s = 0; s < kSteps; ++s) w[s] = *reinterpret_cast<const uint4*>(base + s * kStepCols * 2 + voff);
+    for (int s = 0; s < N; ++s) w[s] = *reinterpret_cast<const uint4*>(base + s * kStepCols * 2 + voff);
     return;
   }
   const uint32_t vlast = T == 2 || (ns - 1) * kStepCols + 8 * lq < ncol ? voff : row_off;
 #pragma unroll
-  for (int s = 0; s < kSteps; ++s)
+  for (int s = 0; s < N; ++s)
     w[s] = *reinterpret_cast<const uint4*>(base + (size_t)(min(s, ns - 1) * kStepCols * 2) + (s < ns - 1 ? voff : vlast));
 }
-template <int T>
-__device__ __forceinline__ void weights_clear_tail(uint4 (&w)[kSteps], int lq, int ncol, int ns) {
+template <int T, int N>
+__device__ __forceinline__ void weights_clear_tail(uint4 (&w)[N], int lq, int ncol, int ns) {
   if (T == 2 || ncol % kStepCols == 0) return;  // uniform
   const bool dead = (ns - 1) * kStepCols + 8 * lq >= ncol;
 #pragma unroll
-  for (int s = 0; s < kSteps; ++s)
+  for (int s = 0; s < N; ++s)
     if (s == ns - 1 && dead) w[s] = uint4{0u, 0u, 0u, 0u};
 }
 
@@ -169,8 +169,8 @@ __device__ __forceinline__ f32x4 add_tails(const f32x4& head, const f32x4& tails
 // acc0 / acc1 = the item's weights times the staged tokens 0 .. 15 / 16 .. 31.  Three terms: the head's products of even
 // and odd steps and those of the two remainders have accumulators of their own, so that fewer large partial sums are
 // rounded (the residual's error against 64 bits is then the FMA kernel's, 2.7e-6 at rank 128; 3.6e-6 with one).
-template <int T>
-__device__ __forceinline__ void item_mma(const uint4 (&w)[kSteps], const uint16_t* vt, int vrow, int li, int lq,
+template <int T, int N>
+__device__ __forceinline__ void item_mma(const uint4 (&w)[N], const uint16_t* vt, int vrow, int li, int lq,
                                          int ns, bool two, f32x4& acc0, f32x4& acc1) {
   constexpr int NA = T == 3 ? 3 : 1;
   f32x4 acc[2][NA];
@@ -188,22 +188,22 @@ __device__ __forceinline__ void item_mma(const uint4 (&w)[kSteps], const uint16_
           a, *reinterpret_cast<const bf16x8*>(vt + (q * kRoundTok + 16 * t + li) * vrow + col), d, 0, 0, 0);
     }
   };
-  if (T == 2 && ns == kSteps) {
+  if ((T == 2 || N < kSteps) && ns == N) {
     // a whole slice: no branch per step, so the LDS reads run ahead of the products (the pair, 16 tokens: 72.5 -> 70.5 us
     // with the constant offsets of weights_issue, 32 tokens 77.2 -> 75.0)
     if (two) {
 #pragma unroll
-      for (int s = 0; s < kSteps; ++s) {
+      for (int s = 0; s < N; ++s) {
         step(s, 0);
         step(s, 1);
       }
     } else {
 #pragma unroll
-      for (int s = 0; s < kSteps; ++s) step(s, 0);
+      for (int s = 0; s < N; ++s) step(s, 0);
     }
   } else {
 #pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
+    for (int s = 0; s < N; ++s) {
       if (s < ns) {
         step(s, 0);
         if (two) step(s, 1);
@@ -528,38 +528,47 @@ __global__ __launch_bounds__(256) void tile_proj_reduce(const ProjBatch pb) {
 // after the other, us each: 97.5 -> 93.6 (20 tokens: 75.5 -> 73.7, 128: 125.3 -> 116.8; a block at rank 200, 24 tokens:
 // 54.1 -> 47.2).  With other work between the calls they take 3 to 5 us more.
 // LDS holds the operand of the launch's largest rank only (vrow), so that the short items of small ranks share a unit.
-template <int TI>
-__device__ __forceinline__ void image_item(const TileImg& p, int item, int B, uint16_t* vt, int vrow, int wave,
+template <int TI, int N>
+__device__ __forceinline__ void image_item(const TileImg& p, int item, int B, int per, uint16_t* vt, int vrow, int wave,
                                            int li, int lq) {
   const int nrb = (p.m + kItemRows - 1) / kItemRows;
-  const int rb = item % nrb, g0 = (item / nrb) * kRoundTok;
-  const int count = min(B, g0 + kRoundTok);
+  const int rb = item % nrb, end = min(B, (item / nrb + 1) * per);
+  int g0 = (item / nrb) * per;
   const int m = p.m, k = p.k, ns = (k + kStepCols - 1) / kStepCols;
   const int row0 = rb * kItemRows + 16 * wave;
-  const bool two = count - g0 > 16;  // uniform
   float4 v[2][kHalfVec];
-  stage_issue<TI>(v, two, p.C, GSI_F32, k, nullptr, g0, count, B, 0, k, wave);
+  stage_issue<TI>(v, end - g0 > 16, p.C, GSI_F32, k, nullptr, g0, end, B, 0, k, wave);
   __builtin_amdgcn_sched_barrier(0);
-  uint4 w[kSteps];
+  uint4 w[N];
   weights_issue<TI>(w, reinterpret_cast<const char*>(p.M), (uint32_t)min(row0 + li, m - 1) * (uint32_t)k * 2u, lq, k, ns);
   __builtin_amdgcn_sched_barrier(0);
-  stage_commit<TI>(v, two, vt, vrow, k, wave);
+  stage_commit<TI>(v, end - g0 > 16, vt, vrow, k, wave);
   weights_clear_tail<TI>(w, lq, k, ns);
-  __syncthreads();
-  f32x4 acc0, acc1;
-  item_mma<TI>(w, vt, vrow, li, lq, ns, two, acc0, acc1);
-  const int row = row0 + 4 * lq;
-  if (row >= m) return;  // m is a multiple of 4
+  for (;;) {
+    const bool more = TI == 2 && N < kSteps && end - g0 > kRoundTok;  // uniform
+    if (more) stage_issue<TI>(v, end - g0 > kRoundTok + 16, p.C, GSI_F32, k, nullptr, g0 + kRoundTok, end, B, 0, k, wave);
+    __syncthreads();
+    f32x4 acc0, acc1;
+    item_mma<TI>(w, vt, vrow, li, lq, ns, end - g0 > 16, acc0, acc1);
+    const int row = row0 + 4 * lq;
+    if (row < m) {  // m is a multiple of 4
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int j = g0 + 16 * t + li;
-    const f32x4 a = t ? acc1 : acc0;
-    if (j < count) *reinterpret_cast<float4*>(p.Y + (int64_t)j * m + row) = float4{a[0], a[1], a[2], a[3]};
+      for (int t = 0; t < 2; ++t) {
+        const int j = g0 + 16 * t + li;
+        const f32x4 a = t ? acc1 : acc0;
+        if (j < end) *reinterpret_cast<float4*>(p.Y + (int64_t)j * m + row) = float4{a[0], a[1], a[2], a[3]};
+      }
+    }
+    if (!more) return;
+    __syncthreads();  // the operands of this round have been read
+    g0 += kRoundTok;
+    stage_commit<TI>(v, end - g0 > 16, vt, vrow, k, wave);
   }
 }
 
-template <int T>
-__global__ __launch_bounds__(kTBlock, 4) void tile_residual(const ProjBatch pb, const TileImgBatch ib, int vrow) {
+// N: steps of a rank, 16, or 8 or 4, where the registers of two terms have room for several rounds of 32 tokens (per tokens)
+template <int T, int N>
+__global__ __launch_bounds__(kTBlock, 4) void tile_residual(const ProjBatch pb, const TileImgBatch ib, int vrow, int per) {
   extern __shared__ __align__(16) uint16_t vt[];  // [T][kRoundTok][vrow]
   __shared__ int s_last;
   __shared__ float red[kTWaves][kRoundTok][2];
@@ -574,80 +583,102 @@ __global__ __launch_bounds__(kTBlock, 4) void tile_residual(const ProjBatch pb, 
     for (int i = 1; i < kMaxLinTasks; ++i)
       if (i < ib.n && item >= ib.t[i].blk_begin) ii = i;
     const TileImg& p = ib.t[ii];
-    if (T == 2 || p.terms == 2) image_item<2>(p, item - p.blk_begin, B, vt, vrow, wave, li, lq);
-    else image_item<T>(p, item - p.blk_begin, B, vt, vrow, wave, li, lq);
+    if (T == 2 || p.terms == 2) image_item<2, N>(p, item - p.blk_begin, B, per, vt, vrow, wave, li, lq);
+    else image_item<T, N>(p, item - p.blk_begin, B, per, vt, vrow, wave, li, lq);
     return;
   }
   const int ti = find_task(pb.b_begin, pb.n, blockIdx.x);
   const ProjTask& p = pb.t[ti];
-  const int rounds = (B + kRoundTok - 1) / kRoundTok;
+  const int groups = (B + per - 1) / per;
   const int item = blockIdx.x - pb.b_begin[ti];
-  const int nrb = p.d / kItemRows;  // row blocks; the rounds of a row block are nrb workgroups apart (same XCD)
-  const int rb = item % nrb, g0 = (item / nrb) * kRoundTok;
-  const int count = min(B, g0 + kRoundTok);
+  const int nrb = p.d / kItemRows;  // row blocks; the token groups of a row block are nrb workgroups apart (same XCD)
+  const int rb = item % nrb, end = min(B, (item / nrb + 1) * per);
+  int g0 = (item / nrb) * per;
   const int d = p.d, k = p.k, ns = (k + kStepCols - 1) / kStepCols;
   const int row0 = rb * kItemRows + 16 * wave;  // d is a multiple of 128: every row exists
   const uint16_t* U = reinterpret_cast<const uint16_t*>(p.U);
 
   float4 v[2][kHalfVec];
-  const bool two = count - g0 > 16;  // uniform
-  stage_issue<T>(v, two, p.C, GSI_F32, k, nullptr, g0, count, B, 0, k, wave);
+  stage_issue<T>(v, end - g0 > 16, p.C, GSI_F32, k, nullptr, g0, end, B, 0, k, wave);
   __builtin_amdgcn_sched_barrier(0);
-  uint4 w[kSteps];
+  uint4 w[N];
   weights_issue<T>(w, reinterpret_cast<const char*>(U), (uint32_t)(row0 + li) * (uint32_t)k * 2u, lq, k, ns);
   // x of the lane's outputs: token g0 + 16 t + li, rows row0 + 4 lq .. + 3
   float4 xv[2];
+  auto request_x = [&](int g) {
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int j = min(g0 + 16 * t + li, B - 1);
-    xv[t] = load_act4<T == 2>(p.X, p.xdtype, (int64_t)j * d + row0 + 4 * lq);
-  }
+    for (int t = 0; t < 2; ++t) {
+      const int j = min(g + 16 * t + li, B - 1);
+      xv[t] = load_act4<T == 2>(p.X, p.xdtype, (int64_t)j * d + row0 + 4 * lq);
+    }
+  };
+  request_x(g0);
   __builtin_amdgcn_sched_barrier(0);
-  stage_commit<T>(v, two, vt, vrow, k, wave);
+  stage_commit<T>(v, end - g0 > 16, vt, vrow, k, wave);
   weights_clear_tail<T>(w, lq, k, ns);
-  __syncthreads();
-  f32x4 acc0, acc1;
-  item_mma<T>(w, vt, vrow, li, lq, ns, two, acc0, acc1);
+  float4 r[2];
+  auto store_r = [&]() {
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int j = g0 + 16 * t + li;
-    const f32x4 a = t ? acc1 : acc0;
-    const float4 x = xv[t];
-    const float4 r = float4{x.x - a[0], x.y - a[1], x.z - a[2], x.w - a[3]};
-    float sr = 0.f, sx = 0.f;
-    if (j < count) {
-      *reinterpret_cast<float4*>(p.R + (int64_t)j * d + row0 + 4 * lq) = r;
-      sr = fmaf(r.x, r.x, fmaf(r.y, r.y, fmaf(r.z, r.z, r.w * r.w)));
-      sx = fmaf(x.x, x.x, fmaf(x.y, x.y, fmaf(x.z, x.z, x.w * x.w)));
+    for (int t = 0; t < 2; ++t) {
+      const int j = g0 + 16 * t + li;
+      if (j < end) *reinterpret_cast<float4*>(p.R + (int64_t)j * d + row0 + 4 * lq) = r[t];
     }
-    // the four row groups of the wave (lanes li, li+16, li+32, li+48), fixed order
-    sr += __shfl_xor(sr, 16); sr += __shfl_xor(sr, 32);
-    sx += __shfl_xor(sx, 16); sx += __shfl_xor(sx, 32);
-    if (lq == 0) {
-      red[wave][16 * t + li][0] = sr;
-      red[wave][16 * t + li][1] = sx;
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < 2 * kRoundTok) {
-    const int tl = threadIdx.x >> 1, c = threadIdx.x & 1;
-    if (g0 + tl < count) {
-      float sum = 0.f;
+  };
+  for (;;) {
+    const bool more = T == 2 && N < kSteps && end - g0 > kRoundTok;  // uniform
+    if (more) stage_issue<T>(v, end - g0 > kRoundTok + 16, p.C, GSI_F32, k, nullptr, g0 + kRoundTok, end, B, 0, k, wave);
+    __syncthreads();
+    f32x4 acc0, acc1;
+    item_mma<T>(w, vt, vrow, li, lq, ns, end - g0 > 16, acc0, acc1);
 #pragma unroll
-      for (int wv = 0; wv < kTWaves; ++wv) sum += red[wv][tl][c];
-      // written through to memory (a store that is coherent across the chip), so that the workgroup that finishes
-      // last can read it without anybody writing a whole L2 back: such a write-back costs about a microsecond per
-      // workgroup, one after the other
-      __hip_atomic_store(&p.part_n[((int64_t)rb * B + g0 + tl) * 2 + c], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int t = 0; t < 2; ++t) {
+      const int j = g0 + 16 * t + li;
+      const f32x4 a = t ? acc1 : acc0;
+      const float4 x = xv[t];
+      r[t] = float4{x.x - a[0], x.y - a[1], x.z - a[2], x.w - a[3]};
+      float sr = 0.f, sx = 0.f;
+      if (j < end) {
+        sr = fmaf(r[t].x, r[t].x, fmaf(r[t].y, r[t].y, fmaf(r[t].z, r[t].z, r[t].w * r[t].w)));
+        sx = fmaf(x.x, x.x, fmaf(x.y, x.y, fmaf(x.z, x.z, x.w * x.w)));
+      }
+      // the four row groups of the wave (lanes li, li+16, li+32, li+48), fixed order
+      sr += __shfl_xor(sr, 16); sr += __shfl_xor(sr, 32);
+      sx += __shfl_xor(sx, 16); sx += __shfl_xor(sx, 32);
+      if (lq == 0) {
+        red[wave][16 * t + li][0] = sr;
+        red[wave][16 * t + li][1] = sx;
+      }
     }
+    __syncthreads();
+    if (threadIdx.x < 2 * kRoundTok) {
+      const int tl = threadIdx.x >> 1, c = threadIdx.x & 1;
+      if (g0 + tl < end) {
+        float sum = 0.f;
+#pragma unroll
+        for (int wv = 0; wv < kTWaves; ++wv) sum += red[wv][tl][c];
+        // written through to memory (a store that is coherent across the chip), so that the workgroup that finishes
+        // last can read it without anybody writing a whole L2 back: such a write-back costs about a microsecond per
+        // workgroup, one after the other
+        __hip_atomic_store(&p.part_n[((int64_t)rb * B + g0 + tl) * 2 + c], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    if (!more) break;
+    store_r();
+    g0 += kRoundTok;
+    request_x(g0);
+    stage_commit<T>(v, end - g0 > 16, vt, vrow, k, wave);  // (every wave has read the operands of the round before)
   }
-  if (!pb.norms) return;  // uniform
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores have completed ...
+  if (!pb.norms) {  // uniform
+    store_r();
+    return;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the shares have reached memory ...
   __syncthreads();                                  // ... in every wave before the workgroup counts as done
   if (threadIdx.x == 0) {
     const unsigned done = __hip_atomic_fetch_add(p.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = done + 1u == (unsigned)(nrb * rounds);
+    s_last = done + 1u == (unsigned)(nrb * groups);
   }
+  store_r();  // (nothing of this launch reads R: behind the count, so that the wait above is not for it)
   __syncthreads();
   if (!s_last) return;  // uniform
   norms_and_gate<kTBlock>(p, B, pb.gate, pb.eps, reinterpret_cast<float2*>(vt),
@@ -672,6 +703,7 @@ static int tile_slab_rows(int64_t) { return kPSteps * kStepCols; }
 // 70.6 against 71.5.  With more, two share
 // a unit: a block at rank 200, 8 tokens (512 workgroups) 41.9 us against 46.4; the pair with 128 tokens 116.8 against 124.8.
 constexpr int kFewItems = 384;
+constexpr int kResident = 512;  // workgroups: two per compute unit
 constexpr size_t kWholeUnit = 84 * 1024;
 
 size_t tile_project_ws(int64_t d, int64_t k, int64_t B) {
@@ -702,7 +734,19 @@ hipError_t tile_proj_reduce_launch(const ProjBatch& pb, hipStream_t s) {
 
 hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, float eps, hipStream_t s, TileImgBatch& ib) {
   if (pb.n == 0 || pb.B == 0) return hipSuccess;
-  const int rounds = (int)ceil_div(pb.B, kRoundTok);
+  int max_k = 0;
+  for (int i = 0; i < pb.n; ++i) max_k = std::max(max_k, pb.t[i].k);  // (an image's rank is that of its input)
+  const int steps = max_k <= kSliceCols / 4 ? kSteps / 4 : pb.t[0].tile == 2 && max_k <= kSliceCols / 2 ? kSteps / 2 : kSteps;
+  // Tokens of a workgroup: as many rounds of 32, which share its rows, as let the whole launch be resident at once, while the registers of
+  // the rank's steps leave room for the next round's tokens (two terms, ranks of up to 256).  us a call, 32 tokens a workgroup and
+  // 16 steps / so: the pair 4096 / 16384 at rank 256, 64 tokens 96.9 / 92.6, 128 tokens 124.7 / 118.0, 4 tokens 74.2 / 71.6 (its eight
+  // steps); a block at rank 128, 128 tokens 171 / 151; three terms, a block of 2560 / 10240 at rank 128, 23 tokens 64.4 / 62.8.
+  int64_t blocks = 0;
+  for (int i = 0; i < pb.n; ++i) blocks += pb.t[i].b_slabs;
+  for (int i = 0; i < ib.n; ++i) blocks += ceil_div(ib.t[i].m, kItemRows);
+  int per = kRoundTok;
+  while (pb.t[0].tile == 2 && steps < kSteps && per < pb.B && blocks * ceil_div(pb.B, per) > kResident) per *= 2;
+  const int rounds = (int)ceil_div(pb.B, per);
   int ta = 0, tb = 0;
   for (int i = 0; i < pb.n; ++i) {
     pb.a_begin[i] = ta;
@@ -714,29 +758,33 @@ hipError_t tile_project_launch(ProjBatch& pb, bool with_norms, bool with_gate, f
   pb.norms = with_norms ? 1 : 0;
   pb.gate = with_gate ? 1 : 0;
   pb.eps = eps;
-  int imgs = 0, max_k = 0;
+  int imgs = 0;
   for (int i = 0; i < ib.n; ++i) {
     ib.t[i].blk_begin = imgs;
     imgs += (int)ceil_div(ib.t[i].m, kItemRows) * rounds;
   }
-  for (int i = 0; i < pb.n; ++i) max_k = std::max(max_k, pb.t[i].k);  // (an image's rank is that of its input)
   const int vrow = (int)align_up((size_t)max_k, kStepCols) + 8;
   hipError_t err = hipSuccess;
   auto launch = [&](auto terms) {
     constexpr int T = decltype(terms)::value;
     constexpr size_t kScratch = kTBlock * sizeof(float2) + 16;  // norms_and_gate
     size_t smem = std::max((size_t)T * kRoundTok * vrow * sizeof(uint16_t), kScratch);
-    if (imgs > 0 && tb + imgs <= kFewItems) smem = std::max(smem, kWholeUnit);
-    static LdsLimit lds;  // more than the default 64 KB at the largest ranks
-    err = lds.allow(reinterpret_cast<const void*>(&tile_residual<T>),
-                    std::max(T * kRoundTok * kVRow * (int)sizeof(uint16_t), (int)kWholeUnit));
-    if (err != hipSuccess) return;
+    if (imgs > 0 && per == kRoundTok && tb + imgs <= kFewItems) smem = std::max(smem, kWholeUnit);
+    auto residual = [&](auto n) {  // (LDS: more than the default 64 KB at the largest ranks)
+      constexpr int N = decltype(n)::value;
+      static LdsLimit lds;
+      const int most = std::max(T * kRoundTok * (N * kStepCols + 8) * (int)sizeof(uint16_t), (int)kWholeUnit);
+      if (err == hipSuccess) err = lds.allow(reinterpret_cast<const void*>(&tile_residual<T, N>), most);
+      if (err == hipSuccess) tile_residual<T, N><<<tb + imgs, kTBlock, smem, s>>>(pb, ib, vrow, per);
+    };
     if (pb.B <= 32) tile_proj_partial<1, T><<<ta, kPBlock, 0, s>>>(pb);
     else if (pb.B <= 64) tile_proj_partial<2, T><<<ta, kPBlock, 0, s>>>(pb);
     else tile_proj_partial<4, T><<<ta, kPBlock, 0, s>>>(pb);
     err = tile_proj_reduce_launch(pb, s);
     if (err != hipSuccess) return;
-    tile_residual<T><<<tb + imgs, kTBlock, smem, s>>>(pb, ib, vrow);
+    if (steps == kSteps / 4) residual(std::integral_constant<int, kSteps / 4>{});
+    else if (steps == kSteps) residual(std::integral_constant<int, kSteps>{});
+    else if constexpr (T == 2) residual(std::integral_constant<int, kSteps / 2>{});
   };
   if (pb.t[0].tile == 3) launch(std::integral_constant<int, 3>{});
   else launch(std::integral_constant<int, 2>{});
