@@ -1,5 +1,6 @@
-"""Images on the products that read the basis as stored: ranks that are no multiple of the column tile or of a fragment, row tiles and
-column tiles with remainders, contractions of one k-tile, of an odd number, in parts, and shorter than the tiles on their way."""
+"""Images and coefficients of prefill-sized calls on the products that read the basis as stored: ranks that are no multiple of the column
+tile or of a fragment, row tiles and column tiles with remainders, contractions of one k-tile, of an odd number, in parts, and shorter
+than the tiles on their way."""
 import pytest
 import torch
 
@@ -47,3 +48,28 @@ def test_coefficients(d, k, B):
     x, u = X.double(), U.double()
     # 32-bit sums of d exact products
     assert ((C.double() - x @ u).abs() <= (8 + d**0.5) * 2.0**-24 * (x.abs() @ u.abs())).all()
+
+
+# fp32 activations: contractions too short to cut, at the four tiles that are cut to four k-tiles and one more, an odd number of k-tiles on
+# eight and nine tiles, the most parts
+@pytest.mark.parametrize("d,k,B", [(256, 64, 512), (512, 64, 129), (1024, 64, 512), (1024, 64, 513), (4160, 512, 400), (4160, 192, 1025), (16384, 64, 130),
+                                   (16384, 512, 400)])
+def test_coefficients_of_fp32_rows(d, k, B):
+    from paper_2605_03109_amd import gsi
+
+    g = torch.Generator(device="cuda").manual_seed(d + k + B)
+    X = torch.randn(B, d, generator=g, device="cuda")
+    U = (torch.randn(d, k, generator=g, device="cuda") / d**0.5).to(torch.bfloat16)
+    print(f"case fp32 coefficients d={d} k={k} B={B}", flush=True)
+    need = gsi.workspace_bytes(gsi.CALL_PROJECT, 0, d, k, B)
+    ws = torch.full((need + (1 << 20),), 0x5A, dtype=torch.uint8, device="cuda")
+    C, R = torch.empty(B, k, device="cuda"), torch.empty(B, d, device="cuda")
+    rn, xn = torch.empty(B, device="cuda"), torch.empty(B, device="cuda")
+    rc = gsi.lib.gsi_project(U.data_ptr(), X.data_ptr(), d, k, B, gsi.GSI_BF16, gsi.GSI_F32, C.data_ptr(), R.data_ptr(), rn.data_ptr(), xn.data_ptr(),
+                             ws.data_ptr(), need, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == gsi.GSI_OK, gsi.last_error()
+    x, u = X.double(), U.double()
+    # head and tail of x leave 2^-18 of it (half a unit of bf16, twice); 32-bit sums of 2 d exact products
+    assert ((C.double() - x @ u).abs() <= (2.0**-17 + (8 + (2 * d) ** 0.5) * 2.0**-24) * (x.abs() @ u.abs())).all()
+    assert bool((ws[need:] == 0x5A).all())
