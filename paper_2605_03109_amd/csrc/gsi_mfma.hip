@@ -675,14 +675,15 @@ bool image_rows64(int64_t M, int64_t N, int64_t K) { return mfma_image_work(M, N
 // (calls replayed from a graph): 129 x 4096 x 4096 48 / 23, two-term 97 / 36; 512 rows 50 / 33, 101 / 47; 1024 rows 53 / 50,
 // 104 / 77; W r of 4096 x 4096 with 205 of 1024 rows fired 78 / 42; the projection of 2048 fp32 tokens, 4096 x 512
 // 141 / 77; the block of 2048 tokens 742 / 730 (its W r launch 295 + 15 / 268 + 31).
-// Where the workspace has room, two-term coefficients are cut a third time, up to half the chip: the second cut ends at eight parts,
+// Where the workspace has room, two-term coefficients are cut into as many parts as half the chip takes: the second cut ends at eight,
 // which leaves a long contraction of few tiles on a quarter of it (4096 / 16384, 400 tokens at rank 512: 192 workgroups, the longest of 32
-// k-tiles).  Down to 256 columns where there are at most four tiles; with more, the other inputs of a block fill the chip already, and half
-// as deep again was slower: a block of 2048 / 8192 and 4096 / 16384 at rank 256, 777 tokens 98 / 104, 158 / 165; 4096 / 16384, 640 tokens
-// 128 / 133; cut to the whole chip, 4096 / 16384 at rank 512, 1000 tokens 272 / 295.  us a call, none fired, without / with it: the
-// pair 1024 / 4096 at rank 64, 200 tokens 44 / 40; 2560 / 10240 54 / 46; at rank 256, 500 tokens 71 / 65; 4096 / 16384 at rank 256, 400 tokens 87 / 79,
-// 900 134 / 117; at rank 512, 400 tokens 126 / 106; a block of 2560 / 10240 at rank 64, 200 tokens 63 / 55; 4096 / 16384 at rank 256, 900
-// tokens 184 / 171; of 85 calls none slower by more than the 2 % that runs differ.
+// k-tiles), and it doubles, which leaves 40 or 160 k-tiles in parts of 10 and 13.  Down to 512 columns, or 256 where there are at most
+// four tiles; with more, the other inputs of a block fill the chip already, and half as deep again was slower: a block of 2048 / 8192 and
+// 4096 / 16384 at rank 256, 777 tokens 98 / 104, 158 / 165; 4096 / 16384, 640 tokens 128 / 133; cut to the whole chip, 4096 / 16384 at rank
+// 512, 1000 tokens 272 / 295.  us a call, none fired, without / with it: the pair 1024 / 4096 at rank 64, 200 tokens 44 / 40;
+// 2560 / 10240 54 / 46, 640 tokens 66 / 60; at rank 256, 500 tokens 71 / 65; 4096 / 16384 at rank 256, 400 tokens 87 / 79, 900 134 / 117; at rank
+// 512, 400 tokens 126 / 106; a block of 2560 / 10240 at rank 64, 200 tokens 63 / 55, 640 86 / 80; 4096 / 16384 at rank 256, 900 tokens
+// 184 / 171; of 85 calls none slower by more than runs differ.
 int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool two_term, WsLevel level) {
   if (epi == EPI_RESIDUAL) return 1;
   const int64_t m = rows_expected(M, epi), nk = ceil_div(K, BK);
@@ -709,7 +710,7 @@ int mfma_splits(int64_t M, int64_t N, int64_t K, int epi, bool two_term, WsLevel
          nk / (s * 2) >= (tiles * s > kUnits / 8 ? 2 * kMinDepth : kMinDepth))
     s *= 2;
   if (level == kWsFull && epi == EPI_COEFF)
-    while (s * 2 <= kMaxSplits && tiles * s * 2 <= kUnits / 2 && nk / (s * 2) >= (tiles <= kUnits / 64 ? kMinDepth / 2 : kMinDepth)) s *= 2;
+    s = (int)std::min<int64_t>(std::max<int64_t>(s, std::min<int64_t>(kUnits / 2 / tiles, nk / (tiles <= kUnits / 64 ? kMinDepth / 2 : kMinDepth))), kMaxSplits);
   return s;
 }
 

@@ -34,8 +34,9 @@ def test_image(m, d, k):
     assert bool((M[m] == 7.0).all()) and bool((ws[need:] == 0x5A).all())
 
 
-# one row over a tile of 128; one k-tile, an odd number; many parts of four k-tiles; column tiles with remainders
-@pytest.mark.parametrize("d,k,B", [(64, 64, 129), (192, 128, 300), (1088, 192, 257), (4096, 64, 140), (2048, 320, 640), (16384, 256, 385)])
+# one row over a tile of 128; one k-tile, an odd number; many parts of four k-tiles, of eight, of unequal length; column tiles with remainders
+@pytest.mark.parametrize("d,k,B", [(64, 64, 129), (192, 128, 300), (1088, 192, 257), (4096, 64, 140), (2048, 320, 640), (16384, 256, 385),
+                                   (10240, 64, 640), (4160, 512, 400), (16384, 512, 700)])
 def test_coefficients(d, k, B):
     from paper_2605_03109_amd import gsi
 
@@ -53,7 +54,7 @@ def test_coefficients(d, k, B):
 # fp32 activations: contractions too short to cut, at the four tiles that are cut to four k-tiles and one more, an odd number of k-tiles on
 # eight and nine tiles, the most parts
 @pytest.mark.parametrize("d,k,B", [(256, 64, 512), (512, 64, 129), (1024, 64, 512), (1024, 64, 513), (4160, 512, 400), (4160, 192, 1025), (16384, 64, 130),
-                                   (16384, 512, 400)])
+                                   (16384, 512, 400), (10240, 64, 640), (4160, 512, 700)])
 def test_coefficients_of_fp32_rows(d, k, B):
     from paper_2605_03109_amd import gsi
 
