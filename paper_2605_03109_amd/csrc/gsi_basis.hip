@@ -155,11 +155,12 @@ int basis_splits(int64_t M, int64_t N, int64_t K, int tm) {
 // chip units; those of few tiles as many parts as half the chip takes, of 512 rows at least, or 256 where there are at most four
 // tiles.  us a call, none fired, cut by doubling to half the chip or just beyond, 256 rows at least / so: a block of 2048 / 8192 at
 // rank 256, 777 tokens 100 / 90, at rank 512, 500 tokens 100 / 90; 2560 / 10240 at rank 256, 1024 tokens 122 / 114; 4096 / 16384, 777
-// tokens 150 / 138; the pair 2048 / 8192 at rank 256, 777 tokens 74 / 68; 4096 / 16384, 1024 tokens 105 / 100; of 73 calls none slower by
-// more than runs differ.
+// tokens 150 / 138; the pair 2048 / 8192 at rank 256, 777 tokens 74 / 68; 4096 / 16384, 1024 tokens 105 / 100; of 110 calls none slower by
+// more than runs differ.  From an eighth of the units on they are left: a block of 4096 / 16384 at rank 512, 2048 tokens 398 / 423 if cut so.
 int basis_coeff_splits(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ceil_div(M, 128) * ceil_div(N, kBasisCols), nk = ceil_div(K, BK);
   int s = tiles < kUnits ? (int)std::min<int64_t>(ceil_div(nk, kMaxDepth), 32) : 1;
+  if (tiles >= kUnits / 8) return s;
   return (int)std::min<int64_t>(std::max<int64_t>(s, std::min<int64_t>(kUnits / 2 / tiles, nk / (tiles <= kUnits / 64 ? 4 : 8))), 32);
 }
 
