@@ -162,16 +162,27 @@ static size_t project_ws_bytes(int64_t d, int64_t k, int64_t B, WsLevel level) {
   return need;
 }
 
-// Images on the products that read the basis as stored (gsi_basis.hip), and the workspace of their partial sums: where a part is no
-// longer than 24 k-tiles.  Longer ones are bound by the basis, which every tile of 64 rows reads again.  us, product and sums, on tiles of
-// 128 rows that transpose it on its way / here: 4096 x 4096 x 256 20.0 + 7.8 / 19.3 + 5.4, 16384 x 4096 x 256 50.0 + 7.8 / 54.6, 4096 x 16384 x
-// 256 53.6 + 9.4 / 70.1 + 5.4.
+// Images on the products that read the basis as stored (gsi_basis.hip), and the workspace of their partial sums.  Tiles of 64 rows
+// where their parts are no longer than 32 k-tiles, or 64 where they fill the chip unsplit; the basis, which every tile reads again, is what
+// longer ones wait for, and those of more tiles than the chip units: tiles of 128 rows there.  Not where these are two rounds of the
+// chip and more, or parts of 128 k-tiles and more whose sums are still to be made: the tiles of up to 256 rows that transpose the
+// basis on its way are as fast or faster.  us a build, weights that no cache holds, there / on 64 / on 128 rows: 1024 x 1024 x 64 13.2 /
+// 12.3 / 14.0; 4096 x 4096 x 64 21.8 / 19.0 / 19.4, x 256 .. / 23.6 / 26.8, x 512 35.4 / 33.4 / 32.5; 8192 x 2048 x 512 36.3 / 27.1 / 33.4;
+// 16384 x 4096 x 256 59.3 / 51.0 / 54.6, x 512 80.5 / 92.3 / 69.6; 4096 x 16384 x 64 47.6 / 50.3 / 43.6, x 256 58.5 / 69.6 / 55.8; 10240 x 2560 x 256
+// 45.3 / 32.5 / 30.9; 4096 x 11008 x 256 58.7 / 42.1 / 40.5; 28672 x 8192 x 256 182 / 183 / 167; 8192 x 28672 x 256 185 / 183 / 138; 16384 x 16384 x
+// 256 179 / 240 / 188, x 512 288 / 426 / 259; 16384 x 4096 x 1024 133 / .. / 153.
+static int image_basis_rows(int64_t m, int64_t d, int64_t k) {
+  const int64_t depth = d / 64 / gsi::basis_splits(m, k, d, 64), tiles = gsi::ceil_div(m, 64) * gsi::ceil_div(k, 256);
+  return tiles <= 256 && depth <= (tiles > 192 ? 64 : 32) ? 64 : 128;
+}
 static bool image_basis_ok(int64_t m, int64_t d, int64_t k, WsLevel level) {
-  return level == kWsFull && k > 128 && gsi::basis_ok(d, k) && d / gsi::basis_splits(m, k, d, 64) <= 1536;
+  if (level != kWsFull || !gsi::basis_ok(d, k)) return false;
+  const int s = gsi::basis_splits(m, k, d, 128);
+  return gsi::ceil_div(m, 128) * gsi::ceil_div(k, 256) < 512 && (s == 1 || d / 64 / s < 128);
 }
 static size_t image_part_bytes(int64_t m, int64_t d, int64_t k, WsLevel level) {
   if (!image_basis_ok(m, d, k, level)) return 0;
-  const int s = gsi::basis_splits(m, k, d, 64);
+  const int s = gsi::basis_splits(m, k, d, image_basis_rows(m, d, k));
   return s > 1 ? gsi::align_up((size_t)s * m * k * sizeof(float), 256) : 0;
 }
 
@@ -231,18 +242,19 @@ int gsi_build_image(const void* W, const void* U, void* M, int64_t m, int64_t d,
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (wdtype == GSI_BF16 && mfma_image_ok(m, d, k) && aligned(W, 16) && aligned(U, 2) && aligned(M, 8)) {
-    // matrix cores; the basis is transposed on its way to LDS, or, where its rows are no whole 8-byte pieces, once into the
-    // workspace, and for large images too: every row tile pays for the first.  us, transposed first / as stored, weights that no
-    // cache holds: 4096 x 4096 x 256 30.8 / 27.7, x 512 36.3 / 34.7 (the first limit), 8192 x 4096 x 512 53.3 / 55.7, 11008 x 4096 x 64
+    // matrix cores; the basis as it is stored (above), or transposed on its way to LDS, or, where its rows are no whole 8-byte
+    // pieces, once into the workspace, and for large images too: every row tile pays for the second.  us, transposed first / on its way, weights
+    // that no cache holds: 4096 x 4096 x 256 30.8 / 27.7, x 512 36.3 / 34.7 (the first limit), 8192 x 4096 x 512 53.3 / 55.7, 11008 x 4096 x 64
     // 43.5 / 47.3, x 128 47.7 / 50.5, x 256 57.8 / 58.3, 4096 x 11008 x 256 60.3 / 57.2, 16384 x 4096 x 64 47.4 / 50.0, x 256 62.7 / 60.0 (the
     // second limit: a rank that all but fills the column tile; x 192 57.7 / 57.9), x 512 81.1 / 87.9.
     const bool basis = image_basis_ok(m, d, k, level) && aligned(U, 16);
     if (basis) {
       gsi::GemmProb g = gemm_prob(W, d, U, k, M, k, m, k, d, gsi::EPI_STORE_BF16);
-      g.max_splits = gsi::basis_splits(m, k, d, 64);
+      const int tm = image_basis_rows(m, d, k);
+      g.max_splits = gsi::basis_splits(m, k, d, tm);
       if (g.max_splits > 1)
         g.part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + gsi::align_up((size_t)k * d * 2, 256));
-      e = gsi::basis_products(&g, 1, gsi::EPI_STORE_BF16, 64, m * k <= (1 << 19) ? 1 : 0, s);
+      e = gsi::basis_products(&g, 1, gsi::EPI_STORE_BF16, tm, m * k <= (1 << 19) ? 1 : 0, s);
       return e == hipSuccess ? GSI_OK : hip_fail(e, "gsi_build_image");
     }
     const int64_t work = gsi::mfma_image_work(m, k, d);

@@ -8,7 +8,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("m,d,k", [(64, 192, 136), (63, 256, 192), (130, 320, 256), (1000, 1088, 200), (68, 1024, 264), (4096, 4096, 256),
-                                   (257, 2048, 512), (1028, 8256, 144), (16384, 1024, 256)])
+                                   (257, 2048, 512), (1028, 8256, 144), (16384, 1024, 256),
+                                   # one fragment of columns and less; tiles of 128 rows in parts, unsplit, the last before two rounds of them
+                                   (64, 64, 8), (200, 320, 24), (2600, 8192, 520), (16500, 192, 64), (65400, 256, 16), (12400, 4160, 136)])
 def test_image(m, d, k):
     from paper_2605_03109_amd import gsi
 
