@@ -4,6 +4,9 @@
 //     C = X U            R = X - C U^T  (+ per-token partial norms)          Algorithm 1, lines 1-3
 //     Y = C M^T          Y[fired] += R[fired] W^T                            Eq. (exact)
 //
+// Where the call's workspace is what the query names (kWsFull), images and the coefficients of bf16 activations run on the products of
+// gsi_basis.hip, residual rows, image terms and W r of many tokens on those of gsi_wide.hip; here is what these do not take.
+//
 // One kernel, D = A B^T with both operands K-contiguous ("NT"): A[M,K], B[N,K] row-major.  A is bf16,
 // or fp32 split on the fly into a bf16 head and a bf16 tail (two MFMA passes) so that an fp32 operand
 // on the main term is not rounded to 8 bits (the bf16 image already uses most of the 2e-3 budget).
@@ -21,7 +24,8 @@
 // traffic (192 KB of operand reads at 128 bytes a cycle, 64 KB of staging writes at about 75) is 2400.
 // (Built and measured beside it: 256 x 256 tiles by four waves of 128 x 128, accumulators in AGPRs, memory to LDS without
 // registers: 1012 TFLOP/s against 1004 on 2048 x 16384 x 4096, 899 against 998 at 16384 columns, and no second workgroup
-// to cover an epilogue; 128 x 256 x 32 tiles by four waves, two workgroups per unit: 795.)
+// to cover an epilogue; with eight waves in two groups half a step apart it pays, gsi_wide.hip; 128 x 256 x 32 tiles by four waves, two
+// workgroups per unit: 795.)
 // A launch takes the products of all inputs, or of all maps, of a call (GemmProb): one product of a block is 64 to 512
 // tiles, one or two rounds of the 256 compute units with a ramp and a tail of its own.  The row tile is chosen
 // for the whole launch (plan_rows).  A block's prefill, 2048 tokens at rank 512: 36 launches 1007 us, 7 launches

@@ -36,6 +36,27 @@ def test_image(m, d, k):
     assert bool((M[m] == 7.0).all()) and bool((ws[need:] == 0x5A).all())
 
 
+# a workspace of the size that the query named before is served as it was, and gives the same to rounding
+@pytest.mark.parametrize("m,d,k,former", [(64, 2560, 16, 98304), (64, 6144, 512, 7340032)])
+def test_image_in_a_former_workspace(m, d, k, former):
+    from paper_2605_03109_amd import gsi
+
+    g = torch.Generator(device="cuda").manual_seed(m + d + k)
+    W = torch.randn(m, d, generator=g, device="cuda").to(torch.bfloat16)
+    U = (torch.randn(d, k, generator=g, device="cuda") / d**0.5).to(torch.bfloat16)
+    print(f"case image in a former workspace m={m} d={d} k={k}", flush=True)
+    ws = torch.full((former + (1 << 20),), 0x5A, dtype=torch.uint8, device="cuda")
+    M = torch.empty(m, k, dtype=torch.bfloat16, device="cuda")
+    rc = gsi.lib.gsi_build_image(W.data_ptr(), U.data_ptr(), M.data_ptr(), m, d, k, gsi.GSI_BF16, ws.data_ptr(), former,
+                                 torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == gsi.GSI_OK, gsi.last_error()
+    w, u = W.double(), U.double()
+    want = w @ u
+    assert ((M.double() - want).abs() <= 2.0**-8 * want.abs() + (8 + d**0.5) * 2.0**-24 * (w.abs() @ u.abs())).all()
+    assert bool((ws[former:] == 0x5A).all())
+
+
 # one row over a tile of 128; one k-tile, an odd number; many parts of four k-tiles, of eight, of unequal length; column tiles with remainders
 @pytest.mark.parametrize("d,k,B", [(64, 64, 129), (192, 128, 300), (1088, 192, 257), (4096, 64, 140), (2048, 320, 640), (16384, 256, 385),
                                    (10240, 64, 640), (4160, 512, 400), (16384, 512, 700)])

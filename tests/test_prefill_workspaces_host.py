@@ -28,3 +28,13 @@ def test_gated_map(m, d, k, B, former):
     assert call(ADDR if former else None, former) == gsi.GSI_ERR_HIP, gsi.last_error()
     full = gsi.workspace_bytes(gsi.CALL_GATED_LINEAR, m, d, k, B)
     assert full > former and call(ADDR, full) == gsi.GSI_ERR_HIP
+
+
+@pytest.mark.parametrize("m,d,k,former", [(64, 2560, 16, 98304), (64, 10240, 16, 376832), (64, 6144, 512, 7340032)])
+def test_image(m, d, k, former):
+    from paper_2605_03109_amd import gsi
+
+    call = lambda n: gsi.lib.gsi_build_image(ADDR, ADDR, ADDR, m, d, k, gsi.GSI_BF16, ADDR, n, None)
+    assert call(former) == gsi.GSI_ERR_HIP, gsi.last_error()
+    full = gsi.workspace_bytes(gsi.CALL_BUILD_IMAGE, m, d, k, 0)
+    assert full > former and call(full) == gsi.GSI_ERR_HIP
