@@ -611,9 +611,17 @@ static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, WsLevel level,
   pr.clear();
   wide.clear();
   st.clear();
+  // a map by itself: c is split on its way to LDS, and the same launch rounds the fired rows
+  const bool alone = n == 1 && mp[0].Ht && !mp[0].image_done && gsi::wide_image_ok(B, mp[0].m, mp[0].k);
+  if (alone) {
+    const MfmaMap& q = mp[0];
+    const gsi::RoundTask round{q.R, q.rounded, q.fired_idx, q.n_fired, (int)B, (int)q.d};
+    const gsi::GemmProb g = gemm_prob(q.C, q.k, q.M, q.k, q.Y, q.m, B, q.m, q.k, gsi::EPI_STORE_F32);
+    if (hipError_t e = gsi::wide_image(g, !q.Xwx && q.rounded ? &round : nullptr, s); e != hipSuccess) return e;
+  }
   for (int j = 0; j < n; ++j) {
     const MfmaMap& q = mp[j];
-    if (q.image_done) continue;
+    if (q.image_done || alone) continue;
     if (q.Ht && std::none_of(st.begin(), st.end(), [&](const gsi::SplitTask& t) { return t.Ht == q.Ht; }))
       st.push_back(gsi::SplitTask{q.C, q.Ht, (int)B, (int)q.k});
     (q.Ht ? wide : pr).push_back(gemm_prob(q.Ht ? static_cast<const void*>(q.Ht) : q.C, q.k, q.M, q.k, q.Y, q.m, B, q.m, q.k, gsi::EPI_STORE_F32));
@@ -636,7 +644,7 @@ static hipError_t mfma_gated(const MfmaMap* mp, int n, int64_t B, WsLevel level,
   for (int j = 0; j < n; ++j) {
     const MfmaMap& q = mp[j];
     if (q.Xwx || !q.rounded) continue;
-    if (std::none_of(rt.begin(), rt.end(), [&](const gsi::RoundTask& t) { return t.out == q.rounded; }))
+    if (!alone && std::none_of(rt.begin(), rt.end(), [&](const gsi::RoundTask& t) { return t.out == q.rounded; }))
       rt.push_back(gsi::RoundTask{q.R, q.rounded, q.fired_idx, q.n_fired, (int)B, (int)q.d});
     gsi::GemmProb g = gemm_prob(q.rounded, q.d, q.W, q.d, q.Y, q.m, B, q.m, q.d, gsi::EPI_SCATTER_ADD);
     g.row_idx = q.fired_idx; g.n_rows_dev = q.n_fired;

@@ -76,6 +76,12 @@ struct SplitTask {
 inline int64_t wide_two_term_ld(int64_t k) { return 64 * ceil_div(k, 32); }  // elements of a row of Ht
 hipError_t wide_split_rows(const SplitTask* tasks, int n, hipStream_t s);
 hipError_t wide_two_term(const GemmProb* probs, int n, int once, hipStream_t s);
+// One such product (EPI_STORE_F32) by itself, whose A is fp32, K a multiple of 64; round: fired rows that the launch rounds beside it, or
+// null.  wide_image_ok: where that is no slower than wide_split_rows and wide_two_term, whose larger tiles pay for a launch more at large
+// ranks once tiles of 64 rows are more than three a unit (us, laid out first / split on the way: 11008 rows, rank 512, 1000 tokens 46.6 / 39.4,
+// 1200 46.8 / 54.0, 2048 64.8 / 68.7; rank 192, 1200 32.4 / 31.8, 2048 41.1 / 41.8; 28672 rows, rank 64, 2048 tokens 59.5 / 58.0).
+inline bool wide_image_ok(int64_t M, int64_t N, int64_t K) { return K <= 192 || ceil_div(M, 64) * ceil_div(N, 256) <= 3 * 256; }
+hipError_t wide_image(const GemmProb& prob, const RoundTask* round, hipStream_t s);
 // the split of such a product, the row tiles it is meant for, and the workspace of its partial sums
 int wide_splits(int64_t M, int64_t N, int64_t K);
 int wide_follow(int64_t M, int64_t K, int splits);

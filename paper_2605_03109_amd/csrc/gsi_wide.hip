@@ -226,23 +226,24 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_scatter_kernel(const Gem
     }
 }
 
-// The fired rows of R, one after the other, rounded once to bf16.
+// The rows of C in two terms.
 constexpr int kMaxSplitTasks = 64;
 struct SplitArgs {
   SplitTask t[kMaxSplitTasks];
 };
 static_assert(sizeof(SplitArgs) <= 4096, "kernel arguments are limited to 4 KB");
+// The fired rows of R, one after the other, rounded once to bf16.
 constexpr int kMaxRoundTasks = 64;
 struct RoundArgs {
   RoundTask t[kMaxRoundTasks];
 };
 static_assert(sizeof(RoundArgs) <= 4096, "kernel arguments are limited to 4 KB");
+// pieces of eight: first, first + stride ..
 template <int ONCE>
-__global__ __launch_bounds__(256) void round_rows(const RoundArgs args) {
-  const RoundTask& t = args.t[blockIdx.y];
+__device__ __forceinline__ void round_part(const RoundTask& t, int64_t first, int64_t stride) {
   const int n = min(t.n_fired[0], t.rows), d8 = t.d >> 3;
   const int64_t total = (int64_t)n * d8;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t e = first; e < total; e += stride) {
     const int row = (int)(e / d8), c = 8 * (int)(e - (int64_t)row * d8);
     const float* const src = t.R + (int64_t)t.fired_idx[row] * t.d + c;
     const float4 x = load_row<ONCE != 0>(src), y = load_row<ONCE != 0>(src + 4);
@@ -255,6 +256,10 @@ __global__ __launch_bounds__(256) void round_rows(const RoundArgs args) {
     }
     *reinterpret_cast<u32x4*>(t.out + (int64_t)row * t.d + c) = u32x4{o[0], o[1], o[2], o[3]};
   }
+}
+template <int ONCE>
+__global__ __launch_bounds__(256) void round_rows(const RoundArgs args) {
+  round_part<ONCE>(args.t[blockIdx.y], (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
 }
 
 // Products of an operand in two terms: A is fp32 laid out as bf16 head and tail (split_rows), D = head B^T + tail B^T.  The
@@ -485,6 +490,113 @@ __global__ __launch_bounds__(kTwoThreads, 2) void wide_two_term_kernel(const Gem
   }
 }
 
+// The image term of a map by itself: the products of wide_two_term_kernel in the same order, so the same bits, from c as the caller has it,
+// in fp32.  A lane splits what it reads from LDS; laid out in two terms by a launch of its own (split_rows) first, it took 6 us of
+// calls of 12 to 30.  Tiles of 64 x 256, a workgroup of four waves (2 x 2, 32 x 128 each), k-tiles of 32 columns, one barrier each: where every
+// tile has a place at once two workgroups a unit with three k-tiles in LDS, else three with two.  A row of A is 128 bytes, piece c at
+// c ^ (row / 2 % 8), one of B 64, as above.  Bound by the chain of a tile (few tiles), by LDS and the products (many).  The workgroups behind the
+// tiles lay out fired rows for the W term, which is a launch less, too.
+// us a call, none fired, on gemm_nt / with split_rows / so: 1024 x 1024 at rank 64, 140 tokens 13.4 / 19.0 / 12.6; 4096 x 512, rank 512, 1000
+// 26.1 / 32.2 / 22.0; 11008 x 512, rank 512, 700 36.7 / 41.6 / 32.4; 16384 x 512, rank 64, 1200 31.2 / 29.2 / 25.9; 28672 x 512, rank 512, 330
+// 38.0 / 45.3 / 40.4, 600 57.9 / 61.3 / 57.4.  Tiles of 128 rows, or waves of 64 x 64 (which split every row of A twice as often), 3 to 15 % more.
+constexpr int kImageRows = 64;
+template <int S>
+__global__ __launch_bounds__(kTwoThreads, S == 2 ? 3 : 2) void wide_image_kernel(const GemmProb g, const int tiles, const RoundTask round) {
+  constexpr int kA = kImageRows * 128, kStage = kA + kTwoCols * 64;
+  __shared__ __align__(1024) char lds[S * kStage];
+  const int tid = threadIdx.x, lane = tid & 63;
+  if ((int)blockIdx.x >= tiles) {
+    round_part<0>(round, (int64_t)(blockIdx.x - tiles) * kTwoThreads + tid, (int64_t)(gridDim.x - tiles) * kTwoThreads);
+    return;
+  }
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1, lc = lane & 15, lq = lane >> 4;
+  const int row_tiles = (g.M + kImageRows - 1) / kImageRows;
+  int tile_m = blockIdx.x % row_tiles, tile_n = blockIdx.x / row_tiles;
+  if (g.col_tiles % 8 == 0) {  // the row tiles of a column tile on one XCD
+    tile_m = (blockIdx.x >> 3) % row_tiles;
+    tile_n = (blockIdx.x >> 3) / row_tiles * 8 + (blockIdx.x & 7);
+  }
+  const int row0 = tile_m * kImageRows, col0 = tile_n * kTwoCols, nk = g.K / 32;
+  const int64_t lda = g.lda, ldb = g.ldb;
+  // (rows past the end: zeros)
+  const u32x4 a = buffer_of(reinterpret_cast<const float*>(g.A) + row0 * lda, ((min(kImageRows, g.M - row0) - 1) * lda + g.K) * 4);
+  const u32x4 b = buffer_of(reinterpret_cast<const uint16_t*>(g.B) + col0 * ldb, ((min(kTwoCols, g.N - col0) - 1) * ldb + g.K) * 2);
+  const uint32_t sa = 4u * g.lda, sb = 2u * g.ldb;
+  const uint32_t va = (8 * w + (lane >> 3)) * sa + 16u * ((lane & 7) ^ ((4 * w + (lane >> 4)) & 7));
+  const uint32_t vb = (16 * w + (lane >> 2)) * sb + 16u * ((lane & 3) ^ ((4 - ((lane >> 4) & 3)) & 3));
+  const uint32_t to = (uint32_t)(uintptr_t)(lds_char*)lds + w * 1024;
+  auto request = [&](int kt, uint32_t stage) {  // (past the last k-tile that again, never read)
+    const uint32_t k = (uint32_t)min(kt, nk - 1);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) load_to_lds(to + stage + q * 4096, a, va + 32 * q * sa, k * 128u);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) load_to_lds(to + stage + kA + q * 4096, b, vb + 64 * q * sb, k * 64u);
+  };
+  const char* const pa = lds + (32 * wm + lc) * 128;
+  const int p0 = 16 * ((2 * lq) ^ (lc >> 1)), p1 = 16 * ((2 * lq + 1) ^ (lc >> 1));
+  const char* const pb = lds + kA + (128 * wn + lc) * 64 + 16 * (lq ^ ((4 - (lc >> 2)) & 3));
+  f32x4 acc[2][8];
+#pragma unroll
+  for (int f = 0; f < 16; ++f) acc[f >> 3][f & 7] = f32x4{0.f, 0.f, 0.f, 0.f};
+  request(0, 0);
+  if constexpr (S == 3) request(1, kStage);
+  uint32_t stage = 0, free = (S - 1) * kStage;
+  for (int t = 0; t < nk; ++t) {
+    wait_loads<(S - 2) * 6>();  // this k-tile has arrived
+    wait_lds();                 // and the one before is in registers
+    barrier();                  // ... in every wave
+    f32x4 av[2][2];
+    bf16x8 bb[8];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      av[i][0] = *reinterpret_cast<const f32x4*>(pa + stage + i * 2048 + p0);
+      av[i][1] = *reinterpret_cast<const f32x4*>(pa + stage + i * 2048 + p1);
+    }
+#pragma unroll
+    for (int n = 0; n < 8; ++n) bb[n] = *reinterpret_cast<const bf16x8*>(pb + stage + n * 1024);
+    request(t + S - 1, free);
+    free = stage;
+    stage = stage == (S - 1) * kStage ? 0 : stage + kStage;
+    bf16x8 ah[2], al[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float x = av[i][e >> 2][e & 3];
+        const __bf16 h = (__bf16)x;
+        ah[i][e] = h;
+        al[i][e] = (__bf16)(x - __uint_as_float((uint32_t)__builtin_bit_cast(uint16_t, h) << 16));
+      }
+#pragma unroll
+    for (int n = 0; n < 8; ++n)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb[n], al[i], acc[i][n], 0, 0, 0);
+#pragma unroll
+    for (int n = 0; n < 8; ++n)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb[n], ah[i], acc[i][n], 0, 0, 0);
+  }
+  wait_loads<0>();
+  wait_lds();
+  barrier();  // every k-tile has been read: the strips of the epilogue (as in wide_two_term_kernel) lie over them
+  char* const strip = lds + w * kTwoStrip;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) *reinterpret_cast<f32x4*>(strip + lc * 256 + 16 * ((4 * n + lq) ^ lc)) = acc[s >> 1][4 * (s & 1) + n];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = 4 * q + lq, row = row0 + 32 * wm + 16 * (s >> 1) + r, col = col0 + 128 * wn + 64 * (s & 1) + 4 * lc;
+      const f32x4 v = *reinterpret_cast<const f32x4*>(strip + r * 256 + 16 * (lc ^ r));
+      if (row < g.M && col < g.N) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.D) + (int64_t)row * g.ldd + col) = v;  // N is a multiple of 4
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 // Ht[row] = the heads of 32 columns of a row of C, their tails, the next 32 columns ...
 __global__ __launch_bounds__(256) void split_rows(const SplitArgs args) {
   const SplitTask& t = args.t[blockIdx.y];
@@ -535,6 +647,20 @@ hipError_t wide_two_term(const GemmProb* probs, int n, int once, hipStream_t s) 
   return hipSuccess;
 }
 
+// workgroups that round the fired rows of a task: what a quarter of the tokens keeps busy
+static int64_t round_groups(const RoundTask& t) { return ceil_div(wide_rows_expected(t.rows) * (t.d / 8), 256); }
+
+hipError_t wide_image(const GemmProb& prob, const RoundTask* round, hipStream_t s) {
+  GemmProb g = prob;
+  g.col_tiles = (int)ceil_div(g.N, kTwoCols);
+  const int64_t tiles = g.col_tiles * ceil_div(g.M, kImageRows), rest = round ? std::min<int64_t>(round_groups(*round), 1024) : 0;
+  if (tiles >= (1ll << 31) - rest) return hipErrorInvalidValue;
+  const RoundTask r = round ? *round : RoundTask{};
+  if (tiles <= 2 * kUnits) wide_image_kernel<3><<<(unsigned)(tiles + rest), kTwoThreads, 0, s>>>(g, (int)tiles, r);
+  else wide_image_kernel<2><<<(unsigned)(tiles + rest), kTwoThreads, 0, s>>>(g, (int)tiles, r);
+  return hipGetLastError();
+}
+
 hipError_t wide_round_rows(const RoundTask* tasks, int n, bool once, hipStream_t s) {
   for (int i = 0; i < n;) {
     RoundArgs a;
@@ -542,7 +668,7 @@ hipError_t wide_round_rows(const RoundTask* tasks, int n, bool once, hipStream_t
     int64_t most = 0;
     for (; i < n && c < kMaxRoundTasks; ++i, ++c) {
       a.t[c] = tasks[i];
-      most = std::max(most, ceil_div((int64_t)wide_rows_expected(tasks[i].rows) * (tasks[i].d / 8), 256));
+      most = std::max(most, round_groups(tasks[i]));
     }
     const dim3 grid((unsigned)std::min<int64_t>(most, 2048), (unsigned)c);
     if (once) round_rows<1><<<grid, 256, 0, s>>>(a);
