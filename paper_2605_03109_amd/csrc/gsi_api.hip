@@ -122,12 +122,13 @@ static uint16_t* two_term_rows(void* ws, int64_t d, int64_t k, int64_t B, WsLeve
   const size_t n = two_term_bytes(k, B, level);
   return n ? reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + mfma_project_ws(d, k, B, level) - n) : nullptr;
 }
-// The W term of a prefill-sized call on tiles of 256 rows, its fired rows laid out as bf16 first: where more than one tile of 128
+// The W term of a prefill-sized call on tiles of up to 256 rows, its fired rows laid out as bf16 first: where more than one tile of 128
 // rows is to be expected (a quarter of the tokens) and the weights are not small.  Otherwise the weights are what is waited for,
-// or the launches, and one more costs.  us a call, rows converted on their way / laid out: the pair 4096 / 16384 at rank 256, 50 of 333
-// tokens fired 136 / 143; 128 of 640 185 / 180; 409 of 2048 402 / 352; the pair 1024 / 4096 at rank 64, 204 of 1024 67 / 72; 2048 / 8192 106 /
-// 111; 2560 / 10240 135 / 131; 3072 / 12288 171 / 149; a block of 2048 / 8192 at rank 256, 409 of 2048 305 / 287, 4096 / 16384 at
-// rank 512 687 / 628.
+// or the launches, and one more costs.  Blocks and pairs are at worst even.  us a call, rows converted on their way / laid out: a block of
+// 4096 / 16384 at rank 512, 120 of 600 tokens fired 331 / 330, 102 of 2048 594 / 574, 409 706 / 646; of 2048 / 8192 at rank 256, 220 of 1100 205 /
+// 194; the pair 2560 / 10240 at rank 256, 45 of 900 136 / 141, 180 166 / 163, 409 of 2048 258 / 246; the pair 4096 / 16384, 50 of 333 136 / 143; 1024 /
+// 4096 at rank 64, 204 of 1024 67 / 72.  One map, whose pieces leave units idle, gains where many tokens fire and loses where few do: 4096 /
+// 11008 at rank 256, 55 of 1100 117 / 132, 220 178 / 143, 102 of 2048 132 / 147, 614 209 / 205; 2048 / 8192, 409 of 2048 116 / 124, 614 139 / 131.
 static bool wide_scatter_ok(int64_t m, int64_t d, int64_t B, WsLevel level) {
   return level == kWsFull && B > 512 && d >= 64 && d % 64 == 0 && gsi::wide_ok(d) && B < (1ll << 30) && B * d < (1ll << 31) &&
          std::min(m, d) * B > (1ll << 21);

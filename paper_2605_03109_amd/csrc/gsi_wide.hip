@@ -141,17 +141,29 @@ __device__ __forceinline__ void wide_loop(char* lds, const u32x4& a, int64_t lda
 // many as the counts make; the others leave.  The row tiles of a product are of one height, a multiple of 16 rows, and the
 // products of rows past it are left out (410 rows: two of 208).  Row tiles of a column tile are eight workgroups apart, on the
 // same XCD: its L2 reads the weights once.
+// The tiles are as high as 256 rows let them be only where the pieces of all products fill the chip: the parts, which the order of a sum
+// follows, are the same for a map by itself as for one beside others, and a square map alone was 64 pieces.  With fewer pieces than half the
+// chip has units there are up to eight times the row tiles, of as many rows less.  us a call of gsi_gated_linear at rank 128, one
+// height / so: 4096 x 4096, 409 of 2048 tokens 83 / 72, 580 of 2900 117 / 96; 2176 x 7168, 409 of 2048 96 / 78; 2560 x 10240, 300 of 1500 104 / 91.
 template <int ONCE>
 __global__ __launch_bounds__(kWideThreads, 2) void wide_scatter_kernel(const GemmArgs args) {
   __shared__ __align__(1024) char lds[2 * kWideStage];
   const int lane = threadIdx.x & 63;
   // lane q: the pieces of product q
-  int rows = 0, pieces = 0;
+  int rows = 0, tiles = 0, each = 0;
   if (lane < args.n) {
     const GemmProb& g = args.p[lane];
     rows = min(g.n_rows_dev[0], g.M);
-    if (rows > 0) pieces = g.col_tiles * ((rows + kWideTile - 1) / kWideTile) * parts_for(g, rows);
+    if (rows > 0) {
+      tiles = (rows + kWideTile - 1) / kWideTile;
+      each = g.col_tiles * parts_for(g, rows);
+    }
   }
+  int all = 0;  // pieces of the launch
+  for (int q = 0; q < args.n; ++q) all += __builtin_amdgcn_readlane(tiles * each, q);
+  const int fold = max(1, min(8, kUnits / max(all, 1)));
+  tiles = min(fold * tiles, (rows + 15) / 16);
+  const int pieces = tiles * each;
   int local = blockIdx.x, pi = 0;
   for (; pi < args.n; ++pi) {
     const int n = __builtin_amdgcn_readlane(pieces, pi);
@@ -161,7 +173,7 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_scatter_kernel(const Gem
   if (pi == args.n) return;
   const GemmProb& g = args.p[pi];
   const int Mrows = __builtin_amdgcn_readlane(rows, pi);
-  const int row_tiles = (Mrows + kWideTile - 1) / kWideTile, parts = parts_for(g, Mrows), ct = g.col_tiles;
+  const int row_tiles = __builtin_amdgcn_readlane(tiles, pi), parts = parts_for(g, Mrows), ct = g.col_tiles;
   const int split = local / (ct * row_tiles), q = local - split * ct * row_tiles;
   int tile_m, tile_n;
   if (ct % 8 == 0) {
@@ -694,6 +706,7 @@ hipError_t wide_scatter(const GemmProb* probs, int n, bool once, hipStream_t s) 
       const int64_t want = p.row_tiles ? (int64_t)p.splits * p.row_tiles : 0, tiles = ceil_div(p.M, kWideTile);
       blocks += p.col_tiles * (p.row_tiles ? std::max({want, (int64_t)kUnits / p.col_tiles, tiles * p.min_parts}) : tiles * p.splits);
     }
+    blocks = std::max<int64_t>(blocks, kUnits);  // (lower tiles, where the pieces are fewer)
     if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
     std::stable_sort(g.p, g.p + g.n, [](const GemmProb& x, const GemmProb& y) {  // the longest parts first, as in mfma_gemm_nt
       return (int64_t)x.K * y.splits > (int64_t)y.K * x.splits;
