@@ -539,7 +539,7 @@ static hipError_t mfma_project(const MfmaInput* in, int n, const ImageRider* img
       g.Ht = two_term_rows(in[i].ws, d, k, B, level);
       (basis(i) ? wide : pr).push_back(g);
     }
-    if (hipError_t e = gsi::basis_products(wide.data(), (int)wide.size(), gsi::EPI_STORE_F32, 128, once == 2 ? 1 : 0, s); e != hipSuccess) return e;
+    if (hipError_t e = gsi::basis_products(wide.data(), (int)wide.size(), gsi::EPI_STORE_F32, 0, once == 2 ? 1 : 0, s); e != hipSuccess) return e;
     wide.clear();
     if (hipError_t e = gsi::mfma_gemm_nt(pr.data(), (int)pr.size(), xdt == GSI_F32 ? 1 : 0, gsi::EPI_STORE_F32, s, xdt == GSI_F32 || bf16_stored, once == 2 ? 1 : 0);
         e != hipSuccess)

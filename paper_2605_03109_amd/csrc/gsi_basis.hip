@@ -157,8 +157,10 @@ int basis_splits(int64_t M, int64_t N, int64_t K, int tm) {
 // chip units; those of few tiles as many parts as half the chip takes, of 512 rows at least, or 256 where there are at most four
 // tiles.  us a call, none fired, cut by doubling to half the chip or just beyond, 256 rows at least / so: a block of 2048 / 8192 at
 // rank 256, 777 tokens 100 / 90, at rank 512, 500 tokens 100 / 90; 2560 / 10240 at rank 256, 1024 tokens 122 / 114; 4096 / 16384, 777
-// tokens 150 / 138; the pair 2048 / 8192 at rank 256, 777 tokens 74 / 68; 4096 / 16384, 1024 tokens 105 / 100; of 110 calls none slower by
-// more than runs differ.  From an eighth of the units on they are left: a block of 4096 / 16384 at rank 512, 2048 tokens 398 / 423 if cut so.
+// tokens 150 / 138; the pair 2048 / 8192 at rank 256, 777 tokens 74 / 68; 4096 / 16384, 1024 tokens 105 / 100.  From an eighth of the units on they
+// are left: beside others they fill the chip.  us a call, none fired, left from a sixteenth on / from an eighth: a block of 4096 / 16384 at
+// rank 512, 1664 tokens 361 / 365, 1920 395 / 407; the pair, 1024 tokens 202 / 178, 1664 262 / 259, 1920 286 / 283; one input of 4096, 1664 tokens 101 / 65.
+// From an eighth / from a quarter: the block, 2048 tokens 414 / 435, 2304 453 / 480; the pair, 2048 307 / 308.
 int basis_coeff_splits(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ceil_div(M, 128) * ceil_div(N, kBasisCols), nk = ceil_div(K, BK);
   int s = tiles < kUnits ? (int)std::min<int64_t>(ceil_div(nk, kMaxDepth), 32) : 1;
@@ -174,7 +176,13 @@ hipError_t basis_products(const GemmProb* probs, int n, int epi, int tm, int onc
     std::stable_sort(g.p, g.p + g.n, [](const GemmProb& x, const GemmProb& y) {  // the longest parts first, as in mfma_gemm_nt
       return (int64_t)x.K * y.max_splits > (int64_t)y.K * x.max_splits;
     });
-    if (hipError_t e = epi == EPI_STORE_BF16 ? launch<EPI_STORE_BF16>(g, tm, once, s) : launch<EPI_STORE_F32>(g, tm, once, s); e != hipSuccess)
+    // Coefficients: tiles of 64 rows where those of 128 leave half the chip idle.  (The parts are those of the product, whatever its launch,
+    // and a tile has the same sums in the same order.)  A projection by itself, us, tiles of 128 / so: 4096 at rank 384, 2048 tokens 98 / 88, rank
+    // 512, 2304 111 / 99; 2048 at rank 384, 2048 tokens 69 / 61; 1024 at rank 512, 2048 58 / 51; 768 at rank 320, 600 48 / 41, rank 64 33 / 29.
+    int64_t blocks = 0;
+    for (int q = 0; q < g.n; ++q) blocks += ceil_div(g.p[q].M, 128) * ceil_div(g.p[q].N, kBasisCols) * (g.p[q].part ? g.p[q].max_splits : 1);
+    const int rows = tm ? tm : 2 * blocks <= kUnits ? 64 : 128;
+    if (hipError_t e = epi == EPI_STORE_BF16 ? launch<EPI_STORE_BF16>(g, rows, once, s) : launch<EPI_STORE_F32>(g, rows, once, s); e != hipSuccess)
       return e;
   }
   return hipSuccess;

@@ -89,7 +89,8 @@ size_t wide_part_bytes(int64_t M, int64_t N, int64_t K);
 inline bool wide_ok(int64_t K) { return K <= (1 << 22); }  // (offsets in a tile of 256 rows are 32 bits)
 inline int64_t wide_rows_expected(int64_t M) { return M < 512 ? (M < 128 ? M : 128) : M / 4; }
 // Products with a stored basis as the right factor (gsi_basis.hip): D = A B, A[M, K] bf16, B[K, N] bf16 as stored (ldb), K a multiple of
-// 64, N of 8, B 16-byte aligned and below 2 GiB; epi EPI_STORE_BF16 or EPI_STORE_F32 (with Ht).  tm: rows of a tile, 64 or 128.
+// 64, N of 8, B 16-byte aligned and below 2 GiB; epi EPI_STORE_BF16 or EPI_STORE_F32 (with Ht).  tm: rows of a tile, 64 or 128, or
+// 0: as the launch has it.
 hipError_t basis_products(const GemmProb* probs, int n, int epi, int tm, int once, hipStream_t s);
 int basis_splits(int64_t M, int64_t N, int64_t K, int tm);  // of an image
 int basis_coeff_splits(int64_t M, int64_t N, int64_t K);     // of coefficients (tm 128)
