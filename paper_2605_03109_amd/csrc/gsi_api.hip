@@ -164,17 +164,22 @@ static size_t project_ws_bytes(int64_t d, int64_t k, int64_t B, WsLevel level) {
 }
 
 // Images on the products that read the basis as stored (gsi_basis.hip), and the workspace of their partial sums.  Tiles of 64 rows
-// where their parts are no longer than 32 k-tiles, or 64 where they fill the chip unsplit; the basis, which every tile reads again, is what
-// longer ones wait for, and those of more tiles than the chip units: tiles of 128 rows there.  Not where these are two rounds of the
-// chip and more, or parts of 128 k-tiles and more whose sums are still to be made: the tiles of up to 256 rows that transpose the
-// basis on its way are as fast or faster.  us a build, weights that no cache holds, there / on 64 / on 128 rows: 1024 x 1024 x 64 13.2 /
-// 12.3 / 14.0; 4096 x 4096 x 64 21.8 / 19.0 / 19.4, x 256 .. / 23.6 / 26.8, x 512 35.4 / 33.4 / 32.5; 8192 x 2048 x 512 36.3 / 27.1 / 33.4;
-// 16384 x 4096 x 256 59.3 / 51.0 / 54.6, x 512 80.5 / 92.3 / 69.6; 4096 x 16384 x 64 47.6 / 50.3 / 43.6, x 256 58.5 / 69.6 / 55.8; 10240 x 2560 x 256
-// 45.3 / 32.5 / 30.9; 4096 x 11008 x 256 58.7 / 42.1 / 40.5; 28672 x 8192 x 256 182 / 183 / 167; 8192 x 28672 x 256 185 / 183 / 138; 16384 x 16384 x
-// 256 179 / 240 / 188, x 512 288 / 426 / 259; 16384 x 4096 x 1024 133 / .. / 153.
+// where their parts are no longer than 28 k-tiles, 32 if there is one, or 64 where they fill the chip unsplit; the basis, which every tile
+// reads again, is what longer ones wait for, and those of more tiles than the chip units: tiles of 128 rows there.  Not where these are two
+// rounds of the chip and more, or parts of 128 k-tiles and more whose sums are still to be made: the tiles of up to 256 rows that transpose the
+// basis on its way are as fast or faster.  us a build, one after the other, each with weights that no cache holds, there / on 64 / on 128 rows:
+//   in parts, k-tiles of one: 1024 x 3584 x 256 (7 parts of 8) 20.3 / 17.3 / 21.0; 4096 x 4096 x 256 (16) 30.5 / 25.6 / 29.8; 4096 x 7168 x 256 (28) 37.2 / 34.8 /
+//   35.9; 6144 x 3584 x 64 (28) 26.2 / 24.3 / 22.7, x 256 31.1 / 32.0 / 33.2; 6144 x 3712 x 64 (29) 27.8 / 25.1 / 23.4, x 256 32.1 / 33.1 / 31.4; 4096 x 7936 x 256
+//   (31) 37.8 / 36.5 / 36.9; 8192 x 4096 x 256 (32) 38.8 / 40.2 / 37.8; 4096 x 8192 x 256 (32) 38.0 / 40.2 / 37.6; 3072 x 4096 x 512 (32) 41.9 / 32.8 / 29.4;
+//   4096 x 10240 x 256 (40) 60.3 / 45.0 / 43.4; 4096 x 16384 x 256 (64) 65.3 / 76.1 / 67.0;
+//   unsplit: 10240 x 2048 x 256 (32) 41.6 / 28.9 / 30.2; 10240 x 4096 x 256 (64, 160 tiles) 59.5 / 51.8 / 43.0; 12800 x 3072 x 128 (48, 200 tiles) 45.7 / 33.6 /
+//   36.7; 12800 x 4096 x 256 (64) 62.4 / 53.7 / 55.2; 16384 x 4096 x 128 (64, 256 tiles) 59.9 / 48.7 / 54.9, x 256 64.7 / 58.3 / 63.8; 6912 x 4096 x 512 (64, 216
+//   tiles) 60.4 / 48.8 / 46.9; 8192 x 4096 x 512 (64, 256 tiles) 55.0 / 50.1 / 49.6; 12800 x 5504 x 256 (86) 85.3 / 76.8 / 70.4.
+// Slower than there by more than 3 %: a few small images in parts of eight k-tiles, 1280 x 4096 x 256 17.4 / 19.6, 2048 x 4096 x 256 20.9 / 23.8.
 static int image_basis_rows(int64_t m, int64_t d, int64_t k) {
-  const int64_t depth = d / 64 / gsi::basis_splits(m, k, d, 64), tiles = gsi::ceil_div(m, 64) * gsi::ceil_div(k, 256);
-  return tiles <= 256 && depth <= (tiles > 192 ? 64 : 32) ? 64 : 128;
+  const int parts = gsi::basis_splits(m, k, d, 64);
+  const int64_t depth = d / 64 / parts, tiles = gsi::ceil_div(m, 64) * gsi::ceil_div(k, 256);
+  return tiles <= 256 && depth <= (tiles > 192 ? 64 : parts > 1 ? 28 : 32) ? 64 : 128;
 }
 static bool image_basis_ok(int64_t m, int64_t d, int64_t k, WsLevel level) {
   if (level != kWsFull || !gsi::basis_ok(d, k)) return false;
