@@ -494,8 +494,8 @@ struct ImageRider {
   int64_t m;
 };
 // Do the rows of R and Y of a call go past the caches?  If they, x and the weights, which are read beside them, leave the
-// 256 MB of the memory-side cache little room for anything else (store_row in gsi_mfma.hip has both sides of larger and of far
-// smaller calls), and no Y is the input of another projection of the call.  us a call, through the caches / past them, the caller
+// 256 MB of the memory-side cache little room for anything else (store_row in gsi_mfma_device.h has both sides of larger and of
+// far smaller calls), and no Y is the input of another projection of the call.  us a call, through the caches / past them, the caller
 // reading every Y behind it: the pair 2944 / 11392, bf16, 500 tokens (196 MB), none fired 83.8 / 86.3, 5 % 114.5 / 115.4, 18 % 129.2 / 123.8;
 // a block of 1280 / 4096, 1800 tokens (186 MB) 111 / 116, 139 / 139, 164 / 171; of 2048 / 8192, 800 tokens (218 MB) 114 / 115, 154 / 145,
 // 173 / 170; the pair 3584 / 12544, 400 tokens (233 MB) 75.9 / 78.0, 113.5 / 112.6, 122.7 / 119.0.

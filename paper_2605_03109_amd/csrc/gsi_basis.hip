@@ -20,7 +20,7 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 constexpr int kBasisThreads = 512, kBasisCols = 256;
 
-template <int TM, int EPI, int ONCE>
+template <int TM, int EPI>
 __global__ __launch_bounds__(kBasisThreads, 2) void basis_product(const GemmArgs args) {
   constexpr int WM = TM / 64, WN = 8 / WM, NF = kBasisCols / WN / 16;  // waves, and fragments of 16 columns of a wave (of 64 rows)
   constexpr int kA = TM * 128, kStage = kA + 64 * kBasisCols * 2, S = TM == 64 ? 4 : 3, kLoads = TM / 64 + 4;
@@ -138,8 +138,8 @@ hipError_t launch(GemmArgs& g, int tm, int once, hipStream_t s) {
     split |= p.splits > 1;
   }
   if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
-  if (tm == 64) basis_product<64, EPI, 0><<<(unsigned)blocks, kBasisThreads, 0, s>>>(g);
-  else basis_product<128, EPI, 0><<<(unsigned)blocks, kBasisThreads, 0, s>>>(g);
+  if (tm == 64) basis_product<64, EPI><<<(unsigned)blocks, kBasisThreads, 0, s>>>(g);
+  else basis_product<128, EPI><<<(unsigned)blocks, kBasisThreads, 0, s>>>(g);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   return split ? mfma_finish_basis(g, EPI, once != 0, s) : hipSuccess;
 }

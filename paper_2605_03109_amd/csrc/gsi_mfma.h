@@ -67,13 +67,13 @@ hipError_t wide_round_rows(const RoundTask* tasks, int n, bool once, hipStream_t
 hipError_t wide_scatter(const GemmProb* probs, int n, bool once, hipStream_t s);
 // Products of an operand in two terms: A is Ht, the rows of an fp32 operand as bf16 (of 32 columns the heads, their tails, the
 // next 32 columns: wide_split_rows, or GemmProb::Ht of the product that makes the operand); epi EPI_RESIDUAL or EPI_STORE_F32,
-// K a multiple of 8, more than 32.
+// K a multiple of 64.
 struct SplitTask {
   const float* C;
   uint16_t* Ht;               // [rows, wide_two_term_ld(k)]
-  int rows, k;                // k a multiple of 4
+  int rows, k;                // k a multiple of 64
 };
-inline int64_t wide_two_term_ld(int64_t k) { return 64 * ceil_div(k, 32); }  // elements of a row of Ht
+inline int64_t wide_two_term_ld(int64_t k) { return 2 * k; }  // elements of a row of Ht
 hipError_t wide_split_rows(const SplitTask* tasks, int n, hipStream_t s);
 hipError_t wide_two_term(const GemmProb* probs, int n, int once, hipStream_t s);
 // One such product (EPI_STORE_F32) by itself, whose A is fp32, K a multiple of 64; round: fired rows that the launch rounds beside it, or

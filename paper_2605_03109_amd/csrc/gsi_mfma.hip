@@ -733,7 +733,7 @@ int mfma_follow(int64_t M, int64_t K, int epi, int splits, WsLevel level) {
 
 // The same for products on tiles of 256 rows over the fired rows (gsi_wide.hip): parts of 4096 columns where a product has fewer
 // tiles than the chip units, and cut further, down to 1024 columns (512 for an eighth of the units), while the parts of one row
-// tile fit the chip and those of several half of it.
+// tile fit the chip and those of several a quarter of it: others of their block share the launch.
 int wide_splits(int64_t M, int64_t N, int64_t K) {
   const int64_t m = wide_rows_expected(M), nk = ceil_div(K, BK), tiles = ceil_div(m, 256) * ceil_div(N, BN);
   int64_t s = tiles < kUnits ? std::min<int64_t>(ceil_div(nk, kMaxDepth), kMaxSplits) : 1;

@@ -1,4 +1,4 @@
-// Device code that the matrix-core products of gsi_mfma.hip and gsi_wide.hip share.
+// Device code that the matrix-core products of gsi_mfma.hip, gsi_wide.hip and gsi_basis.hip share.
 #pragma once
 #include "gsi_device.h"
 #include "gsi_mfma.h"
@@ -15,7 +15,7 @@ constexpr int BK = 64;           // the host's unit of the contraction (K is a m
 // Parts of the contraction of a product over `rows` rows (a device-side count).  It is sized for row_tiles tiles of
 // tile_rows rows.  With fewer, the same number of workgroups: each tile is cut into more parts (the workgroups of the row tiles that
 // are not there take them).  With more, fewer parts, down to min_parts, as long as they fill the chip: what is cut for
-// nothing writes partial sums for nothing.  Tiles of tile_rows rows (gemm_nt: 128 whatever the launch's tile; wide_nt: 256): the
+// nothing writes partial sums for nothing.  Tiles of tile_rows rows (gemm_nt: 128, wide_scatter_kernel: 256, whatever the launch's tile): the
 // order of a sum is the product's and the count's own.  W r beside the image term, us a call, parts fixed / following the count: 16384 x 4096, 102 of 2048
 // rows 137 / 102, all of 512 rows 167 / 106; 4096 x 16384, 51 of 1024 rows 75 / 52; a block, 2048 tokens that all fire
 // 1480 / 1414, 102 fired 644 / 632.  A product whose expected rows take one part has the launch of the sums all the same:
@@ -66,9 +66,9 @@ __device__ __forceinline__ uint2 load_row(const uint16_t* p) {
 __device__ __forceinline__ float4 widen_row(const float4& v) { return v; }
 __device__ __forceinline__ float4 widen_row(const uint2& v) { return float4{bf16_lo(v.x), bf16_hi(v.x), bf16_lo(v.y), bf16_hi(v.y)}; }
 
-// four columns of a row of k in two bf16 terms: of 32 columns the heads, then the tails (those past k are not written)
+// four columns of a row of k (a multiple of 64) in two bf16 terms: of 32 columns the heads, then the tails
 __device__ __forceinline__ void store_two_terms(uint16_t* Ht, int64_t row, int k, int col, const float4& v) {
-  uint16_t* const p = Ht + row * (64 * ((k + 31) / 32)) + col / 32 * 64 + col % 32;
+  uint16_t* const p = Ht + row * (2 * k) + col / 32 * 64 + col % 32;
   const float x[4] = {v.x, v.y, v.z, v.w};
   uint32_t h[4], l[4];
 #pragma unroll

@@ -278,10 +278,9 @@ __global__ __launch_bounds__(256) void round_rows(const RoundArgs args) {
 // residual and image products of a prefill-sized call: short (the rank) with long epilogues (every row of R and Y), so a
 // workgroup is four waves (2 x 2, 64 x 128 each) with a tile of 128 x 256 and half a compute unit: one's epilogue beside the
 // other's products.  A k-tile is 32 columns: a row of A is 64 bytes of head and 64 of tail, laid out in LDS as in wide_loop, a
-// row of B 64 bytes, whose piece c lies at c ^ {0, 3, 2, 1}[row / 4 % 4].  One read of B serves both terms.  Columns past the rank
-// (the last k-tile of one that is no multiple of 32), like rows past the end, are read as zero: their lanes ask for an address
-// behind the buffer.  A wave has all the
-// operands of a k-tile in registers before its products, so that the k-tile after the next is requested over it at once.
+// row of B 64 bytes, whose piece c lies at c ^ {0, 3, 2, 1}[row / 4 % 4].  One read of B serves both terms.  Rows past the end are read as
+// zero.  A wave has all the operands of a k-tile in registers before its products, so that the k-tile after the next is requested over it
+// at once.
 // As many workgroups as the chip holds take tile after tile; the first two k-tiles of a tile are requested beside the last
 // two of the one before, and arrive before its epilogue begins.
 // A block of 2048 tokens at rank 512 (275 GFLOP, 0.65 GB of x, R and Y): 310 to 350 us in gemm_nt, 290 here; without the
@@ -338,13 +337,11 @@ __global__ __launch_bounds__(kTwoThreads, 2) void wide_two_term_kernel(const Gem
   // a wave requests rows 32 q + 8 w .. + 7 of A and 64 q + 16 w .. + 15 of B; rows past the end read as zero
   u32x4 a, b;
   uint32_t va, vb, sa, sb;
-  int ka;
   auto aim = [&](const Tile& t) {
     const GemmProb& g = args.p[t.problem];
     const int row0 = t.m * kTwoRows, col0 = t.n * kTwoCols;
     const int a_rows = min(kTwoRows, g.M - row0), b_rows = min(kTwoCols, g.N - col0);
-    ka = g.K;
-    sa = 128u * ((ka + 31) / 32);
+    sa = 4u * g.K;
     sb = 2u * g.ldb;
     a = buffer_of(reinterpret_cast<const char*>(g.A) + (int64_t)row0 * sa, (int64_t)a_rows * sa);
     b = buffer_of(reinterpret_cast<const uint16_t*>(g.B) + (int64_t)col0 * g.ldb, ((int64_t)(b_rows - 1) * g.ldb + g.K) * 2);
@@ -355,20 +352,10 @@ __global__ __launch_bounds__(kTwoThreads, 2) void wide_two_term_kernel(const Gem
   };
   auto request = [&](int kt, uint32_t stage) {
     const uint32_t sk = (uint32_t)kt;
-    if (32 * kt + 32 <= ka) {  // (uniform)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        load_to_lds(to + stage + q * 4096, a, va + 32 * q * sa, sk * 128u);
-        load_to_lds(to + stage + kTwoA + q * 4096, b, vb + 64 * q * sb, sk * 64u);
-      }
-    } else {
-      const int rest = ka - 32 * kt;  // columns of the k-tile, a multiple of 8
-      const bool out_a = 8 * (((lane & 7) ^ ((4 * w + (lane >> 4)) & 7)) & 3) >= rest, out_b = 8 * ((lane & 3) ^ ((4 - ((lane >> 4) & 3)) & 3)) >= rest;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        load_to_lds(to + stage + q * 4096, a, out_a ? 0xfffffff0u : va + 32 * q * sa, sk * 128u);
-        load_to_lds(to + stage + kTwoA + q * 4096, b, out_b ? 0xfffffff0u : vb + 64 * q * sb, sk * 64u);
-      }
+    for (int q = 0; q < 4; ++q) {
+      load_to_lds(to + stage + q * 4096, a, va + 32 * q * sa, sk * 128u);
+      load_to_lds(to + stage + kTwoA + q * 4096, b, vb + 64 * q * sb, sk * 64u);
     }
   };
   const char* const pb = lds + kTwoA + (128 * wn + lc) * 64 + 16 * (lq ^ ((4 - (lc >> 2)) & 3));
@@ -387,7 +374,7 @@ __global__ __launch_bounds__(kTwoThreads, 2) void wide_two_term_kernel(const Gem
     if (tile == g.blk_begin && tid == 0 && g.sync) *g.sync = 0u;
     const bool more = tile + (int)gridDim.x < tiles;
     const Tile next = tile_of(more ? tile + (int)gridDim.x : tile);
-    const int nk = (g.K + 31) / 32;  // two or more
+    const int nk = g.K / 32;  // two or more
     f32x4 acc[4][8];
 #pragma unroll
     for (int f = 0; f < 32; ++f) acc[f >> 3][f & 7] = f32x4{0.f, 0.f, 0.f, 0.f};
