@@ -1,5 +1,6 @@
-"""Both sides of the lines that decide whether a basis is read as stored or transposed first, against the oracle's tolerances of
-test_gpu_image_tiles."""
+"""The sizes of the lines that decide whether a basis is transposed on its way or first, against the oracle's tolerances of test_gpu_image_tiles.
+With the workspace that the queries name only the basis that starts 8 bytes off and fp32 tokens come to those lines, the others run on the products
+that read the basis as stored; test_gpu_former_prefill brings all of them there."""
 import pytest
 
 pytestmark = pytest.mark.gpu
